@@ -411,6 +411,10 @@ int seer_csr_check(const seer_csr *A, int64_t *bad_row_ptr, int64_t *bad_col_idx
  *               launch of its own (both 0: always)
  *   "auto_prune" 0: seer_spmv_auto does not prune the tree with the known features (every
  *               schedule counts as reachable, the features are always gathered); default 1
+ *   "gather_range" log2 of the columns per range, 1..28, where CSR,BM, CSR,MP, CSR,WO and CSR,A
+ *               order their gathers in time by column range, whatever the sizes (if that makes 2
+ *               to 32 ranges); 0: never.  Default: matrices of 2^23 nonzeros and more whose x
+ *               is larger than 5 MB.  y is the same but for CSR,BM's summation order
  *   "slab_shift" CSR,S: log2 of the columns per slab, 1..30 (default: 19 or 20, see
  *               seer_slab_plan_bytes); the size functions follow it
  *   "coo_runs"  COO,WM: 1 (default): a lane sums a run of eight consecutive triples,

@@ -11,8 +11,16 @@ namespace seer {
 constexpr int kBmMaxRows = 2048;  // most rows one CSR,BM workgroup owns (8 per lane, bounds in registers)
 constexpr int kAutoBmMaxRows = 1024;   // ... inside the combined kernel (4 per lane: keeps it at eight waves per SIMD)
 constexpr int kBmChunk = 2048;    // products staged in LDS per CSR,BM pass (4096 is the other choice)
+constexpr int kRangedChunk = 4096;   // ... and with its gathers ordered by column range
 constexpr int kMpIptSmall = 7;    // merge items per thread, small problems (tile = 1792 items)
 constexpr int kMpIptLarge = 15;   // merge items per thread, large problems (tile = 3840 items)
+
+// Gathers ordered in time by column range (ranged_chunk_finish): x is cut into `count` ranges
+// of range_bytes = 2^shift bytes, and the chip turns to the next one every `ticks` of the
+// constant-rate clock.  count == 0: gathers in the order of the entries.
+struct GatherRanges {
+    uint32_t count, shift, range_bytes, ticks, x_bytes;
+};
 
 struct SpmvArgs {
     int rows, cols, nnz;
@@ -21,6 +29,7 @@ struct SpmvArgs {
     float *y;
     int remap;  // 1: tiles laid out contiguously per XCD
     int nt;     // 1: matrix streams are loaded with the non-temporal hint (keeps x in L2)
+    GatherRanges ranges = GatherRanges{};   // count > 0 only where the 16-byte loads are used, too
 };
 
 bool tm_short_rows(int rows, int nnz);
@@ -127,6 +136,9 @@ struct AutoShape {                          // launch shapes, all from rows and 
     int tm_short;                           // CSR,TM fetches the first eight entries of a row at once (mean row length <= 8)
     int tm_pair;                            // ... and takes two rows per lane (tiles of 512 rows)
     int tm_remap;                           // CSR,TM's tile order: 1 XCD-contiguous, 0 round-robin
+    GatherRanges ranges;                    // as in SpmvArgs; ticks: CSR,WO's
+    uint32_t bm_ticks, mp_ticks;
+    int bm_ranged;                          // CSR,BM orders its gathers, too
     uint32_t reachable;                     // bit k: the tree can answer kernel k given rows, cols and nnz (never 0)
 };
 constexpr size_t kAutoSelOffset = 32768;    // after the 1024 feature partials of 32 bytes

@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -49,6 +50,7 @@ std::atomic<int> g_tune_vec{-1};
 std::atomic<int> g_tune_poll{-1};
 std::atomic<int> g_tune_coo_runs{-1};
 std::atomic<int> g_tune_slab_shift{-1};
+std::atomic<int> g_tune_gather_range{-1};
 
 std::mutex g_mailbox_mutex;
 FeatureRaw *g_mailbox_host = nullptr;   // pinned, mapped
@@ -115,6 +117,51 @@ int wm_lanes(int rows, int nnz)
     return g;
 }
 
+// Whether the gathers of CSR,MP, CSR,WO, CSR,A and (bm_ranged) CSR,BM are ordered in time by column range
+// (ranged_chunk_finish), and into how many ranges: where the 16-byte loads are used, x is larger
+// than an XCD's 4 MB L2 (measured, without and with: 4 MB 148 and 147 us, 4.6 MB 151 and 143, 5.7
+// MB 116 and 105) and not so large that hardly any line is wanted twice while a range lasts (61
+// MB 1044 and 654, 122 MB 1026 and 797), and there is more than one generation of workgroups.
+// Ranges of 1 MB or more, at most sixteen: fewer and larger ones leave L2 no room for the
+// streams, more cost a pass over the entries each (8 MB of x: 8 ranges 289 us, 16 290, 4 297).
+// The "gather_range" knob: 0 never, 1..28 log2 of the columns per range whatever the sizes.
+GatherRanges gather_ranges(int64_t cols, int64_t nnz, bool vec)
+{
+    GatherRanges g{};
+    const int t = g_tune_gather_range.load();
+    int shift = 18;
+    if (t >= 1 && t <= 28) {
+        shift = t;
+    } else {
+        if (t == 0 || cols <= 5 << 18 || cols > 32 << 20 || nnz < 1 << 23) return g;
+        while (((cols - 1) >> shift) + 1 > 16) ++shift;
+    }
+    const int64_t count = ((std::max<int64_t>(cols, 1) - 1) >> shift) + 1;
+    if (!vec || count < 2 || count > 32 || cols >= 1 << 30) return g;
+    g.count = (uint32_t)count;
+    g.shift = (uint32_t)shift + 2u;
+    g.range_bytes = 4u << shift;
+    g.x_bytes = 4u * (uint32_t)cols;
+    return g;
+}
+
+// Clock ticks (10 ns) per range.  A whole turn over x has to take about as long as the gathers
+// under way do: with less the waves fall behind the clock and spread over all of x again (8 M
+// columns: 503 us per product at 64 us per turn, 772 at 48), with more they wait for it (709 at
+// 96).  12 + 9.5 sqrt(MB of x) us suits the 2^23 gathers that 8 workgroups of 4096 entries per
+// CU have under way (measured best 36, 50, 64, 96, 100 us at 8, 15, 31, 61, 95 MB); with fewer
+// entries per workgroup, fewer workgroups per CU or a last generation that is not full it is
+// shorter in proportion.
+uint32_t gather_ticks(const GatherRanges &g, int64_t nnz, double entries_per_wg, int waves)
+{
+    if (!g.count) return 0;
+    const double cap = std::max(entries_per_wg, 1.0) * waves * 256.0;
+    const double generations = std::ceil(std::max((double)nnz, 1.0) / cap);
+    const double under_way = (double)nnz / generations / (double)(1 << 23);
+    const double turn_us = (12.0 + 9.5 * std::sqrt(g.x_bytes / 1048576.0)) * under_way;
+    return (uint32_t)std::max(1.0, turn_us * 100.0 / g.count);
+}
+
 // Rows per workgroup for CSR,BM, from measurements over banded / random matrices:
 // short rows want fat blocks (5 K to 8 K nonzeros: fewer blocks, longer streams).  Rows
 // longer than a wave get 16 per block, the most for which the kernel shares out the lanes
@@ -122,11 +169,23 @@ int wm_lanes(int rows, int nnz)
 // nonzeros into a block (measured best at mean lengths 65 to 500: 16 rows; 1200: 4 to 8;
 // 2000: 8).  A small matrix is cut finer (down to about one LDS chunk per block) so
 // that every CU gets at least four blocks.
-int bm_rows(int rows, int nnz)
+// With gathers ordered by column range (bm_ranged) a block is three quarters of one chunk of
+// 4096: a second chunk would take a second turn over x (2 M columns, 20 per row: 281 us, 290 at
+// 3700 entries, 311 at 7300, 303 at 1500), and 256 rows at most, one per lane (16 long ones, as
+// above).  Not with rows of at most eight entries: fat blocks in small chunks whose loads run
+// ahead suit stencils better than scattered columns gain (5-point 67 us, by range 75).
+bool bm_ranged(const GatherRanges &g, int rows, int nnz)
+{
+    const int t = g_tune_bm_rows.load();
+    return g.count && (int64_t)nnz > 8 * (int64_t)rows && !(t >= 1 && t <= kBmMaxRows);
+}
+
+int bm_rows(int rows, int nnz, bool ranged)
 {
     const int t = g_tune_bm_rows.load();
     if (t >= 1 && t <= kBmMaxRows) return t;
     const double mean = rows > 0 ? (double)nnz / (double)rows : 0.0;
+    if (ranged) return (int)std::min(mean > 64.0 ? 16.0 : 256.0, std::max(1.0, 3000.0 / std::max(mean, 1.0)));
     int r = 1;
     if (mean > 64.0) {
         r = 16;
@@ -175,6 +234,16 @@ int mp_ipt(int rows, int nnz)
     // measured crossover: below ~6 M merge items the smaller tile (more workgroups) wins
     const uint64_t total = (uint64_t)rows + (uint64_t)nnz;
     return total < 6000000u ? kMpIptSmall : kMpIptLarge;
+}
+
+// Entries a workgroup of each schedule has under way at a time, on average.
+constexpr double kAdaptEntries = 2048.0;
+double wo_entries(int nnz) { return nnz >= 1 << 23 ? 4096.0 : 2048.0; }
+double mp_entries(int rows, int nnz, int ipt) { return 256.0 * ipt * ((double)nnz / ((double)rows + (double)nnz)); }
+double bm_entries(int rows, int nnz, int rows_per_block)
+{
+    const double block = (double)rows_per_block * (double)nnz / (double)std::max(rows, 1);
+    return block / std::max(1.0, std::ceil(block / kRangedChunk));
 }
 
 int auto_fused_rows()
@@ -451,6 +520,7 @@ int seer_set_tuning(const char *name, int value)
     else if (!std::strcmp(name, "poll")) g_tune_poll.store(value);
     else if (!std::strcmp(name, "coo_runs")) g_tune_coo_runs.store(value);
     else if (!std::strcmp(name, "slab_shift")) g_tune_slab_shift.store(value);
+    else if (!std::strcmp(name, "gather_range")) g_tune_gather_range.store(value);
     else return SEER_EINVAL;
     return SEER_OK;
 }
@@ -631,8 +701,11 @@ static int auto_enqueue(const seer_csr *A, const seer_tree *tree, const float *x
     dt.n_nodes = tree->n_nodes;
     std::memcpy(dt.nodes, tree->nodes, sizeof(seer_node) * (size_t)tree->n_nodes);
     AutoShape sh;
+    const bool vec = aligned16(A->col_idx) && aligned16(A->values) && g_tune_vec.load() != 0;
+    sh.ranges = gather_ranges(A->cols, A->nnz, vec);
     sh.wm_lanes = wm_lanes(A->rows, A->nnz);
-    sh.bm_rows = std::min(bm_rows(A->rows, A->nnz), kAutoBmMaxRows);   // (more only through the tuning knob)
+    sh.bm_ranged = bm_ranged(sh.ranges, A->rows, A->nnz);
+    sh.bm_rows = std::min(bm_rows(A->rows, A->nnz, sh.bm_ranged), kAutoBmMaxRows);   // (more only through the tuning knob)
     sh.bm_own_shift = bm_own_shift(sh.bm_rows);
     sh.mp_ipt = mp_ipt(A->rows, A->nnz);
     sh.tm_short = tm_short_rows(A->rows, A->nnz);
@@ -645,7 +718,9 @@ static int auto_enqueue(const seer_csr *A, const seer_tree *tree, const float *x
     sh.tiles[SEER_CSR_MP] = mp_num_tiles(A->rows, A->nnz, sh.mp_ipt);
     sh.tiles[SEER_CSR_WO] = wo_num_tiles(A->rows, A->nnz);
     SpmvArgs a{A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, x, y, use_remap(), 1};
-    const bool vec = aligned16(A->col_idx) && aligned16(A->values) && g_tune_vec.load() != 0;
+    sh.ranges.ticks = gather_ticks(sh.ranges, A->nnz, wo_entries(A->nnz), 8);
+    sh.bm_ticks = gather_ticks(sh.ranges, A->nnz, bm_entries(A->rows, A->nnz, sh.bm_rows), 8);
+    sh.mp_ticks = gather_ticks(sh.ranges, A->nnz, mp_entries(A->rows, A->nnz, sh.mp_ipt), 8);
     // What the host knows without looking at the matrix prunes the tree: the grid is sized
     // for the schedules that stay reachable, the carry fix-up is enqueued only if merge path
     // or the nonzero split is among them, and if a single kernel is left nothing is gathered.
@@ -867,6 +942,7 @@ static int spmv_dispatch(int kernel_id, const seer_csr *A, const float *x, float
     hipStream_t st = static_cast<hipStream_t>(stream);
     SpmvArgs a{A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, x, y, use_remap(), nt};
     const bool vec = aligned16(A->col_idx) && aligned16(A->values) && g_tune_vec.load() != 0;
+    a.ranges = gather_ranges(A->cols, A->nnz, vec);
     switch (kernel_id) {
     case SEER_CSR_TM: {
         SpmvArgs t = a;
@@ -875,7 +951,13 @@ static int spmv_dispatch(int kernel_id, const seer_csr *A, const float *x, float
         break;
     }
     case SEER_CSR_WM: launch_wm(a, wm_lanes(A->rows, A->nnz), st); break;
-    case SEER_CSR_BM: launch_bm(a, bm_rows(A->rows, A->nnz), bm_chunk(), vec, st); break;
+    case SEER_CSR_BM: {
+        if (!bm_ranged(a.ranges, A->rows, A->nnz)) a.ranges.count = 0;
+        const int r = bm_rows(A->rows, A->nnz, a.ranges.count != 0);
+        a.ranges.ticks = gather_ticks(a.ranges, A->nnz, bm_entries(A->rows, A->nnz, r), 8);
+        launch_bm(a, r, bm_chunk(), vec, st);
+        break;
+    }
     case SEER_CSR_A: {
         // single call: the preprocessing pass runs first, on the same stream, every time
         const size_t carry = carry_workspace_bytes(adaptive_num_tiles(A->rows, A->nnz));
@@ -883,6 +965,7 @@ static int spmv_dispatch(int kernel_id, const seer_csr *A, const float *x, float
             return SEER_EWORKSPACE;
         void *plan_mem = static_cast<char *>(workspace) + carry;
         launch_adaptive_plan(A->rows, A->nnz, A->row_ptr, plan_mem, false, st);
+        a.ranges.ticks = gather_ticks(a.ranges, A->nnz, kAdaptEntries, 8);
         launch_adaptive(a, vec, plan_mem, workspace, st);
         break;
     }
@@ -899,12 +982,14 @@ static int spmv_dispatch(int kernel_id, const seer_csr *A, const float *x, float
         if (!workspace || !aligned16(workspace) ||
             workspace_bytes < carry_workspace_bytes(wo_num_tiles(A->rows, A->nnz)))
             return SEER_EWORKSPACE;
+        a.ranges.ticks = gather_ticks(a.ranges, A->nnz, wo_entries(A->nnz), 8);
         launch_wo(a, vec, workspace, st);
         break;
     default: {
         const int ipt = mp_ipt(A->rows, A->nnz);
         if (!workspace || !aligned16(workspace) || workspace_bytes < mp_workspace_bytes(A->rows, A->nnz, ipt))
             return SEER_EWORKSPACE;
+        a.ranges.ticks = gather_ticks(a.ranges, A->nnz, mp_entries(A->rows, A->nnz, ipt), 8);
         launch_mp(a, ipt, vec, workspace, st);
         break;
     }
@@ -1121,6 +1206,8 @@ int seer_spmv_prepared(const seer_plan *plan, const seer_csr *A, const float *x,
     SpmvArgs a{A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, x, y, use_remap(),
                use_nt_repeated(csr_footprint(A))};
     const bool vec = aligned16(A->col_idx) && aligned16(A->values) && g_tune_vec.load() != 0;
+    a.ranges = gather_ranges(A->cols, A->nnz, vec);
+    a.ranges.ticks = gather_ticks(a.ranges, A->nnz, kAdaptEntries, 8);
     launch_adaptive(a, vec, plan->device, carry, static_cast<hipStream_t>(stream));
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? SEER_OK : hip_fail(e);

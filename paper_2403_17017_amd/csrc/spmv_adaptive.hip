@@ -11,17 +11,17 @@ __global__ __launch_bounds__(kWG) void adaptive_plan_kernel(
     adaptive_plan_body<kAdaptChunk>(rows, nnz, rp, plan, n_tiles, split_flag);
 }
 
-template <bool VEC, bool NT>
+template <bool VEC, bool NT, bool RANGED = false>
 __global__ __launch_bounds__(kWG) void spmv_adaptive_kernel(
     int rows, const int *__restrict__ rp, const int *__restrict__ ci, const float *__restrict__ va,
     const float *__restrict__ x, float *__restrict__ y, const int2 *__restrict__ plan,
-    int *__restrict__ carry_row, float *__restrict__ carry_val, uint32_t n_tiles, int remap)
+    int *__restrict__ carry_row, float *__restrict__ carry_val, uint32_t n_tiles, int remap, const GatherRanges g)
 {
     __shared__ __attribute__((aligned(16))) float s_prod[2 * kAdaptChunk];
     __shared__ float s_red[4];
     const uint32_t tile = tile_of_block(blockIdx.x, n_tiles, remap);
     if (tile >= n_tiles) return;
-    adaptive_body<kAdaptChunk, VEC, NT>(rows, rp, ci, va, x, y, plan, carry_row, carry_val, tile, s_prod, s_red);
+    adaptive_body<kAdaptChunk, VEC, NT, RANGED>(rows, rp, ci, va, x, y, plan, carry_row, carry_val, tile, s_prod, s_red, g);
 }
 
 uint32_t adaptive_num_tiles(int rows, int nnz)
@@ -61,10 +61,12 @@ void launch_adaptive(const SpmvArgs &a, bool vec, const void *plan_mem, void *ca
     float *carry_val = carry_ws ? reinterpret_cast<float *>(static_cast<char *>(carry_ws) + one) : nullptr;
     const int2 *plan = static_cast<const int2 *>(plan_mem);
     const dim3 grid(a.remap ? tiles_per_xcd(n_tiles) * kXCD : n_tiles);
-#define SEER_A_LAUNCH(V, N)                                                                            \
-    hipLaunchKernelGGL((spmv_adaptive_kernel<V, N>), grid, dim3(kWG), 0, st, a.rows, a.rp, a.ci, a.va, a.x, \
-                       a.y, plan, carry_row, carry_val, n_tiles, a.remap)
-    if (vec) {
+#define SEER_A_LAUNCH(...)                                                                             \
+    hipLaunchKernelGGL((spmv_adaptive_kernel<__VA_ARGS__>), grid, dim3(kWG), 0, st, a.rows, a.rp, a.ci, a.va, a.x, \
+                       a.y, plan, carry_row, carry_val, n_tiles, a.remap, a.ranges)
+    if (a.ranges.count) {
+        if (a.nt) SEER_A_LAUNCH(true, true, true); else SEER_A_LAUNCH(true, false, true);
+    } else if (vec) {
         if (a.nt) SEER_A_LAUNCH(true, true); else SEER_A_LAUNCH(true, false);
     } else {
         if (a.nt) SEER_A_LAUNCH(false, true); else SEER_A_LAUNCH(false, false);

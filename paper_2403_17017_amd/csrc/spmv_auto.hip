@@ -248,7 +248,8 @@ constexpr int kAutoLds = kAutoLdsMpBm > bm_lds_words<kWoChunkLarge>() + 2 ? kAut
 static_assert(bm_lds_words<kWoChunk>() + 2 <= kAutoLds, "CSR,WO's products and its two bounds share the overlay");
 
 // This workgroup's share of schedule k (the same k in every workgroup of the grid).
-template <int IPT, bool VEC>
+// RANGED: with gathers ordered by column range (shape.ranges), as the stand-alone kernels.
+template <int IPT, bool VEC, bool RANGED = false>
 __device__ __forceinline__ void auto_dispatch(
     int k, int rows, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
@@ -282,42 +283,60 @@ __device__ __forceinline__ void auto_dispatch(
         else if (shape.tm_short) tm_body<true>(rows, nnz, rp, ci, va, x, y, tile);
         else tm_body<false>(rows, nnz, rp, ci, va, x, y, tile);
     } else if (k == SEER_CSR_BM) {
+        float *s_prod = reinterpret_cast<float *>(smem);
+        if constexpr (RANGED) {
+            static_assert(bm_lds_words<kRangedChunk>() <= kAutoLds, "LDS overlay too small");
+            if (shape.bm_ranged) {
+                GatherRanges g = shape.ranges;
+                g.ticks = shape.bm_ticks;
+                if (shape.bm_rows <= (int)kWoGroupRows)
+                    bm_body<kRangedChunk, VEC, true, false, false, true, 256, true>(rows, rp, ci, va, x, y, shape.bm_rows,
+                                                                                    shape.bm_own_shift, tile, s_prod, g);
+                else
+                    bm_body<kRangedChunk, VEC, true, false, false, false, 256, true>(rows, rp, ci, va, x, y, shape.bm_rows,
+                                                                                     shape.bm_own_shift, tile, s_prod, g);
+                return;
+            }
+        }
         if (shape.bm_rows <= (int)kWoGroupRows)
             bm_body<kBmChunk, VEC, true, true, false, true, 256>(rows, rp, ci, va, x, y, shape.bm_rows,
-                                                                 shape.bm_own_shift, tile, reinterpret_cast<float *>(smem));
+                                                                 shape.bm_own_shift, tile, s_prod);
         else   // (the host keeps bm_rows within kAutoBmMaxRows here)
             bm_body<kBmChunk, VEC, true, true, false, false, kAutoBmMaxRows>(rows, rp, ci, va, x, y, shape.bm_rows,
-                                                                             shape.bm_own_shift, tile, reinterpret_cast<float *>(smem));
+                                                                             shape.bm_own_shift, tile, s_prod);
     } else if (k == SEER_CSR_WO) {
         if (wo_chunk_of(nnz) == kWoChunkLarge)
-            wo_body<kWoChunkLarge, VEC, true>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile,
-                                              reinterpret_cast<float *>(smem),
-                                              reinterpret_cast<uint32_t *>(smem) + bm_lds_words<kWoChunkLarge>());
+            wo_body<kWoChunkLarge, VEC, true, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile,
+                                                      reinterpret_cast<float *>(smem),
+                                                      reinterpret_cast<uint32_t *>(smem) + bm_lds_words<kWoChunkLarge>(),
+                                                      shape.ranges);
         else
-            wo_body<kWoChunk, VEC, true>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile,
-                                         reinterpret_cast<float *>(smem),
-                                         reinterpret_cast<uint32_t *>(smem) + bm_lds_words<kWoChunk>());
+            wo_body<kWoChunk, VEC, true, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile,
+                                                 reinterpret_cast<float *>(smem),
+                                                 reinterpret_cast<uint32_t *>(smem) + bm_lds_words<kWoChunk>(), shape.ranges);
     } else {
-        mp_body<IPT, VEC, true>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile, smem);
+        GatherRanges g = shape.ranges;
+        g.ticks = shape.mp_ticks;
+        mp_body<IPT, VEC, true, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile, smem, g);
     }
 }
 
-template <int IPT, bool VEC>
-__global__ __launch_bounds__(kWG) void spmv_auto_kernel(
+template <int IPT, bool VEC, bool RANGED = false>
+__global__ __launch_bounds__(kWG, RANGED ? 8 : 1) void spmv_auto_kernel(
     int rows, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
     int *__restrict__ carry_row, float *__restrict__ carry_val, const AutoSel *__restrict__ sel,
     const AutoShape shape, int remap)
 {
     __shared__ __attribute__((aligned(16))) int smem[kAutoLds];
-    auto_dispatch<IPT, VEC>(sel->kernel_id, rows, nnz, rp, ci, va, x, y, carry_row, carry_val, shape, remap, smem);
+    auto_dispatch<IPT, VEC, RANGED>(sel->kernel_id, rows, nnz, rp, ci, va, x, y, carry_row, carry_val, shape, remap, smem);
 }
 
 // The product when the host could decide alone: every leaf the tree can reach from rows,
 // cols and nnz names the same kernel, so nothing is gathered.  Workgroup 0 leaves the record
 // (valid = 2: no statistics, known features only).
-template <int IPT, bool VEC>
-__global__ __launch_bounds__(kWG) void spmv_auto_decided_kernel(
+template <int IPT, bool VEC, bool RANGED = false>
+__global__ __launch_bounds__(kWG, RANGED ? 8 : 1) void spmv_auto_decided_kernel(
     int rows, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
     int *__restrict__ carry_row, float *__restrict__ carry_val, AutoSel *__restrict__ sel,
@@ -325,7 +344,7 @@ __global__ __launch_bounds__(kWG) void spmv_auto_decided_kernel(
 {
     __shared__ __attribute__((aligned(16))) int smem[kAutoLds];
     if (blockIdx.x == 0 && threadIdx.x == 0) *sel = record;
-    auto_dispatch<IPT, VEC>(record.kernel_id, rows, nnz, rp, ci, va, x, y, carry_row, carry_val, shape, remap, smem);
+    auto_dispatch<IPT, VEC, RANGED>(record.kernel_id, rows, nnz, rp, ci, va, x, y, carry_row, carry_val, shape, remap, smem);
 }
 
 // Selection inside the product's launch.  The first wave of every workgroup finishes the
@@ -442,10 +461,13 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
     const bool carries = reachable(SEER_CSR_MP) || reachable(SEER_CSR_WO);
 
     if (decided) {
-#define SEER_DECIDED_LAUNCH(I, V)                                                                          \
-    hipLaunchKernelGGL((spmv_auto_decided_kernel<I, V>), dim3(grid), dim3(kWG), 0, st, a.rows, a.nnz, a.rp, \
+#define SEER_DECIDED_LAUNCH(...)                                                                           \
+    hipLaunchKernelGGL((spmv_auto_decided_kernel<__VA_ARGS__>), dim3(grid), dim3(kWG), 0, st, a.rows, a.nnz, a.rp, \
                        a.ci, a.va, a.x, a.y, carry_row, carry_val, sel, *decided, shape, a.remap)
-        if (shape.mp_ipt == kMpIptSmall) {
+        if (shape.ranges.count) {
+            if (shape.mp_ipt == kMpIptSmall) SEER_DECIDED_LAUNCH(kMpIptSmall, true, true);
+            else SEER_DECIDED_LAUNCH(kMpIptLarge, true, true);
+        } else if (shape.mp_ipt == kMpIptSmall) {
             if (vec) SEER_DECIDED_LAUNCH(kMpIptSmall, true); else SEER_DECIDED_LAUNCH(kMpIptSmall, false);
         } else {
             if (vec) SEER_DECIDED_LAUNCH(kMpIptLarge, true); else SEER_DECIDED_LAUNCH(kMpIptLarge, false);
@@ -457,7 +479,7 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
     }
 
     const bool rp_vec = (reinterpret_cast<uintptr_t>(a.rp) & 15u) == 0;
-    if (heap && (grid <= (uint32_t)policy.fused_grid || a.rows <= policy.fused_max_rows)) {
+    if (heap && !shape.ranges.count && (grid <= (uint32_t)policy.fused_grid || a.rows <= policy.fused_max_rows)) {
         // one launch for a small matrix; else a first pass that leaves a few partials
         const uint32_t n_part = a.rows > policy.fused_rows ? launch_fused_partials(a, part, rp_vec, st) : 0u;
 #define SEER_FUSED_LAUNCH(I, V, R)                                                                          \
@@ -504,10 +526,13 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
                                n_part, sel, tree, shape.reachable);
     }
 
-#define SEER_AUTO_LAUNCH(I, V)                                                                             \
-    hipLaunchKernelGGL((spmv_auto_kernel<I, V>), dim3(grid), dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, \
+#define SEER_AUTO_LAUNCH(...)                                                                              \
+    hipLaunchKernelGGL((spmv_auto_kernel<__VA_ARGS__>), dim3(grid), dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, \
                        a.va, a.x, a.y, carry_row, carry_val, sel, shape, a.remap)
-    if (shape.mp_ipt == kMpIptSmall) {
+    if (shape.ranges.count) {
+        if (shape.mp_ipt == kMpIptSmall) SEER_AUTO_LAUNCH(kMpIptSmall, true, true);
+        else SEER_AUTO_LAUNCH(kMpIptLarge, true, true);
+    } else if (shape.mp_ipt == kMpIptSmall) {
         if (vec) SEER_AUTO_LAUNCH(kMpIptSmall, true); else SEER_AUTO_LAUNCH(kMpIptSmall, false);
     } else {
         if (vec) SEER_AUTO_LAUNCH(kMpIptLarge, true); else SEER_AUTO_LAUNCH(kMpIptLarge, false);

@@ -26,16 +26,17 @@ __global__ __launch_bounds__(kWG) void spmv_wm_kernel(
     wm_body<G>(rows, rp, ci, va, x, y, tile);
 }
 
-template <int CH, bool VEC, bool NT, bool GRP = false, int MAXR = kBmMaxRows, bool PIPE = true, bool PAD = false>
-__global__ __launch_bounds__(kWG) void spmv_bm_kernel(
+template <int CH, bool VEC, bool NT, bool GRP = false, int MAXR = kBmMaxRows, bool RANGED = false>
+__global__ __launch_bounds__(kWG, RANGED ? 8 : 1) void spmv_bm_kernel(
     int rows, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
-    int rows_per_block, int own_shift, uint32_t n_tiles, int remap)
+    int rows_per_block, int own_shift, uint32_t n_tiles, int remap, const GatherRanges g)
 {
     __shared__ __attribute__((aligned(16))) float s_prod[bm_lds_words<CH>()];
     const uint32_t tile = tile_of_block(blockIdx.x, n_tiles, remap);
     if (tile >= n_tiles) return;
-    bm_body<CH, VEC, NT, PIPE, PAD, GRP, MAXR>(rows, rp, ci, va, x, y, rows_per_block, own_shift, tile, s_prod);
+    bm_body<CH, VEC, NT, !RANGED, false, GRP, MAXR, RANGED>(rows, rp, ci, va, x, y, rows_per_block, own_shift, tile,
+                                                             s_prod, g);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -89,16 +90,19 @@ void launch_wm(const SpmvArgs &a, int G, hipStream_t st)
     }
 }
 
-template <int CH, bool VEC, bool NT>
+template <int CH, bool VEC, bool NT, bool RANGED = false>
 static void launch_bm_v(const SpmvArgs &a, int rows_per_block, hipStream_t st)
 {
     const uint32_t n_tiles = ((uint32_t)a.rows + rows_per_block - 1) / (uint32_t)rows_per_block;
     const int own_shift = bm_own_shift(rows_per_block);
 #define SEER_BM_LAUNCH(G, M)                                                                              \
-    hipLaunchKernelGGL((spmv_bm_kernel<CH, VEC, NT, G, M>), dim3(grid_for(n_tiles, a.remap)), dim3(kWG), 0, st, \
-                       a.rows, a.rp, a.ci, a.va, a.x, a.y, rows_per_block, own_shift, n_tiles, a.remap)
-    if (rows_per_block <= (int)kWoGroupRows) SEER_BM_LAUNCH(true, 256);   // long rows: several lanes per row
-    else if (rows_per_block <= 256) SEER_BM_LAUNCH(false, 256);           // else the smallest instance that fits
+    hipLaunchKernelGGL((spmv_bm_kernel<CH, VEC, NT, G, M, RANGED>), dim3(grid_for(n_tiles, a.remap)), dim3(kWG), 0, st, \
+                       a.rows, a.rp, a.ci, a.va, a.x, a.y, rows_per_block, own_shift, n_tiles, a.remap, a.ranges)
+    // rows of well over a hundred entries: several lanes per row; else the smallest instance that
+    // fits (RANGED: the caller keeps it at 256 rows)
+    if (rows_per_block <= (int)kWoGroupRows) SEER_BM_LAUNCH(true, 256);
+    else if constexpr (RANGED) SEER_BM_LAUNCH(false, 256);
+    else if (rows_per_block <= 256) SEER_BM_LAUNCH(false, 256);
     else if (rows_per_block <= 1024) SEER_BM_LAUNCH(false, 1024);
     else SEER_BM_LAUNCH(false, kBmMaxRows);
 #undef SEER_BM_LAUNCH
@@ -118,7 +122,10 @@ static void launch_bm_c(const SpmvArgs &a, int rows_per_block, bool vec, hipStre
 
 void launch_bm(const SpmvArgs &a, int rows_per_block, int chunk, bool vec, hipStream_t st)
 {
-    if (chunk == 4096) launch_bm_c<4096>(a, rows_per_block, vec, st);
+    if (a.ranges.count) {
+        if (a.nt) launch_bm_v<kRangedChunk, true, true, true>(a, rows_per_block, st);
+        else launch_bm_v<kRangedChunk, true, false, true>(a, rows_per_block, st);
+    } else if (chunk == 4096) launch_bm_c<4096>(a, rows_per_block, vec, st);
     else launch_bm_c<2048>(a, rows_per_block, vec, st);
 }
 

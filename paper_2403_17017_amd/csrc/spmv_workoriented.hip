@@ -5,17 +5,17 @@
 
 namespace seer {
 
-template <int CH, bool VEC, bool NT>
+template <int CH, bool VEC, bool NT, bool RANGED = false>
 __global__ __launch_bounds__(kWG) void spmv_wo_kernel(
     int rows, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
-    int *__restrict__ carry_row, float *__restrict__ carry_val, uint32_t n_tiles, int remap)
+    int *__restrict__ carry_row, float *__restrict__ carry_val, uint32_t n_tiles, int remap, const GatherRanges g)
 {
     __shared__ __attribute__((aligned(16))) float s_prod[bm_lds_words<CH>()];
     __shared__ uint32_t s_bounds[2];
     const uint32_t tile = tile_of_block(blockIdx.x, n_tiles, remap);
     if (tile >= n_tiles) return;
-    wo_body<CH, VEC, NT>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile, s_prod, s_bounds);
+    wo_body<CH, VEC, NT, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile, s_prod, s_bounds, g);
 }
 
 uint32_t wo_num_tiles(int rows, int nnz)
@@ -41,11 +41,13 @@ void launch_wo(const SpmvArgs &a, bool vec, void *workspace, hipStream_t st)
     int *carry_row = static_cast<int *>(workspace);
     float *carry_val = reinterpret_cast<float *>(static_cast<char *>(workspace) + one);
     const dim3 grid(a.remap ? tiles_per_xcd(n_tiles) * kXCD : n_tiles);
-#define SEER_WO_LAUNCH(C, V, N)                                                                           \
-    hipLaunchKernelGGL((spmv_wo_kernel<C, V, N>), grid, dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, a.va, \
-                       a.x, a.y, carry_row, carry_val, n_tiles, a.remap)
+#define SEER_WO_LAUNCH(C, ...)                                                                                 \
+    hipLaunchKernelGGL((spmv_wo_kernel<C, __VA_ARGS__>), grid, dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, a.va, \
+                       a.x, a.y, carry_row, carry_val, n_tiles, a.remap, a.ranges)
 #define SEER_WO_PICK(C)                                                                     \
-    if (vec) {                                                                              \
+    if (a.ranges.count) {                                                                   \
+        if (a.nt) SEER_WO_LAUNCH(C, true, true, true); else SEER_WO_LAUNCH(C, true, false, true); \
+    } else if (vec) {                                                                              \
         if (a.nt) SEER_WO_LAUNCH(C, true, true); else SEER_WO_LAUNCH(C, true, false);       \
     } else {                                                                                \
         if (a.nt) SEER_WO_LAUNCH(C, false, true); else SEER_WO_LAUNCH(C, false, false);     \
