@@ -26,10 +26,10 @@
  *   - Every call returns SEER_OK (0) or a negative seer_status; on error no output
  *     is written.  Nothing throws or aborts.  Matrix contents (monotone row_ptr,
  *     column range) are NOT validated: they are the caller's contract.
- *   - The first seer_features call allocates one 64-byte pinned host buffer per
+ *   - The first seer_features or seer_csr_check call allocates one 64-byte pinned host buffer per
  *     process (its result mailbox); no other state is kept, on the host or the device.
- *   - Calls that use the same workspace must not overlap in time; seer_features calls
- *     are serialised inside the library (they share the mailbox).
+ *   - Calls that use the same workspace must not overlap in time; seer_features and
+ *     seer_csr_check calls are serialised inside the library (they share the mailbox).
  */
 #ifndef SEER_H
 #define SEER_H

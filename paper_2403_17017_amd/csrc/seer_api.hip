@@ -316,6 +316,34 @@ int ensure_mailbox()
     return SEER_OK;
 }
 
+// Waits until the kernel that writes `seq` into the mailbox has done so, and copies the mailbox
+// out (the caller holds g_mailbox_mutex).  The kernel writes its result, then the sequence
+// number, into pinned host memory.  Watching that word is quicker than waiting for the stream;
+// if it does not show up soon, wait for the stream and look again.
+int wait_for_mailbox(uint64_t seq, hipStream_t st, FeatureRaw *raw)
+{
+    volatile uint64_t *seq_word = &g_mailbox_host->seq;
+    bool seen = false;
+    if (g_tune_poll.load() != 0) {
+        const auto t0 = std::chrono::steady_clock::now();
+        for (uint32_t spin = 0;; ++spin) {
+            if (*seq_word == seq) { seen = true; break; }
+            if ((spin & 1023u) == 1023u &&
+                std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2))
+                break;
+            __builtin_ia32_pause();
+        }
+    }
+    if (!seen) {
+        const hipError_t e = hipStreamSynchronize(st);
+        if (e != hipSuccess) return hip_fail(e);
+        if (*seq_word != seq) return hip_fail(hipErrorUnknown);
+    }
+    std::atomic_thread_fence(std::memory_order_acquire);
+    std::memcpy(raw, const_cast<const FeatureRaw *>(g_mailbox_host), sizeof *raw);
+    return SEER_OK;
+}
+
 // f[] from the exact integers; every entry is one fp64 quotient rounded once to fp32.
 void derive(seer_features_t *o)
 {
@@ -592,31 +620,11 @@ int seer_features(const seer_csr *A, seer_features_t *out, void *workspace, size
         hipStream_t st = static_cast<hipStream_t>(stream);
         const uint64_t seq = ++g_feature_seq;
         launch_features(A->rows, A->row_ptr, workspace, g_mailbox_dev, seq, st);
-        hipError_t e = hipGetLastError();
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e);
-        // The kernel writes the statistics, then the sequence number, into pinned host
-        // memory.  Watching that word is quicker than waiting for the stream; if it does
-        // not show up soon, wait for the stream and look again.
-        volatile uint64_t *seq_word = &g_mailbox_host->seq;
-        bool seen = false;
-        if (g_tune_poll.load() != 0) {
-            const auto t0 = std::chrono::steady_clock::now();
-            for (uint32_t spin = 0;; ++spin) {
-                if (*seq_word == seq) { seen = true; break; }
-                if ((spin & 1023u) == 1023u &&
-                    std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2))
-                    break;
-                __builtin_ia32_pause();
-            }
-        }
-        if (!seen) {
-            e = hipStreamSynchronize(st);
-            if (e != hipSuccess) return hip_fail(e);
-            if (*seq_word != seq) return hip_fail(hipErrorUnknown);
-        }
-        std::atomic_thread_fence(std::memory_order_acquire);
         FeatureRaw raw;
-        std::memcpy(&raw, const_cast<const FeatureRaw *>(g_mailbox_host), sizeof raw);
+        const int wrc = wait_for_mailbox(seq, st, &raw);
+        if (wrc != SEER_OK) return wrc;
         o.nnz = (int64_t)raw.last - (int64_t)raw.first;
         o.max_len = raw.max_len;
         o.min_len = raw.min_len;
@@ -887,19 +895,19 @@ int seer_csr_check(const seer_csr *A, int64_t *bad_row_ptr, int64_t *bad_col_idx
     if (!A || !bad_row_ptr || !bad_col_idx) return SEER_EINVAL;
     if (A->rows < 0 || A->cols < 0 || A->nnz < 0 || !A->row_ptr) return SEER_EINVAL;
     if (!workspace || !aligned16(workspace) || workspace_bytes < 16) return SEER_EWORKSPACE;
+    std::lock_guard<std::mutex> lock(g_mailbox_mutex);
+    const int mrc = ensure_mailbox();
+    if (mrc != SEER_OK) return mrc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipError_t e = hipMemsetAsync(workspace, 0, 16, st);
+    const uint64_t seq = ++g_feature_seq;
+    launch_csr_check(A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, workspace, g_mailbox_dev, seq, st);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e);
-    launch_csr_check(A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, workspace, st);
-    e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e);
-    unsigned long long counts[2] = {0, 0};
-    e = hipMemcpyAsync(counts, workspace, sizeof counts, hipMemcpyDeviceToHost, st);
-    if (e != hipSuccess) return hip_fail(e);
-    e = hipStreamSynchronize(st);
-    if (e != hipSuccess) return hip_fail(e);
-    *bad_row_ptr = (int64_t)counts[0];
-    *bad_col_idx = (int64_t)counts[1];
+    FeatureRaw raw;
+    const int wrc = wait_for_mailbox(seq, st, &raw);
+    if (wrc != SEER_OK) return wrc;
+    *bad_row_ptr = (int64_t)raw.sum_sq;
+    *bad_col_idx = (int64_t)raw.empty;
     return SEER_OK;
 }
 

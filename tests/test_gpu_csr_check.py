@@ -74,3 +74,33 @@ def test_status_codes():
     with pytest.raises(S.SeerError) as ei:
         S.seer_csr_check(d, small)
     assert ei.value.status == -4
+
+
+@pytest.mark.parametrize("rows,nnz", [(1, 1), (2, 3), (3, 4), (4, 5), (5, 2), (1023, 4099), (4096, 16384), (70_001, 131_075)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_every_position_counts_whatever_the_alignment(rows, nnz, shift):
+    """The first and the last few offsets and columns, in arrays that start on 16 bytes and 4
+    bytes past that (the kernel reads four of them at a time)."""
+    import torch
+    rng = np.random.default_rng(rows + nnz)
+    rp = np.zeros(rows + 1, np.int32)
+    rp[1:] = np.sort(rng.integers(0, nnz + 1, rows))
+    rp[-1] = nnz
+    ci = rng.integers(0, 50, nnz).astype(np.int32)
+
+    def counts(p, c):
+        dp, dc = torch.zeros(rows + 1 + shift, dtype=torch.int32, device="cuda:0"), \
+            torch.zeros(nnz + shift, dtype=torch.int32, device="cuda:0")
+        dp[shift:] = torch.from_numpy(p).cuda()
+        dc[shift:] = torch.from_numpy(c).cuda()
+        return S.seer_csr_check(S.DeviceCSR(rows, 50, dp[shift:], dc[shift:], torch.zeros(nnz, device="cuda:0"), nnz))
+    announce(f"csr check at every position rows={rows} nnz={nnz} shift={shift}")
+    assert counts(rp, ci) == O.csr_defects(rows, 50, nnz, rp, ci)
+    for k in sorted({k for k in (0, 1, 2, 3, 4, nnz // 2, nnz - 4, nnz - 3, nnz - 2, nnz - 1) if 0 <= k < nnz}):
+        bad = ci.copy()
+        bad[k] = 50 if k % 2 else -1
+        assert counts(rp, bad) == O.csr_defects(rows, 50, nnz, rp, bad), f"column {k}"
+    for i in sorted({i for i in (0, 1, 2, 3, 4, 5, rows // 2, rows - 3, rows - 2, rows - 1, rows) if 0 <= i <= rows}):
+        bad = rp.copy()
+        bad[i] += nnz + 1
+        assert counts(bad, ci) == O.csr_defects(rows, 50, nnz, bad, ci), f"offset {i}"
