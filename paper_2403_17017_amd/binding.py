@@ -15,6 +15,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libseer.so")
+_MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 
 NUM_FEATURES = 13
 NUM_KERNELS = 9
@@ -78,6 +79,17 @@ seer_model._fields_ = [("selector", C.POINTER(seer_tree)), ("known", C.POINTER(s
                        ("gathered", C.POINTER(seer_tree))]
 
 _lib = None
+_marshal = None
+
+
+def _bind_marshal(L):
+    """The native marshalling of the asynchronous calls, bound to the functions of L."""
+    global _marshal
+    if not os.path.exists(_MARSHAL_PATH):
+        raise ImportError(f"{_MARSHAL_PATH} is missing: build it with `python -m paper_2403_17017_amd.build`")
+    from . import _marshal as m
+    m.bind(*(C.cast(f, C.c_void_p).value for f in (L.seer_spmv, L.seer_spmv_auto, L.seer_spmv_model, L.seer_spmv_prepared)))
+    _marshal = m
 
 
 def lib():
@@ -150,6 +162,7 @@ def lib():
         L.seer_strerror.argtypes = [C.c_int]
         L.seer_strerror.restype = C.c_char_p
         L.seer_last_hip_error.restype = C.c_int
+        _bind_marshal(L)
         _lib = L
     return _lib
 
@@ -222,11 +235,16 @@ class Tree:
         return cls([-1], [0.0], [-1], [-1], [klass])
 
 
-def _stream_ptr(stream):
+def _stream_handle(stream) -> int:
+    """The hipStream_t of a torch stream, of a raw handle, or (None) of torch's current stream."""
     if stream is None:
         import torch
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(int(stream.cuda_stream)) if hasattr(stream, "cuda_stream") else C.c_void_p(int(stream))
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())   # torch.cuda.current_stream() without the object
+    return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _stream_ptr(stream):
+    return C.c_void_p(_stream_handle(stream))
 
 
 def features_workspace_bytes(rows: int) -> int:
@@ -325,10 +343,7 @@ def seer_spmv(kernel_id: int, A: DeviceCSR, x, y, workspace=None, stream=None) -
     need = spmv_workspace_bytes(kernel_id, A.rows, A.nnz) if 0 <= kernel_id < NUM_KERNELS else 0
     if need and workspace is None:
         workspace = _temporary_workspace(need, A.row_ptr.device, stream)
-    cs = A.c_struct()
-    rc = lib().seer_spmv(int(kernel_id), C.byref(cs), x.data_ptr(), y.data_ptr(),
-                         workspace.data_ptr() if workspace is not None else None,
-                         workspace.numel() if workspace is not None else 0, _stream_ptr(stream))
+    rc = _marshal.spmv(int(kernel_id), A, x, y, workspace, _stream_handle(stream))
     if rc:
         raise SeerError(rc, f"seer_spmv(kernel {kernel_id})")
 
@@ -366,9 +381,9 @@ def spmv_auto_workspace_bytes(rows: int, nnz: int) -> int:
 
 def seer_spmv_auto(A: DeviceCSR, tree: Tree, x, y, workspace, stream=None) -> None:
     """Features, tree walk and SpMV enqueued back to back; returns without waiting."""
-    cs = A.c_struct()
-    rc = lib().seer_spmv_auto(C.byref(cs), C.byref(tree.c), x.data_ptr(), y.data_ptr(),
-                              workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
+    if _lib is None:
+        lib()
+    rc = _marshal.spmv_auto(C.addressof(tree.c), A, x, y, workspace, _stream_handle(stream))
     if rc:
         raise SeerError(rc, "seer_spmv_auto")
 
@@ -408,14 +423,12 @@ class Model:
 def seer_spmv_model(A: DeviceCSR, model: Model, x, y, workspace, stream=None):
     """Classifier-selection inference; returns (path, kernel_id): path 0 = known model
     (kernel_id valid), 1 = features gathered on the device (kernel_id -1)."""
-    cs = A.c_struct()
-    path, kid = C.c_int(-1), C.c_int(-1)
-    rc = lib().seer_spmv_model(C.byref(cs), C.byref(model.c), x.data_ptr(), y.data_ptr(),
-                               workspace.data_ptr(), workspace.numel(), _stream_ptr(stream),
-                               C.byref(path), C.byref(kid))
+    if _lib is None:
+        lib()
+    rc, path, kid = _marshal.spmv_model(C.addressof(model.c), A, x, y, workspace, _stream_handle(stream))
     if rc:
         raise SeerError(rc, "seer_spmv_model")
-    return int(path.value), int(kid.value)
+    return path, kid
 
 
 def seer_model_host_ns(model: Model, rows: int, cols: int, nnz: int, reps: int = 2000) -> float:
@@ -517,13 +530,13 @@ def spmv_prepared_workspace_bytes(plan: Plan) -> int:
 
 def seer_spmv_prepared(plan: Plan, A: DeviceCSR, x, y, workspace=None, stream=None) -> None:
     """y = A x with a prepared plan; asynchronous on the stream."""
-    need = spmv_prepared_workspace_bytes(plan)
-    if need and workspace is None:
-        workspace = _temporary_workspace(need, A.row_ptr.device, stream)
-    cs = A.c_struct()
-    rc = lib().seer_spmv_prepared(C.byref(plan.c), C.byref(cs), x.data_ptr(), y.data_ptr(),
-                                  workspace.data_ptr() if workspace is not None else None,
-                                  workspace.numel() if workspace is not None else 0, _stream_ptr(stream))
+    if workspace is None:
+        need = spmv_prepared_workspace_bytes(plan)
+        if need:
+            workspace = _temporary_workspace(need, A.row_ptr.device, stream)
+    if _lib is None:
+        lib()
+    rc = _marshal.spmv_prepared(C.addressof(plan.c), A, x, y, workspace, _stream_handle(stream))
     if rc:
         raise SeerError(rc, f"seer_spmv_prepared(kernel {plan.kernel_id})")
 

@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -16,12 +17,25 @@ FLAGS = [
 ]
 
 
+MARSHAL = os.path.join(HERE, "_marshal.so")    # the binding's argument marshalling (host code only)
+
+
+def build_marshal(verbose: bool = False) -> str:
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"],
+           "-o", MARSHAL, os.path.join(CSRC, "marshal.c")]
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.check_call(cmd)
+    return MARSHAL
+
+
 def build_library(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc, *FLAGS, "-o", LIB, *[os.path.join(CSRC, s) for s in SOURCES]]
     if verbose:
         print(" ".join(cmd))
     subprocess.check_call(cmd)
+    build_marshal(verbose)
     return LIB
 
 

@@ -704,10 +704,6 @@ static int auto_check(const seer_csr *A, const seer_tree *tree, const float *x, 
 static int auto_enqueue(const seer_csr *A, const seer_tree *tree, const float *x, float *y, void *workspace,
                         void *stream)
 {
-    AutoTree dt;
-    std::memset(&dt, 0, sizeof dt);
-    dt.n_nodes = tree->n_nodes;
-    std::memcpy(dt.nodes, tree->nodes, sizeof(seer_node) * (size_t)tree->n_nodes);
     AutoShape sh;
     const bool vec = aligned16(A->col_idx) && aligned16(A->values) && g_tune_vec.load() != 0;
     sh.ranges = gather_ranges(A->cols, A->nnz, vec);
@@ -752,6 +748,12 @@ static int auto_enqueue(const seer_csr *A, const seer_tree *tree, const float *x
                             g_tune_select_wave.load() != 0, pr >= 256 ? (uint32_t)pr : 0u};
     AutoHeap heap;
     const bool flat = flatten_tree(tree, &heap);
+    AutoTree dt;                        // three kilobytes that only a tree too deep for the heap needs
+    if (!flat) {
+        std::memset(&dt, 0, sizeof dt);
+        dt.n_nodes = tree->n_nodes;
+        std::memcpy(dt.nodes, tree->nodes, sizeof(seer_node) * (size_t)tree->n_nodes);
+    }
     launch_auto(a, dt, flat ? &heap : nullptr, sh, vec, policy, decided ? &record : nullptr, workspace,
                 static_cast<hipStream_t>(stream));
     const hipError_t e = hipGetLastError();

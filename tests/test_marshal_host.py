@@ -1,0 +1,78 @@
+"""The native marshalling of the binding's asynchronous calls, without a GPU: what it hands to the
+library is what the same call through ctypes hands over.  Every input here is refused (or has no
+rows) before anything would be enqueued."""
+import ctypes as C
+
+import pytest
+import torch
+
+import paper_2403_17017_amd as S
+from paper_2403_17017_amd import binding as B
+
+
+def matrix(rows=4, cols=5, nnz=3):
+    return S.DeviceCSR(rows, cols, torch.zeros(rows + 1, dtype=torch.int32), torch.zeros(max(nnz, 1), dtype=torch.int32),
+                       torch.zeros(max(nnz, 1)), nnz)
+
+
+def through_ctypes(call, handle, A, x, y, ws):
+    L, cs = S.lib(), A.c_struct()
+    tail = (x.data_ptr(), y.data_ptr(), ws.data_ptr() if ws is not None else None, ws.numel() if ws is not None else 0, None)
+    if call == "spmv":
+        return L.seer_spmv(handle, C.byref(cs), *tail)
+    if call == "auto":
+        return L.seer_spmv_auto(C.byref(cs), C.byref(handle.c), *tail)
+    if call == "model":
+        return L.seer_spmv_model(C.byref(cs), C.byref(handle.c), *tail, None, None)
+    return L.seer_spmv_prepared(C.byref(handle.c), C.byref(cs), *tail)
+
+
+def through_marshal(call, handle, A, x, y, ws):
+    S.lib()
+    if call == "spmv":
+        return B._marshal.spmv(handle, A, x, y, ws, 0)
+    f = {"auto": B._marshal.spmv_auto, "model": B._marshal.spmv_model, "prepared": B._marshal.spmv_prepared}[call]
+    rc = f(C.addressof(handle.c), A, x, y, ws, 0)
+    return rc[0] if call == "model" else rc
+
+
+def handles(call):
+    if call == "spmv":
+        return [0, 3, 4, 5, 6, 8, 9, -1]
+    if call == "prepared":
+        return [S.Plan(B.seer_plan(k, rows, 3, 1, split, 0, None, 0), None) for k in (3, 5, 6, 7, 8, 99) for rows in (4, 5)
+                for split in (0, 1)]
+    deep = S.Tree([0, -1, -1], [1.0, 0, 0], [1, -1, -1], [7, -1, -1], [-1, 0, 1])          # a child that is not there
+    trees = [S.Tree.constant(S.CSR_MP), S.Tree.constant(S.CSR_A), deep]
+    return trees if call == "auto" else [S.Model(t) for t in trees]
+
+
+@pytest.mark.parametrize("call", ["spmv", "auto", "model", "prepared"])
+def test_same_status_as_through_ctypes(call):
+    both = torch.zeros(16)
+    aligned = torch.zeros(64, dtype=torch.uint8)
+    seen = set()
+    for h in handles(call):
+        for A in (matrix(), matrix(nnz=0), matrix(rows=0, nnz=0)):
+            for x, y in ((both[:5], both[2:6]), (both[:5], both[4:9])):             # overlapping: refused in every call
+                for ws in (None, aligned, aligned[1:]):
+                    if A.rows and not B.lib().seer_num_kernels() == S.NUM_KERNELS:
+                        continue
+                    want = through_ctypes(call, h, A, x, y, ws)
+                    assert through_marshal(call, h, A, x, y, ws) == want
+                    assert want <= 0 and (want < 0 or A.rows == 0)
+                    seen.add(want)
+    assert len(seen) >= 3                                                              # accepted, and refused in several ways
+
+
+def test_errors_of_the_objects_come_through():
+    S.lib()
+    x = torch.zeros(8)
+    with pytest.raises(AttributeError):
+        B._marshal.spmv(0, object(), x, x, None, 0)
+    with pytest.raises(AttributeError):
+        B._marshal.spmv(0, matrix(), 3, x, None, 0)
+    with pytest.raises(TypeError):
+        B._marshal.spmv(0, matrix(), x, x, None)
+    with pytest.raises(S.SeerError):
+        S.seer_spmv_prepared(handles("prepared")[0], matrix(), x, x, workspace=torch.zeros(64, dtype=torch.uint8), stream=0)
