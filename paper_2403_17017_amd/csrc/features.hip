@@ -12,12 +12,13 @@ __global__ __launch_bounds__(kFeatWG) void features_kernel(
     FeatureRaw *__restrict__ mailbox, uint64_t seq)
 {
     __shared__ FeatLds s;
-    features_total<VEC>(rows, rp, part, n_part, &s);
+    const int ends[2] = {rp[0], rp[rows]};
+    const FeatTotals t = features_total<VEC>(rows, rp, part, n_part, &s);
     if (threadIdx.x == 0) {
         FeatureRaw r;
-        r.max_len = s.mx; r.min_len = s.mn;
-        r.first = rp[0]; r.last = rp[rows];
-        r.sum_sq = s.sq; r.empty = s.em; r.seq = 0;
+        r.max_len = t.mx; r.min_len = t.mn;
+        r.first = ends[0]; r.last = ends[1];
+        r.sum_sq = t.sq; r.empty = t.em; r.seq = 0;
         *mailbox = r;
         __threadfence_system();            // the statistics land before the sequence number
         *reinterpret_cast<volatile uint64_t *>(&mailbox->seq) = seq;
@@ -241,8 +242,7 @@ void launch_features(int rows, const int *rp, void *workspace, FeatureRaw *mailb
     const uint32_t n_part = features_num_parts(rows);
     const bool vec = (reinterpret_cast<uintptr_t>(rp) & 15u) == 0;
     if (n_part) {                                    // a first pass, then one wave
-        if (vec) hipLaunchKernelGGL(features_partial_kernel<true>, dim3(n_part), dim3(kFeatPartWG), 0, st, rows, rp, part);
-        else hipLaunchKernelGGL(features_partial_kernel<false>, dim3(n_part), dim3(kFeatPartWG), 0, st, rows, rp, part);
+        launch_feature_partials(rows, rp, part, n_part, vec, st);
         hipLaunchKernelGGL(features_wave_kernel, dim3(1), dim3(kWave), 0, st, rows, rp, static_cast<const FeatPartial *>(part),
                            n_part, mailbox_dev, seq);
     } else if (vec) {

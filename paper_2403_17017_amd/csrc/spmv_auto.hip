@@ -73,7 +73,7 @@ __device__ __forceinline__ void derive_features_device(
     }
 }
 
-// One lane's work once the workgroup holds the matrix's statistics in *s: derive the
+// One lane's work once it holds the matrix's statistics: derive the
 // feature vector (into LDS, so that the tree can index it without forcing it into
 // private scratch memory), walk the tree where it lies in the kernel arguments, and, if
 // `sel` is given, leave the record that seer_spmv_auto_result reads.  Returns the kernel
@@ -81,11 +81,11 @@ __device__ __forceinline__ void derive_features_device(
 // measured: it is slower by more than a microsecond, the bulk read of the 3 KB argument
 // block costs more than the few nodes a walk touches.)
 __device__ __forceinline__ int select_on_device(
-    int rows, int cols, const int *__restrict__ rp, const FeatLds *s, float *s_f, const AutoTree &tree,
+    int rows, int cols, const int *__restrict__ rp, const FeatTotals &t, float *s_f, const AutoTree &tree,
     uint32_t reachable, AutoSel *__restrict__ sel)
 {
     const int64_t nnz = (int64_t)rp[rows] - (int64_t)rp[0];
-    derive_features_device(rows, cols, nnz, s->mx, s->mn, (int64_t)s->em, s->sq, s_f);
+    derive_features_device(rows, cols, nnz, t.mx, t.mn, (int64_t)t.em, t.sq, s_f);
     int n = 0, k = SEER_CSR_MP;            // a malformed tree cannot get here (host checks); MP is the safe answer
     for (int steps = 0; steps <= tree.n_nodes; ++steps) {
         const int feature = tree.nodes[n].feature;
@@ -98,8 +98,8 @@ __device__ __forceinline__ int select_on_device(
         sel->kernel_id = k;
         sel->valid = 1;
         sel->rows = rows; sel->cols = cols; sel->nnz = nnz;
-        sel->max_len = s->mx; sel->min_len = s->mn;
-        sel->sum_sq = s->sq; sel->empty = s->em;
+        sel->max_len = t.mx; sel->min_len = t.mn;
+        sel->sum_sq = t.sq; sel->empty = t.em;
 #pragma unroll
         for (int i = 0; i < SEER_NUM_FEATURES; ++i) sel->f[i] = s_f[i];
     }
@@ -223,8 +223,8 @@ __global__ __launch_bounds__(kFeatWG) void features_select_heap_kernel(
         hr = heap_load(heap);
         nnz = (int64_t)rp[rows] - (int64_t)rp[0];
     }
-    features_total<VEC>(rows, rp, part, n_part, &s);
-    if (threadIdx.x < kWave) select_in_wave(rows, cols, nnz, FeatTotals{s.mx, s.mn, s.sq, s.em}, hr, reachable, sel);
+    const FeatTotals t = features_total<VEC>(rows, rp, part, n_part, &s);
+    if (threadIdx.x < kWave) select_in_wave(rows, cols, nnz, t, hr, reachable, sel);
 }
 
 template <bool VEC>
@@ -234,8 +234,8 @@ __global__ __launch_bounds__(kFeatWG) void features_select_kernel(
 {
     __shared__ FeatLds s;
     __shared__ float s_f[SEER_NUM_FEATURES];
-    features_total<VEC>(rows, rp, part, n_part, &s);
-    if (threadIdx.x == 0) select_on_device(rows, cols, rp, &s, s_f, tree, reachable, sel);
+    const FeatTotals t = features_total<VEC>(rows, rp, part, n_part, &s);
+    if (threadIdx.x == 0) select_on_device(rows, cols, rp, t, s_f, tree, reachable, sel);
 }
 
 static_assert(kFeatMaxParts * sizeof(FeatPartial) <= kAutoSelOffset && sizeof(AutoSel) <= kAutoCarryOffset - kAutoSelOffset,
@@ -378,9 +378,8 @@ __global__ __launch_bounds__(kWG) void spmv_auto_fused_kernel(
         nnz_dev = (int64_t)rp[rows] - (int64_t)rp[0];
     }
     if (n_part == 0) {                                // block-uniform
-        features_accumulate_strided<RPVEC>(rows, rp, threadIdx.x, kWG, t.mx, t.mn, t.sq, t.em);
-        features_block_fold(t.mx, t.mn, t.sq, t.em, &s);
-        t = FeatTotals{s.mx, s.mn, s.sq, s.em};
+        features_accumulate_strided<RPVEC, 8>(rows, rp, threadIdx.x, kWG, t.mx, t.mn, t.sq, t.em);
+        t = features_block_fold<kWG>(t.mx, t.mn, t.sq, t.em, &s);
     } else if (first_wave) {
         t = fold_partials_wave(part, n_part);
     }
@@ -416,13 +415,13 @@ static uint32_t launch_fused_partials(const SpmvArgs &a, FeatPartial *part, bool
     const uint32_t rows = (uint32_t)a.rows;
     if (rows <= kAutoFusedParts * kFeatPartWG * 16u) {
         const uint32_t n = (rows + kFeatPartWG * 16u - 1u) / (kFeatPartWG * 16u);
-        if (rp_vec) hipLaunchKernelGGL((features_partial_kernel<true, kFeatPartWG>), dim3(n), dim3(kFeatPartWG), 0, st, a.rows, a.rp, part);
+        if (rp_vec) hipLaunchKernelGGL((features_partial_kernel<true, kFeatPartWG, 4>), dim3(n), dim3(kFeatPartWG), 0, st, a.rows, a.rp, part);
         else hipLaunchKernelGGL((features_partial_kernel<false, kFeatPartWG>), dim3(n), dim3(kFeatPartWG), 0, st, a.rows, a.rp, part);
         return n;
     }
     uint32_t n = (rows + kFeatWG * 16u - 1u) / (kFeatWG * 16u);
     n = n > kAutoFusedParts ? kAutoFusedParts : n;
-    if (rp_vec) hipLaunchKernelGGL((features_partial_kernel<true, kFeatWG>), dim3(n), dim3(kFeatWG), 0, st, a.rows, a.rp, part);
+    if (rp_vec) hipLaunchKernelGGL((features_partial_kernel<true, kFeatWG, 4>), dim3(n), dim3(kFeatWG), 0, st, a.rows, a.rp, part);
     else hipLaunchKernelGGL((features_partial_kernel<false, kFeatWG>), dim3(n), dim3(kFeatWG), 0, st, a.rows, a.rp, part);
     return n;
 }
@@ -500,9 +499,8 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
     }
 
     const uint32_t n_part = features_num_parts(a.rows, policy.part_rows);
+    if (n_part) launch_feature_partials(a.rows, a.rp, part, n_part, rp_vec, st);
     if (rp_vec) {
-        if (n_part)
-            hipLaunchKernelGGL(features_partial_kernel<true>, dim3(n_part), dim3(kFeatPartWG), 0, st, a.rows, a.rp, part);
         if (heap && n_part && policy.select_wave)
             hipLaunchKernelGGL(features_select_wave_kernel, dim3(1), dim3(kWave), 0, st, a.rows, a.cols, a.rp, part,
                                n_part, sel, *heap, shape.reachable);
@@ -513,8 +511,6 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
             hipLaunchKernelGGL(features_select_kernel<true>, dim3(1), dim3(kFeatWG), 0, st, a.rows, a.cols, a.rp, part,
                                n_part, sel, tree, shape.reachable);
     } else {
-        if (n_part)
-            hipLaunchKernelGGL(features_partial_kernel<false>, dim3(n_part), dim3(kFeatPartWG), 0, st, a.rows, a.rp, part);
         if (heap && n_part && policy.select_wave)
             hipLaunchKernelGGL(features_select_wave_kernel, dim3(1), dim3(kWave), 0, st, a.rows, a.cols, a.rp, part,
                                n_part, sel, *heap, shape.reachable);

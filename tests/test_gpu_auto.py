@@ -379,3 +379,29 @@ def test_builtin_model_chooses_like_the_shipped_trees(cases):
             rc = L.seer_spmv_plan(C.byref(cs), None, n, plan_mem.data_ptr(), plan_mem.numel(), fws.data_ptr(), fws.numel(),
                                   None, C.byref(c), C.byref(pp0))
             assert rc == 0 and (pp0.value, c.kernel_id) == (pp1, plan1.kernel_id), (A.name, n)
+
+
+@pytest.mark.parametrize("rows", [1, 3, 4, 5, 255, 1023, 1024, 1025, 8191, 8192, 8193, 10_241, 32_771, 524_287, 2_097_152,
+                                  2_097_155, 4_300_001])
+def test_statistics_at_the_edges_of_the_reduction(rows):
+    """Row counts around one workgroup's lanes, its loads in flight, the single launch, whole and
+    ragged parts of the first pass; lengths whose squares need 64 bits and empty rows at both ends."""
+    import torch
+    rng = np.random.default_rng(rows)
+    lens = rng.integers(0, 5, rows).astype(np.int64)
+    lens[0] = 0
+    lens[rows // 2] = 1_000_003
+    lens[rows - 1] = 0 if rows > 2 else 77
+    rp = np.zeros(rows + 1, np.int32)
+    rp[1:] = np.cumsum(lens)
+    announce(f"statistics of {rows} rows")
+    want = O.features(rows, 2_000_000, rp)
+    for shift in (0, 1):                                  # row_ptr on 16 bytes, and 4 bytes past that
+        d = torch.zeros(rows + 1 + shift, dtype=torch.int32, device="cuda:0")
+        d[shift:] = torch.from_numpy(rp).cuda()
+        A = S.DeviceCSR(rows, 2_000_000, d[shift:], torch.zeros(1, dtype=torch.int32, device="cuda:0"),
+                        torch.zeros(1, device="cuda:0"), 0)
+        f = S.seer_features(A)
+        for k in ("max_len", "min_len", "empty_rows", "sum_sq_len"):
+            assert int(getattr(f, k)) == int(want[k]), k
+        assert f.vector().tobytes() == want["f"].tobytes()
