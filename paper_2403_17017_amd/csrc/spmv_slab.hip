@@ -81,36 +81,45 @@ __device__ __forceinline__ SlabWalk slab_walk_begin(
     return w;
 }
 
-// One step: the lane's entry (row i, column c, slab s), whether it is valid, and the first
-// entry of its piece.  Updates the carry.  All lanes of the wave call it together.
-__device__ __forceinline__ uint32_t slab_walk_step(
-    SlabWalk &w, uint32_t base, uint32_t lane, int shift, uint32_t n_slabs, const int *__restrict__ ci,
-    const int *__restrict__ crow, bool &valid, uint32_t &i, int &c, uint32_t &s, bool &descends)
+// One step over the entries base + lane, already fetched (row i, column c): the lane's slab,
+// whether it starts a piece, whether its column descends, the row and slab of the entry before
+// it, and the first entry of its own piece (`mine`) and of the piece before it (`before`: where
+// that piece started, if the lane starts a new one).  Updates the carry.  All lanes of the wave
+// call it together.
+struct SlabStep {
+    uint32_t s, pi, ps, mine, before;
+    bool starts, descends;
+};
+__device__ __forceinline__ SlabStep slab_walk_step(
+    SlabWalk &w, uint32_t base, uint32_t lane, int shift, uint32_t n_slabs, bool valid, uint32_t i, int c)
 {
-    const uint32_t k = base + lane;
-    valid = k < w.k1;
-    i = valid ? (uint32_t)crow[k] : 0u;
-    c = valid ? ci[k] : 0;
-    s = min((uint32_t)c >> shift, n_slabs - 1u);
-    uint32_t pi = (uint32_t)__shfl_up((int)i, 1), ps = (uint32_t)__shfl_up((int)s, 1);
-    int pc = __shfl_up(c, 1);
-    if (lane == 0) { pi = w.last_i; ps = w.last_s; pc = w.last_c; }
-    const bool starts = valid && (i != pi || s != ps);
-    descends = valid && i == pi && c < pc;
-    const uint64_t mask = __ballot(starts);
-    const uint64_t upto = mask & (lane == kWave - 1 ? ~0ull : ((1ull << (lane + 1u)) - 1ull));
-    const uint32_t mine = upto ? base + 63u - (uint32_t)__clzll((long long)upto) : w.cur_start;
+    SlabStep r;
+    r.s = min((uint32_t)c >> shift, n_slabs - 1u);
+    // the lane before (DPP wave shift by one; lane 0: the carry)
+    r.pi = (uint32_t)__builtin_amdgcn_update_dpp((int)w.last_i, (int)i, 0x138, 0xF, 0xF, false);
+    r.ps = (uint32_t)__builtin_amdgcn_update_dpp((int)w.last_s, (int)r.s, 0x138, 0xF, 0xF, false);
+    const int pc = __builtin_amdgcn_update_dpp(w.last_c, c, 0x138, 0xF, 0xF, false);
+    r.starts = valid && (i != r.pi || r.s != r.ps);
+    r.descends = valid && i == r.pi && c < pc;
+    const uint64_t mask = __ballot(r.starts), below = mask & ((1ull << lane) - 1ull);
+    r.before = below ? base + 63u - (uint32_t)__clzll((long long)below) : w.cur_start;
+    r.mine = r.starts ? base + lane : r.before;
     if (mask) w.cur_start = base + 63u - (uint32_t)__clzll((long long)mask);
-    const int last = (int)min(w.k1 - base, (uint32_t)kWave) - 1;
-    w.last_i = (uint32_t)__shfl((int)i, last);
-    w.last_s = (uint32_t)__shfl((int)s, last);
-    w.last_c = __shfl(c, last);
-    return mine;
+    const int last = __builtin_amdgcn_readfirstlane((int)min(w.k1 - base, (uint32_t)kWave) - 1);
+    w.last_i = (uint32_t)__builtin_amdgcn_readlane((int)i, last);
+    w.last_s = (uint32_t)__builtin_amdgcn_readlane((int)r.s, last);
+    w.last_c = __builtin_amdgcn_readlane(c, last);
+    return r;
 }
 
-// preprocessing 1: entries per virtual row (cnt [S * rows + 1], zero on entry), written by the
-// last entry of each piece; *flag is set if some row's columns do not ascend or lie outside
-// the matrix (then the form is refused instead of written out of bounds).
+// preprocessing 1: entries per virtual row (cnt [S * rows + 1], zero on entry), written where
+// the next piece starts (the matrix's last one by the wave that holds the last entry); *flag is
+// set if some row's columns do not ascend or lie outside the matrix (then the form is refused
+// instead of written out of bounds).
+// Both walks fetch kSlabAhead steps at once: with one step's loads in flight a wave spent its time
+// waiting for them (40 M entries: this pass 134 us, now 86, the scatter 283 us, now 224).
+constexpr uint32_t kSlabAhead = 4;
+
 __global__ __launch_bounds__(kWG) void slab_count_kernel(
     int rows, int cols, uint32_t nnz, int shift, uint32_t n_slabs, const int *__restrict__ rp,
     const int *__restrict__ ci, const int *__restrict__ crow, uint32_t *__restrict__ cnt, int *__restrict__ flag)
@@ -118,38 +127,58 @@ __global__ __launch_bounds__(kWG) void slab_count_kernel(
     const uint32_t lane = threadIdx.x % kWave;
     SlabWalk w = slab_walk_begin(nnz, shift, n_slabs, rp, ci, crow);
     bool bad = false;
-    for (uint32_t base = w.k0; base < w.k1; base += kWave) {       // wave-uniform
-        bool valid, desc;
-        uint32_t i, s;
-        int c;
-        const uint32_t mine = slab_walk_step(w, base, lane, shift, n_slabs, ci, crow, valid, i, c, s, desc);
-        bad |= desc || (valid && (uint32_t)c >= (uint32_t)cols);
-        if (!valid) continue;
-        const uint32_t k = base + lane;
-        bool ends = k + 1u == nnz;
-        if (!ends) {
-            const uint32_t ni = (uint32_t)crow[k + 1u];
-            const uint32_t ns = min((uint32_t)ci[k + 1u] >> shift, n_slabs - 1u);
-            ends = ni != i || ns != s;
+    for (uint32_t base = w.k0; base < w.k1; base += kWave * kSlabAhead) {       // wave-uniform
+        uint32_t i[kSlabAhead];
+        int c[kSlabAhead];
+#pragma unroll
+        for (uint32_t u = 0; u < kSlabAhead; ++u) {
+            const uint32_t k = min(base + u * kWave + lane, w.k1 - 1u);
+            i[u] = (uint32_t)crow[k];
+            c[u] = ci[k];
         }
-        if (ends) cnt[(size_t)s * (uint32_t)rows + i] = k + 1u - mine;
+#pragma unroll
+        for (uint32_t u = 0; u < kSlabAhead; ++u) {
+            const uint32_t b = base + u * kWave;
+            if (b >= w.k1) break;                                               // wave-uniform
+            const bool valid = b + lane < w.k1;
+            const SlabStep r = slab_walk_step(w, b, lane, shift, n_slabs, valid, i[u], c[u]);
+            bad |= r.descends || (valid && (uint32_t)c[u] >= (uint32_t)cols);
+            if (r.starts && b + lane > 0u) cnt[(size_t)r.ps * (uint32_t)rows + r.pi] = b + lane - r.before;
+        }
     }
+    if (lane == 0 && w.k0 < w.k1 && w.k1 == nnz) cnt[(size_t)w.last_s * (uint32_t)rows + w.last_i] = nnz - w.cur_start;
     if (bad) *flag = 1;
 }
 
 // ---- preprocessing 2: exclusive prefix sum over n unsigned words, in place, in three kinds
 // of launches: sums of tiles of 2048, the same prefix sum over those sums (recursively), and
 // the tiles again with their offsets.  The total stays below 2^31 (it is nnz).
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+// A lane's eight words, as two 16-byte accesses unless the tile is cut by the end (base is a
+// multiple of eight and the arrays start on 256 bytes; with eight 4-byte accesses behind bounds
+// checks the two passes over 8 M words took 16 and 34 us, now 6 and 12).
+__device__ __forceinline__ void scan_load(const uint32_t *__restrict__ p, size_t base, size_t n, uint32_t *v)
+{
+    if (base + kScanItems <= n) {
+        const v4u a = *reinterpret_cast<const v4u *>(p + base), b = *reinterpret_cast<const v4u *>(p + base + 4);
+        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+    } else {
+#pragma unroll
+        for (uint32_t j = 0; j < kScanItems; ++j) v[j] = base + j < n ? p[base + j] : 0u;
+    }
+}
+
 __global__ __launch_bounds__(kWG) void scan_tile_sums_kernel(const uint32_t *__restrict__ in, size_t n, uint32_t *__restrict__ sums)
 {
     __shared__ uint32_t s_w[kWG / kWave];
     const size_t base = (size_t)blockIdx.x * kScanTile + (size_t)threadIdx.x * kScanItems;
-    uint32_t t = 0;
+    uint32_t v[kScanItems], t = 0;
+    scan_load(in, base, n, v);
 #pragma unroll
-    for (uint32_t j = 0; j < kScanItems; ++j)
-        if (base + j < n) t += in[base + j];
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) t += (uint32_t)__shfl_xor((int)t, off);
+    for (uint32_t j = 0; j < kScanItems; ++j) t += v[j];
+    t = wave_fold(t, [](uint32_t a, uint32_t b) { return a + b; });
     if (threadIdx.x % kWave == 0) s_w[threadIdx.x / kWave] = t;
     __syncthreads();
     if (threadIdx.x == 0) sums[blockIdx.x] = (s_w[0] + s_w[1]) + (s_w[2] + s_w[3]);
@@ -161,11 +190,9 @@ __global__ __launch_bounds__(kWG) void scan_tiles_kernel(uint32_t *__restrict__ 
     const uint32_t lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     const size_t base = (size_t)blockIdx.x * kScanTile + (size_t)threadIdx.x * kScanItems;
     uint32_t v[kScanItems], t = 0;
+    scan_load(data, base, n, v);
 #pragma unroll
-    for (uint32_t j = 0; j < kScanItems; ++j) {
-        v[j] = base + j < n ? data[base + j] : 0u;
-        t += v[j];
-    }
+    for (uint32_t j = 0; j < kScanItems; ++j) t += v[j];
     uint32_t incl = t;                               // inclusive sum over the lanes of the wave
 #pragma unroll
     for (int off = 1; off < kWave; off <<= 1) {
@@ -179,8 +206,17 @@ __global__ __launch_bounds__(kWG) void scan_tiles_kernel(uint32_t *__restrict__ 
     uint32_t run = before + (incl - t);
 #pragma unroll
     for (uint32_t j = 0; j < kScanItems; ++j) {
-        if (base + j < n) data[base + j] = run;
-        run += v[j];
+        const uint32_t next = run + v[j];
+        v[j] = run;
+        run = next;
+    }
+    if (base + kScanItems <= n) {
+        *reinterpret_cast<v4u *>(data + base) = v4u{v[0], v[1], v[2], v[3]};
+        *reinterpret_cast<v4u *>(data + base + 4) = v4u{v[4], v[5], v[6], v[7]};
+    } else {
+#pragma unroll
+        for (uint32_t j = 0; j < kScanItems; ++j)
+            if (base + j < n) data[base + j] = v[j];
     }
 }
 
@@ -215,16 +251,32 @@ __global__ __launch_bounds__(kWG) void slab_scatter_kernel(
 {
     const uint32_t lane = threadIdx.x % kWave;
     SlabWalk w = slab_walk_begin(nnz, shift, n_slabs, rp, ci, crow);
-    for (uint32_t base = w.k0; base < w.k1; base += kWave) {       // wave-uniform
-        bool valid, desc;
-        uint32_t i, s;
-        int c;
-        const uint32_t mine = slab_walk_step(w, base, lane, shift, n_slabs, ci, crow, valid, i, c, s, desc);
-        if (!valid) continue;
-        const uint32_t k = base + lane;
-        const uint32_t dst = rp_v[(size_t)s * (uint32_t)rows + i] + (k - mine);
-        out_ci[dst] = c;
-        out_va[dst] = va[k];
+    for (uint32_t base = w.k0; base < w.k1; base += kWave * kSlabAhead) {       // wave-uniform
+        uint32_t i[kSlabAhead], dst[kSlabAhead];
+        int c[kSlabAhead];
+        float v[kSlabAhead];
+#pragma unroll
+        for (uint32_t u = 0; u < kSlabAhead; ++u) {
+            const uint32_t k = min(base + u * kWave + lane, w.k1 - 1u);
+            i[u] = (uint32_t)__builtin_nontemporal_load(crow + k);   // (the streams leave L2 to the lines being written)
+            c[u] = __builtin_nontemporal_load(ci + k);
+            v[u] = __builtin_nontemporal_load(va + k);
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kSlabAhead; ++u) {
+            const uint32_t b = base + u * kWave;
+            dst[u] = 0;
+            if (b >= w.k1) continue;                                            // wave-uniform
+            const bool valid = b + lane < w.k1;
+            const SlabStep r = slab_walk_step(w, b, lane, shift, n_slabs, valid, i[u], c[u]);
+            if (valid) dst[u] = rp_v[(size_t)r.s * (uint32_t)rows + i[u]] + (b + lane - r.mine);
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kSlabAhead; ++u) {
+            if (base + u * kWave + lane >= w.k1) continue;
+            out_ci[dst[u]] = c[u];
+            out_va[dst[u]] = v[u];
+        }
     }
 }
 
