@@ -167,8 +167,11 @@ uint32_t gather_ticks(const GatherRanges &g, int64_t nnz, double entries_per_wg,
 // longer than a wave get 16 per block, the most for which the kernel shares out the lanes
 // among the rows (16 lanes each) -- fewer only where that would put more than 12 K
 // nonzeros into a block (measured best at mean lengths 65 to 500: 16 rows; 1200: 4 to 8;
-// 2000: 8).  A small matrix is cut finer (down to about one LDS chunk per block) so
-// that every CU gets at least four blocks.
+// 2000: 8).  A small matrix is cut finer, to blocks of about one LDS chunk, until every CU has
+// four of them, and as far as there are not more than that, to blocks of about 500 nonzeros (long
+// rows: 800), for it is all latency: 20 011 rows of 20 in 626 blocks 4.1 us,
+// in 313 (of 1250 nonzeros, the limit before) 4.8; 8003 rows of 15 3.3 and 4.4; 40 003 of 8 3.9
+// and 5.1; 4096 of 16 2.6 and 2.9; with 200 nonzeros or fewer per block every one of them is slower.
 // With gathers ordered by column range (bm_ranged) a block is three quarters of one chunk of
 // 4096: a second chunk would take a second turn over x (2 M columns, 20 per row: 281 us, 290 at
 // 3700 entries, 311 at 7300, 303 at 1500), and 256 rows at most, one per lane (16 long ones, as
@@ -195,6 +198,8 @@ int bm_rows(int rows, int nnz, bool ranged)
         while (r < 1024 && (double)r * mean * 1.41421356 < target) r <<= 1;   // nearest power of two
     }
     while (r > 1 && rows / r < 1024 && (double)r * mean > 2048.0) r >>= 1;
+    const double least = mean > 64.0 ? 1024.0 : 768.0;
+    while (r > 1 && 2 * (int64_t)rows <= 1024 * (int64_t)r && (double)r * mean > least) r >>= 1;
     return r;
 }
 
