@@ -117,15 +117,21 @@ int wm_lanes(int rows, int nnz)
     return g;
 }
 
+constexpr int64_t kAdaptRangedNnz = 1 << 21;
+
 // Whether the gathers of CSR,MP, CSR,WO, CSR,A and (bm_ranged) CSR,BM are ordered in time by column range
 // (ranged_chunk_finish), and into how many ranges: where the 16-byte loads are used, x is larger
 // than an XCD's 4 MB L2 (measured, without and with: 4 MB 148 and 147 us, 4.6 MB 151 and 143, 5.7
 // MB 116 and 105) and not so large that hardly any line is wanted twice while a range lasts (61
-// MB 1044 and 654, 122 MB 1026 and 797), and there is more than one generation of workgroups.
+// MB 1044 and 654, 122 MB 1026 and 797), and there is more than one generation of workgroups:
+// below 2^23 entries random columns gain (2.5 M in 7.6 MB of x: CSR,WO 31.4 and 27.6 us; but
+// CSR,MP 35.4 and 37.4), stencils and bands lose (a stencil of 7.2 M: CSR,WO 21.3 and 22.4).
+// CSR,A gains on all of those, down to 2^21 entries (kAdaptRangedNnz: random 2.1 M 27.4 and 23.5,
+// 7 M 77.4 and 62.1; bands and stencils of 4 to 9 M 15.2 and 14.5, 17.9 and 17.5, 21.2 and 20.4).
 // Ranges of 1 MB or more, at most sixteen: fewer and larger ones leave L2 no room for the
 // streams, more cost a pass over the entries each (8 MB of x: 8 ranges 289 us, 16 290, 4 297).
 // The "gather_range" knob: 0 never, 1..28 log2 of the columns per range whatever the sizes.
-GatherRanges gather_ranges(int64_t cols, int64_t nnz, bool vec)
+GatherRanges gather_ranges(int64_t cols, int64_t nnz, bool vec, int64_t at_least = 1 << 23)
 {
     GatherRanges g{};
     const int t = g_tune_gather_range.load();
@@ -133,7 +139,7 @@ GatherRanges gather_ranges(int64_t cols, int64_t nnz, bool vec)
     if (t >= 1 && t <= 28) {
         shift = t;
     } else {
-        if (t == 0 || cols <= 5 << 18 || cols > 32 << 20 || nnz < 1 << 23) return g;
+        if (t == 0 || cols <= 5 << 18 || cols > 32 << 20 || nnz < at_least) return g;
         while (((cols - 1) >> shift) + 1 > 16) ++shift;
     }
     const int64_t count = ((std::max<int64_t>(cols, 1) - 1) >> shift) + 1;
@@ -980,6 +986,7 @@ static int spmv_dispatch(int kernel_id, const seer_csr *A, const float *x, float
             return SEER_EWORKSPACE;
         void *plan_mem = static_cast<char *>(workspace) + carry;
         launch_adaptive_plan(A->rows, A->nnz, A->row_ptr, plan_mem, false, st);
+        a.ranges = gather_ranges(A->cols, A->nnz, vec, kAdaptRangedNnz);
         a.ranges.ticks = gather_ticks(a.ranges, A->nnz, kAdaptEntries, 8);
         launch_adaptive(a, vec, plan_mem, workspace, st);
         break;
@@ -1221,7 +1228,7 @@ int seer_spmv_prepared(const seer_plan *plan, const seer_csr *A, const float *x,
     SpmvArgs a{A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, x, y, use_remap(),
                use_nt_repeated(csr_footprint(A))};
     const bool vec = aligned16(A->col_idx) && aligned16(A->values) && g_tune_vec.load() != 0;
-    a.ranges = gather_ranges(A->cols, A->nnz, vec);
+    a.ranges = gather_ranges(A->cols, A->nnz, vec, kAdaptRangedNnz);
     a.ranges.ticks = gather_ticks(a.ranges, A->nnz, kAdaptEntries, 8);
     launch_adaptive(a, vec, plan->device, carry, static_cast<hipStream_t>(stream));
     const hipError_t e = hipGetLastError();

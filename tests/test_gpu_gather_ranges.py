@@ -110,3 +110,22 @@ def test_misaligned_entries_and_odd_range_counts_take_the_plain_order():
             got = run_spmv(k, dA, xd, A.rows)
             assert_parity(got, y_ref, bound, f"kernel {k}")
             assert got.tobytes() == plain.tobytes()
+
+
+@pytest.mark.parametrize("nnz", [(1 << 21) - 1, 1 << 21])
+def test_adaptive_from_two_million_entries_on(nnz):
+    """Either side of the size from which CSR,A orders its gathers by itself: the same bits."""
+    import torch
+    A = G.explicit_lengths([21] * (nnz // 21) + [nnz % 21], (5 << 18) + 1, 95, f"rows-of-21-{nnz}")
+    assert A.nnz == nnz
+    dA, xd = upload(A), torch.from_numpy(G.dense_vector(A.cols, 6)).cuda()
+    S.set_tuning("gather_range", 0)
+    plain = run_spmv(S.CSR_A, dA, xd, A.rows)
+    S.set_tuning("gather_range", -1)
+    y_ref, bound = oracle_of(A, xd.cpu().numpy())
+    plan, y = S.seer_spmv_prepare(S.CSR_A, dA), torch.full((A.rows,), float("nan"), device="cuda:0")
+    S.seer_spmv_prepared(plan, dA, xd, y)
+    torch.cuda.synchronize()
+    for got in (run_spmv(S.CSR_A, dA, xd, A.rows), y.cpu().numpy()):
+        assert_parity(got, y_ref, bound, f"CSR,A at {nnz} entries")
+        assert got.tobytes() == plain.tobytes()
