@@ -127,7 +127,8 @@ constexpr int64_t kAdaptRangedNnz = 1 << 21;
 // below 2^23 entries random columns gain (2.5 M in 7.6 MB of x: CSR,WO 31.4 and 27.6 us; but
 // CSR,MP 35.4 and 37.4), stencils and bands lose (a stencil of 7.2 M: CSR,WO 21.3 and 22.4).
 // CSR,A gains on all of those, down to 2^21 entries (kAdaptRangedNnz: random 2.1 M 27.4 and 23.5,
-// 7 M 77.4 and 62.1; bands and stencils of 4 to 9 M 15.2 and 14.5, 17.9 and 17.5, 21.2 and 20.4).
+// 7 M 77.4 and 62.1; bands and stencils of 4 to 9 M 15.2 and 14.5, 17.9 and 17.5, 21.2 and 20.4), from
+// 5.5 MB of x on (5.3 MB 36.8 and 38.0, 5.7 MB 52.7 and 47.2).
 // Ranges of 1 MB or more, at most sixteen: fewer and larger ones leave L2 no room for the
 // streams, more cost a pass over the entries each (8 MB of x: 8 ranges 289 us, 16 290, 4 297).
 // The "gather_range" knob: 0 never, 1..28 log2 of the columns per range whatever the sizes.
@@ -139,7 +140,7 @@ GatherRanges gather_ranges(int64_t cols, int64_t nnz, bool vec, int64_t at_least
     if (t >= 1 && t <= 28) {
         shift = t;
     } else {
-        if (t == 0 || cols <= 5 << 18 || cols > 32 << 20 || nnz < at_least) return g;
+        if (t == 0 || cols <= (nnz < 1 << 23 ? 11 << 17 : 5 << 18) || cols > 32 << 20 || nnz < at_least) return g;
         while (((cols - 1) >> shift) + 1 > 16) ++shift;
     }
     const int64_t count = ((std::max<int64_t>(cols, 1) - 1) >> shift) + 1;
@@ -249,6 +250,11 @@ int mp_ipt(int rows, int nnz)
 
 // Entries a workgroup of each schedule has under way at a time, on average.
 constexpr double kAdaptEntries = 2048.0;
+// CSR,A's blocks hold more than their nominal share and end at different times: at the pace of the
+// other schedules its waves fell behind the clock (4 M rows of 4: 161.6 us a product, now 145.4; 2 M
+// of 5 81.9 and 76.2; 8 M of 8 862 and 687; 6 M columns 166 and 123; power-law 241.6 and 225.4; 110
+// is still too fast for some, 118 the best for most, 140 slower again).
+constexpr int kAdaptPacePercent = 125;
 double wo_entries(int nnz) { return nnz >= 1 << 23 ? 4096.0 : 2048.0; }
 double mp_entries(int rows, int nnz, int ipt) { return 256.0 * ipt * ((double)nnz / ((double)rows + (double)nnz)); }
 double bm_entries(int rows, int nnz, int rows_per_block)
@@ -987,7 +993,7 @@ static int spmv_dispatch(int kernel_id, const seer_csr *A, const float *x, float
         void *plan_mem = static_cast<char *>(workspace) + carry;
         launch_adaptive_plan(A->rows, A->nnz, A->row_ptr, plan_mem, false, st);
         a.ranges = gather_ranges(A->cols, A->nnz, vec, kAdaptRangedNnz);
-        a.ranges.ticks = gather_ticks(a.ranges, A->nnz, kAdaptEntries, 8);
+        a.ranges.ticks = gather_ticks(a.ranges, A->nnz, kAdaptEntries, 8) * kAdaptPacePercent / 100;
         launch_adaptive(a, vec, plan_mem, workspace, st);
         break;
     }
@@ -1229,7 +1235,7 @@ int seer_spmv_prepared(const seer_plan *plan, const seer_csr *A, const float *x,
                use_nt_repeated(csr_footprint(A))};
     const bool vec = aligned16(A->col_idx) && aligned16(A->values) && g_tune_vec.load() != 0;
     a.ranges = gather_ranges(A->cols, A->nnz, vec, kAdaptRangedNnz);
-    a.ranges.ticks = gather_ticks(a.ranges, A->nnz, kAdaptEntries, 8);
+    a.ranges.ticks = gather_ticks(a.ranges, A->nnz, kAdaptEntries, 8) * kAdaptPacePercent / 100;
     launch_adaptive(a, vec, plan->device, carry, static_cast<hipStream_t>(stream));
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? SEER_OK : hip_fail(e);

@@ -116,7 +116,7 @@ def test_misaligned_entries_and_odd_range_counts_take_the_plain_order():
 def test_adaptive_from_two_million_entries_on(nnz):
     """Either side of the size from which CSR,A orders its gathers by itself: the same bits."""
     import torch
-    A = G.explicit_lengths([21] * (nnz // 21) + [nnz % 21], (5 << 18) + 1, 95, f"rows-of-21-{nnz}")
+    A = G.explicit_lengths([21] * (nnz // 21) + [nnz % 21], (11 << 17) + 1, 95, f"rows-of-21-{nnz}")
     assert A.nnz == nnz
     dA, xd = upload(A), torch.from_numpy(G.dense_vector(A.cols, 6)).cuda()
     S.set_tuning("gather_range", 0)
