@@ -181,13 +181,14 @@ uint32_t gather_ticks(const GatherRanges &g, int64_t nnz, double entries_per_wg,
 // and 5.1; 4096 of 16 2.6 and 2.9; with 200 nonzeros or fewer per block every one of them is slower.
 // With gathers ordered by column range (bm_ranged) a block is three quarters of one chunk of
 // 4096: a second chunk would take a second turn over x (2 M columns, 20 per row: 281 us, 290 at
-// 3700 entries, 311 at 7300, 303 at 1500), and 256 rows at most, one per lane (16 long ones, as
-// above).  Not with rows of at most eight entries: fat blocks in small chunks whose loads run
-// ahead suit stencils better than scattered columns gain (5-point 67 us, by range 75).
+// 3700 entries, 311 at 7300, 303 at 1500), and 256 rows at most, one per lane.  Not with rows longer
+// than 64 on average (480 M nonzeros of a power law, 240 per row: 3290 us, by range 3730), nor with
+// rows of at most eight entries: fat blocks in small chunks whose loads run ahead suit stencils better than scattered columns gain (5-point 67 us, by range 75).
 bool bm_ranged(const GatherRanges &g, int rows, int nnz)
 {
     const int t = g_tune_bm_rows.load();
-    return g.count && (int64_t)nnz > 8 * (int64_t)rows && !(t >= 1 && t <= kBmMaxRows);
+    return g.count && (int64_t)nnz > 8 * (int64_t)rows && (int64_t)nnz <= 64 * (int64_t)rows &&
+           !(t >= 1 && t <= kBmMaxRows);
 }
 
 int bm_rows(int rows, int nnz, bool ranged)
@@ -195,7 +196,7 @@ int bm_rows(int rows, int nnz, bool ranged)
     const int t = g_tune_bm_rows.load();
     if (t >= 1 && t <= kBmMaxRows) return t;
     const double mean = rows > 0 ? (double)nnz / (double)rows : 0.0;
-    if (ranged) return (int)std::min(mean > 64.0 ? 16.0 : 256.0, std::max(1.0, 3000.0 / std::max(mean, 1.0)));
+    if (ranged) return (int)std::min(256.0, 3000.0 / std::max(mean, 1.0));
     int r = 1;
     if (mean > 64.0) {
         r = 16;

@@ -289,12 +289,8 @@ __device__ __forceinline__ void auto_dispatch(
             if (shape.bm_ranged) {
                 GatherRanges g = shape.ranges;
                 g.ticks = shape.bm_ticks;
-                if (shape.bm_rows <= (int)kWoGroupRows)
-                    bm_body<kRangedChunk, VEC, true, false, false, true, 256, true>(rows, rp, ci, va, x, y, shape.bm_rows,
-                                                                                    shape.bm_own_shift, tile, s_prod, g);
-                else
-                    bm_body<kRangedChunk, VEC, true, false, false, false, 256, true>(rows, rp, ci, va, x, y, shape.bm_rows,
-                                                                                     shape.bm_own_shift, tile, s_prod, g);
+                bm_body<kRangedChunk, VEC, true, false, false, false, 256, true>(rows, rp, ci, va, x, y, shape.bm_rows,
+                                                                                 shape.bm_own_shift, tile, s_prod, g);
                 return;
             }
         }

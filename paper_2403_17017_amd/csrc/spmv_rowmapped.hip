@@ -99,9 +99,9 @@ static void launch_bm_v(const SpmvArgs &a, int rows_per_block, hipStream_t st)
     hipLaunchKernelGGL((spmv_bm_kernel<CH, VEC, NT, G, M, RANGED>), dim3(grid_for(n_tiles, a.remap)), dim3(kWG), 0, st, \
                        a.rows, a.rp, a.ci, a.va, a.x, a.y, rows_per_block, own_shift, n_tiles, a.remap, a.ranges)
     // rows of well over a hundred entries: several lanes per row; else the smallest instance that
-    // fits (RANGED: the caller keeps it at 256 rows)
-    if (rows_per_block <= (int)kWoGroupRows) SEER_BM_LAUNCH(true, 256);
-    else if constexpr (RANGED) SEER_BM_LAUNCH(false, 256);
+    // fits (RANGED: the caller keeps it between 46 and 256 rows)
+    if constexpr (RANGED) SEER_BM_LAUNCH(false, 256);
+    else if (rows_per_block <= (int)kWoGroupRows) SEER_BM_LAUNCH(true, 256);
     else if (rows_per_block <= 256) SEER_BM_LAUNCH(false, 256);
     else if (rows_per_block <= 1024) SEER_BM_LAUNCH(false, 1024);
     else SEER_BM_LAUNCH(false, kBmMaxRows);
