@@ -343,6 +343,8 @@ def seer_spmv(kernel_id: int, A: DeviceCSR, x, y, workspace=None, stream=None) -
     need = spmv_workspace_bytes(kernel_id, A.rows, A.nnz) if 0 <= kernel_id < NUM_KERNELS else 0
     if need and workspace is None:
         workspace = _temporary_workspace(need, A.row_ptr.device, stream)
+    if _lib is None:
+        lib()
     rc = _marshal.spmv(int(kernel_id), A, x, y, workspace, _stream_handle(stream))
     if rc:
         raise SeerError(rc, f"seer_spmv(kernel {kernel_id})")

@@ -2,6 +2,9 @@
 library is what the same call through ctypes hands over.  Every input here is refused (or has no
 rows) before anything would be enqueued."""
 import ctypes as C
+import os
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -76,3 +79,16 @@ def test_errors_of_the_objects_come_through():
         B._marshal.spmv(0, matrix(), x, x, None)
     with pytest.raises(S.SeerError):
         S.seer_spmv_prepared(handles("prepared")[0], matrix(), x, x, workspace=torch.zeros(64, dtype=torch.uint8), stream=0)
+
+
+def test_first_call_of_a_process_may_name_a_kernel_that_does_not_exist():
+    """The library is loaded by whatever call comes first, also one that asks it for no size."""
+    code = ("import torch, paper_2403_17017_amd as S\n"
+            "A = S.DeviceCSR(4, 5, torch.zeros(5, dtype=torch.int32), torch.zeros(3, dtype=torch.int32), torch.zeros(3), 3)\n"
+            "try:\n"
+            "    S.seer_spmv(99, A, torch.zeros(5), torch.zeros(4), stream=0)\n"
+            "except S.SeerError as e:\n"
+            "    print('status', e.status)\n")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=300)
+    assert out.stdout.strip() == "status -2", out.stderr
