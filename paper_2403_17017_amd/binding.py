@@ -235,6 +235,13 @@ class Tree:
         return cls([-1], [0.0], [-1], [-1], [klass])
 
 
+def _address(c, kind) -> int:
+    """Where the structure c lies, for a parameter of type `kind *`; another type is refused as ctypes does."""
+    if not isinstance(c, kind):
+        raise C.ArgumentError(f"expected a {kind.__name__}, got {type(c).__name__}")
+    return C.addressof(c)
+
+
 def _stream_handle(stream) -> int:
     """The hipStream_t of a torch stream, of a raw handle, or (None) of torch's current stream."""
     if stream is None:
@@ -385,7 +392,7 @@ def seer_spmv_auto(A: DeviceCSR, tree: Tree, x, y, workspace, stream=None) -> No
     """Features, tree walk and SpMV enqueued back to back; returns without waiting."""
     if _lib is None:
         lib()
-    rc = _marshal.spmv_auto(C.addressof(tree.c), A, x, y, workspace, _stream_handle(stream))
+    rc = _marshal.spmv_auto(_address(tree.c, seer_tree), A, x, y, workspace, _stream_handle(stream))
     if rc:
         raise SeerError(rc, "seer_spmv_auto")
 
@@ -427,7 +434,7 @@ def seer_spmv_model(A: DeviceCSR, model: Model, x, y, workspace, stream=None):
     (kernel_id valid), 1 = features gathered on the device (kernel_id -1)."""
     if _lib is None:
         lib()
-    rc, path, kid = _marshal.spmv_model(C.addressof(model.c), A, x, y, workspace, _stream_handle(stream))
+    rc, path, kid = _marshal.spmv_model(_address(model.c, seer_model), A, x, y, workspace, _stream_handle(stream))
     if rc:
         raise SeerError(rc, "seer_spmv_model")
     return path, kid
@@ -538,7 +545,7 @@ def seer_spmv_prepared(plan: Plan, A: DeviceCSR, x, y, workspace=None, stream=No
             workspace = _temporary_workspace(need, A.row_ptr.device, stream)
     if _lib is None:
         lib()
-    rc = _marshal.spmv_prepared(C.addressof(plan.c), A, x, y, workspace, _stream_handle(stream))
+    rc = _marshal.spmv_prepared(_address(plan.c, seer_plan), A, x, y, workspace, _stream_handle(stream))
     if rc:
         raise SeerError(rc, f"seer_spmv_prepared(kernel {plan.kernel_id})")
 

@@ -92,3 +92,17 @@ def test_first_call_of_a_process_may_name_a_kernel_that_does_not_exist():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     out = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=300)
     assert out.stdout.strip() == "status -2", out.stderr
+
+
+def test_a_structure_of_another_type_is_refused():
+    """A Model where a Tree belongs (and so on) is an error, not memory read as something else."""
+    A, x, ws = matrix(), torch.zeros(16), torch.zeros(64, dtype=torch.uint8)
+    tree = S.Tree.constant(S.CSR_MP)
+    model, plan = S.Model(tree), handles("prepared")[0]
+    for call, right in ((S.seer_spmv_auto, tree), (S.seer_spmv_model, model), (S.seer_spmv_prepared, plan)):
+        for h in (tree, model, plan):
+            with pytest.raises(S.SeerError if h is right else C.ArgumentError):
+                if call is S.seer_spmv_prepared:
+                    call(h, A, x[:5], x[2:6], workspace=ws, stream=0)
+                else:
+                    call(A, h, x[:5], x[2:6], ws, stream=0)
