@@ -242,6 +242,11 @@ def _address(c, kind) -> int:
     return C.addressof(c)
 
 
+def _require_workspace(workspace) -> None:
+    if workspace is None:
+        raise AttributeError("this call has no workspace of its own: pass one (alloc_workspace)")
+
+
 def _stream_handle(stream) -> int:
     """The hipStream_t of a torch stream, of a raw handle, or (None) of torch's current stream."""
     if stream is None:
@@ -392,6 +397,7 @@ def seer_spmv_auto(A: DeviceCSR, tree: Tree, x, y, workspace, stream=None) -> No
     """Features, tree walk and SpMV enqueued back to back; returns without waiting."""
     if _lib is None:
         lib()
+    _require_workspace(workspace)
     rc = _marshal.spmv_auto(_address(tree.c, seer_tree), A, x, y, workspace, _stream_handle(stream))
     if rc:
         raise SeerError(rc, "seer_spmv_auto")
@@ -434,6 +440,7 @@ def seer_spmv_model(A: DeviceCSR, model: Model, x, y, workspace, stream=None):
     (kernel_id valid), 1 = features gathered on the device (kernel_id -1)."""
     if _lib is None:
         lib()
+    _require_workspace(workspace)
     rc, path, kid = _marshal.spmv_model(_address(model.c, seer_model), A, x, y, workspace, _stream_handle(stream))
     if rc:
         raise SeerError(rc, "seer_spmv_model")

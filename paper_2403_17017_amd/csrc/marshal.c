@@ -18,37 +18,45 @@ static int (*f_prepared)(const seer_plan *, const seer_csr *, const float *, flo
 
 static PyObject *s_rows, *s_cols, *s_nnz, *s_row_ptr, *s_col_idx, *s_values, *s_data_ptr, *s_numel;
 
-/* An integer as ctypes would pass it: any int, reduced to the width of the parameter. */
-static int as_u64(PyObject *o, uint64_t *out)
+/* What ctypes takes: for a size anything that is an integer (None and floats raise TypeError),
+ * reduced to the width of the parameter; for an address an int, or None for a null pointer. */
+static int as_size(PyObject *o, uint64_t *out)
 {
-    if (o == Py_None) { *out = 0; return 0; }
     *out = (uint64_t)PyLong_AsUnsignedLongLongMask(o);
     return PyErr_Occurred() ? -1 : 0;
 }
 
-static int call_u64(PyObject *o, PyObject *method, uint64_t *out)
+static int as_address(PyObject *o, uint64_t *out)
 {
-    PyObject *r = PyObject_CallMethodNoArgs(o, method);
+    if (o == Py_None) { *out = 0; return 0; }
+    if (!PyLong_Check(o)) {
+        PyErr_Format(PyExc_TypeError, "an address must be an int, not %.100s", Py_TYPE(o)->tp_name);
+        return -1;
+    }
+    return as_size(o, out);
+}
+
+/* Takes over the reference r (null: an exception is set). */
+static int taken(PyObject *r, int (*as)(PyObject *, uint64_t *), uint64_t *out)
+{
     if (!r) return -1;
-    const int rc = as_u64(r, out);
+    const int rc = as(r, out);
     Py_DECREF(r);
     return rc;
 }
 
-static int attr_u64(PyObject *o, PyObject *name, uint64_t *out)
+static int size_attr(PyObject *o, PyObject *name, uint64_t *out) { return taken(PyObject_GetAttr(o, name), as_size, out); }
+
+static int address_of(PyObject *tensor, uint64_t *out)
 {
-    PyObject *r = PyObject_GetAttr(o, name);
-    if (!r) return -1;
-    const int rc = as_u64(r, out);
-    Py_DECREF(r);
-    return rc;
+    return taken(PyObject_CallMethodNoArgs(tensor, s_data_ptr), as_address, out);
 }
 
-static int attr_ptr(PyObject *o, PyObject *name, uint64_t *out)
+static int address_attr(PyObject *o, PyObject *name, uint64_t *out)
 {
     PyObject *t = PyObject_GetAttr(o, name);
     if (!t) return -1;
-    const int rc = call_u64(t, s_data_ptr, out);
+    const int rc = address_of(t, out);
     Py_DECREF(t);
     return rc;
 }
@@ -57,9 +65,10 @@ static int attr_ptr(PyObject *o, PyObject *name, uint64_t *out)
 static int csr_of(PyObject *A, seer_csr *c)
 {
     uint64_t rows, cols, nnz, rp, ci = 0, va = 0;
-    if (attr_u64(A, s_rows, &rows) || attr_u64(A, s_cols, &cols) || attr_u64(A, s_nnz, &nnz) || attr_ptr(A, s_row_ptr, &rp))
+    if (size_attr(A, s_rows, &rows) || size_attr(A, s_cols, &cols) || size_attr(A, s_nnz, &nnz) ||
+        address_attr(A, s_row_ptr, &rp))
         return -1;
-    if (nnz && (attr_ptr(A, s_col_idx, &ci) || attr_ptr(A, s_values, &va))) return -1;
+    if (nnz && (address_attr(A, s_col_idx, &ci) || address_attr(A, s_values, &va))) return -1;
     c->rows = (int32_t)rows;
     c->cols = (int32_t)cols;
     c->nnz = (int32_t)nnz;
@@ -82,11 +91,11 @@ static int parse(PyObject *const *a, Py_ssize_t n, call_args *c)
         return -1;
     }
     c->ws = c->ws_bytes = 0;
-    if (as_u64(a[0], &c->handle) || csr_of(a[1], &c->csr) || call_u64(a[2], s_data_ptr, &c->x) ||
-        call_u64(a[3], s_data_ptr, &c->y))
+    if (as_size(a[0], &c->handle) || csr_of(a[1], &c->csr) || address_of(a[2], &c->x) || address_of(a[3], &c->y)) return -1;
+    if (a[4] != Py_None &&
+        (address_of(a[4], &c->ws) || taken(PyObject_CallMethodNoArgs(a[4], s_numel), as_size, &c->ws_bytes)))
         return -1;
-    if (a[4] != Py_None && (call_u64(a[4], s_data_ptr, &c->ws) || call_u64(a[4], s_numel, &c->ws_bytes))) return -1;
-    return as_u64(a[5], &c->stream);
+    return as_size(a[5], &c->stream);
 }
 
 #define P(T, v) ((T)(uintptr_t)(v))

@@ -106,3 +106,53 @@ def test_a_structure_of_another_type_is_refused():
                     call(h, A, x[:5], x[2:6], workspace=ws, stream=0)
                 else:
                     call(A, h, x[:5], x[2:6], ws, stream=0)
+
+
+class Odd:
+    """Something with an address and a size of any type."""
+    def __init__(self, address, size=64):
+        self.address, self.size = address, size
+
+    def data_ptr(self):
+        return self.address
+
+    def numel(self):
+        return self.size
+
+
+@pytest.mark.parametrize("what", ["rows", "cols", "nnz"])
+@pytest.mark.parametrize("value", [None, 4.0, "4"])
+def test_sizes_that_are_no_integers_are_refused(what, value):
+    A, x = matrix(), torch.zeros(16)
+    setattr(A, what, value)
+    with pytest.raises(TypeError):
+        A.c_struct()
+    with pytest.raises(TypeError):
+        S.seer_spmv_auto(A, S.Tree.constant(S.CSR_MP), x[:5], x[2:6], torch.zeros(64, dtype=torch.uint8), stream=0)
+
+
+def test_addresses_and_workspaces_that_are_none_are_refused():
+    import numpy as np
+    tree, x, ws = S.Tree.constant(S.CSR_MP), torch.zeros(16), torch.zeros(64, dtype=torch.uint8)
+
+    def auto(A=None, xx=x[:5], w=ws):
+        S.seer_spmv_auto(A or matrix(), tree, xx, x[2:6], w, stream=0)
+    for bad in (Odd(16.0), Odd(np.int64(16)), Odd(ws.data_ptr(), None), Odd(ws.data_ptr(), 64.0)):
+        with pytest.raises(TypeError):
+            auto(w=bad)
+    for w in (None, 3):                                                  # no optional argument of these two calls
+        with pytest.raises(AttributeError):
+            auto(matrix(rows=0, nnz=0), w=w)
+        with pytest.raises(AttributeError):
+            S.seer_spmv_model(matrix(rows=0, nnz=0), S.Model(tree), x[:5], x[2:6], w, stream=0)
+    with pytest.raises(TypeError):
+        auto(xx=Odd(16.0))
+    A = matrix()
+    A.row_ptr = Odd(16.0)
+    with pytest.raises(TypeError):
+        auto(A)
+    for A, xx in ((matrix(), Odd(None)), (matrix(), x[:5])):              # a null x; x and y that overlap
+        A.cols = np.int32(5)
+        with pytest.raises(S.SeerError) as e:
+            auto(A, xx)
+        assert e.value.status == -1
