@@ -82,11 +82,19 @@ _lib = None
 _marshal = None
 
 
+class _NoMarshal:
+    """Stands in for a module that has not been built: only the four calls that need it fail."""
+
+    def __getattr__(self, name):
+        raise ImportError(f"{_MARSHAL_PATH} is missing: build it with `python -m paper_2403_17017_amd.build`")
+
+
 def _bind_marshal(L):
     """The native marshalling of the asynchronous calls, bound to the functions of L."""
     global _marshal
     if not os.path.exists(_MARSHAL_PATH):
-        raise ImportError(f"{_MARSHAL_PATH} is missing: build it with `python -m paper_2403_17017_amd.build`")
+        _marshal = _NoMarshal()
+        return
     from . import _marshal as m
     m.bind(*(C.cast(f, C.c_void_p).value for f in (L.seer_spmv, L.seer_spmv_auto, L.seer_spmv_model, L.seer_spmv_prepared)))
     _marshal = m

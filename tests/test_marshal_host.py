@@ -156,3 +156,20 @@ def test_addresses_and_workspaces_that_are_none_are_refused():
         with pytest.raises(S.SeerError) as e:
             auto(A, xx)
         assert e.value.status == -1
+
+
+def test_host_calls_work_without_the_native_marshalling():
+    """Only the calls that go through it need the module; they say what is missing."""
+    code = ("import torch, paper_2403_17017_amd as S\n"
+            "from paper_2403_17017_amd import binding as B\n"
+            "B._MARSHAL_PATH += '.not-built'\n"
+            "print(S.seer_select(S.seer_known_features(4, 5, 3), S.Tree.constant(S.CSR_WO)))\n"
+            "S.set_tuning('nt', -1)\n"
+            "A = S.DeviceCSR(4, 5, torch.zeros(5, dtype=torch.int32), torch.zeros(3, dtype=torch.int32), torch.zeros(3), 3)\n"
+            "try:\n"
+            "    S.seer_spmv(0, A, torch.zeros(5), torch.zeros(4), stream=0)\n"
+            "except ImportError as e:\n"
+            "    print('.not-built is missing' in str(e))\n")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=300)
+    assert out.stdout.split() == [str(S.CSR_WO), "True"], out.stderr
