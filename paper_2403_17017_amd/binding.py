@@ -259,7 +259,9 @@ def _stream_handle(stream) -> int:
     """The hipStream_t of a torch stream, of a raw handle, or (None) of torch's current stream."""
     if stream is None:
         import torch
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())   # torch.cuda.current_stream() without the object
+        if not torch.cuda.is_initialized():              # initializes, or refuses in a forked child
+            return int(torch.cuda.current_stream().cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())   # ... without the object
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
 

@@ -173,3 +173,15 @@ def test_host_calls_work_without_the_native_marshalling():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     out = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=300)
     assert out.stdout.split() == [str(S.CSR_WO), "True"], out.stderr
+
+
+def test_the_current_stream_is_asked_for_only_where_torch_has_initialized(monkeypatch):
+    """A forked child of a process that used the GPU must be refused by torch, not handed a stream."""
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 4711, raising=False)
+    monkeypatch.setattr(torch.cuda, "_initialized", True)
+    monkeypatch.setattr(torch.cuda, "_is_in_bad_fork", lambda: False)
+    assert B._stream_handle(None) == 4711
+    monkeypatch.setattr(torch.cuda, "_is_in_bad_fork", lambda: True)
+    with pytest.raises(RuntimeError, match="forked subprocess"):
+        B._stream_handle(None)
