@@ -26,10 +26,11 @@
  *   - Every call returns SEER_OK (0) or a negative seer_status; on error no output
  *     is written.  Nothing throws or aborts.  Matrix contents (monotone row_ptr,
  *     column range) are NOT validated: they are the caller's contract.
- *   - The first seer_features or seer_csr_check call allocates one 64-byte pinned host buffer per
- *     process (its result mailbox); no other state is kept, on the host or the device.
- *   - Calls that use the same workspace must not overlap in time; seer_features and
- *     seer_csr_check calls are serialised inside the library (they share the mailbox).
+ *   - The first seer_features or seer_csr_check call allocates 4096 bytes of pinned host memory
+ *     per process (64 result mailboxes); no other state is kept, on the host or the device.
+ *   - Calls that use the same workspace must not overlap in time.  seer_features and
+ *     seer_csr_check calls of different threads run side by side, up to 64 of them; a further
+ *     one waits until one of those has ended.
  */
 #ifndef SEER_H
 #define SEER_H

@@ -11,6 +11,7 @@
 #include <atomic>
 #include <chrono>
 #include <cmath>
+#include <condition_variable>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -52,10 +53,17 @@ std::atomic<int> g_tune_coo_runs{-1};
 std::atomic<int> g_tune_slab_shift{-1};
 std::atomic<int> g_tune_gather_range{-1};
 
-std::mutex g_mailbox_mutex;
-FeatureRaw *g_mailbox_host = nullptr;   // pinned, mapped
-FeatureRaw *g_mailbox_dev = nullptr;
-uint64_t g_feature_seq = 0;
+// Where the waiting calls (seer_features, seer_csr_check) get their results: kMailboxes slots of
+// pinned, mapped host memory, one per call under way, so that calls of different threads do not
+// wait for each other's streams.
+constexpr int kMailboxes = 64;
+constexpr size_t kMailboxStride = 64;
+static_assert(sizeof(FeatureRaw) <= kMailboxStride && kMailboxes <= 64, "a slot per bit of the mask, a cache line each");
+std::mutex g_mailbox_mutex;             // guards the four below; never held while waiting for the device
+std::condition_variable g_mailbox_freed;
+char *g_mailbox_host = nullptr, *g_mailbox_dev = nullptr;
+uint64_t g_mailbox_free = ~0ull;        // bit k: slot k is free
+uint64_t g_mailbox_seq = 0;
 
 int hip_fail(hipError_t e)
 {
@@ -316,51 +324,85 @@ uint64_t csr_footprint(const seer_csr *A)
     return 8ull * (uint64_t)A->nnz + 8ull * (uint64_t)A->rows + 4ull * (uint64_t)A->cols;
 }
 
-int ensure_mailbox()
-{
-    if (g_mailbox_host) return SEER_OK;
-    void *h = nullptr;
-    hipError_t e = hipHostMalloc(&h, 64, hipHostMallocPortable | hipHostMallocMapped);
-    if (e != hipSuccess) return hip_fail(e);
-    void *d = nullptr;
-    e = hipHostGetDevicePointer(&d, h, 0);
-    if (e != hipSuccess) {
-        (void)hipHostFree(h);
-        return hip_fail(e);
-    }
-    std::memset(h, 0, 64);
-    g_mailbox_host = static_cast<FeatureRaw *>(h);
-    g_mailbox_dev = static_cast<FeatureRaw *>(d);
-    return SEER_OK;
-}
-
-// Waits until the kernel that writes `seq` into the mailbox has done so, and copies the mailbox
-// out (the caller holds g_mailbox_mutex).  The kernel writes its result, then the sequence
-// number, into pinned host memory.  Watching that word is quicker than waiting for the stream;
-// if it does not show up soon, wait for the stream and look again.
-int wait_for_mailbox(uint64_t seq, hipStream_t st, FeatureRaw *raw)
-{
-    volatile uint64_t *seq_word = &g_mailbox_host->seq;
-    bool seen = false;
-    if (g_tune_poll.load() != 0) {
-        const auto t0 = std::chrono::steady_clock::now();
-        for (uint32_t spin = 0;; ++spin) {
-            if (*seq_word == seq) { seen = true; break; }
-            if ((spin & 1023u) == 1023u &&
-                std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2))
-                break;
-            __builtin_ia32_pause();
+// One slot, for the length of a call.
+class Mailbox {
+public:
+    Mailbox() = default;
+    Mailbox(const Mailbox &) = delete;
+    Mailbox &operator=(const Mailbox &) = delete;
+    ~Mailbox()
+    {
+        if (slot_ < 0) return;
+        {
+            std::lock_guard<std::mutex> lock(g_mailbox_mutex);
+            g_mailbox_free |= 1ull << slot_;
         }
+        g_mailbox_freed.notify_one();
     }
-    if (!seen) {
-        const hipError_t e = hipStreamSynchronize(st);
-        if (e != hipSuccess) return hip_fail(e);
-        if (*seq_word != seq) return hip_fail(hipErrorUnknown);
+
+    // Waits only if kMailboxes calls are under way already.  The first one allocates the slots.
+    int take()
+    {
+        std::unique_lock<std::mutex> lock(g_mailbox_mutex);
+        if (!g_mailbox_host) {
+            void *h = nullptr;
+            hipError_t e = hipHostMalloc(&h, kMailboxes * kMailboxStride, hipHostMallocPortable | hipHostMallocMapped);
+            if (e != hipSuccess) return hip_fail(e);
+            void *d = nullptr;
+            e = hipHostGetDevicePointer(&d, h, 0);
+            if (e != hipSuccess) {
+                (void)hipHostFree(h);
+                return hip_fail(e);
+            }
+            std::memset(h, 0, kMailboxes * kMailboxStride);
+            g_mailbox_host = static_cast<char *>(h);
+            g_mailbox_dev = static_cast<char *>(d);
+        }
+        g_mailbox_freed.wait(lock, [] { return g_mailbox_free != 0; });
+        slot_ = __builtin_ctzll(g_mailbox_free);
+        g_mailbox_free &= ~(1ull << slot_);
+        seq_ = ++g_mailbox_seq;
+        host_ = reinterpret_cast<FeatureRaw *>(g_mailbox_host + (size_t)slot_ * kMailboxStride);
+        dev_ = reinterpret_cast<FeatureRaw *>(g_mailbox_dev + (size_t)slot_ * kMailboxStride);
+        return SEER_OK;
     }
-    std::atomic_thread_fence(std::memory_order_acquire);
-    std::memcpy(raw, const_cast<const FeatureRaw *>(g_mailbox_host), sizeof *raw);
-    return SEER_OK;
-}
+
+    FeatureRaw *device() const { return dev_; }
+    uint64_t seq() const { return seq_; }
+
+    // Waits until the kernel that writes seq() into the slot has done so, and copies the slot out.
+    // The kernel writes its result, then the sequence number, into pinned host memory.  Watching
+    // that word is quicker than waiting for the stream; if it does not show up soon, wait for the
+    // stream and look again.
+    int wait(hipStream_t st, FeatureRaw *raw) const
+    {
+        const volatile uint64_t *seq_word = &host_->seq;
+        bool seen = false;
+        if (g_tune_poll.load() != 0) {
+            const auto t0 = std::chrono::steady_clock::now();
+            for (uint32_t spin = 0;; ++spin) {
+                if (*seq_word == seq_) { seen = true; break; }
+                if ((spin & 1023u) == 1023u &&
+                    std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2))
+                    break;
+                __builtin_ia32_pause();
+            }
+        }
+        if (!seen) {
+            const hipError_t e = hipStreamSynchronize(st);
+            if (e != hipSuccess) return hip_fail(e);
+            if (*seq_word != seq_) return hip_fail(hipErrorUnknown);
+        }
+        std::atomic_thread_fence(std::memory_order_acquire);
+        std::memcpy(raw, host_, sizeof *raw);
+        return SEER_OK;
+    }
+
+private:
+    int slot_ = -1;
+    uint64_t seq_ = 0;
+    FeatureRaw *host_ = nullptr, *dev_ = nullptr;
+};
 
 // f[] from the exact integers; every entry is one fp64 quotient rounded once to fp32.
 void derive(seer_features_t *o)
@@ -632,16 +674,15 @@ int seer_features(const seer_csr *A, seer_features_t *out, void *workspace, size
     if (A->rows > 0) {
         if (!workspace || !aligned16(workspace) || workspace_bytes < features_workspace_bytes(A->rows))
             return SEER_EWORKSPACE;
-        std::lock_guard<std::mutex> lock(g_mailbox_mutex);
-        const int mrc = ensure_mailbox();
+        Mailbox mail;
+        const int mrc = mail.take();
         if (mrc != SEER_OK) return mrc;
         hipStream_t st = static_cast<hipStream_t>(stream);
-        const uint64_t seq = ++g_feature_seq;
-        launch_features(A->rows, A->row_ptr, workspace, g_mailbox_dev, seq, st);
+        launch_features(A->rows, A->row_ptr, workspace, mail.device(), mail.seq(), st);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e);
         FeatureRaw raw;
-        const int wrc = wait_for_mailbox(seq, st, &raw);
+        const int wrc = mail.wait(st, &raw);
         if (wrc != SEER_OK) return wrc;
         o.nnz = (int64_t)raw.last - (int64_t)raw.first;
         o.max_len = raw.max_len;
@@ -915,16 +956,15 @@ int seer_csr_check(const seer_csr *A, int64_t *bad_row_ptr, int64_t *bad_col_idx
     if (!A || !bad_row_ptr || !bad_col_idx) return SEER_EINVAL;
     if (A->rows < 0 || A->cols < 0 || A->nnz < 0 || !A->row_ptr) return SEER_EINVAL;
     if (!workspace || !aligned16(workspace) || workspace_bytes < 16) return SEER_EWORKSPACE;
-    std::lock_guard<std::mutex> lock(g_mailbox_mutex);
-    const int mrc = ensure_mailbox();
+    Mailbox mail;
+    const int mrc = mail.take();
     if (mrc != SEER_OK) return mrc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const uint64_t seq = ++g_feature_seq;
-    launch_csr_check(A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, workspace, g_mailbox_dev, seq, st);
+    launch_csr_check(A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, workspace, mail.device(), mail.seq(), st);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e);
     FeatureRaw raw;
-    const int wrc = wait_for_mailbox(seq, st, &raw);
+    const int wrc = mail.wait(st, &raw);
     if (wrc != SEER_OK) return wrc;
     *bad_row_ptr = (int64_t)raw.sum_sq;
     *bad_col_idx = (int64_t)raw.empty;

@@ -104,3 +104,41 @@ def test_every_position_counts_whatever_the_alignment(rows, nnz, shift):
         bad = rp.copy()
         bad[i] += nnz + 1
         assert counts(bad, ci) == O.csr_defects(rows, 50, nnz, bad, ci), f"offset {i}"
+
+
+@pytest.mark.parametrize("first", ["check", "features"])
+def test_a_call_behind_long_work_holds_up_no_other_thread(first):
+    """One thread's call waits for its own stream, which is busy; the others' streams are not."""
+    import threading
+
+    import torch
+    A = G.random_lengths(2_003, 5_000, 0, 20, 7)
+    dA = S.DeviceCSR.from_host(A)
+    S.seer_features(dA)
+    assert S.seer_csr_check(dA) == (0, 0)                             # code loaded, mailboxes allocated
+    streams = [torch.cuda.Stream() for _ in range(5)]
+    left = torch.cuda.Event()
+    done, results = [], []
+    torch.cuda.synchronize()
+
+    def call(k):
+        ws = S.alloc_workspace(max(256, S.features_workspace_bytes(A.rows)))
+        if k == 0 and first == "features":
+            results.append((0, 0) if int(S.seer_features(dA, ws, streams[0]).nnz) == A.nnz else None)
+        else:
+            results.append(S.seer_csr_check(dA, ws, streams[k]))
+        done.append((k, left.query()))                                # was the busy stream through by then?
+    with torch.cuda.stream(streams[0]):
+        torch.cuda._sleep(1_500_000_000)                              # 0.6 s and more of the GPU's clock
+        left.record()
+    announce(f"one {first} behind a busy stream, csr checks on four others")
+    threads = [threading.Thread(target=call, args=(k,)) for k in range(5)]
+    threads[0].start()
+    threads[0].join(0.05)
+    for t in threads[1:]:
+        t.start()
+    for t in threads:
+        t.join(60)
+    assert results == [(0, 0)] * 5
+    # (a few streams share a hardware queue, so not necessarily all of them)
+    assert any(k != 0 and not through for k, through in done), "every call waited for the busy stream"
