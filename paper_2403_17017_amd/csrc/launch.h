@@ -17,9 +17,12 @@ constexpr int kMpIptLarge = 15;   // merge items per thread, large problems (til
 
 // Gathers ordered in time by column range (ranged_chunk_finish): x is cut into `count` ranges
 // of range_bytes = 2^shift bytes, and the chip turns to the next one every `ticks` of the
-// constant-rate clock.  count == 0: gathers in the order of the entries.
+// constant-rate clock.  count == 0: gathers in the order of the entries.  Cells of 2^cell_shift
+// bytes, at most 64, a power of two of them to a range, tell how much of x a wave touches;
+// few_cells of them are little enough for an L2.
 struct GatherRanges {
     uint32_t count, shift, range_bytes, ticks, x_bytes;
+    uint32_t cell_shift, few_cells;
 };
 
 struct SpmvArgs {

@@ -157,6 +157,9 @@ GatherRanges gather_ranges(int64_t cols, int64_t nnz, bool vec, int64_t at_least
     g.shift = (uint32_t)shift + 2u;
     g.range_bytes = 4u << shift;
     g.x_bytes = 4u * (uint32_t)cols;
+    g.cell_shift = g.shift;
+    while (g.cell_shift > 0 && ((g.x_bytes - 1u) >> (g.cell_shift - 1u)) < 64u) --g.cell_shift;
+    g.few_cells = t >= 1 && t <= 28 ? 2u : std::max(2u, (3u << 20) >> g.cell_shift);   // 3 MB; by the knob: whatever the sizes
     return g;
 }
 

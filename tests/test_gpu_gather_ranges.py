@@ -129,3 +129,82 @@ def test_adaptive_from_two_million_entries_on(nnz):
     for got in (run_spmv(S.CSR_A, dA, xd, A.rows), y.cpu().numpy()):
         assert_parity(got, y_ref, bound, f"CSR,A at {nnz} entries")
         assert got.tobytes() == plain.tobytes()
+
+
+def localities(rows, n_loc, width, band=1):
+    """Row i touches `width` columns at each of n_loc places i + l * rows / n_loc (wrapping around);
+    band > 1: each of them somewhere in the `band` columns that follow its place."""
+    rng = np.random.default_rng(rows + n_loc + width + band)
+    place = np.arange(rows)[:, None] + np.repeat(np.arange(n_loc) * (rows // n_loc), width)[None, :]
+    step = rng.integers(0, band, place.shape) if band > 1 else np.tile(np.arange(width), n_loc)[None, :]
+    ci = np.sort((place + step) % rows, axis=1).astype(np.int32).ravel()
+    k = n_loc * width
+    return G.HostCSR(rows, rows, np.arange(rows + 1, dtype=np.int64).astype(np.int32) * k, ci,
+                 rng.uniform(-1, 1, ci.size).astype(np.float32), f"{n_loc}-localities-of-{width}-in-{band}")
+
+
+def arrow(rows):
+    i = np.arange(rows)[:, None]
+    ci = np.concatenate([np.zeros_like(i), np.clip(i, 1, rows - 2), np.full_like(i, rows - 1)], axis=1).astype(np.int32)
+    return G.HostCSR(rows, rows, np.arange(rows + 1, dtype=np.int32) * 3, ci.ravel(),
+                 np.random.default_rng(rows).uniform(-1, 1, ci.size).astype(np.float32), "arrow")
+
+
+LOCAL = ((lambda n: localities(n, 2, 5), 2_000_003), (lambda n: localities(n, 3, 3), 2_000_003),
+         (lambda n: localities(n, 16, 1), 1_400_003), (lambda n: localities(n, 1, 9), 2_000_003),
+         (lambda n: localities(n, 1, 12, band=n // 10), 1_500_007), (arrow, 3_000_003))
+
+
+@pytest.mark.parametrize("i", range(len(LOCAL)))
+@pytest.mark.parametrize("shift", [10, 11, 13])
+def test_few_distant_localities_keep_the_plain_bits(i, shift):
+    """Waves that gather at once for one reason or another, beside waves that wait."""
+    import torch
+    A = LOCAL[i][0](16_411)
+    x = G.dense_vector(A.cols, 70 + i)
+    y_ref, bound = oracle_of(A, x)
+    dA, xd = upload(A), torch.from_numpy(x).cuda()
+    for k in RANGED:
+        announce(f"gather_range={shift} kernel {k} {A.name}")
+        S.set_tuning("gather_range", 0)
+        plain = run_spmv(k, dA, xd, A.rows)
+        S.set_tuning("gather_range", shift)
+        ranged = run_spmv(k, dA, xd, A.rows)
+        assert_parity(ranged, y_ref, bound, f"kernel {k} on {A.name}, ranges of 2^{shift}")
+        if k != S.CSR_BM:
+            assert ranged.tobytes() == plain.tobytes(), f"kernel {k} on {A.name}: the order of gathers changed y"
+
+
+def times_of_both_orders(kid, A, xd, y, n=10):
+    """Least us per product of a few batches, with gathers in the plain order and as the sizes choose."""
+    import torch
+    plan = S.seer_spmv_prepare(kid, A)
+
+    def batch():
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(n):
+            S.seer_spmv_prepared(plan, A, xd, y)
+        b.record()
+        torch.cuda.synchronize()
+        return a.elapsed_time(b) * 1e3 / n
+    best = {0: np.inf, -1: np.inf}
+    for _ in range(6):
+        for knob in best:
+            S.set_tuning("gather_range", knob)
+            best[knob] = min(best[knob], batch())
+    return best[0], best[-1]
+
+
+@pytest.mark.parametrize("i", range(len(LOCAL)))
+def test_few_distant_localities_cost_no_waiting(i):
+    """At the sizes where gathers are ordered by default, a matrix whose rows are local in a few places
+    takes about the plain order's time: 0.93 to 1.06 of it was measured, 1.2 to 8 while its waves waited."""
+    import torch
+    A = LOCAL[i][0](LOCAL[i][1])
+    dA = upload(A)
+    xd, y = torch.rand(A.cols, device="cuda:0"), torch.empty(A.rows, device="cuda:0")
+    for k in RANGED:
+        announce(f"times of kernel {k} on {A.name} rows={A.rows} nnz={A.nnz}")
+        plain, chosen = times_of_both_orders(k, dA, xd, y)
+        assert chosen <= 1.15 * plain, f"kernel {k} on {A.name}: {plain:.1f} us in the plain order, {chosen:.1f} us as chosen"
