@@ -208,3 +208,24 @@ def test_few_distant_localities_cost_no_waiting(i):
         announce(f"times of kernel {k} on {A.name} rows={A.rows} nnz={A.nnz}")
         plain, chosen = times_of_both_orders(k, dA, xd, y)
         assert chosen <= 1.15 * plain, f"kernel {k} on {A.name}: {plain:.1f} us in the plain order, {chosen:.1f} us as chosen"
+
+
+def test_long_unsorted_rows_do_not_wait_chunk_after_chunk():
+    """CSR,BM takes a block's chunks one after the other, and every chunk of a long row of unordered
+    columns touches all ranges: all of them together may wait no longer than one would."""
+    import torch
+    n, k, long = 2_000_003, 12, 200_000
+    lens = np.full(n, k)
+    lens[n // 3] = long
+    rp = np.zeros(n + 1, np.int32)
+    rp[1:] = np.cumsum(lens)
+    rng = np.random.default_rng(97)
+    ci = rng.integers(0, n, rp[-1]).astype(np.int32)
+    A = G.HostCSR(n, n, rp, ci, rng.uniform(-1, 1, ci.size).astype(np.float32), "one-long-unsorted-row")
+    x = G.dense_vector(n, 98)
+    dA, xd, y = upload(A), torch.from_numpy(x).cuda(), torch.empty(n, device="cuda:0")
+    announce(f"times of kernel {S.CSR_BM} on {A.name}")
+    plain, chosen = times_of_both_orders(S.CSR_BM, dA, xd, y, n=5)
+    y_ref, bound = oracle_of(A, x)
+    assert_parity(y.cpu().numpy(), y_ref, bound, A.name)
+    assert chosen <= 1.15 * plain, f"{plain:.1f} us in the plain order, {chosen:.1f} us as chosen"
