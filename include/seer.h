@@ -408,20 +408,24 @@ int seer_csr_check(const seer_csr *A, int64_t *bad_row_ptr, int64_t *bad_col_idx
  *               multiplied in one launch; a larger one gets a first reduction pass and the
  *               selection runs inside the product's launch if that launch has at most
  *               auto_fused_grid workgroups (default 1024) or the matrix at most
- *               auto_fused_max_rows rows (default 2^21); otherwise the selection is a
- *               launch of its own (both 0: always)
+ *               auto_fused_max_rows rows (default 0); otherwise, and where gathers are ordered
+ *               by column range, the selection is a launch of its own (both 0: always)
  *   "auto_prune" 0: seer_spmv_auto does not prune the tree with the known features (every
  *               schedule counts as reachable, the features are always gathered); default 1
  *   "gather_range" log2 of the columns per range, 1..28, where CSR,BM, CSR,MP, CSR,WO and CSR,A
- *               order their gathers in time by column range, whatever the sizes (if that makes 2
- *               to 32 ranges); 0: never.  Default: matrices of 2^23 nonzeros and more whose x
- *               is larger than 5 MB.  y is the same but for CSR,BM's summation order
+ *               order their gathers in time by column range; 0: never.  It needs 2 to 32
+ *               ranges, 16-byte aligned col_idx and values, and "vec" not 0; CSR,BM also rows
+ *               of more than 8 and at most 64 nonzeros on average and "bm_rows" not set.
+ *               Default: where x has more than 1 310 720 (5 MB) and at most 2^25 columns
+ *               (128 MB) and the matrix 2^23 nonzeros or more; CSR,A also from 2^21 nonzeros
+ *               on where x has more than 1 441 792 columns (5.5 MB).  y is the same but for
+ *               CSR,BM's summation order
  *   "slab_shift" CSR,S: log2 of the columns per slab, 1..30 (default: 19 or 20, see
  *               seer_slab_plan_bytes); the size functions follow it
  *   "coo_runs"  COO,WM: 1 (default): a lane sums a run of eight consecutive triples,
  *               0: lane <-> triple in rounds of 64
- *   "poll"      0: seer_features waits with hipStreamSynchronize only; otherwise
- *               (default) it first watches its pinned result word for up to 2 ms
+ *   "poll"      0: seer_features and seer_csr_check wait with hipStreamSynchronize only;
+ *               otherwise (default) they first watch their pinned result word for up to 2 ms
  * Unknown name: SEER_EINVAL.  A value outside the listed set selects the default. */
 int seer_set_tuning(const char *name, int value);
 

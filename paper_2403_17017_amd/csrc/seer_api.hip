@@ -129,17 +129,18 @@ constexpr int64_t kAdaptRangedNnz = 1 << 21;
 
 // Whether the gathers of CSR,MP, CSR,WO, CSR,A and (bm_ranged) CSR,BM are ordered in time by column range
 // (ranged_chunk_finish), and into how many ranges: where the 16-byte loads are used, x is larger
-// than an XCD's 4 MB L2 (measured, without and with: 4 MB 148 and 147 us, 4.6 MB 151 and 143, 5.7
-// MB 116 and 105) and not so large that hardly any line is wanted twice while a range lasts (61
-// MB 1044 and 654, 122 MB 1026 and 797), and there is more than one generation of workgroups:
-// below 2^23 entries random columns gain (2.5 M in 7.6 MB of x: CSR,WO 31.4 and 27.6 us; but
-// CSR,MP 35.4 and 37.4), stencils and bands lose (a stencil of 7.2 M: CSR,WO 21.3 and 22.4).
-// CSR,A gains on all of those, down to 2^21 entries (kAdaptRangedNnz: random 2.1 M 27.4 and 23.5,
-// 7 M 77.4 and 62.1; bands and stencils of 4 to 9 M 15.2 and 14.5, 17.9 and 17.5, 21.2 and 20.4), from
-// 5.5 MB of x on (5.3 MB 36.8 and 38.0, 5.7 MB 52.7 and 47.2).
+// than an XCD's 4 MB L2 (CSR,WO, 2^23 to 2^25 random nonzeros, without and with: 4 MB of x 148 and 147 us,
+// 4.6 MB 151 and 143 or 65.0 and 68.3, 5.7 MB 116 and 105 or 71.6 and 71.0) and not so large that hardly
+// any line is wanted twice while a range lasts (40 M nonzeros: 61 MB 727 and 458, 122 MB 763 and
+// 596), and there is more than one generation of workgroups: below 2^23 entries random columns gain
+// with CSR,WO (2.5 M in 7.6 MB of x 33.2 and 28.9) but not with CSR,MP (39.3 and 40.8), and short local
+// rows lose (a stencil of 7.4 M CSR,WO 21.3 and 22.7, a band of 7 M 18.6 and 19.4).
+// CSR,A gains or keeps on all of those, down to 2^21 entries (kAdaptRangedNnz: random 2.1 M 25.4 and 20.6,
+// 7 M 72.1 and 53.4; bands and stencils of 4.5, 7.4 and 12 M 15.5 and 15.3, 17.8 and 17.8, 25.6 and 24.1), from
+// 5.5 MB of x on (4 M: 5.3 MB 34.0 and 36.3, 5.7 MB 36.0 and 36.2; 9 M: 5.7 MB 73.7 and 65.2).
 // Ranges of 1 MB or more, at most sixteen: fewer and larger ones leave L2 no room for the
 // streams, more cost a pass over the entries each (8 MB of x: 8 ranges 289 us, 16 290, 4 297).
-// The "gather_range" knob: 0 never, 1..28 log2 of the columns per range whatever the sizes.
+// The "gather_range" knob: 0 never, 1..28 log2 of the columns per range, 2 to 32 ranges, whatever the sizes.
 GatherRanges gather_ranges(int64_t cols, int64_t nnz, bool vec, int64_t at_least = 1 << 23)
 {
     GatherRanges g{};
@@ -170,10 +171,11 @@ GatherRanges gather_ranges(int64_t cols, int64_t nnz, bool vec, int64_t at_least
 // CU have under way (measured best 36, 50, 64, 96, 100 us at 8, 15, 31, 61, 95 MB); with fewer
 // entries per workgroup, fewer workgroups per CU or a last generation that is not full it is
 // shorter in proportion.
-uint32_t gather_ticks(const GatherRanges &g, int64_t nnz, double entries_per_wg, int waves)
+constexpr double kWorkgroupsUnderWay = 8.0 * 256.0;   // eight per CU: 2048 lanes of 64 registers
+uint32_t gather_ticks(const GatherRanges &g, int64_t nnz, double entries_per_wg)
 {
     if (!g.count) return 0;
-    const double cap = std::max(entries_per_wg, 1.0) * waves * 256.0;
+    const double cap = std::max(entries_per_wg, 1.0) * kWorkgroupsUnderWay;
     const double generations = std::ceil(std::max((double)nnz, 1.0) / cap);
     const double under_way = (double)nnz / generations / (double)(1 << 23);
     const double turn_us = (12.0 + 9.5 * std::sqrt(g.x_bytes / 1048576.0)) * under_way;
@@ -193,7 +195,7 @@ uint32_t gather_ticks(const GatherRanges &g, int64_t nnz, double entries_per_wg,
 // With gathers ordered by column range (bm_ranged) a block is three quarters of one chunk of
 // 4096: a second chunk would take a second turn over x (2 M columns, 20 per row: 281 us, 290 at
 // 3700 entries, 311 at 7300, 303 at 1500), and 256 rows at most, one per lane.  Not with rows longer
-// than 64 on average (480 M nonzeros of a power law, 240 per row: 3290 us, by range 3730), nor with
+// than 64 on average (480 M nonzeros of a power law, 240 per row: 3290 us, by range 3730, when every chunk could wait a turn), nor with
 // rows of at most eight entries: fat blocks in small chunks whose loads run ahead suit stencils better than scattered columns gain (5-point 67 us, by range 75).
 bool bm_ranged(const GatherRanges &g, int rows, int nnz)
 {
@@ -784,9 +786,9 @@ static int auto_enqueue(const seer_csr *A, const seer_tree *tree, const float *x
     sh.tiles[SEER_CSR_MP] = mp_num_tiles(A->rows, A->nnz, sh.mp_ipt);
     sh.tiles[SEER_CSR_WO] = wo_num_tiles(A->rows, A->nnz);
     SpmvArgs a{A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, x, y, use_remap(), 1};
-    sh.ranges.ticks = gather_ticks(sh.ranges, A->nnz, wo_entries(A->nnz), 8);
-    sh.bm_ticks = gather_ticks(sh.ranges, A->nnz, bm_entries(A->rows, A->nnz, sh.bm_rows), 8);
-    sh.mp_ticks = gather_ticks(sh.ranges, A->nnz, mp_entries(A->rows, A->nnz, sh.mp_ipt), 8);
+    sh.ranges.ticks = gather_ticks(sh.ranges, A->nnz, wo_entries(A->nnz));
+    sh.bm_ticks = gather_ticks(sh.ranges, A->nnz, bm_entries(A->rows, A->nnz, sh.bm_rows));
+    sh.mp_ticks = gather_ticks(sh.ranges, A->nnz, mp_entries(A->rows, A->nnz, sh.mp_ipt));
     // What the host knows without looking at the matrix prunes the tree: the grid is sized
     // for the schedules that stay reachable, the carry fix-up is enqueued only if merge path
     // or the nonzero split is among them, and if a single kernel is left nothing is gathered.
@@ -1025,7 +1027,7 @@ static int spmv_dispatch(int kernel_id, const seer_csr *A, const float *x, float
     case SEER_CSR_BM: {
         if (!bm_ranged(a.ranges, A->rows, A->nnz)) a.ranges.count = 0;
         const int r = bm_rows(A->rows, A->nnz, a.ranges.count != 0);
-        a.ranges.ticks = gather_ticks(a.ranges, A->nnz, bm_entries(A->rows, A->nnz, r), 8);
+        a.ranges.ticks = gather_ticks(a.ranges, A->nnz, bm_entries(A->rows, A->nnz, r));
         launch_bm(a, r, bm_chunk(), vec, st);
         break;
     }
@@ -1037,7 +1039,7 @@ static int spmv_dispatch(int kernel_id, const seer_csr *A, const float *x, float
         void *plan_mem = static_cast<char *>(workspace) + carry;
         launch_adaptive_plan(A->rows, A->nnz, A->row_ptr, plan_mem, false, st);
         a.ranges = gather_ranges(A->cols, A->nnz, vec, kAdaptRangedNnz);
-        a.ranges.ticks = gather_ticks(a.ranges, A->nnz, kAdaptEntries, 8) * kAdaptPacePercent / 100;
+        a.ranges.ticks = gather_ticks(a.ranges, A->nnz, kAdaptEntries) * kAdaptPacePercent / 100;
         launch_adaptive(a, vec, plan_mem, workspace, st);
         break;
     }
@@ -1054,14 +1056,14 @@ static int spmv_dispatch(int kernel_id, const seer_csr *A, const float *x, float
         if (!workspace || !aligned16(workspace) ||
             workspace_bytes < carry_workspace_bytes(wo_num_tiles(A->rows, A->nnz)))
             return SEER_EWORKSPACE;
-        a.ranges.ticks = gather_ticks(a.ranges, A->nnz, wo_entries(A->nnz), 8);
+        a.ranges.ticks = gather_ticks(a.ranges, A->nnz, wo_entries(A->nnz));
         launch_wo(a, vec, workspace, st);
         break;
     default: {
         const int ipt = mp_ipt(A->rows, A->nnz);
         if (!workspace || !aligned16(workspace) || workspace_bytes < mp_workspace_bytes(A->rows, A->nnz, ipt))
             return SEER_EWORKSPACE;
-        a.ranges.ticks = gather_ticks(a.ranges, A->nnz, mp_entries(A->rows, A->nnz, ipt), 8);
+        a.ranges.ticks = gather_ticks(a.ranges, A->nnz, mp_entries(A->rows, A->nnz, ipt));
         launch_mp(a, ipt, vec, workspace, st);
         break;
     }
@@ -1279,7 +1281,7 @@ int seer_spmv_prepared(const seer_plan *plan, const seer_csr *A, const float *x,
                use_nt_repeated(csr_footprint(A))};
     const bool vec = aligned16(A->col_idx) && aligned16(A->values) && g_tune_vec.load() != 0;
     a.ranges = gather_ranges(A->cols, A->nnz, vec, kAdaptRangedNnz);
-    a.ranges.ticks = gather_ticks(a.ranges, A->nnz, kAdaptEntries, 8) * kAdaptPacePercent / 100;
+    a.ranges.ticks = gather_ticks(a.ranges, A->nnz, kAdaptEntries) * kAdaptPacePercent / 100;
     launch_adaptive(a, vec, plan->device, carry, static_cast<hipStream_t>(stream));
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? SEER_OK : hip_fail(e);
