@@ -80,6 +80,7 @@ seer_model._fields_ = [("selector", C.POINTER(seer_tree)), ("known", C.POINTER(s
 
 _lib = None
 _marshal = None
+_torch = None
 
 
 class _NoMarshal:
@@ -257,11 +258,15 @@ def _require_workspace(workspace) -> None:
 
 def _stream_handle(stream) -> int:
     """The hipStream_t of a torch stream, of a raw handle, or (None) of torch's current stream."""
+    global _torch
     if stream is None:
-        import torch
-        if not torch.cuda.is_initialized():              # initializes, or refuses in a forked child
-            return int(torch.cuda.current_stream().cuda_stream)
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())   # ... without the object
+        if _torch is None:                               # (an import statement per call costs 0.25 us)
+            import torch
+            _torch = torch
+        cuda, native = _torch.cuda, _torch._C
+        if not cuda._initialized or cuda._is_in_bad_fork():   # initializes, or refuses in a forked child
+            return int(cuda.current_stream().cuda_stream)
+        return native._cuda_getCurrentRawStream(native._cuda_getDevice())   # ... without the object
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
 
