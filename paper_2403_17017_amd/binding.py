@@ -244,16 +244,14 @@ class Tree:
         return cls([-1], [0.0], [-1], [-1], [klass])
 
 
+_addressof = C.addressof
+
+
 def _address(c, kind) -> int:
     """Where the structure c lies, for a parameter of type `kind *`; another type is refused as ctypes does."""
     if not isinstance(c, kind):
         raise C.ArgumentError(f"expected a {kind.__name__}, got {type(c).__name__}")
-    return C.addressof(c)
-
-
-def _require_workspace(workspace) -> None:
-    if workspace is None:
-        raise AttributeError("this call has no workspace of its own: pass one (alloc_workspace)")
+    return _addressof(c)
 
 
 def _stream_handle(stream) -> int:
@@ -412,8 +410,10 @@ def seer_spmv_auto(A: DeviceCSR, tree: Tree, x, y, workspace, stream=None) -> No
     """Features, tree walk and SpMV enqueued back to back; returns without waiting."""
     if _lib is None:
         lib()
-    _require_workspace(workspace)
-    rc = _marshal.spmv_auto(_address(tree.c, seer_tree), A, x, y, workspace, _stream_handle(stream))
+    if workspace is None:
+        raise AttributeError("this call has no workspace of its own: pass one (alloc_workspace)")
+    c = tree.c
+    rc = _marshal.spmv_auto(_addressof(c) if type(c) is seer_tree else _address(c, seer_tree), A, x, y, workspace, _stream_handle(stream))
     if rc:
         raise SeerError(rc, "seer_spmv_auto")
 
@@ -455,8 +455,10 @@ def seer_spmv_model(A: DeviceCSR, model: Model, x, y, workspace, stream=None):
     (kernel_id valid), 1 = features gathered on the device (kernel_id -1)."""
     if _lib is None:
         lib()
-    _require_workspace(workspace)
-    rc, path, kid = _marshal.spmv_model(_address(model.c, seer_model), A, x, y, workspace, _stream_handle(stream))
+    if workspace is None:
+        raise AttributeError("this call has no workspace of its own: pass one (alloc_workspace)")
+    c = model.c
+    rc, path, kid = _marshal.spmv_model(_addressof(c) if type(c) is seer_model else _address(c, seer_model), A, x, y, workspace, _stream_handle(stream))
     if rc:
         raise SeerError(rc, "seer_spmv_model")
     return path, kid
@@ -567,7 +569,8 @@ def seer_spmv_prepared(plan: Plan, A: DeviceCSR, x, y, workspace=None, stream=No
             workspace = _temporary_workspace(need, A.row_ptr.device, stream)
     if _lib is None:
         lib()
-    rc = _marshal.spmv_prepared(_address(plan.c, seer_plan), A, x, y, workspace, _stream_handle(stream))
+    c = plan.c
+    rc = _marshal.spmv_prepared(_addressof(c) if type(c) is seer_plan else _address(c, seer_plan), A, x, y, workspace, _stream_handle(stream))
     if rc:
         raise SeerError(rc, f"seer_spmv_prepared(kernel {plan.kernel_id})")
 
