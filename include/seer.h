@@ -288,7 +288,8 @@ typedef struct {
     int32_t n_blocks;     /* SEER_CSR_A: row blocks in the plan; SEER_CSR_S: column slabs  */
     int32_t split_rows;   /* SEER_CSR_A: 1 if some row is shared between blocks (the
                              product then needs the carry workspace and a second launch);
-                             SEER_CSR_S: the number of virtual rows kept                 */
+                             SEER_CSR_S: the number of virtual rows kept, or, in bins (see
+                             seer_spmv_prepare), -1: no row is cut, -2: some row is cut  */
     int32_t ell_width;    /* SEER_ELL_TM: slots per row = the longest row; SEER_CSR_S: log2
                              of the columns per slab                                     */
     void *device;         /* DEVICE, inside plan_mem; NULL for kernels without a plan   */
@@ -311,7 +312,8 @@ size_t seer_ell_plan_bytes(int32_t rows, int32_t max_len);
  * S < 2 (x is one slab) or S * rows >= 2^31.
  * The slab width: w = 19 (2 MiB of x); w = 20 if that gives at least four slabs and fewer
  * than three entries are to be expected per piece of a row (nnz / rows < 3 * ceil(cols / 2^19));
- * the "slab_shift" tuning knob overrides both.  The plan keeps its w in ell_width. */
+ * the "slab_shift" tuning knob overrides both.  The plan keeps its w in ell_width.  Where the
+ * preparation may choose bins (see seer_spmv_prepare) the larger of both forms' sizes. */
 size_t seer_slab_plan_bytes(int32_t rows, int32_t cols, int32_t nnz);
 
 /* Runs the preprocessing of `kernel_id` for A on `stream` and fills *plan.  For
@@ -339,6 +341,10 @@ size_t seer_slab_plan_bytes(int32_t rows, int32_t cols, int32_t nnz);
  * are pieces of row 0, then of row 1, ..., in slab order), rp_j (uint32 [rows + 1]: the pieces
  * before row i), then col_idx and values ([nnz + 1] each) in the order of the kept rows;
  * plan->n_blocks = S, plan->split_rows = K.
+ * A matrix of 9 * 2^20 nonzeros or more and at most 2^23 columns whose columns are not local (256
+ * consecutive entries, looked at in 64 places, mostly touch 128 lines of x or more) is kept in bins
+ * instead: w = 15, n_blocks = ceil(cols / 2^15), split_rows = -1 or -2; what plan_mem holds then is
+ * the library's own affair, and a product takes 4.5 to 7 bytes of workspace per nonzero.
  * plan_mem must hold seer_slab_plan_bytes(rows, cols, nnz) (SEER_EWORKSPACE otherwise, with
  * the bytes needed in plan->device_bytes, as for SEER_ELL_TM).  SEER_EINVAL if the form does
  * not apply: by size (seer_slab_plan_bytes gives 0), or because some row's columns do not
@@ -421,7 +427,9 @@ int seer_csr_check(const seer_csr *A, int64_t *bad_row_ptr, int64_t *bad_col_idx
  *               on where x has more than 1 441 792 columns (5.5 MB).  y is the same but for
  *               CSR,BM's summation order
  *   "slab_shift" CSR,S: log2 of the columns per slab, 1..30 (default: 19 or 20, see
- *               seer_slab_plan_bytes); the size functions follow it
+ *               seer_slab_plan_bytes); the size functions follow it, and bins are not used
+ *   "slab_bins" CSR,S: 0: never in bins; 1: in bins whatever nnz is and however local the columns
+ *               are; default: from 9 * 2^20 nonzeros on, columns not local (seer_spmv_prepare)
  *   "coo_runs"  COO,WM: 1 (default): a lane sums a run of eight consecutive triples,
  *               0: lane <-> triple in rounds of 64
  *   "poll"      0: seer_features and seer_csr_check wait with hipStreamSynchronize only;

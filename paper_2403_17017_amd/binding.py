@@ -477,8 +477,8 @@ class Plan:
     """A prepared kernel for one matrix: the host-side record plus the device memory
     the preprocessing wrote (kept alive here)."""
 
-    def __init__(self, c: seer_plan, plan_mem):
-        self.c, self.plan_mem = c, plan_mem
+    def __init__(self, c: seer_plan, plan_mem, row_ptr=None):
+        self.c, self.plan_mem, self.row_ptr = c, plan_mem, row_ptr
 
     kernel_id = property(lambda self: int(self.c.kernel_id))
     n_blocks = property(lambda self: int(self.c.n_blocks))
@@ -500,6 +500,8 @@ class Plan:
         values fp32 [nnz]) of a CSR,S plan for a matrix of `cols` columns, as host arrays."""
         import torch
         rows, nnz, S_, K = int(self.c.rows), int(self.c.nnz), self.n_blocks, int(self.c.split_rows)
+        if K < 0:
+            return self._bins_as_slabs()
         pad = lambda b: (b + 255) & ~255
         m = min(nnz, S_ * rows)
         o_idx = pad((m + 1) * 4)
@@ -510,6 +512,50 @@ class Plan:
         ci = self.plan_mem[o_ci: o_ci + nnz * 4].view(torch.int32).cpu().numpy()
         va = self.plan_mem[o_va: o_va + nnz * 4].view(torch.float32).cpu().numpy()
         return u32(0, K + 1), u32(o_idx, K), u32(o_j, rows + 1), ci, va
+
+    def _bins_as_slabs(self):
+        """The same five arrays from a plan in bins, whose memory holds the entries in another order (the
+        sizes below are those of csrc/spmv_bins.hip) and takes the rows from the matrix."""
+        import torch
+        rows, nnz, n_slabs, w = int(self.c.rows), int(self.c.nnz), self.n_blocks, self.ell_width
+        n = max(1, -(-nnz // 15360))
+        stride, entry_stride = (16384 + 33 * n_slabs + 15) & ~15, (16384 + 27 * n_slabs + 15) & ~15
+        most = (nnz + 27 * min(n_slabs * n, nnz)) // 16 + 1
+        offset = 0
+
+        def take(dtype, count, size):
+            nonlocal offset
+            a = self.plan_mem[offset: offset + count * size].view(dtype).cpu().numpy()
+            offset += (count * size + 255) & ~255
+            return a
+        va, ci = take(torch.float32, most * 16, 4), take(torch.int16, most * 16, 2).view(np.uint16)
+        take(torch.int32, most, 4), take(torch.int16, n * stride, 2), take(torch.int16, rows, 2)
+        starts, _ = take(torch.int32, 3 * n_slabs * n + 1, 4).astype(np.int64), take(torch.int32, n, 4)
+        first = take(torch.int32, 4 * (n + 1), 4)[1::4].astype(np.int64)
+        order = take(torch.int16, n * entry_stride, 2).view(np.uint16).reshape(n, entry_stride // 16, 16)
+        groups = int(starts[-1])
+        counts = np.diff(starts).reshape(n_slabs, n, 3)
+        by_chunk = counts.transpose(0, 2, 1).reshape(3 * n_slabs, n)
+        local = (np.cumsum(by_chunk, axis=0) - by_chunk).reshape(n_slabs, 3, n).transpose(0, 2, 1)   # groups before, in the chunk
+        G = np.arange(groups)
+        bucket = np.searchsorted(starts, G, side="right") - 1
+        chunk = bucket // 3 % n
+        place = order[chunk, local.ravel()[bucket] + G - starts[bucket]]       # [groups, 16]: numbers in the chunk
+        kept = (place != 0xFFFF).ravel()
+        k = (first[chunk][:, None] + place).ravel()[kept]
+        col = ((bucket // (3 * n)) << w)[:, None] | ci[: groups * 16].reshape(-1, 16)
+        col = col.ravel()[kept]
+        csr_col, csr_va = np.empty(nnz, np.int32), np.empty(nnz, np.float32)
+        csr_col[k], csr_va[k] = col, va[: groups * 16][kept]
+        rp = self.row_ptr[: rows + 1].cpu().numpy().astype(np.int64)
+        row = np.repeat(np.arange(rows, dtype=np.int64), np.diff(rp))
+        virtual = (csr_col.astype(np.int64) >> w) * rows + row
+        order = np.argsort(virtual, kind="stable")
+        ids, counts = np.unique(virtual, return_counts=True)
+        rp_z = np.concatenate([[0], np.cumsum(counts)]).astype(np.uint32)
+        p_idx = np.argsort(ids % max(rows, 1), kind="stable").astype(np.uint32)
+        rp_j = np.concatenate([[0], np.cumsum(np.bincount(ids % max(rows, 1), minlength=rows))]).astype(np.uint32)
+        return rp_z, p_idx, rp_j, csr_col[order], csr_va[order]
 
     def coo_rows(self) -> np.ndarray:
         """Row index of every nonzero (int32 [nnz]) as a host array."""
@@ -554,7 +600,7 @@ def seer_spmv_prepare(kernel_id: int, A: DeviceCSR, plan_mem=None, stream=None, 
                                  plan_mem.numel() if plan_mem is not None else 0, _stream_ptr(stream), C.byref(c))
     if rc:
         raise SeerError(rc, f"seer_spmv_prepare(kernel {kernel_id})")
-    return Plan(c, plan_mem)
+    return Plan(c, plan_mem, A.row_ptr)
 
 
 def spmv_prepared_workspace_bytes(plan: Plan) -> int:
@@ -595,4 +641,4 @@ def seer_spmv_plan(A: DeviceCSR, model: Model, iterations: int, plan_mem=None, w
                               C.byref(path))
     if rc:
         raise SeerError(rc, "seer_spmv_plan")
-    return Plan(c, plan_mem), int(path.value)
+    return Plan(c, plan_mem, A.row_ptr), int(path.value)

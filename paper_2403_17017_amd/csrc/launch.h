@@ -90,6 +90,27 @@ void launch_slab_fill(int rows, int cols, int nnz, int shift, uint32_t n_kept, c
                       void *plan_mem, hipStream_t st);
 void launch_slab(const SpmvArgs &a, uint32_t n_slabs, uint32_t n_kept, const void *plan_mem, void *workspace, hipStream_t st);
 
+// exclusive prefix sum over n words in place (a total below 2^32), and the words of scratch it takes
+size_t scan_scratch_words(size_t n);
+void launch_scan_exclusive(uint32_t *data, size_t n, uint32_t *scratch, hipStream_t st);
+
+// CSR,S in bins: the slabs of x lie in LDS.  plan_mem: bins_plan_bytes(); workspace:
+// bins_workspace_bytes() (the products, then carries)
+constexpr int kBinShift = 15;               // 2^15 columns, 128 KB of LDS
+constexpr uint32_t kBinMaxSlabs = 256;      // at most (the preparation's counters, 3 per wave and slab, lie in LDS, too)
+uint32_t bins_num_slabs(int cols);
+bool bins_fit(int cols, int nnz);           // the form can hold a matrix of these sizes
+size_t bins_plan_bytes(int rows, int cols, int nnz);
+size_t bins_workspace_bytes(uint32_t n_slabs, int nnz);
+constexpr size_t kBinFlags = 4;             // words that the preparation leaves at bins_flags(), for the host to read:
+const uint32_t *bins_flags(const void *plan_mem, int rows, int cols, int nnz);
+bool bins_not_taken(const uint32_t *flags); // columns are local, nothing was prepared: the other form is faster
+bool bins_refused(const uint32_t *flags);   // columns do not ascend in a row, or lie outside the matrix
+bool bins_cut(const uint32_t *flags);       // some row is cut: products leave carries
+hipError_t launch_bins_prepare(int rows, int cols, int nnz, const int *rp, const int *ci, const float *va, void *plan_mem,
+                               bool always /* also if columns are local */, hipStream_t st);
+void launch_bins(const SpmvArgs &a, uint32_t n_slabs, bool cut_rows, const void *plan_mem, void *workspace, hipStream_t st);
+
 // feature reduction
 struct FeatureRaw {           // written by the device into pinned host memory
     int32_t max_len, min_len;

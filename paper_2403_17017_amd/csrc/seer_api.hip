@@ -37,6 +37,7 @@ std::atomic<int> g_last_hip_error{0};
 // Tuning hooks (negative = choose automatically).
 std::atomic<int> g_tune_wm_lanes{-1};
 std::atomic<int> g_tune_bm_rows{-1};
+std::atomic<int> g_tune_slab_bins{-1};
 std::atomic<int> g_tune_bm_chunk{-1};
 std::atomic<int> g_tune_mp_ipt{-1};
 std::atomic<int> g_tune_fused_rows{-1};
@@ -245,6 +246,27 @@ int slab_shift(int rows, int cols, int nnz)
     const int64_t slabs = ((int64_t)cols + ((int64_t)1 << kSlabShift) - 1) >> kSlabShift;
     if (rows > 0 && slabs >= 4 && (int64_t)nnz < 3 * slabs * (int64_t)rows) return kSlabShift + 1;
     return kSlabShift;
+}
+
+// Whether CSR,S is prepared in bins (slabs of x in LDS) where its form applies and the columns are not
+// local: from 9.4 M nonzeros on.  Measured, products and preparation, the other form and this: 10 M nonzeros in
+// 4 MB of x 62 and 38 us, 200 and 135; 40 M in 8 MB 227 and 126, 590 and 409; Zipf rows, 62 M in 16 MB
+// 393 and 198, 972 and 602; 35 M in 28 MB 327 and 140.  (Below it, the arrays described in seer.h are what a program finds in plan_mem.)
+// The "slab_bins" knob: 0 never, 1 wherever the number of slabs allows it, also if columns are local; a slab
+// width set by "slab_shift" is the other form's.
+bool slab_bins(int cols, int nnz)
+{
+    const int t = g_tune_slab_bins.load(), w = g_tune_slab_shift.load();
+    if (t == 0 || (w >= 1 && w <= 30) || !bins_fit(cols, nnz)) return false;
+    return t > 0 || nnz >= 9 << 20;
+}
+
+// A plan of CSR,S in bins has no virtual rows to count: split_rows says whether a row is cut.
+constexpr int32_t kBinsWhole = -1, kBinsCut = -2;
+bool is_bins(const seer_plan *plan)
+{
+    return plan->kernel_id == SEER_CSR_S && plan->ell_width == kBinShift && plan->n_blocks >= 2 &&
+           plan->n_blocks <= (int32_t)kBinMaxSlabs && (plan->split_rows == kBinsWhole || plan->split_rows == kBinsCut);
 }
 
 int bm_chunk()
@@ -599,6 +621,7 @@ int seer_set_tuning(const char *name, int value)
     if (!name) return SEER_EINVAL;
     if (!std::strcmp(name, "wm_lanes")) g_tune_wm_lanes.store(value);
     else if (!std::strcmp(name, "bm_rows")) g_tune_bm_rows.store(value);
+    else if (!std::strcmp(name, "slab_bins")) g_tune_slab_bins.store(value);
     else if (!std::strcmp(name, "bm_chunk")) g_tune_bm_chunk.store(value);
     else if (!std::strcmp(name, "mp_ipt")) g_tune_mp_ipt.store(value);
     else if (!std::strcmp(name, "auto_fused_rows")) g_tune_fused_rows.store(value);
@@ -1085,7 +1108,32 @@ size_t seer_ell_plan_bytes(int32_t rows, int32_t max_len) { return ell_plan_byte
 size_t seer_slab_plan_bytes(int32_t rows, int32_t cols, int32_t nnz)
 {
     if (rows < 0 || cols < 0 || nnz < 0) return 0;
-    return slab_plan_bytes(rows, cols, nnz, slab_shift(rows, cols, nnz));
+    const int shift = slab_shift(rows, cols, nnz);
+    const size_t slabs = slab_plan_bytes(rows, cols, nnz, shift);      // 0: the form does not apply
+    return slabs && slab_bins(cols, nnz) ? std::max(slabs, bins_plan_bytes(rows, cols, nnz)) : slabs;
+}
+
+// The column-slabbed form in bins: everything is enqueued, then the flags are read.  *taken: false if the
+// columns are local and the other form is wanted.
+static int prepare_bins(const seer_csr *A, void *plan_mem, void *stream, seer_plan *plan, bool *taken)
+{
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const bool always = g_tune_slab_bins.load() > 0;
+    hipError_t e = launch_bins_prepare(A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, plan_mem, always, st);
+    if (e != hipSuccess) return hip_fail(e);
+    uint32_t flags[kBinFlags] = {};
+    e = hipMemcpyAsync(flags, bins_flags(plan_mem, A->rows, A->cols, A->nnz), sizeof flags, hipMemcpyDeviceToHost, st);
+    if (e != hipSuccess) return hip_fail(e);
+    e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return hip_fail(e);
+    *taken = !bins_not_taken(flags);
+    if (!*taken) return SEER_OK;
+    if (bins_refused(flags)) return SEER_EINVAL;
+    plan->n_blocks = (int32_t)bins_num_slabs(A->cols);
+    plan->ell_width = kBinShift;
+    plan->split_rows = bins_cut(flags) ? kBinsCut : kBinsWhole;
+    plan->device = plan_mem;
+    return SEER_OK;
 }
 
 // The column-slabbed form: counts, the check of the column order and the number of virtual
@@ -1096,9 +1144,14 @@ static int prepare_slab(const seer_csr *A, void *plan_mem, size_t plan_bytes, vo
     const int shift = slab_shift(A->rows, A->cols, A->nnz);
     const uint32_t S = slab_count(A->rows, A->cols, shift);
     if (S == 0) return SEER_EINVAL;                        // one slab, or too many virtual rows
-    const size_t need = slab_plan_bytes(A->rows, A->cols, A->nnz, shift);
+    const size_t need = seer_slab_plan_bytes(A->rows, A->cols, A->nnz);
     plan->device_bytes = need;
     if (!plan_mem || !aligned16(plan_mem) || plan_bytes < need) return SEER_EWORKSPACE;
+    if (slab_bins(A->cols, A->nnz)) {
+        bool taken = false;
+        const int rc = prepare_bins(A, plan_mem, stream, plan, &taken);
+        if (rc != SEER_OK || taken) return rc;
+    }
     hipStream_t st = static_cast<hipStream_t>(stream);
     launch_slab_count(A->rows, A->cols, A->nnz, shift, A->row_ptr, A->col_idx, plan_mem, st);
     hipError_t e = hipGetLastError();
@@ -1223,6 +1276,7 @@ size_t seer_spmv_prepared_workspace_bytes(const seer_plan *plan)
     if (plan->kernel_id == SEER_CSR_A)
         return plan->split_rows ? carry_workspace_bytes((uint32_t)plan->n_blocks) : 0;
     if (plan->kernel_id == SEER_ELL_TM) return 0;
+    if (is_bins(plan)) return bins_workspace_bytes((uint32_t)plan->n_blocks, plan->nnz);
     if (plan->kernel_id == SEER_CSR_S)      // one partial per kept virtual row, then CSR,WO's carries over them
         return plan->split_rows < 0 ? 0 : slab_workspace_bytes((uint32_t)plan->split_rows, plan->nnz);
     return seer_spmv_workspace_bytes(plan->kernel_id, plan->rows, plan->nnz);
@@ -1248,6 +1302,16 @@ int seer_spmv_prepared(const seer_plan *plan, const seer_csr *A, const float *x,
         SpmvArgs a{A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, x, y, use_remap(),
                    use_nt_repeated(csr_footprint(A) + 4ull * (uint64_t)A->nnz)};
         launch_coo(a, coo_runs(), plan->device, workspace, static_cast<hipStream_t>(stream));
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess ? SEER_OK : hip_fail(e);
+    }
+    if (is_bins(plan)) {
+        if ((uint32_t)plan->n_blocks != bins_num_slabs(A->cols)) return SEER_EINVAL;
+        if (!workspace || !aligned16(workspace) || workspace_bytes < seer_spmv_prepared_workspace_bytes(plan))
+            return SEER_EWORKSPACE;
+        SpmvArgs a{A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, x, y, use_remap(), 1};
+        launch_bins(a, (uint32_t)plan->n_blocks, plan->split_rows == kBinsCut, plan->device, workspace,
+                    static_cast<hipStream_t>(stream));
         const hipError_t e = hipGetLastError();
         return e == hipSuccess ? SEER_OK : hip_fail(e);
     }

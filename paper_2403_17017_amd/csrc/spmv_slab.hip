@@ -22,6 +22,7 @@
 // (A first form kept all S * rows virtual rows.  A band or a stencil leaves almost all of
 // them empty, in runs of hundreds of thousands that CSR,WO hands to single workgroups: 50
 // times the plain kernels' time on such matrices.)
+// Large matrices with scattered columns are kept in another form, with slabs that fit LDS (spmv_bins.hip).
 #include "spmv_bodies.hiph"
 
 namespace seer {
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(kWG) void scan_tiles_kernel(uint32_t *__restrict__ 
     }
 }
 
-static size_t scan_scratch_words(size_t n)
+size_t scan_scratch_words(size_t n)
 {
     size_t total = 0;
     while (n > kScanTile) {
@@ -230,7 +231,7 @@ static size_t scan_scratch_words(size_t n)
     return total;
 }
 
-static void launch_scan_exclusive(uint32_t *data, size_t n, uint32_t *scratch, hipStream_t st)
+void launch_scan_exclusive(uint32_t *data, size_t n, uint32_t *scratch, hipStream_t st)
 {
     if (n <= kScanTile) {
         hipLaunchKernelGGL(scan_tiles_kernel, dim3(1), dim3(kWG), 0, st, data, n, static_cast<const uint32_t *>(nullptr));
