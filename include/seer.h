@@ -285,7 +285,9 @@ int seer_spmv_auto_result(const void *workspace, void *stream, seer_features_t *
 typedef struct {
     int32_t kernel_id;
     int32_t rows, nnz;    /* of the matrix it was prepared for                          */
-    int32_t n_blocks;     /* SEER_CSR_A: row blocks in the plan; SEER_CSR_S: column slabs  */
+    int32_t n_blocks;     /* SEER_CSR_A: row blocks in the plan; SEER_CSR_S: column slabs;
+                             SEER_ELL_TM: 1 if products take the columns of most rows from
+                             distances kept behind the arrays (see seer_spmv_prepare), else 0 */
     int32_t split_rows;   /* SEER_CSR_A: 1 if some row is shared between blocks (the
                              product then needs the carry workspace and a second launch);
                              SEER_CSR_S: the number of virtual rows kept, or, in bins (see
@@ -327,7 +329,10 @@ size_t seer_slab_plan_bytes(int32_t rows, int32_t cols, int32_t nnz);
  * workspace, so plan_mem must hold at least seer_features_workspace_bytes(rows)), then
  * writes cols[j * R + i] / vals[j * R + i] = the j-th entry of row i in CSR order, or
  * -1 / 0 where the row is shorter, R = roundup(rows, 64), cols first, vals at half of
- * seer_ell_plan_bytes(rows, longest row).  If plan_mem is too small the call returns
+ * seer_ell_plan_bytes(rows, longest row).  If plan_mem has room for R / 64 * (longest row) more
+ * words, padded to 256 bytes, and 256 bytes, and the arrays take 16 MB or more, the distance from row to column of every 64 rows and
+ * slot is kept there, and where it is mostly one for the 64 rows (stencils, bands) a product hardly
+ * reads the columns.  If plan_mem is too small the call returns
  * SEER_EWORKSPACE and stores the bytes needed in plan->device_bytes, the one output written
  * on an error (the rest of *plan stays as it was): seer_features_workspace_bytes(rows) while
  * plan_mem cannot even hold the reduction's workspace, the size of the ELL form after that,

@@ -589,7 +589,8 @@ def seer_spmv_prepare(kernel_id: int, A: DeviceCSR, plan_mem=None, stream=None, 
     if kernel_id == ELL_TM and plan_mem is None:
         if max_len is None:
             max_len = int(seer_features(A, stream=stream).max_len)
-        need = max(ell_plan_bytes(A.rows, max_len), features_workspace_bytes(A.rows))
+        # (behind the arrays, room for the distances from row to column: a word per 64 rows and slot)
+        need = max(ell_plan_bytes(A.rows, max_len) + -(-A.rows // 64) * max_len * 4 + 512, features_workspace_bytes(A.rows))
     if kernel_id == CSR_S and plan_mem is None:
         need = slab_plan_bytes(A.rows, A.cols, A.nnz)
     if plan_mem is None and need:

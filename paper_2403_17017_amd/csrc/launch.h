@@ -65,9 +65,15 @@ void launch_adaptive(const SpmvArgs &a, bool vec, const void *plan_mem, void *ca
 // ELL,TM: plan_mem holds the ELL columns, then the ELL values (ell_plan_bytes())
 uint32_t ell_rows_pad(int rows);
 size_t ell_plan_bytes(int rows, int width);
+// with_shift: behind the arrays lie ell_shift_bytes() more, the distances from row to column of every 64 rows;
+// ell_sampled(): kEllSampled words that the conversion leaves for ell_shift_pays()
+constexpr size_t kEllSampled = 64;
+bool ell_shift_pays(int rows, int width, const uint32_t *sampled);     // three quarters of the slots looked at have one distance
+size_t ell_shift_bytes(int rows, int width);
+uint32_t *ell_sampled(void *plan_mem, int rows, int width);
 void launch_ell_convert(int rows, int width, const int *rp, const int *ci, const float *va, void *plan_mem,
-                        hipStream_t st);
-void launch_ell(const SpmvArgs &a, int width, const void *plan_mem, hipStream_t st);
+                        bool with_shift, hipStream_t st);
+void launch_ell(const SpmvArgs &a, int width, bool with_shift, const void *plan_mem, hipStream_t st);
 
 // COO,WM: plan_mem holds the row index of every nonzero; carry_ws: carry_workspace_bytes(coo_num_intervals())
 uint32_t coo_num_intervals(int rows, int nnz);

@@ -1200,11 +1200,21 @@ static int prepare_ell(const seer_csr *A, void *plan_mem, size_t plan_bytes, voi
     plan->device_bytes = need;
     if (plan_bytes < need) return SEER_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    launch_ell_convert(A->rows, (int)max_len, A->row_ptr, A->col_idx, A->values, plan_mem, st);
+    // With room behind the arrays the distances from row to column are kept, too, and used if three
+    // quarters of those sampled are one for their 64 rows: the others cost a product a scalar load for
+    // nothing before their columns are asked for.  Not for arrays below 16 MB: their products are a launch and
+    // a chain of loads whatever they read, and the sample's way to the host takes about 8 us.
+    const bool with_shift = need >= 16u << 20 && plan_bytes - need >= ell_shift_bytes(A->rows, (int)max_len);
+    uint32_t sampled[kEllSampled] = {};
+    launch_ell_convert(A->rows, (int)max_len, A->row_ptr, A->col_idx, A->values, plan_mem, with_shift, st);
     hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e);
+    if (with_shift)
+        e = hipMemcpyAsync(sampled, ell_sampled(plan_mem, A->rows, (int)max_len), sizeof sampled, hipMemcpyDeviceToHost, st);
     if (e != hipSuccess) return hip_fail(e);
     e = hipStreamSynchronize(st);
     if (e != hipSuccess) return hip_fail(e);
+    plan->n_blocks = with_shift && ell_shift_pays(A->rows, (int)max_len, sampled) ? 1 : 0;
     plan->ell_width = (int32_t)max_len;
     plan->device = plan_mem;
     return SEER_OK;
@@ -1328,9 +1338,11 @@ int seer_spmv_prepared(const seer_plan *plan, const seer_csr *A, const float *x,
         return e == hipSuccess ? SEER_OK : hip_fail(e);
     }
     if (plan->kernel_id == SEER_ELL_TM) {
+        const bool with_shift = plan->n_blocks == 1;       // then the columns, half of the bytes, are hardly read
         SpmvArgs a{A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, x, y, use_remap(),
-                   use_nt_repeated((uint64_t)plan->device_bytes + 4ull * ((uint64_t)A->rows + (uint64_t)A->cols))};
-        launch_ell(a, plan->ell_width, plan->device, static_cast<hipStream_t>(stream));
+                   use_nt_repeated((uint64_t)plan->device_bytes / (with_shift ? 2u : 1u) +
+                                   4ull * ((uint64_t)A->rows + (uint64_t)A->cols))};
+        launch_ell(a, plan->ell_width, with_shift, plan->device, static_cast<hipStream_t>(stream));
         const hipError_t e = hipGetLastError();
         return e == hipSuccess ? SEER_OK : hip_fail(e);
     }
