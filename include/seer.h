@@ -433,6 +433,11 @@ int seer_csr_check(const seer_csr *A, int64_t *bad_row_ptr, int64_t *bad_col_idx
  *               CSR,BM's summation order
  *   "slab_shift" CSR,S: log2 of the columns per slab, 1..30 (default: 19 or 20, see
  *               seer_slab_plan_bytes); the size functions follow it, and bins are not used
+ *   "long_rows" CSR,WO: 1: from 2^23 nonzeros on and whatever the mean, 0: never: rows of 32 entries
+ *               and more per 2^15 columns are summed apart, with x in LDS, where gathers go by
+ *               column range and the workspace has room; default: from 2^28 nonzeros on with 64
+ *               or more to a row on average and at most 2^22 rows.  The size functions of CSR,WO and
+ *               seer_spmv_auto follow it; with less workspace (their sizes under 0) the stage is left out
  *   "slab_bins" CSR,S: 0: never in bins; 1: in bins whatever nnz is and however local the columns
  *               are; default: from 9 * 2^20 nonzeros on, columns not local (seer_spmv_prepare)
  *   "coo_runs"  COO,WM: 1 (default): a lane sums a run of eight consecutive triples,

@@ -25,6 +25,11 @@ struct GatherRanges {
     uint32_t cell_shift, few_cells;
 };
 
+// Entries of a chunk of CSR,WO that belong to rows summed elsewhere (spmv_long.hip): the first `head`
+// (kLongWhole: all of them, and the row goes on) and the last `tail`.
+struct LongSkip { uint16_t head, tail; };
+constexpr uint16_t kLongWhole = 0x8000u;
+
 struct SpmvArgs {
     int rows, cols, nnz;
     const int *rp, *ci;
@@ -33,6 +38,7 @@ struct SpmvArgs {
     int remap;  // 1: tiles laid out contiguously per XCD
     int nt;     // 1: matrix streams are loaded with the non-temporal hint (keeps x in L2)
     GatherRanges ranges = GatherRanges{};   // count > 0 only where the 16-byte loads are used, too
+    const LongSkip *skip = nullptr;         // CSR,WO with ranges only; null: no entry is left out
 };
 
 bool tm_short_rows(int rows, int nnz);
@@ -160,6 +166,13 @@ struct AutoSel {                            // what the selection leaves in the 
     uint64_t sum_sq, empty;
     float f[SEER_NUM_FEATURES];
 };
+// The long rows of CSR,WO with slabs of x in LDS.  sel: null, or the selection (nothing is done unless it says
+// CSR,WO).  Returns the words for the chunks of CSR,WO (of kWoChunkLarge entries), which lie in the workspace.
+bool long_rows_fit(int rows);                           // rows the stage can list
+size_t long_workspace_bytes(int rows, int cols, int nnz);
+size_t long_workspace_most(int rows, int nnz);          // for any number of columns
+const LongSkip *launch_long(const SpmvArgs &a, const AutoSel *sel, void *workspace, hipStream_t st);
+
 struct AutoShape {                          // launch shapes, all from rows and nnz alone
     uint32_t tiles[SEER_NUM_DIRECT_KERNELS];
     int wm_lanes, bm_rows, bm_own_shift, mp_ipt;
@@ -167,6 +180,7 @@ struct AutoShape {                          // launch shapes, all from rows and 
     int tm_pair;                            // ... and takes two rows per lane (tiles of 512 rows)
     int tm_remap;                           // CSR,TM's tile order: 1 XCD-contiguous, 0 round-robin
     GatherRanges ranges;                    // as in SpmvArgs; ticks: CSR,WO's
+    const LongSkip *skip;                   // as in SpmvArgs
     uint32_t bm_ticks, mp_ticks;
     int bm_ranged;                          // CSR,BM orders its gathers, too
     uint32_t reachable;                     // bit k: the tree can answer kernel k given rows, cols and nnz (never 0)
@@ -189,7 +203,8 @@ struct AutoPolicy {                         // when the selection runs inside th
 // decided: null, or the record of a choice the host could make alone (shape.reachable has
 // one bit): nothing is gathered then.
 void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, const AutoShape &shape, bool vec,
-                 const AutoPolicy &policy, const AutoSel *decided, void *workspace, hipStream_t st);
+                 const AutoPolicy &policy, const AutoSel *decided, void *workspace, void *long_workspace /* null: no
+                 stage for the long rows of CSR,WO */, hipStream_t st);
 
 // counts: two 8-byte words of scratch; the result goes to the mailbox's sum_sq (offsets) and empty (columns)
 void launch_csr_check(int rows, int cols, int nnz, const int *rp, const int *ci, void *counts, FeatureRaw *mailbox_dev,

@@ -38,6 +38,7 @@ std::atomic<int> g_last_hip_error{0};
 std::atomic<int> g_tune_wm_lanes{-1};
 std::atomic<int> g_tune_bm_rows{-1};
 std::atomic<int> g_tune_slab_bins{-1};
+std::atomic<int> g_tune_long_rows{-1};
 std::atomic<int> g_tune_bm_chunk{-1};
 std::atomic<int> g_tune_mp_ipt{-1};
 std::atomic<int> g_tune_fused_rows{-1};
@@ -181,6 +182,18 @@ uint32_t gather_ticks(const GatherRanges &g, int64_t nnz, double entries_per_wg)
     const double under_way = (double)nnz / generations / (double)(1 << 23);
     const double turn_us = (12.0 + 9.5 * std::sqrt(g.x_bytes / 1048576.0)) * under_way;
     return (uint32_t)std::max(1.0, turn_us * 100.0 / g.count);
+}
+
+// Whether CSR,WO sums its long rows apart, with slabs of x in LDS (where its gathers go by range and there is
+// scratch memory for it): from 2^28 nonzeros on, 64 or more to a row on average.  (Zipf rows, 2 M columns, without and
+// with: 471 M nonzeros 2385 and 1255 us, 171 M 928 and 593, 44 M 292 and 256.  A matrix without such rows pays
+// for four launches that find nothing, 12 to 15 us, which on smaller ones is more than the runs of one differ.)
+// The "long_rows" knob: 0 never, 1 from 2^23 nonzeros on, whatever the mean.
+bool long_rows(int rows, int nnz)
+{
+    const int t = g_tune_long_rows.load();
+    if (t == 0 || !long_rows_fit(rows)) return false;
+    return t == 1 ? nnz >= 1 << 23 : nnz >= 1 << 28 && nnz / 64 >= rows;
 }
 
 // Rows per workgroup for CSR,BM, from measurements over banded / random matrices:
@@ -621,6 +634,7 @@ int seer_set_tuning(const char *name, int value)
     if (!name) return SEER_EINVAL;
     if (!std::strcmp(name, "wm_lanes")) g_tune_wm_lanes.store(value);
     else if (!std::strcmp(name, "bm_rows")) g_tune_bm_rows.store(value);
+    else if (!std::strcmp(name, "long_rows")) g_tune_long_rows.store(value);
     else if (!std::strcmp(name, "slab_bins")) g_tune_slab_bins.store(value);
     else if (!std::strcmp(name, "bm_chunk")) g_tune_bm_chunk.store(value);
     else if (!std::strcmp(name, "mp_ipt")) g_tune_mp_ipt.store(value);
@@ -646,7 +660,7 @@ size_t seer_features_workspace_bytes(int32_t rows) { return rows < 0 ? 0 : featu
 size_t seer_spmv_workspace_bytes(int kernel_id, int32_t rows, int32_t nnz)
 {
     if (rows <= 0 || nnz < 0) return 0;
-    if (kernel_id == SEER_CSR_WO) return carry_workspace_bytes(wo_num_tiles(rows, nnz));
+    if (kernel_id == SEER_CSR_WO) return carry_workspace_bytes(wo_num_tiles(rows, nnz)) + (long_rows(rows, nnz) ? long_workspace_most(rows, nnz) : 0);
     if (kernel_id == SEER_CSR_A)   // the carries, then the plan that the call builds for itself
         return carry_workspace_bytes(adaptive_num_tiles(rows, nnz)) + adaptive_plan_bytes(rows, nnz);
     if (kernel_id == SEER_COO_WM)
@@ -763,7 +777,7 @@ int seer_tree_reachable(const seer_tree *tree, const seer_features_t *known, uin
 size_t seer_spmv_auto_workspace_bytes(int32_t rows, int32_t nnz)
 {
     if (rows < 0 || nnz < 0) return 0;
-    return auto_workspace_bytes(rows, nnz);
+    return auto_workspace_bytes(rows, nnz) + (long_rows(rows, nnz) ? long_workspace_most(rows, nnz) : 0);
 }
 
 // Everything seer_spmv_auto checks before it needs scratch memory.  SEER_OK with *enqueue
@@ -789,7 +803,7 @@ static int auto_check(const seer_csr *A, const seer_tree *tree, const float *x, 
 // Launch shapes from rows and nnz, then the launches; `workspace` holds at least
 // auto_workspace_bytes(rows, nnz) bytes.
 static int auto_enqueue(const seer_csr *A, const seer_tree *tree, const float *x, float *y, void *workspace,
-                        void *stream)
+                        size_t workspace_bytes, void *stream)
 {
     AutoShape sh;
     const bool vec = aligned16(A->col_idx) && aligned16(A->values) && g_tune_vec.load() != 0;
@@ -809,6 +823,12 @@ static int auto_enqueue(const seer_csr *A, const seer_tree *tree, const float *x
     sh.tiles[SEER_CSR_MP] = mp_num_tiles(A->rows, A->nnz, sh.mp_ipt);
     sh.tiles[SEER_CSR_WO] = wo_num_tiles(A->rows, A->nnz);
     SpmvArgs a{A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, x, y, use_remap(), 1};
+    sh.skip = nullptr;
+    void *long_ws = nullptr;            // behind the rest, where there is room
+    const size_t before_long = auto_workspace_bytes(A->rows, A->nnz);
+    if (sh.ranges.count && long_rows(A->rows, A->nnz) && workspace_bytes >= before_long &&
+        workspace_bytes - before_long >= long_workspace_bytes(A->rows, A->cols, A->nnz))
+        long_ws = static_cast<char *>(workspace) + before_long;
     sh.ranges.ticks = gather_ticks(sh.ranges, A->nnz, wo_entries(A->nnz));
     sh.bm_ticks = gather_ticks(sh.ranges, A->nnz, bm_entries(A->rows, A->nnz, sh.bm_rows));
     sh.mp_ticks = gather_ticks(sh.ranges, A->nnz, mp_entries(A->rows, A->nnz, sh.mp_ipt));
@@ -842,7 +862,7 @@ static int auto_enqueue(const seer_csr *A, const seer_tree *tree, const float *x
         std::memcpy(dt.nodes, tree->nodes, sizeof(seer_node) * (size_t)tree->n_nodes);
     }
     launch_auto(a, dt, flat ? &heap : nullptr, sh, vec, policy, decided ? &record : nullptr, workspace,
-                static_cast<hipStream_t>(stream));
+                long_ws, static_cast<hipStream_t>(stream));
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? SEER_OK : hip_fail(e);
 }
@@ -855,7 +875,7 @@ int seer_spmv_auto(const seer_csr *A, const seer_tree *tree, const float *x, flo
     if (rc != SEER_OK || !enqueue) return rc;
     if (!workspace || !aligned16(workspace) || workspace_bytes < auto_workspace_bytes(A->rows, A->nnz))
         return SEER_EWORKSPACE;
-    return auto_enqueue(A, tree, x, y, workspace, stream);
+    return auto_enqueue(A, tree, x, y, workspace, workspace_bytes, stream);
 }
 
 int seer_spmv_auto_static(const seer_csr *A, const seer_tree *tree, const float *x, float *y, void *stream)
@@ -881,7 +901,7 @@ int seer_spmv_auto_static(const seer_csr *A, const seer_tree *tree, const float 
         }
         ptr = g_scratch_ptr[dev];
     }
-    return auto_enqueue(A, tree, x, y, ptr, stream);
+    return auto_enqueue(A, tree, x, y, ptr, kStaticScratchBytes, stream);
 }
 
 int seer_spmv_model(const seer_csr *A, const seer_model *model, const float *x, float *y, void *workspace,
@@ -1080,6 +1100,11 @@ static int spmv_dispatch(int kernel_id, const seer_csr *A, const float *x, float
             workspace_bytes < carry_workspace_bytes(wo_num_tiles(A->rows, A->nnz)))
             return SEER_EWORKSPACE;
         a.ranges.ticks = gather_ticks(a.ranges, A->nnz, wo_entries(A->nnz));
+        if (a.ranges.count && long_rows(A->rows, A->nnz)) {
+            const size_t before = carry_workspace_bytes(wo_num_tiles(A->rows, A->nnz));      // (a multiple of 512)
+            if (workspace_bytes - before >= long_workspace_bytes(A->rows, A->cols, A->nnz))
+                a.skip = launch_long(a, nullptr, static_cast<char *>(workspace) + before, st);
+        }
         launch_wo(a, vec, workspace, st);
         break;
     default: {

@@ -305,7 +305,7 @@ __device__ __forceinline__ void auto_dispatch(
             wo_body<kWoChunkLarge, VEC, true, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile,
                                                       reinterpret_cast<float *>(smem),
                                                       reinterpret_cast<uint32_t *>(smem) + bm_lds_words<kWoChunkLarge>(),
-                                                      shape.ranges);
+                                                      shape.ranges, shape.skip);
         else
             wo_body<kWoChunk, VEC, true, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile,
                                                  reinterpret_cast<float *>(smem),
@@ -422,9 +422,10 @@ static uint32_t launch_fused_partials(const SpmvArgs &a, FeatPartial *part, bool
     return n;
 }
 
-void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, const AutoShape &shape, bool vec,
-                 const AutoPolicy &policy, const AutoSel *decided, void *workspace, hipStream_t st)
+void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, const AutoShape &given, bool vec,
+                 const AutoPolicy &policy, const AutoSel *decided, void *workspace, void *long_workspace, hipStream_t st)
 {
+    AutoShape shape = given;
     char *ws = static_cast<char *>(workspace);
     FeatPartial *part = reinterpret_cast<FeatPartial *>(ws);
     AutoSel *sel = reinterpret_cast<AutoSel *>(ws + kAutoSelOffset);
@@ -456,6 +457,7 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
     const bool carries = reachable(SEER_CSR_MP) || reachable(SEER_CSR_WO);
 
     if (decided) {
+        if (long_workspace && decided->kernel_id == SEER_CSR_WO) shape.skip = launch_long(a, nullptr, long_workspace, st);
 #define SEER_DECIDED_LAUNCH(...)                                                                           \
     hipLaunchKernelGGL((spmv_auto_decided_kernel<__VA_ARGS__>), dim3(grid), dim3(kWG), 0, st, a.rows, a.nnz, a.rp, \
                        a.ci, a.va, a.x, a.y, carry_row, carry_val, sel, *decided, shape, a.remap)
@@ -518,6 +520,7 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
                                n_part, sel, tree, shape.reachable);
     }
 
+    if (long_workspace && reachable(SEER_CSR_WO)) shape.skip = launch_long(a, sel, long_workspace, st);
 #define SEER_AUTO_LAUNCH(...)                                                                              \
     hipLaunchKernelGGL((spmv_auto_kernel<__VA_ARGS__>), dim3(grid), dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, \
                        a.va, a.x, a.y, carry_row, carry_val, sel, shape, a.remap)

@@ -1,0 +1,410 @@
+// The long rows of CSR,WO's largest matrices, with slabs of x in LDS.
+// In a matrix of hundreds of millions of nonzeros and skewed row lengths most nonzeros lie in
+// rows of thousands of entries with columns all over x, and CSR,WO gathers them out of L2, one
+// 128-byte request each (Zipf rows, s = 1.6, 2 M columns, 480 M nonzeros: 200 G/s, a third of the rate at
+// which the entries could be read).  Here such rows are cut into slabs of x that LDS holds (2^15 columns)
+// without any preparation: a search per row and slab finds the cuts, one launch takes the pieces
+// of a slab in all long rows with that slab in LDS, a last one adds up each row's pieces, in
+// slab order.  CSR,WO takes the rest: it is told per chunk which entries belong to a long row.
+//
+// A row is long from 32 entries per slab on, if it crosses a chunk boundary, and if its columns at a
+// quarter, half and three quarters of it are within a sixteenth of x of where ascending columns spread
+// evenly would be: then its pieces are of about equal size, and the tasks below are balanced.
+// The cuts are right for any order of columns: a cut is a place in the row, cuts never descend
+// (each is raised to the ones before it), and an entry whose column lies outside the slab of its piece
+// is gathered from x.
+// 471 M nonzeros, Zipf s = 1.6: list 10 us, cuts 79, products 664 (five sixths of the nonzeros, read at 4.8 TB/s),
+// sums 7, CSR,WO over the rest 480; all of them by CSR,WO 2370.  Tried: rows from 16 entries per slab on, the same
+// with twice the scratch memory; a wave per piece from 128 entries on, 1289 in all against 1255.
+#include "spmv_bodies.hiph"
+
+namespace seer {
+
+constexpr uint32_t kLongShift = 15;
+constexpr uint32_t kLongCols = 1u << kLongShift;    // columns per slab: 128 KB of LDS
+constexpr uint32_t kLongWG = 1024;
+constexpr uint32_t kLongGrid = 256;                 // workgroups of long_multiply_kernel: one per CU
+constexpr uint32_t kLongRows = 4096;                // rows per workgroup of long_list_kernel
+// Rows by the length of their pieces: 8 lanes, 16 lanes and a wave take a piece of class 0 (32 entries on
+// average and more), 1 (64) and 2 (256).
+constexpr uint32_t kLongClasses = 3;
+__host__ __device__ inline uint32_t long_class_piece(uint32_t k) { return k == 0 ? 32u : k == 1 ? 64u : 256u; }
+
+struct LongRow { uint32_t row, start, end, pad; };
+
+static uint32_t long_slabs(int cols) { return ((uint32_t)cols + kLongCols - 1u) >> kLongShift; }
+
+// ---- 1: the long rows of every 4096 rows into the workgroup's part of a list, and the words per chunk of
+// CSR,WO to zero.  A part is placed by the nonzeros before it, so that none runs into the next and nothing is
+// counted by atomics (a list per class filled that way took 13 us and a launch to clear its counters, 2 M rows; this 9).
+__host__ __device__ inline uint32_t long_part(uint32_t nnz_before, uint32_t least, uint32_t part) { return nnz_before / least + part; }
+
+__global__ __launch_bounds__(kWG) void long_list_kernel(
+    int rows, uint32_t cols, uint32_t n_slabs, const int *__restrict__ rp, const int *__restrict__ ci,
+    uint32_t *__restrict__ counts /* [parts][4]: rows of each class, where the part begins */, LongRow *__restrict__ list,
+    uint32_t *__restrict__ skip_words, uint32_t n_skip, const AutoSel *__restrict__ sel)
+{
+    __shared__ uint32_t s_row[kLongRows], s_n, s_class[kLongClasses];
+    if (sel && sel->kernel_id != SEER_CSR_WO) return;
+    const uint32_t r0 = blockIdx.x * kLongRows, tid = threadIdx.x, r1 = min(r0 + kLongRows, (uint32_t)rows);
+    if (tid == 0) s_n = 0;
+    if (tid < kLongClasses) s_class[tid] = 0;
+    for (uint32_t i = blockIdx.x * kWG + tid; i < n_skip; i += gridDim.x * kWG) skip_words[i] = 0;
+    __syncthreads();
+    const uint32_t least = long_class_piece(0) * n_slabs;
+#pragma unroll 8
+    for (uint32_t i = 0; i < kLongRows / kWG; ++i) {
+        const uint32_t r = r0 + i * kWG + tid, rc = min(r, r1 - 1u);
+        const uint32_t a = (uint32_t)rp[rc], e = (uint32_t)rp[rc + 1u];
+        if (r < r1 && e - a >= least && a / kWoChunkLarge != (e - 1u) / kWoChunkLarge) s_row[atomicAdd(&s_n, 1u)] = r;
+    }
+    __syncthreads();
+    const uint32_t n = s_n;
+    const uint32_t first = long_part(r0 < r1 ? (uint32_t)rp[r0] : 0u, least, blockIdx.x);
+    // two looks at the rows found: how many of each class, then each into its class's place
+    for (uint32_t look = 0; look < 2; ++look) {
+        uint32_t at[kLongClasses] = {0, s_class[0], s_class[0] + s_class[1]};
+        __syncthreads();
+        if (look == 1 && tid == 0)
+            *reinterpret_cast<uint4 *>(counts + 4u * blockIdx.x) = make_uint4(s_class[0], s_class[1], s_class[2], first);
+        if (look == 1 && tid < kLongClasses) s_class[tid] = 0;
+        __syncthreads();
+        for (uint32_t i = tid; i < n; i += kWG) {
+            const uint32_t row = s_row[i], a = (uint32_t)rp[row], e = (uint32_t)rp[row + 1], len = e - a;
+            bool spread = true;
+#pragma unroll
+            for (uint32_t q = 1; q < 4; ++q) {
+                const int64_t want = (int64_t)(cols / 4u) * q, got = ci[a + (uint32_t)((uint64_t)len * q / 4u)];
+                spread = spread && (got > want ? got - want : want - got) <= (int64_t)(cols / 16u);
+            }
+            if (!spread) continue;
+            const uint32_t k = len >= long_class_piece(2) * n_slabs ? 2u : len >= long_class_piece(1) * n_slabs ? 1u : 0u;
+            const uint32_t j = atomicAdd(&s_class[k], 1u);
+            if (look == 1) list[first + at[k] + j] = LongRow{row, a, e, 0u};
+        }
+        __syncthreads();
+    }
+}
+
+// ---- 2: the cuts.  The parts of the list, class by class, make one order of all long rows: number j of the
+// first part's class 0 row, then the next part's ..., then class 1, class 2.  Every workgroup finds
+// the parts' first numbers for itself (s_from).  Returns N, the number of long rows.  kWG lanes; parts > 0.
+constexpr uint32_t kLongParts = 1024;                // of the list, at most: 4 M rows (long_rows_fit)
+__device__ __forceinline__ uint32_t long_numbers(
+    uint32_t parts, const uint32_t *__restrict__ counts, uint32_t *s_from /* LDS [kLongClasses * parts + 1] */,
+    uint32_t *s_w /* LDS [kWG / kWave] */, uint32_t *s_n /* LDS [kLongClasses]: rows of each class */)
+{
+    constexpr uint32_t E = kLongParts / kWG;
+    const uint32_t tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    uint4 c[E];                                                  // of consecutive parts, all fetched at once
+#pragma unroll
+    for (uint32_t i = 0; i < E; ++i) {
+        const uint32_t p = min(tid * E + i, parts - 1u);
+        c[i] = *reinterpret_cast<const uint4 *>(counts + 4u * p);
+        if (tid * E + i >= parts) c[i] = make_uint4(0, 0, 0, 0);
+    }
+    uint32_t run = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kLongClasses; ++k) {
+        uint32_t v[E], sum = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < E; ++i) {
+            v[i] = sum;
+            sum += k == 0 ? c[i].x : k == 1 ? c[i].y : c[i].z;
+        }
+        uint32_t incl = sum;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const uint32_t up = (uint32_t)__shfl_up((int)incl, off);
+            if ((int)lane >= off) incl += up;
+        }
+        if (lane == kWave - 1) s_w[wave] = incl;
+        __syncthreads();
+        uint32_t before = run + incl - sum, all = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < kWG / kWave; ++w) {
+            before += w < wave ? s_w[w] : 0u;
+            all += s_w[w];
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < E; ++i)
+            if (tid * E + i < parts) s_from[k * parts + tid * E + i] = before + v[i];
+        if (tid == 0) s_n[k] = all;
+        run += all;
+        __syncthreads();
+    }
+    if (tid == 0) s_from[kLongClasses * parts] = run;
+    __syncthreads();
+    return run;
+}
+
+// Wave <-> row, lane <-> slab: cut[s * N + j] = first place of slab s in row j.  The search begins where the
+// column would be if the row's columns were spread evenly, comes nearer twice by the distance of the column
+// found, then widens in steps that double; every one ends at the row's ends at the latest.  The words per
+// chunk are set here, too, and the rows listed by number for the last pass.
+__global__ __launch_bounds__(kWG) void long_cut_kernel(
+    uint32_t cols, uint32_t n_slabs, uint32_t parts, const int *__restrict__ ci, const uint32_t *__restrict__ counts,
+    const LongRow *__restrict__ list, uint32_t *__restrict__ numbers /* [4]: rows of each class, all */,
+    uint32_t *__restrict__ rows_by_number, uint32_t *__restrict__ cut, LongSkip *__restrict__ skip, const AutoSel *__restrict__ sel)
+{
+    __shared__ uint32_t s_from[kLongClasses * kLongParts + 1], s_w[kWG / kWave], s_n[kLongClasses];
+    if (sel && sel->kernel_id != SEER_CSR_WO) return;
+    const uint32_t N = long_numbers(parts, counts, s_from, s_w, s_n);
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        *reinterpret_cast<uint4 *>(numbers) = make_uint4(s_n[0], s_n[1], s_n[2], N);
+    const uint32_t lane = threadIdx.x % kWave, waves = gridDim.x * (kWG / kWave);
+    for (uint32_t j = blockIdx.x * (kWG / kWave) + threadIdx.x / kWave; j < N; j += waves) {
+        uint32_t lo_f = 0, hi_f = kLongClasses * parts;         // the last part whose first number is at most j
+        while (lo_f + 1u < hi_f) {
+            const uint32_t mid = (lo_f + hi_f) / 2u;
+            if (s_from[mid] <= j) lo_f = mid; else hi_f = mid;
+        }
+        const uint32_t k = lo_f / parts, part = lo_f - k * parts;
+        const uint4 c4 = *reinterpret_cast<const uint4 *>(counts + 4u * part);
+        const LongRow r = list[c4.w + (k > 0u ? c4.x : 0u) + (k > 1u ? c4.y : 0u) + (j - s_from[lo_f])];
+        const uint32_t len = r.end - r.start;
+        if (lane == 0) rows_by_number[j] = r.row;
+        {
+            const uint32_t first = r.start / kWoChunkLarge, last = (r.end - 1u) / kWoChunkLarge;
+            if (lane == 0) {
+                // (chunk 0 still has the empty rows before its first nonzero to write)
+                if (r.start % kWoChunkLarge == 0 && r.start > 0u) skip[first].head = kLongWhole | kWoChunkLarge;
+                else skip[first].tail = (uint16_t)(kWoChunkLarge - r.start % kWoChunkLarge);
+                skip[last].head = (uint16_t)(r.end - last * kWoChunkLarge);
+            }
+            for (uint32_t t = first + 1u + lane; t < last; t += kWave) skip[t].head = kLongWhole | kWoChunkLarge;
+        }
+        const float scale = (float)len / (float)cols;
+        uint32_t most = r.start;                                // of the cuts before these 64
+        for (uint32_t s0 = 0; s0 <= n_slabs; s0 += kWave) {
+            const uint32_t s = s0 + lane;
+            uint32_t at = r.start;
+            if (s >= n_slabs) {
+                at = r.end;
+            } else if (s > 0) {
+                const int key = (int)(s << kLongShift);         // (s < n_slabs: below cols)
+                uint32_t lo = r.start, hi = r.end, step = 4;    // the cut is in [lo, hi]
+                int p = (int)((float)key * scale);              // from the row's start
+                p = min(max(p, 0), (int)len - 1);
+                int c = ci[r.start + (uint32_t)p];
+#pragma unroll
+                for (int near = 0; near < 2; ++near) {
+                    p = min(max(p + (int)((float)(key - c) * scale), 0), (int)len - 1);
+                    c = ci[r.start + (uint32_t)p];
+                }
+                if (c < key) {
+                    lo = r.start + (uint32_t)p + 1u;
+                    while (lo < hi) {                           // (each turn raises lo or ends)
+                        const uint32_t q = min(lo + step, r.end - 1u);
+                        if (ci[q] >= key) { hi = q; break; }
+                        lo = q + 1u;
+                        step *= 2u;
+                    }
+                } else {
+                    hi = r.start + (uint32_t)p;
+                    while (lo < hi) {                           // (each turn lowers hi or ends)
+                        const uint32_t q = hi - lo > step ? hi - step : lo;
+                        if (ci[q] < key) { lo = q + 1u; break; }
+                        hi = q;
+                        step *= 2u;
+                    }
+                }
+                while (lo < hi) {
+                    const uint32_t mid = lo + (hi - lo) / 2u;
+                    if (ci[mid] < key) lo = mid + 1u; else hi = mid;
+                }
+                at = lo;
+            }
+            at = max(at, most);
+#pragma unroll
+            for (int off = 1; off < kWave; off <<= 1) {
+                const uint32_t up = (uint32_t)__shfl_up((int)at, off);
+                if ((int)lane >= off) at = max(at, up);
+            }
+            if (s <= n_slabs) cut[(size_t)s * N + j] = at;
+            most = (uint32_t)__shfl((int)at, kWave - 1);
+        }
+    }
+}
+
+// ---- 3: the pieces.  Task (slab, q) takes every Q-th row's piece in the slab; G lanes take a piece, four
+// entries a lane at a time, twice.
+template <uint32_t G>
+__device__ __forceinline__ void long_pieces(
+    uint32_t j0, uint32_t n, uint32_t q, uint32_t Q, uint32_t N, uint32_t s, uint32_t c0, uint32_t nc, uint32_t nnz,
+    const int *__restrict__ ci, const float *__restrict__ va, const float *__restrict__ x, const float *__restrict__ s_x,
+    const uint32_t *__restrict__ cut, float *__restrict__ part)
+{
+    constexpr uint32_t U = 2, kGroups = kLongWG / G;
+    const uint32_t lg = threadIdx.x % G, group = threadIdx.x / G;
+    const uint32_t *lo = cut + (size_t)s * N + j0, *hi = lo + N;
+    const uint32_t stride = Q * kGroups;
+    uint32_t i = q + Q * group;
+    uint32_t a = i < n ? lo[i] : 0u, e = i < n ? hi[i] : 0u;
+    // whole waves go on together (the sum below is over lanes): until no group of the wave has a piece
+    while (__ballot(i < n)) {
+        const uint32_t next = i + stride;
+        const uint32_t na = next < n ? lo[next] : 0u, ne = next < n ? hi[next] : 0u;
+        float t[4] = {0.f, 0.f, 0.f, 0.f};
+        for (uint32_t k0 = a + 4u * lg; k0 < e; k0 += 4u * G * U) {
+            v4i c[U];
+            v4f v[U];
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t k = k0 + u * 4u * G;
+                c[u] = v4i{0, 0, 0, 0};
+                v[u] = v4f{0.f, 0.f, 0.f, 0.f};
+                if (k + 4u <= nnz) {
+                    if (k < e) {
+                        c[u] = __builtin_nontemporal_load(reinterpret_cast<const v4i_a4 *>(ci + k));
+                        v[u] = __builtin_nontemporal_load(reinterpret_cast<const v4f_a4 *>(va + k));
+                    }
+                } else {                                        // the last three entries of the matrix
+                    if (k < e) { c[u].x = ci[k]; v[u].x = va[k]; }
+                    if (k + 1u < e) { c[u].y = ci[k + 1u]; v[u].y = va[k + 1u]; }
+                    if (k + 2u < e) { c[u].z = ci[k + 2u]; v[u].z = va[k + 2u]; }
+                }
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t k = k0 + u * 4u * G;
+                const uint32_t cc[4] = {(uint32_t)c[u].x, (uint32_t)c[u].y, (uint32_t)c[u].z, (uint32_t)c[u].w};
+                const float vv[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+                for (uint32_t w = 0; w < 4; ++w) {
+                    if (k + w >= e) continue;
+                    const uint32_t o = cc[w] - c0;
+                    const float xv = o < nc ? s_x[o] : x[cc[w]];
+                    t[w] += vv[w] * xv;
+                }
+            }
+        }
+        const float sum = group_sum<(int)G>((t[0] + t[1]) + (t[2] + t[3]));
+        if (i < n && lg == 0) part[(size_t)s * N + j0 + i] = sum;
+        i = next;
+        a = na;
+        e = ne;
+    }
+}
+
+__global__ __launch_bounds__(kLongWG) void long_multiply_kernel(
+    uint32_t cols, uint32_t nnz, uint32_t n_slabs, uint32_t Q, const int *__restrict__ ci, const float *__restrict__ va,
+    const float *__restrict__ x, const uint32_t *__restrict__ numbers, const uint32_t *__restrict__ cut,
+    float *__restrict__ part, const AutoSel *__restrict__ sel)
+{
+    __shared__ __attribute__((aligned(16))) float s_x[kLongCols];
+    if (sel && sel->kernel_id != SEER_CSR_WO) return;
+    const uint4 n = *reinterpret_cast<const uint4 *>(numbers);
+    const uint32_t N = n.w, tid = threadIdx.x;
+    if (N == 0) return;
+    for (uint32_t task = tile_of_block(blockIdx.x, gridDim.x, 1); task < n_slabs * Q; task += gridDim.x) {
+        const uint32_t s = task / Q, q = task - s * Q;
+        const uint32_t c0 = s << kLongShift, nc = min(cols - c0, kLongCols);
+        __syncthreads();                                        // the slab before has been used
+        {
+            v4f t[kLongCols / 4u / kLongWG];
+#pragma unroll
+            for (uint32_t m = 0; m < kLongCols / 4u / kLongWG; ++m) {
+                const uint32_t k = 4u * (m * kLongWG + tid);
+                t[m] = v4f{0.f, 0.f, 0.f, 0.f};
+                if (k + 4u <= nc) {
+                    t[m] = *reinterpret_cast<const v4f_a4 *>(x + c0 + k);
+                } else {
+                    if (k < nc) t[m].x = x[c0 + k];
+                    if (k + 1u < nc) t[m].y = x[c0 + k + 1u];
+                    if (k + 2u < nc) t[m].z = x[c0 + k + 2u];
+                }
+            }
+#pragma unroll
+            for (uint32_t m = 0; m < kLongCols / 4u / kLongWG; ++m)
+                *reinterpret_cast<v4f *>(s_x + 4u * (m * kLongWG + tid)) = t[m];
+        }
+        __syncthreads();
+        long_pieces<64>(n.x + n.y, n.z, q, Q, N, s, c0, nc, nnz, ci, va, x, s_x, cut, part);
+        long_pieces<16>(n.x, n.y, q, Q, N, s, c0, nc, nnz, ci, va, x, s_x, cut, part);
+        long_pieces<8>(0u, n.x, q, Q, N, s, c0, nc, nnz, ci, va, x, s_x, cut, part);
+    }
+}
+
+// ---- 4: each long row's pieces, added up in slab order by eight sums.
+__global__ __launch_bounds__(kWG) void long_total_kernel(
+    uint32_t n_slabs, const uint32_t *__restrict__ numbers, const uint32_t *__restrict__ rows_by_number,
+    const float *__restrict__ part, float *__restrict__ y, const AutoSel *__restrict__ sel)
+{
+    if (sel && sel->kernel_id != SEER_CSR_WO) return;
+    const uint32_t N = numbers[3];
+    for (uint32_t j = blockIdx.x * kWG + threadIdx.x; j < N; j += gridDim.x * kWG) {
+        float t[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        uint32_t s = 0;
+        for (; s + 8u <= n_slabs; s += 8u) {
+#pragma unroll
+            for (uint32_t w = 0; w < 8; ++w) t[w] += part[(size_t)(s + w) * N + j];
+        }
+        for (; s < n_slabs; ++s) t[0] += part[(size_t)s * N + j];
+        y[rows_by_number[j]] = ((t[0] + t[4]) + (t[2] + t[6])) + ((t[1] + t[5]) + (t[3] + t[7]));
+    }
+}
+
+// ------------------------------------------------------------------ host side
+static size_t pad256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+struct LongLayout { size_t numbers, counts, skip, list, rows, cut, part, total; uint32_t parts, skip_words; };
+static LongLayout long_layout(int rows, uint32_t nnz, uint32_t n_slabs)
+{
+    LongLayout L;
+    const size_t tiles = ((size_t)nnz + kWoChunkLarge - 1) / kWoChunkLarge;
+    const size_t most = nnz / (long_class_piece(0) * n_slabs);                        // long rows
+    size_t o = 0;
+    L.parts = ((uint32_t)rows + kLongRows - 1) / kLongRows;
+    L.skip_words = (uint32_t)(tiles * sizeof(LongSkip) / 4);
+    L.numbers = o;   o += 256;
+    L.counts = o;    o += pad256((size_t)L.parts * 16);
+    L.skip = o;      o += pad256((size_t)L.skip_words * 4);
+    L.list = o;      o += pad256((most + L.parts) * sizeof(LongRow));
+    L.rows = o;      o += pad256(most * 4 + 4);
+    L.cut = o;       o += pad256(((size_t)n_slabs + 1) * most * 4 + 4);
+    L.part = o;      o += pad256((size_t)n_slabs * most * 4 + 4);
+    L.total = o;
+    return L;
+}
+
+bool long_rows_fit(int rows) { return rows > 0 && ((uint32_t)rows + kLongRows - 1) / kLongRows <= kLongParts; }
+size_t long_workspace_bytes(int rows, int cols, int nnz) { return long_layout(rows, (uint32_t)nnz, long_slabs(cols)).total; }
+// For any number of slabs from two on: 24 bytes per long row, of which there are at most nnz / 64, and 8 bytes for
+// each of at most nnz / 32 pieces.
+size_t long_workspace_most(int rows, int nnz)
+{
+    const size_t n = (size_t)nnz, parts = ((size_t)rows + kLongRows - 1) / kLongRows;
+    return 24 * (n / 64) + 8 * (n / 32) + (n / kWoChunkLarge + 1) * sizeof(LongSkip) + 32 * parts + 4096;
+}
+
+const LongSkip *launch_long(const SpmvArgs &a, const AutoSel *sel, void *workspace, hipStream_t st)
+{
+    const uint32_t S = long_slabs(a.cols), nnz = (uint32_t)a.nnz;
+    const LongLayout L = long_layout(a.rows, nnz, S);
+    char *base = static_cast<char *>(workspace);
+    uint32_t *numbers = reinterpret_cast<uint32_t *>(base + L.numbers), *counts = reinterpret_cast<uint32_t *>(base + L.counts);
+    LongSkip *skip = reinterpret_cast<LongSkip *>(base + L.skip);
+    LongRow *list = reinterpret_cast<LongRow *>(base + L.list);
+    uint32_t *rows = reinterpret_cast<uint32_t *>(base + L.rows), *cut = reinterpret_cast<uint32_t *>(base + L.cut);
+    float *part = reinterpret_cast<float *>(base + L.part);
+    hipLaunchKernelGGL(long_list_kernel, dim3(L.parts), dim3(kWG), 0, st, a.rows, (uint32_t)a.cols, S, a.rp, a.ci, counts, list,
+                       reinterpret_cast<uint32_t *>(skip), L.skip_words, sel);
+    hipLaunchKernelGGL(long_cut_kernel, dim3(2048), dim3(kWG), 0, st, (uint32_t)a.cols, S, L.parts, a.ci,
+                       static_cast<const uint32_t *>(counts), static_cast<const LongRow *>(list), numbers, rows, cut, skip, sel);
+    // tasks per slab: so many that the tasks fill whole rounds of the grid best
+    uint32_t Q = 1;
+    double best = 0.0;
+    for (uint32_t q = 1; q <= 8; ++q) {
+        const uint32_t tasks = S * q, rounds = (tasks + kLongGrid - 1) / kLongGrid;
+        const double filled = (double)tasks / ((double)rounds * kLongGrid);
+        if (rounds <= 4 && filled > best + 0.01) { best = filled; Q = q; }
+    }
+    hipLaunchKernelGGL(long_multiply_kernel, dim3(kLongGrid), dim3(kLongWG), 0, st, (uint32_t)a.cols, nnz, S, Q, a.ci, a.va,
+                       a.x, static_cast<const uint32_t *>(numbers), static_cast<const uint32_t *>(cut), part, sel);
+    hipLaunchKernelGGL(long_total_kernel, dim3(256), dim3(kWG), 0, st, S, static_cast<const uint32_t *>(numbers),
+                       static_cast<const uint32_t *>(rows), static_cast<const float *>(part), a.y, sel);
+    return skip;
+}
+
+} // namespace seer
