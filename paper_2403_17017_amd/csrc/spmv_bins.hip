@@ -162,6 +162,7 @@ __global__ __launch_bounds__(kWG) void bins_table_kernel(
 struct BinEntry {                                               // one entry among the 64 that its wave looks at
     uint32_t slab, part, sub;                                   // sub: its number within its sixteen or four
     bool bad;
+    bool runs;                                                  // some run among the 64 has four entries (wave-uniform)
 };
 // All lanes of a wave together; `prev`: the column before lane 0's, handed on to the next 64.
 __device__ __forceinline__ BinEntry bins_entry(
@@ -174,7 +175,12 @@ __device__ __forceinline__ BinEntry bins_entry(
     r.slab = min(c >> kBinShift, n_slabs - 1u);
     // the run of one row and one slab that the lane is in: n entries from lane - o on
     const bool opens = !in || starts_row || lane == 0 || r.slab != min(before >> kBinShift, n_slabs - 1u);
-    const uint64_t open = __ballot(opens), upto = open & (~0ull >> (63u - lane)), after = lane == 63u ? 0ull : open >> (lane + 1u);
+    const uint64_t open = __ballot(opens);
+    r.part = kSingles;
+    r.sub = 0;
+    r.runs = (~open & ~open >> 1 & ~open >> 2) != 0;
+    if (!r.runs) return r;                                      // (nearly always where rows are short: half of the work)
+    const uint64_t upto = open & (~0ull >> (63u - lane)), after = lane == 63u ? 0ull : open >> (lane + 1u);
     const uint32_t o = lane - (63u - (uint32_t)__clzll((long long)upto));
     const uint32_t n = o + (after ? (uint32_t)__ffsll((long long)after) : 64u - lane);
     r.part = o < (n & ~15u) ? kSixteens : o < (n & ~3u) ? kFours : kSingles;
@@ -298,7 +304,7 @@ __global__ __launch_bounds__(kBinWG, 8) void bins_sort_kernel(
         uint32_t at = 0;
         if (in && e.sub == 0)
             at = atomicAdd(&s_hist[wave * nb + e.slab * kParts + e.part], bins_unit(e.part));
-        at = (uint32_t)__shfl((int)at, (int)(lane - e.sub)) + e.sub;
+        if (e.runs) at = (uint32_t)__shfl((int)at, (int)(lane - e.sub)) + e.sub;
         if (in) s_out[at] = (uint16_t)i;
     });
     __syncthreads();
@@ -315,12 +321,20 @@ __global__ __launch_bounds__(kBinWG, 8) void bins_sort_kernel(
 #pragma unroll 1
         for (uint32_t i = tid; i < total * (kBinGroup / 8u); i += kBinWG) out[i] = reinterpret_cast<const v4u *>(s_order)[i];
     }
+    // perm, four entries of the order at a time: as many words of single entries, one word of fours, and of a
+    // sixteen one for its first four
+    const auto slot_or_none = [&](uint32_t i) { return i == kBinNone ? kBinNone : slot_of(i); };
 #pragma unroll 1
-    for (uint32_t k = tid; k < total * kBinGroup; k += kBinWG) {
-        const uint32_t bucket = s_of[k / kBinGroup], shift = 2u * (bucket % kParts), rel = k - s_loc[bucket];   // log2 of the unit
-        if (rel & ((1u << shift) - 1u)) continue;
-        const uint32_t i = s_out[k];
-        my_perm[s_word[bucket] + (rel >> shift)] = (uint16_t)(i == kBinNone ? kBinNone : slot_of(i));
+    for (uint32_t k = 4u * tid; k < total * kBinGroup; k += 4u * kBinWG) {
+        const uint32_t bucket = s_of[k / kBinGroup], part = bucket % kParts, rel = k - s_loc[bucket];
+        const v2u four = *reinterpret_cast<const v2u *>(s_out + k);
+        uint16_t *to = my_perm + s_word[bucket] + rel / bins_unit(part);
+        const uint32_t first = slot_or_none(four.x & 0xFFFFu);
+        if (part == kSingles)
+            *reinterpret_cast<v2u *>(to) = v2u{first | slot_or_none(four.x >> 16) << 16,
+                                               slot_or_none(four.y & 0xFFFFu) | slot_or_none(four.y >> 16) << 16};
+        else if (part == kFours || (rel & 15u) == 0)
+            *to = (uint16_t)first;
     }
     if (tid == 0) {
         chunk_words[chunk] = words;
