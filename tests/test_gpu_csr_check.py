@@ -142,3 +142,21 @@ def test_a_call_behind_long_work_holds_up_no_other_thread(first):
     assert results == [(0, 0)] * 5
     # (a few streams share a hardware queue, so not necessarily all of them)
     assert any(k != 0 and not through for k, through in done), "every call waited for the busy stream"
+
+
+def test_counters_start_from_zero_after_a_bad_matrix():
+    """Calls share their counters with the calls after them: alternating good and bad matrices, each
+    call gets its own counts, on one stream and on two."""
+    import torch
+    A = G.random_lengths(5_003, 3_000, 0, 40, 21)
+    ci = A.col_idx.copy()
+    ci[[3, 700, 701, ci.size - 1]] = A.cols
+    bad = S.DeviceCSR.from_host(G.HostCSR(A.rows, A.cols, A.row_ptr, ci, A.values, "four-outside"))
+    good = S.DeviceCSR.from_host(A)
+    announce("seer_csr_check, good and bad in turn")
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for k in range(12):
+        stream = other if k % 3 == 2 else None
+        assert tuple(S.seer_csr_check(bad, stream=stream)) == (0, 4)
+        assert tuple(S.seer_csr_check(good, stream=stream)) == (0, 0)
