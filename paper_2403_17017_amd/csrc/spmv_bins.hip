@@ -612,9 +612,15 @@ __global__ __launch_bounds__(kBinWG) void bins_sum_kernel(
     const auto slot_of = [&](uint32_t r) -> uint32_t {          // first slot of row lo + r; of the row after the last: the end
         return r == 0 ? 0u : r < n_rows ? (uint32_t)row_slot[lo + r] : slots;
     };
-    const uint32_t r0 = tid >> gshift;
-    const bool in0 = r0 < n_rows;
-    const uint32_t ra = in0 ? slot_of(r0) : 0u, rb = in0 ? slot_of(r0 + 1u) : 0u;
+    constexpr uint32_t NB = 4;                                  // batches of rows whose slots are fetched ahead: of rows of two or three
+    uint32_t ra[NB], rb[NB];                                    // entries a chunk has several
+#pragma unroll
+    for (uint32_t k = 0; k < NB; ++k) {
+        if (k * kBinWG >= n_rows) break;                        // block-uniform
+        const uint32_t r = (tid >> gshift) + k * kBinWG;
+        ra[k] = r < n_rows ? slot_of(r) : 0u;
+        rb[k] = r < n_rows ? slot_of(r + 1u) : 0u;
+    }
     constexpr uint32_t U = 4;
     for (uint32_t q0 = tid; q0 < quads; q0 += U * kBinWG) {
         v2u pl[U];
@@ -636,8 +642,13 @@ __global__ __launch_bounds__(kBinWG) void bins_sum_kernel(
         }
     }
     __syncthreads();
-    bins_rows(in0, lo + r0, ra, rb, hi, lane, gshift, most, s_prod, y, carry_val, chunk);
-    for (uint32_t base = kBinWG; base < n_rows; base += kBinWG) {    // short and empty rows
+#pragma unroll
+    for (uint32_t k = 0; k < NB; ++k) {
+        if (k * kBinWG >= n_rows) break;                        // block-uniform
+        const uint32_t r = (tid >> gshift) + k * kBinWG;
+        bins_rows(r < n_rows, lo + r, ra[k], rb[k], hi, lane, gshift, most, s_prod, y, carry_val, chunk);
+    }
+    for (uint32_t base = NB * kBinWG; base < n_rows; base += kBinWG) {    // mostly empty rows
         const uint32_t r = base + tid;
         const bool in = r < n_rows;
         const uint32_t a = in ? slot_of(r) : 0u, e = in ? slot_of(r + 1u) : 0u;
