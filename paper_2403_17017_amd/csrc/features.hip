@@ -28,12 +28,13 @@ __global__ __launch_bounds__(kFeatWG) void features_kernel(
 // The same after a first pass, as ONE wave: it folds the partials with shuffles (no LDS, no
 // barrier) and writes the result; as the workgroup of 1024 lanes above the finishing launch
 // took 1.3 us longer.
+template <int U>
 __global__ __launch_bounds__(kWave) void features_wave_kernel(
     int rows, const int *__restrict__ rp, const FeatPartial *__restrict__ part, uint32_t n_part,
     FeatureRaw *__restrict__ mailbox, uint64_t seq)
 {
     const int first = rp[0], last = rp[rows];
-    const FeatTotals t = fold_partials_wave(part, n_part);
+    const FeatTotals t = fold_partials_wave<U>(part, n_part);
     if (threadIdx.x == 0) {
         FeatureRaw r;
         r.max_len = t.mx; r.min_len = t.mn;
@@ -247,8 +248,11 @@ void launch_features(int rows, const int *rp, void *workspace, FeatureRaw *mailb
     const bool vec = (reinterpret_cast<uintptr_t>(rp) & 15u) == 0;
     if (n_part) {                                    // a first pass, then one wave
         launch_feature_partials(rows, rp, part, n_part, vec, st);
-        hipLaunchKernelGGL(features_wave_kernel, dim3(1), dim3(kWave), 0, st, rows, rp, static_cast<const FeatPartial *>(part),
-                           n_part, mailbox_dev, seq);
+#define SEER_FINISH_LAUNCH(U)                                                                              \
+    hipLaunchKernelGGL(features_wave_kernel<U>, dim3(1), dim3(kWave), 0, st, rows, rp, static_cast<const FeatPartial *>(part), \
+                       n_part, mailbox_dev, seq)
+        if (fold_eight(n_part)) SEER_FINISH_LAUNCH(8); else SEER_FINISH_LAUNCH(4);
+#undef SEER_FINISH_LAUNCH
     } else if (vec) {
         hipLaunchKernelGGL(features_kernel<true>, dim3(1), dim3(kFeatWG), 0, st, rows, rp, part, n_part, mailbox_dev, seq);
     } else {

@@ -198,13 +198,14 @@ __device__ __forceinline__ int select_in_wave(
 // Finishing launch of the selection after a first pass: ONE wave folds the partials, derives
 // the features, walks the tree and leaves the record -- no LDS, no barrier (as a workgroup of
 // 1024 lanes that met in LDS atomics it took 4.4 us on the timeline).
+template <int U>
 __global__ __launch_bounds__(kWave) void features_select_wave_kernel(
     int rows, int cols, const int *__restrict__ rp, const FeatPartial *__restrict__ part, uint32_t n_part,
     AutoSel *__restrict__ sel, const AutoHeap heap, uint32_t reachable)
 {
     const HeapRegs hr = heap_load(heap);
     const int64_t nnz = (int64_t)rp[rows] - (int64_t)rp[0];
-    const FeatTotals t = fold_partials_wave(part, n_part);
+    const FeatTotals t = fold_partials_wave<U>(part, n_part);
     select_in_wave(rows, cols, nnz, t, hr, reachable, sel);
 }
 
@@ -503,27 +504,26 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
 
     const uint32_t n_part = features_num_parts(a.rows, policy.part_rows);
     if (n_part) launch_feature_partials(a.rows, a.rp, part, n_part, rp_vec, st);
-    if (rp_vec) {
-        if (heap && n_part && policy.select_wave)
-            hipLaunchKernelGGL(features_select_wave_kernel, dim3(1), dim3(kWave), 0, st, a.rows, a.cols, a.rp, part,
-                               n_part, sel, *heap, shape.reachable);
-        else if (heap)
-            hipLaunchKernelGGL(features_select_heap_kernel<true>, dim3(1), dim3(kFeatWG), 0, st, a.rows, a.cols, a.rp,
-                               part, n_part, sel, *heap, shape.reachable);
-        else
-            hipLaunchKernelGGL(features_select_kernel<true>, dim3(1), dim3(kFeatWG), 0, st, a.rows, a.cols, a.rp, part,
-                               n_part, sel, tree, shape.reachable);
+    const bool one_wave = heap && n_part && policy.select_wave;
+#define SEER_WAVE_LAUNCH(U)                                                                                 \
+    hipLaunchKernelGGL(features_select_wave_kernel<U>, dim3(1), dim3(kWave), 0, st, a.rows, a.cols, a.rp, part, n_part, sel, \
+                       *heap, shape.reachable)
+#define SEER_SELECT_LAUNCH(V)                                                                               \
+    if (heap)                                                                                               \
+        hipLaunchKernelGGL(features_select_heap_kernel<V>, dim3(1), dim3(kFeatWG), 0, st, a.rows, a.cols, a.rp, part, \
+                           n_part, sel, *heap, shape.reachable);                                            \
+    else                                                                                                    \
+        hipLaunchKernelGGL(features_select_kernel<V>, dim3(1), dim3(kFeatWG), 0, st, a.rows, a.cols, a.rp, part, n_part, \
+                           sel, tree, shape.reachable)
+    if (one_wave) {
+        if (fold_eight(n_part)) SEER_WAVE_LAUNCH(8); else SEER_WAVE_LAUNCH(4);
+    } else if (rp_vec) {
+        SEER_SELECT_LAUNCH(true);
     } else {
-        if (heap && n_part && policy.select_wave)
-            hipLaunchKernelGGL(features_select_wave_kernel, dim3(1), dim3(kWave), 0, st, a.rows, a.cols, a.rp, part,
-                               n_part, sel, *heap, shape.reachable);
-        else if (heap)
-            hipLaunchKernelGGL(features_select_heap_kernel<false>, dim3(1), dim3(kFeatWG), 0, st, a.rows, a.cols, a.rp,
-                               part, n_part, sel, *heap, shape.reachable);
-        else
-            hipLaunchKernelGGL(features_select_kernel<false>, dim3(1), dim3(kFeatWG), 0, st, a.rows, a.cols, a.rp, part,
-                               n_part, sel, tree, shape.reachable);
+        SEER_SELECT_LAUNCH(false);
     }
+#undef SEER_WAVE_LAUNCH
+#undef SEER_SELECT_LAUNCH
 
     if (long_workspace && reachable(SEER_CSR_WO)) shape.skip = launch_long(a, sel, long_workspace, st);
 #define SEER_AUTO_LAUNCH(...)                                                                              \
