@@ -356,7 +356,10 @@ __global__ __launch_bounds__(kWG, RANGED ? 8 : 1) void spmv_auto_decided_kernel(
 // Used for grids of up to about a thousand workgroups.  Beyond, it was measured slower than
 // the separate launch (a 54 MB stencil: 24.4 us per step against 22.8; the product itself
 // 17.2 against 13.0 us, and a first pass of 64 fat workgroups 6.3 against 4.6 us for 512).
-template <int IPT, bool VEC, bool RPVEC>
+// RPU: quads of offsets that a lane reduces per trip where there is no first pass.  Four are all there are of up
+// to 4096 rows, and half of the code of eight, which every workgroup runs through for the first time:
+// 4096 rows of 16 5.87 -> 5.53 us a step, 1003 rows of 100 6.15 -> 5.80; more rows would take a second trip (5000 14.2 -> 14.6).
+template <int IPT, bool VEC, bool RPVEC, uint32_t RPU>
 __global__ __launch_bounds__(kWG) void spmv_auto_fused_kernel(
     int rows, int cols, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
@@ -375,7 +378,7 @@ __global__ __launch_bounds__(kWG) void spmv_auto_fused_kernel(
         nnz_dev = (int64_t)rp[rows] - (int64_t)rp[0];
     }
     if (n_part == 0) {                                // block-uniform
-        features_accumulate_strided<RPVEC, 8>(rows, rp, threadIdx.x, kWG, t.mx, t.mn, t.sq, t.em);
+        features_accumulate_strided<RPVEC, RPU>(rows, rp, threadIdx.x, kWG, t.mx, t.mn, t.sq, t.em);
         t = features_block_fold<kWG>(t.mx, t.mn, t.sq, t.em, &s);
     } else if (first_wave) {
         t = fold_partials_wave(part, n_part);
@@ -485,10 +488,13 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
     if (heap && !shape.ranges.count && (grid <= (uint32_t)policy.fused_grid || a.rows <= policy.fused_max_rows)) {
         // one launch for a small matrix; else a first pass that leaves a few partials
         const uint32_t n_part = a.rows > policy.fused_rows ? launch_fused_partials(a, part, rp_vec, st) : 0u;
-#define SEER_FUSED_LAUNCH(I, V, R)                                                                          \
-    hipLaunchKernelGGL((spmv_auto_fused_kernel<I, V, R>), dim3(grid), dim3(kWG), 0, st, a.rows, a.cols, a.nnz, \
+#define SEER_FUSED_LAUNCH(I, V, R) SEER_FUSED_LAUNCH_BY(I, V, R, 8)
+#define SEER_FUSED_LAUNCH_BY(I, V, R, U)                                                                    \
+    hipLaunchKernelGGL((spmv_auto_fused_kernel<I, V, R, U>), dim3(grid), dim3(kWG), 0, st, a.rows, a.cols, a.nnz, \
                        a.rp, a.ci, a.va, a.x, a.y, carry_row, carry_val, part, n_part, sel, *heap, shape, a.remap)
-        if (shape.mp_ipt == kMpIptSmall) {
+        if (shape.mp_ipt == kMpIptSmall && vec && rp_vec && a.rows <= (int)(kWG * 16u)) {
+            SEER_FUSED_LAUNCH_BY(kMpIptSmall, true, true, 4);
+        } else if (shape.mp_ipt == kMpIptSmall) {
             if (vec) { if (rp_vec) SEER_FUSED_LAUNCH(kMpIptSmall, true, true); else SEER_FUSED_LAUNCH(kMpIptSmall, true, false); }
             else     { if (rp_vec) SEER_FUSED_LAUNCH(kMpIptSmall, false, true); else SEER_FUSED_LAUNCH(kMpIptSmall, false, false); }
         } else {
@@ -496,6 +502,7 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
             else     { if (rp_vec) SEER_FUSED_LAUNCH(kMpIptLarge, false, true); else SEER_FUSED_LAUNCH(kMpIptLarge, false, false); }
         }
 #undef SEER_FUSED_LAUNCH
+#undef SEER_FUSED_LAUNCH_BY
         if (carries)
             hipLaunchKernelGGL(spmv_auto_fixup_kernel, dim3((n_carry + kWG - 1) / kWG), dim3(kWG), 0, st, a.rows, n_mp,
                                n_wo, carry_row, carry_val, a.y, sel);
