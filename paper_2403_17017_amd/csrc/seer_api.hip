@@ -263,8 +263,8 @@ int slab_shift(int rows, int cols, int nnz)
 
 // Whether CSR,S is prepared in bins (slabs of x in LDS) where its form applies and the columns are not
 // local: from 9.4 M nonzeros on.  Measured, products and preparation, the other form and this: 10 M nonzeros in
-// 4 MB of x 62 and 38 us, 200 and 135; 40 M in 8 MB 227 and 126, 590 and 409; Zipf rows, 62 M in 16 MB
-// 393 and 198, 972 and 602; 35 M in 28 MB 327 and 140.  (Below it, the arrays described in seer.h are what a program finds in plan_mem.)
+// 4 MB of x 62 and 38 us, 200 and 135; 40 M in 8 MB 227 and 127, 590 and 396; Zipf rows, 62 M in 16 MB
+// 393 and 192, 972 and 626; 35 M in 28 MB 327 and 140.  (Below it, the arrays described in seer.h are what a program finds in plan_mem.)
 // The "slab_bins" knob: 0 never, 1 wherever the number of slabs allows it, also if columns are local; a slab
 // width set by "slab_shift" is the other form's.
 bool slab_bins(int cols, int nnz)

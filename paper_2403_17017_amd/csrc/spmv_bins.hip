@@ -21,7 +21,7 @@
 // beside rows and padding, and that bounds both kernels: 40 M nonzeros, 2 M columns, rows of 20: 427 MB in
 // 84 us (5.1 TB/s, a third of it written) and 258 MB in 43 us (6.0 TB/s); the form with slabs in L2 takes
 // 210 + 5 + 13 us, bound by its gathers.  Zipf rows (s = 1.9), 62 M nonzeros, 4 M columns: 129 + 58 + 5 us
-// and 372 + 6 + 18.  Preparation, kernels alone, 40 M: 212 (sort) + 162 (fill) + 20 us, against about 480.
+// and 372 + 6 + 18.  Preparation, kernels alone, 40 M: 170 (sort) + 162 (fill) + 20 us, against about 480.
 // Tried: without the sums of fours and sixteens, Zipf 133 + 109 us; the parts of all buckets of a slab
 // one after the other, so that a bucket's p is written at three times, 134 instead of 129; streaming stores
 // of p, 82 -> 95 us; four quads ahead, the same; p in 16 MB that stay in the last-level cache, 82 -> 77, not
