@@ -347,7 +347,8 @@ size_t seer_slab_plan_bytes(int32_t rows, int32_t cols, int32_t nnz);
  * before row i), then col_idx and values ([nnz + 1] each) in the order of the kept rows;
  * plan->n_blocks = S, plan->split_rows = K.
  * A matrix of 9 * 2^20 nonzeros or more and at most 2^23 columns whose columns are not local (256
- * consecutive entries, looked at in 64 places, mostly touch 128 lines of x or more) is kept in bins
+ * consecutive entries, looked at in 64 places, mostly touch 128 lines of x or more, or 32 where they
+ * descend at most four times) is kept in bins
  * instead: w = 15, n_blocks = ceil(cols / 2^15), split_rows = -1 or -2; what plan_mem holds then is
  * the library's own affair, and a product takes 4.5 to 7 bytes of workspace per nonzero.
  * plan_mem must hold seer_slab_plan_bytes(rows, cols, nnz) (SEER_EWORKSPACE otherwise, with

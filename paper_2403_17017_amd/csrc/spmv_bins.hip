@@ -108,8 +108,11 @@ __device__ __forceinline__ uint32_t bins_places(uint32_t groups, uint32_t *s_tmp
 // ---- preparation 1: where the chunks begin, a wave for each.  kBinLooks of the waves also look at
 // 256 consecutive entries and vote if these share lines of x, fewer than one line per two entries: in
 // such a matrix (bands, stencils, blocks) gathers out of L1 and L2 cost next to nothing, and
-// the other form is the faster one.  flags: {columns not as they must be, some row is cut, votes, looks},
-// zero on entry.
+// the other form is the faster one.  Long rows share lines, too, but have runs, which take less than half of a
+// single entry's bytes here: where at most four descents are among the 256, fewer than 32 lines are asked for
+// (Zipf rows, s = 1.6, 2 M columns, 471 M nonzeros, products and preparation: the other form 1586 and 3979 us, this
+// 978 and 3789).  flags: {columns not as they must be, some row is cut, votes, looks}, zero on entry.
+constexpr uint32_t kBinLines = 128, kBinLinesInRow = 32, kBinFewRows = 4;
 constexpr uint32_t kBinLooks = 64;                  // (each vote is an atomic on one word: 64 take under two microseconds)
 enum { kFlagBad, kFlagCut, kFlagVotes, kFlagLooks };
 __device__ __forceinline__ bool bins_local(const uint32_t *f) { return 2u * f[kFlagVotes] > f[kFlagLooks]; }
@@ -126,16 +129,20 @@ __global__ __launch_bounds__(kWG) void bins_table_kernel(
         uint32_t *seen = s_seen[threadIdx.x / kWave];           // the wave's own: no barrier
         if (lane < 32u) seen[lane] = 0;
         __builtin_amdgcn_wave_barrier();
+        uint32_t descents = 0;                                  // ends of rows, or nearly so
 #pragma unroll
         for (uint32_t u = 0; u < 4; ++u) {
-            const uint32_t h = (((uint32_t)ci[t + u * kWave + lane] >> 5) * 0x9E3779B1u) >> 22;    // 1024 buckets of lines
+            const uint32_t i = t + u * kWave + lane;
+            const int c = ci[i];
+            const uint32_t h = (((uint32_t)c >> 5) * 0x9E3779B1u) >> 22;                           // 1024 buckets of lines
             atomicOr(&seen[h >> 5], 1u << (h & 31u));
+            descents += (uint32_t)__popcll(__ballot(c < ci[i ? i - 1u : 0u]));
         }
         __builtin_amdgcn_wave_barrier();
         const uint32_t lines = wave_fold(lane < 32u ? (uint32_t)__popc((int)seen[lane]) : 0u, [](uint32_t a, uint32_t b) { return a + b; });
         if (lane == 0) {
             atomicAdd(&flags[kFlagLooks], 1u);
-            if (lines < 128u && !always) atomicAdd(&flags[kFlagVotes], 1u);
+            if (lines < (descents <= kBinFewRows ? kBinLinesInRow : kBinLines) && !always) atomicAdd(&flags[kFlagVotes], 1u);
         }
     }
     if (k == 0 || k == n_chunks) {

@@ -153,3 +153,17 @@ def test_rule_and_scratch_limits():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(y, ref)
+
+
+@pytest.mark.parametrize("by_bins", [True, False])
+def test_lines_shared_within_a_long_row(by_bins):
+    """Entries of one long row share lines of x without being local; a wide band is local although 256 of
+    its entries lie in a few rows."""
+    A = G.explicit_lengths([100_003] * 100, 1_100_011, 81) if by_bins else G.banded(530_003, 40, 82)
+    announce(f"CSR,S by rule {A.name} nnz={A.nnz}")
+    assert A.nnz >= 9 << 20
+    plan = S.seer_spmv_prepare(S.CSR_S, upload(A))
+    assert (int(plan.c.split_rows) < 0) == by_bins
+    if by_bins:
+        x = G.dense_vector(A.cols, 5)
+        assert_parity(product(plan, upload(A), x), *oracle_of(A, x), A.name)
