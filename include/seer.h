@@ -395,7 +395,8 @@ int seer_spmv_plan(const seer_csr *A, const seer_model *model, int32_t iteration
  * contiguous ranges, gathers stay inside x.  Reads row_ptr[0..rows] and col_idx[0..nnz-1]
  * only (A->values may be NULL; with A->col_idx NULL the column count is 0), so the arrays
  * must have those sizes, whatever they hold.  workspace: DEVICE, 16-byte aligned, at least
- * 16 bytes.  Host-synchronous (waits for `stream`; not capturable).  Returns SEER_OK
+ * 16 bytes.  Host-synchronous (waits for `stream`, twice if there is something to count: such a
+ * matrix is read a second time; not capturable).  Returns SEER_OK
  * when the check ran, whatever it found; the counts are the verdict. */
 int seer_csr_check(const seer_csr *A, int64_t *bad_row_ptr, int64_t *bad_col_idx,
                    void *workspace, size_t workspace_bytes, void *stream);

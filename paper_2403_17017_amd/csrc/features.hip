@@ -105,9 +105,12 @@ __device__ __forceinline__ uint32_t outside(const v4i_a4 c, uint32_t cols)
            (uint32_t)((uint32_t)c.w >= cols);
 }
 
+// COUNT: the counts are added to words[0] (offsets) and words[1] (columns), zero on entry.  Else words[0]
+// becomes `tag` if there is anything to count.
+template <bool COUNT>
 __global__ __launch_bounds__(kWG) void csr_check_kernel(
     int rows, int cols, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
-    unsigned long long *__restrict__ counts)
+    unsigned long long *__restrict__ words, uint64_t tag)
 {
     const uint32_t stride = gridDim.x * kWG, first = blockIdx.x * kWG + threadIdx.x;
     uint32_t bad_rp = 0, bad_ci = 0;
@@ -138,38 +141,51 @@ __global__ __launch_bounds__(kWG) void csr_check_kernel(
         bad_ci += __shfl_xor(bad_ci, off);
     }
     if (threadIdx.x % kWave == 0) {
-        if (bad_rp) atomicAdd(&counts[0], (unsigned long long)bad_rp);
-        if (bad_ci) atomicAdd(&counts[1], (unsigned long long)bad_ci);
+        if constexpr (COUNT) {
+            if (bad_rp) atomicAdd(&words[0], (unsigned long long)bad_rp);
+            if (bad_ci) atomicAdd(&words[1], (unsigned long long)bad_ci);
+        } else {
+            if (bad_rp | bad_ci) words[0] = tag;             // (the same word from every wave)
+        }
     }
 }
 
-// The counts into pinned host memory and back to zero, then the sequence number (as features_kernel does).
-__global__ void csr_check_report_kernel(unsigned long long *__restrict__ counts, FeatureRaw *__restrict__ mailbox,
+__global__ void csr_check_clear_kernel(unsigned long long *__restrict__ words) { words[threadIdx.x] = 0; }
+
+// The counts, or whether there is anything to count, into pinned host memory, then the sequence number (as
+// features_kernel does).
+template <bool COUNT>
+__global__ void csr_check_report_kernel(const unsigned long long *__restrict__ words, FeatureRaw *__restrict__ mailbox,
                                         uint64_t seq)
 {
-    mailbox->sum_sq = atomicExch(&counts[0], 0ull);
-    mailbox->empty = atomicExch(&counts[1], 0ull);
+    mailbox->sum_sq = COUNT ? words[0] : (uint64_t)(words[0] == seq);
+    mailbox->empty = COUNT ? words[1] : 0;
     __threadfence_system();
     *reinterpret_cast<volatile uint64_t *>(&mailbox->seq) = seq;
 }
 
-// Two counters per mailbox, on a line of their own: zero when the library is loaded, and left zero by every
-// call, which owns its mailbox alone.  (In the caller's workspace they had to be cleared first: a launch of
-// 1.3 us and its way to the device: a whole call on 120 MB 30.9 us, now 28.0, on 1 MB 14.0 and 12.0.)
-static __device__ unsigned long long check_counts[kMailboxes][8];
-
-hipError_t csr_check_counts(void **counts) { return hipGetSymbolAddress(counts, HIP_SYMBOL(check_counts)); }
-
-void launch_csr_check(int rows, int cols, int nnz, const int *rp, const int *ci, void *counts, int slot,
+// The caller's scratch memory is the only one there is, and what it holds is not known.  A matrix is first
+// looked at for whether anything is wrong: a wave that finds something leaves the call's sequence number
+// there, so that no word has to be cleared before (a launch of 1.3 us and its way to the device: a whole call from
+// Python on 120 MB 42.5 us, without it 39.2, on 1 MB 25.3 and 23.2).  Only if that number is found -- also by chance:
+// then the counts are zero -- does the host have the matrix counted, in cleared words (a malformed matrix takes
+// 68 and 35 us).
+void launch_csr_check(int rows, int cols, int nnz, const int *rp, const int *ci, void *workspace, bool count,
                       FeatureRaw *mailbox_dev, uint64_t seq, hipStream_t st)
 {
-    unsigned long long *n_bad = static_cast<unsigned long long *>(counts) + 8 * slot;
+    unsigned long long *words = static_cast<unsigned long long *>(workspace);
     const size_t n = (size_t)(rows > nnz ? rows : nnz);
     const size_t want = (n + kWG * 16 - 1) / (kWG * 16);               // sixteen items per lane and trip
     // (of 120 MB, four workgroups per CU take 0.4 us less than eight, of 220 MB 1.1)
     const uint32_t blocks = (uint32_t)(want < 1 ? 1 : (want < 256 * 4 ? want : 256 * 4));
-    hipLaunchKernelGGL(csr_check_kernel, dim3(blocks), dim3(kWG), 0, st, rows, cols, nnz, rp, ci, n_bad);
-    hipLaunchKernelGGL(csr_check_report_kernel, dim3(1), dim3(1), 0, st, n_bad, mailbox_dev, seq);
+    if (count) {
+        hipLaunchKernelGGL(csr_check_clear_kernel, dim3(1), dim3(2), 0, st, words);
+        hipLaunchKernelGGL(csr_check_kernel<true>, dim3(blocks), dim3(kWG), 0, st, rows, cols, nnz, rp, ci, words, seq);
+        hipLaunchKernelGGL(csr_check_report_kernel<true>, dim3(1), dim3(1), 0, st, words, mailbox_dev, seq);
+    } else {
+        hipLaunchKernelGGL(csr_check_kernel<false>, dim3(blocks), dim3(kWG), 0, st, rows, cols, nnz, rp, ci, words, seq);
+        hipLaunchKernelGGL(csr_check_report_kernel<false>, dim3(1), dim3(1), 0, st, words, mailbox_dev, seq);
+    }
 }
 
 void launch_stream_sum(const void *src, size_t n_words, void *out64, hipStream_t st)

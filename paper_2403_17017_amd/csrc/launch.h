@@ -206,11 +206,9 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
                  const AutoPolicy &policy, const AutoSel *decided, void *workspace, void *long_workspace /* null: no
                  stage for the long rows of CSR,WO */, hipStream_t st);
 
-// counts: the current device's counters, csr_check_counts(), of which a call uses those of its mailbox's slot;
-// the result goes to the mailbox's sum_sq (offsets) and empty (columns)
-constexpr int kMailboxes = 64;
-hipError_t csr_check_counts(void **counts);
-void launch_csr_check(int rows, int cols, int nnz, const int *rp, const int *ci, void *counts, int slot,
+// workspace: 16 bytes.  The result goes to the mailbox; count: the two counts, sum_sq (offsets) and empty (columns),
+// else sum_sq: 0 if both are zero, 1 if they have to be counted
+void launch_csr_check(int rows, int cols, int nnz, const int *rp, const int *ci, void *workspace, bool count,
                       FeatureRaw *mailbox_dev, uint64_t seq, hipStream_t st);
 void launch_stream_copy(void *dst, const void *src, size_t n_words, hipStream_t st);
 void launch_gather_sum(const int *idx, const float *val, size_t n, const float *x, void *out64, hipStream_t st);

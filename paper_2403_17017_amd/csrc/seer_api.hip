@@ -31,7 +31,6 @@ namespace {
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
 void *g_scratch_ptr[kMaxDevices] = {};     // device address of `scratch` on each device, once looked up
-void *g_check_ptr[kMaxDevices] = {};
 
 std::atomic<int> g_last_hip_error{0};
 
@@ -59,6 +58,7 @@ std::atomic<int> g_tune_gather_range{-1};
 // Where the waiting calls (seer_features, seer_csr_check) get their results: kMailboxes slots of
 // pinned, mapped host memory, one per call under way, so that calls of different threads do not
 // wait for each other's streams.
+constexpr int kMailboxes = 64;
 constexpr size_t kMailboxStride = 64;
 static_assert(sizeof(FeatureRaw) <= kMailboxStride && kMailboxes <= 64, "a slot per bit of the mask, a cache line each");
 std::mutex g_mailbox_mutex;             // guards the four below; never held while waiting for the device
@@ -408,7 +408,6 @@ public:
     }
 
     FeatureRaw *device() const { return dev_; }
-    int slot() const { return slot_; }
     uint64_t seq() const { return seq_; }
 
     // Waits until the kernel that writes seq() into the slot has done so, and copies the slot out.
@@ -999,37 +998,28 @@ int seer_stream_copy(void *dst, const void *src, size_t n_words, void *stream)
     return e == hipSuccess ? SEER_OK : hip_fail(e);
 }
 
+// One look at the matrix: whether anything is wrong, or the counts of what is.
+static int csr_check_once(const seer_csr *A, bool count, void *workspace, hipStream_t st, FeatureRaw *raw)
+{
+    Mailbox mail;
+    const int rc = mail.take();
+    if (rc != SEER_OK) return rc;
+    launch_csr_check(A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, workspace, count, mail.device(), mail.seq(), st);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? mail.wait(st, raw) : hip_fail(e);
+}
+
 int seer_csr_check(const seer_csr *A, int64_t *bad_row_ptr, int64_t *bad_col_idx, void *workspace,
                    size_t workspace_bytes, void *stream)
 {
     if (!A || !bad_row_ptr || !bad_col_idx) return SEER_EINVAL;
     if (A->rows < 0 || A->cols < 0 || A->nnz < 0 || !A->row_ptr) return SEER_EINVAL;
     if (!workspace || !aligned16(workspace) || workspace_bytes < 16) return SEER_EWORKSPACE;
-    Mailbox mail;
-    const int mrc = mail.take();
-    if (mrc != SEER_OK) return mrc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    int dev = -1;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return hip_fail(e);
-    void *counts = nullptr;                                // looked up once per device
-    if (dev < 0 || dev >= kMaxDevices) {
-        e = csr_check_counts(&counts);
-        if (e != hipSuccess) return hip_fail(e);
-    } else {
-        std::lock_guard<std::mutex> lock(g_scratch_mutex);
-        if (!g_check_ptr[dev]) {
-            e = csr_check_counts(&g_check_ptr[dev]);
-            if (e != hipSuccess) return hip_fail(e);
-        }
-        counts = g_check_ptr[dev];
-    }
-    launch_csr_check(A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, counts, mail.slot(), mail.device(), mail.seq(), st);
-    e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e);
     FeatureRaw raw;
-    const int wrc = mail.wait(st, &raw);
-    if (wrc != SEER_OK) return wrc;
+    int rc = csr_check_once(A, false, workspace, st, &raw);
+    if (rc == SEER_OK && raw.sum_sq != 0) rc = csr_check_once(A, true, workspace, st, &raw);
+    if (rc != SEER_OK) return rc;
     *bad_row_ptr = (int64_t)raw.sum_sq;
     *bad_col_idx = (int64_t)raw.empty;
     return SEER_OK;

@@ -145,8 +145,7 @@ def test_a_call_behind_long_work_holds_up_no_other_thread(first):
 
 
 def test_counters_start_from_zero_after_a_bad_matrix():
-    """Calls share their counters with the calls after them: alternating good and bad matrices, each
-    call gets its own counts, on one stream and on two."""
+    """Alternating good and bad matrices, each call gets its own counts, on one stream and on two."""
     import torch
     A = G.random_lengths(5_003, 3_000, 0, 40, 21)
     ci = A.col_idx.copy()
@@ -160,3 +159,64 @@ def test_counters_start_from_zero_after_a_bad_matrix():
         stream = other if k % 3 == 2 else None
         assert tuple(S.seer_csr_check(bad, stream=stream)) == (0, 4)
         assert tuple(S.seer_csr_check(good, stream=stream)) == (0, 0)
+
+
+def test_calls_share_nothing_but_what_they_are_handed():
+    """Two threads with a stream and a workspace each, one matrix bad and one good: each gets its own counts.
+    What a call adds up lies in the caller's workspace, whatever that holds on entry."""
+    import threading
+
+    import torch
+    A = G.random_lengths(5_003, 3_000, 0, 40, 21)
+    ci, rp = A.col_idx.copy(), A.row_ptr.copy()
+    ci[[3, 700, 701, ci.size - 1]] = A.cols
+    rp[0] = 1
+    bad = S.DeviceCSR.from_host(G.HostCSR(A.rows, A.cols, rp, ci, A.values, "offset-and-four-outside"))
+    good = S.DeviceCSR.from_host(A)
+    want = O.csr_defects(A.rows, A.cols, A.nnz, rp, ci)
+    assert want[0] > 0 and want[1] == 4
+    announce("seer_csr_check, good and bad on two threads")
+    poison = torch.full((4,), 0x5A5A5A5A, dtype=torch.int32, device="cuda:0").view(torch.uint8)
+    ws = poison.clone()
+    assert tuple(S.seer_csr_check(bad, ws)) == want
+    assert not torch.equal(ws, poison)
+    results = {}
+
+    def calls(name, matrix):
+        stream = torch.cuda.Stream()
+        results[name] = {tuple(S.seer_csr_check(matrix, poison.clone(), stream)) for _ in range(200)}
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=calls, args=a) for a in (("bad", bad), ("good", good))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    assert results == {"bad": {want}, "good": {(0, 0)}}
+
+
+def test_a_call_that_returns_early_disturbs_no_other():
+    """An error that another library left in the thread is reported behind the launches, so such a call returns
+    while its kernels run: calls that follow it at once get their own counts."""
+    import ctypes
+
+    import torch
+    hip = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    nnz = 400_000_000
+    far = torch.full((nnz,), 9, dtype=torch.int32, device="cuda:0")             # every column outside
+    big = S.DeviceCSR(1, 9, torch.tensor([0, nnz], dtype=torch.int32, device="cuda:0"), far,
+                      far.view(torch.float32), nnz)
+    good = S.DeviceCSR.from_host(G.random_lengths(2_003, 5_000, 0, 20, 7))
+    busy, other = torch.cuda.Stream(), torch.cuda.Stream()
+    ws_big, ws = S.alloc_workspace(16), S.alloc_workspace(16)
+    assert tuple(S.seer_csr_check(big, ws_big, busy)) == (0, nnz)
+    assert tuple(S.seer_csr_check(good, ws, other)) == (0, 0)
+    torch.cuda.synchronize()
+    announce("seer_csr_check that returns early")
+    assert ctypes.CDLL(hip).hipSetDevice(12345) != 0                            # refused; remembered by the runtime
+    with pytest.raises(S.SeerError) as ei:
+        S.seer_csr_check(big, ws_big, busy)
+    assert ei.value.status == -5
+    for _ in range(100):
+        assert tuple(S.seer_csr_check(good, ws, other)) == (0, 0)
+    torch.cuda.synchronize()
+    assert tuple(S.seer_csr_check(big, ws_big, busy)) == (0, nnz)
