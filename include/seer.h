@@ -26,11 +26,11 @@
  *   - Every call returns SEER_OK (0) or a negative seer_status; on error no output
  *     is written.  Nothing throws or aborts.  Matrix contents (monotone row_ptr,
  *     column range) are NOT validated: they are the caller's contract.
- *   - The first seer_features or seer_csr_check call allocates 4096 bytes of pinned host memory
- *     per process (64 result mailboxes); no other state is kept, on the host or the device.
- *   - Calls that use the same workspace must not overlap in time.  seer_features and
- *     seer_csr_check calls of different threads run side by side, up to 64 of them; a further
- *     one waits until one of those has ended.
+ *   - The first seer_features or seer_csr_check call, or preparation of SEER_CSR_S, allocates 4096 bytes
+ *     of pinned host memory per process (64 result mailboxes); no other state is kept, on the host
+ *     or the device.
+ *   - Calls that use the same workspace must not overlap in time.  Such calls of different threads
+ *     run side by side, up to 64 of them; a further one waits until one of those has ended.
  */
 #ifndef SEER_H
 #define SEER_H
@@ -444,8 +444,9 @@ int seer_csr_check(const seer_csr *A, int64_t *bad_row_ptr, int64_t *bad_col_idx
  *               are; default: from 9 * 2^20 nonzeros on, columns not local (seer_spmv_prepare)
  *   "coo_runs"  COO,WM: 1 (default): a lane sums a run of eight consecutive triples,
  *               0: lane <-> triple in rounds of 64
- *   "poll"      0: seer_features and seer_csr_check wait with hipStreamSynchronize only;
- *               otherwise (default) they first watch their pinned result word for up to 2 ms
+ *   "poll"      0: seer_features, seer_csr_check and the preparation of CSR,S wait with
+ *               hipStreamSynchronize only; otherwise (default) they first watch their pinned
+ *               result word for up to 2 ms
  * Unknown name: SEER_EINVAL.  A value outside the listed set selects the default. */
 int seer_set_tuning(const char *name, int value);
 

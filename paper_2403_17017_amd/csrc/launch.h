@@ -114,13 +114,14 @@ uint32_t bins_num_slabs(int cols);
 bool bins_fit(int cols, int nnz);           // the form can hold a matrix of these sizes
 size_t bins_plan_bytes(int rows, int cols, int nnz);
 size_t bins_workspace_bytes(uint32_t n_slabs, int nnz);
-constexpr size_t kBinFlags = 4;             // words that the preparation leaves at bins_flags(), for the host to read:
-const uint32_t *bins_flags(const void *plan_mem, int rows, int cols, int nnz);
-bool bins_not_taken(const uint32_t *flags); // columns are local, nothing was prepared: the other form is faster
-bool bins_refused(const uint32_t *flags);   // columns do not ascend in a row, or lie outside the matrix
-bool bins_cut(const uint32_t *flags);       // some row is cut: products leave carries
-hipError_t launch_bins_prepare(int rows, int cols, int nnz, const int *rp, const int *ci, const float *va, void *plan_mem,
-                               bool always /* also if columns are local */, hipStream_t st);
+// In two steps, each of which leaves its answer in a mailbox.  The first: max_len 1: the other form is faster for the
+// matrix (not if `always`), min_len 1: some row is cut, so that products leave carries.  The second, only if the first
+// says 0: max_len 1: columns do not ascend in a row, or lie outside the matrix.
+struct FeatureRaw;
+void launch_bins_judge(int rows, int cols, int nnz, const int *rp, const int *ci, void *plan_mem, bool always,
+                       FeatureRaw *mailbox_dev, uint64_t seq, hipStream_t st);
+void launch_bins_prepare(int rows, int cols, int nnz, const int *rp, const int *ci, const float *va, void *plan_mem,
+                         FeatureRaw *mailbox_dev, uint64_t seq, hipStream_t st);
 void launch_bins(const SpmvArgs &a, uint32_t n_slabs, bool cut_rows, const void *plan_mem, void *workspace, hipStream_t st);
 
 // feature reduction

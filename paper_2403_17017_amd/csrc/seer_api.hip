@@ -55,7 +55,7 @@ std::atomic<int> g_tune_coo_runs{-1};
 std::atomic<int> g_tune_slab_shift{-1};
 std::atomic<int> g_tune_gather_range{-1};
 
-// Where the waiting calls (seer_features, seer_csr_check) get their results: kMailboxes slots of
+// Where the waiting calls (seer_features, seer_csr_check, seer_spmv_prepare for CSR,S) get their results: kMailboxes slots of
 // pinned, mapped host memory, one per call under way, so that calls of different threads do not
 // wait for each other's streams.
 constexpr int kMailboxes = 64;
@@ -1144,25 +1144,38 @@ size_t seer_slab_plan_bytes(int32_t rows, int32_t cols, int32_t nnz)
     return slabs && slab_bins(cols, nnz) ? std::max(slabs, bins_plan_bytes(rows, cols, nnz)) : slabs;
 }
 
-// The column-slabbed form in bins: everything is enqueued, then the flags are read.  *taken: false if the
-// columns are local and the other form is wanted.
+// The column-slabbed form in bins.  *taken: false if the other form is wanted: then nothing was prepared.  (A mailbox is
+// given back before the next is taken: each call that waits holds one at most.)
 static int prepare_bins(const seer_csr *A, void *plan_mem, void *stream, seer_plan *plan, bool *taken)
 {
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const bool always = g_tune_slab_bins.load() > 0;
-    hipError_t e = launch_bins_prepare(A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, plan_mem, always, st);
-    if (e != hipSuccess) return hip_fail(e);
-    uint32_t flags[kBinFlags] = {};
-    e = hipMemcpyAsync(flags, bins_flags(plan_mem, A->rows, A->cols, A->nnz), sizeof flags, hipMemcpyDeviceToHost, st);
-    if (e != hipSuccess) return hip_fail(e);
-    e = hipStreamSynchronize(st);
-    if (e != hipSuccess) return hip_fail(e);
-    *taken = !bins_not_taken(flags);
+    FeatureRaw judged, made;
+    {
+        Mailbox mail;
+        int rc = mail.take();
+        if (rc != SEER_OK) return rc;
+        launch_bins_judge(A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, plan_mem, g_tune_slab_bins.load() > 0,
+                          mail.device(), mail.seq(), st);
+        const hipError_t e = hipGetLastError();
+        rc = e == hipSuccess ? mail.wait(st, &judged) : hip_fail(e);
+        if (rc != SEER_OK) return rc;
+    }
+    *taken = judged.max_len == 0;
     if (!*taken) return SEER_OK;
-    if (bins_refused(flags)) return SEER_EINVAL;
+    {
+        Mailbox mail;
+        int rc = mail.take();
+        if (rc != SEER_OK) return rc;
+        launch_bins_prepare(A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, plan_mem, mail.device(), mail.seq(), st);
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess) e = hipStreamSynchronize(st);      // (the plan may be used on another stream next)
+        rc = e == hipSuccess ? mail.wait(st, &made) : hip_fail(e);
+        if (rc != SEER_OK) return rc;
+    }
+    if (made.max_len != 0) return SEER_EINVAL;
     plan->n_blocks = (int32_t)bins_num_slabs(A->cols);
     plan->ell_width = kBinShift;
-    plan->split_rows = bins_cut(flags) ? kBinsCut : kBinsWhole;
+    plan->split_rows = judged.min_len != 0 ? kBinsCut : kBinsWhole;
     plan->device = plan_mem;
     return SEER_OK;
 }

@@ -111,21 +111,26 @@ __device__ __forceinline__ uint32_t bins_places(uint32_t groups, uint32_t *s_tmp
 // the other form is the faster one.  Long rows share lines, too, but have runs, which take less than half of a
 // single entry's bytes here: where at most four descents are among the 256, fewer than 32 lines are asked for
 // (Zipf rows, s = 1.6, 2 M columns, 471 M nonzeros, products and preparation: the other form 1586 and 3979 us, this
-// 978 and 3789).  flags: {columns not as they must be, some row is cut, votes, looks}, zero on entry.
+// 978 and 3789).
 constexpr uint32_t kBinLines = 128, kBinLinesInRow = 32, kBinFewRows = 4;
-constexpr uint32_t kBinLooks = 64;                  // (each vote is an atomic on one word: 64 take under two microseconds)
-enum { kFlagBad, kFlagCut, kFlagVotes, kFlagLooks };
-__device__ __forceinline__ bool bins_local(const uint32_t *f) { return 2u * f[kFlagVotes] > f[kFlagLooks]; }
+constexpr uint32_t kBinLooks = 64;
+// The wave of chunk k looks (its vote: number k / apart); so many of the votes exist.
+__device__ __forceinline__ uint32_t bins_apart(uint32_t n_chunks) { return max(1u, n_chunks / kBinLooks); }
+__device__ __forceinline__ bool bins_looks(uint32_t k, uint32_t n_chunks, uint32_t nnz)
+{
+    const uint32_t apart = bins_apart(n_chunks);
+    return k % apart == 0 && k / apart < kBinLooks && k < n_chunks && k * kBinNominal + 256u <= nnz;
+}
 
 __global__ __launch_bounds__(kWG) void bins_table_kernel(
     int rows, uint32_t nnz, uint32_t n_chunks, const int *__restrict__ rp, const int *__restrict__ ci,
-    BinChunk *__restrict__ table, uint32_t *__restrict__ counts_end, int always, uint32_t *__restrict__ flags)
+    BinChunk *__restrict__ table, uint32_t *__restrict__ counts_end, uint32_t *__restrict__ votes)
 {
     __shared__ uint32_t s_seen[kWG / kWave][32];
     const uint32_t k = blockIdx.x * (kWG / kWave) + threadIdx.x / kWave, lane = threadIdx.x % kWave;
     if (k > n_chunks) return;                                   // wave-uniform
-    const uint32_t apart = max(1u, n_chunks / kBinLooks), t = k * kBinNominal;
-    if (k % apart == 0 && k / apart < kBinLooks && k < n_chunks && t + 256u <= nnz) {
+    const uint32_t t = k * kBinNominal;
+    if (bins_looks(k, n_chunks, nnz)) {
         uint32_t *seen = s_seen[threadIdx.x / kWave];           // the wave's own: no barrier
         if (lane < 32u) seen[lane] = 0;
         __builtin_amdgcn_wave_barrier();
@@ -140,10 +145,7 @@ __global__ __launch_bounds__(kWG) void bins_table_kernel(
         }
         __builtin_amdgcn_wave_barrier();
         const uint32_t lines = wave_fold(lane < 32u ? (uint32_t)__popc((int)seen[lane]) : 0u, [](uint32_t a, uint32_t b) { return a + b; });
-        if (lane == 0) {
-            atomicAdd(&flags[kFlagLooks], 1u);
-            if (lines < (descents <= kBinFewRows ? kBinLinesInRow : kBinLines) && !always) atomicAdd(&flags[kFlagVotes], 1u);
-        }
+        if (lane == 0) votes[k / bins_apart(n_chunks)] = lines < (descents <= kBinFewRows ? kBinLinesInRow : kBinLines) ? 1u : 0u;
     }
     if (k == 0 || k == n_chunks) {
         if (lane == 0) {
@@ -160,10 +162,34 @@ __global__ __launch_bounds__(kWG) void bins_table_kernel(
     }
 }
 
+// What was seen, into pinned host memory: whether the other form is to be taken (max_len) and whether some row is cut
+// (min_len).  The host waits for that before it enqueues the rest: a matrix that is not for this form then pays for these
+// two launches and the wait, 15 us at 10 M nonzeros and 24 at 200 M (57 and 83 with the rest enqueued, too, to return
+// at once, a prefix sum run for nothing and the flags copied to the host; where the form is taken 10 us less, as well).
+__global__ __launch_bounds__(kBinWG) void bins_judge_kernel(
+    uint32_t n_chunks, uint32_t nnz, const BinChunk *__restrict__ table, const uint32_t *__restrict__ votes, int always,
+    uint32_t *__restrict__ bad, FeatureRaw *__restrict__ mailbox, uint64_t seq)
+{
+    const uint32_t tid = threadIdx.x;
+    bool cut = false;
+    for (uint32_t k = tid; k < n_chunks; k += kBinWG) cut |= table[k].cut != 0;
+    const bool any_cut = __syncthreads_or(cut ? 1 : 0) != 0;
+    if (tid >= kBinLooks) return;
+    static_assert(kBinLooks == kWave, "a vote per lane of one wave");
+    const bool looked = tid < n_chunks && bins_looks(tid * bins_apart(n_chunks), n_chunks, nnz);
+    const uint32_t looks = (uint32_t)__popcll(__ballot(looked)), local = (uint32_t)__popcll(__ballot(looked && votes[tid] != 0));
+    if (tid != 0) return;
+    *bad = 0;                                                   // (for the next kernels)
+    mailbox->max_len = 2u * local > looks && !always ? 1 : 0;
+    mailbox->min_len = any_cut ? 1 : 0;
+    __threadfence_system();
+    *reinterpret_cast<volatile uint64_t *>(&mailbox->seq) = seq;
+}
+
 // ---- preparation 2: a chunk's entries sorted by slab and part.  Leaves the groups per bucket and part
 // (counts [n_slabs][n_chunks][kParts], for the prefix sum) and the chunk's words of p; order: for every entry
 // in that order its number in the chunk; perm: for every word of the chunk's p its place in row order
-// ("slot"); row_slot: the first slot of every row.  kFlagBad: some row's columns do not ascend or lie outside
+// ("slot"); row_slot: the first slot of every row.  *bad: some row's columns do not ascend or lie outside
 // the matrix.  A wave takes 1024 consecutive entries, 64 at a time (a run does not go on from one 64 to the
 // next), and counts them by itself, so that all places depend on the matrix alone.
 struct BinEntry {                                               // one entry among the 64 that its wave looks at
@@ -198,7 +224,7 @@ __device__ __forceinline__ BinEntry bins_entry(
 __global__ __launch_bounds__(kBinWG, 8) void bins_sort_kernel(
     int rows, int cols, uint32_t n_slabs, uint32_t n_chunks, const int *__restrict__ rp, const int *__restrict__ ci,
     BinChunk *__restrict__ table, uint32_t *__restrict__ counts, uint32_t *__restrict__ chunk_words,
-    uint16_t *__restrict__ perm, uint16_t *__restrict__ order, uint16_t *__restrict__ row_slot, uint32_t *__restrict__ flags)
+    uint16_t *__restrict__ perm, uint16_t *__restrict__ order, uint16_t *__restrict__ row_slot, uint32_t *__restrict__ any_bad)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     const uint32_t entry_stride = bins_entry_stride(n_slabs), nb = kParts * n_slabs;
@@ -214,7 +240,7 @@ __global__ __launch_bounds__(kBinWG, 8) void bins_sort_kernel(
     uint16_t *s_of = reinterpret_cast<uint16_t *>(s_hist + kBinWaves * nb);         // [entry_stride / kBinGroup]: whose group
     const uint32_t tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const uint32_t chunk = tile_of_block(blockIdx.x, n_chunks, 1);
-    if (chunk >= n_chunks || bins_local(flags)) return;         // (local columns: the host will take the other form)
+    if (chunk >= n_chunks) return;
     const BinChunk t0 = table[chunk], t1 = table[chunk + 1];
     const uint32_t b = t0.first_nnz, len = t1.first_nnz - b;
 
@@ -346,9 +372,8 @@ __global__ __launch_bounds__(kBinWG, 8) void bins_sort_kernel(
     if (tid == 0) {
         chunk_words[chunk] = words;
         table[chunk].slots = slots;
-        if (t0.cut) flags[kFlagCut] = 1;
     }
-    if (bad) flags[kFlagBad] = 1;
+    if (bad) *any_bad = 1;
 }
 
 // ---- preparation 3, with the buckets' first groups known (starts): values and 16-bit columns into
@@ -357,7 +382,7 @@ __global__ __launch_bounds__(kBinWG, 8) void bins_sort_kernel(
 __global__ __launch_bounds__(kBinWG, 8) void bins_fill_kernel(
     uint32_t n_slabs, uint32_t n_chunks, const int *__restrict__ ci, const float *__restrict__ va,
     const BinChunk *__restrict__ table, const uint32_t *__restrict__ starts,
-    const uint16_t *__restrict__ order, const uint32_t *__restrict__ flags, float *__restrict__ out_va, uint16_t *__restrict__ out_ci, uint32_t *__restrict__ out_to)
+    const uint16_t *__restrict__ order, float *__restrict__ out_va, uint16_t *__restrict__ out_ci, uint32_t *__restrict__ out_to)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     float *s_val = reinterpret_cast<float *>(lds);              // [kBinMost]
@@ -367,7 +392,7 @@ __global__ __launch_bounds__(kBinWG, 8) void bins_fill_kernel(
     const uint32_t stride = bins_stride(n_slabs), entry_stride = bins_entry_stride(n_slabs);
     const uint32_t tid = threadIdx.x;
     const uint32_t chunk = tile_of_block(blockIdx.x, n_chunks, 1);
-    if (chunk >= n_chunks || bins_local(flags)) return;
+    if (chunk >= n_chunks) return;
     const uint32_t b = table[chunk].first_nnz, len = table[chunk + 1].first_nnz - b;
     float v[kBinAhead];
     uint32_t c[kBinAhead];
@@ -431,6 +456,14 @@ __global__ __launch_bounds__(kBinWG, 8) void bins_fill_kernel(
         o.y = (i2 != kBinNone ? s_col[i2 & (kBinMost - 1u)] : 0u) | (i3 != kBinNone ? s_col[i3 & (kBinMost - 1u)] : 0u) << 16;
         *reinterpret_cast<v2u *>(out_ci + (size_t)to * kBinGroup + 4u * (q % 4u)) = o;
     }
+}
+
+// Whether the form is refused, into pinned host memory (max_len).
+__global__ void bins_report_kernel(const uint32_t *__restrict__ bad, FeatureRaw *__restrict__ mailbox, uint64_t seq)
+{
+    mailbox->max_len = (int32_t)*bad;
+    __threadfence_system();
+    *reinterpret_cast<volatile uint64_t *>(&mailbox->seq) = seq;
 }
 
 // ---- the products.  A workgroup takes an equal share of the groups, slab after slab; a group's four
@@ -667,10 +700,6 @@ __global__ __launch_bounds__(kBinWG) void bins_sum_kernel(
 // ------------------------------------------------------------------ host side
 static size_t pad256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-bool bins_refused(const uint32_t *f) { return f[kFlagBad] != 0; }
-bool bins_cut(const uint32_t *f) { return f[kFlagCut] != 0; }
-bool bins_not_taken(const uint32_t *f) { return 2u * f[kFlagVotes] > f[kFlagLooks]; }
-
 uint32_t bins_num_slabs(int cols) { return cols > 0 ? ((uint32_t)cols + kBinCols - 1u) >> kBinShift : 0u; }
 static uint32_t bins_num_chunks(int nnz) { return nnz > 0 ? ((uint32_t)nnz + kBinNominal - 1u) / kBinNominal : 1u; }
 
@@ -683,11 +712,12 @@ bool bins_fit(int cols, int nnz)
 
 // Where things lie in plan_mem, from the sizes alone: the entries' values, 16-bit columns and
 // groups' places, perm, the rows' first slots, the buckets' first groups (counts before that), words of p
-// per chunk, the chunk table; then what only the preparation uses: order, the prefix sum's scratch, the flags.
+// per chunk, the chunk table; then what only the preparation uses: order (the votes before that), the prefix
+// sum's scratch, a flag.
 struct BinsLayout {
     uint32_t n_chunks, stride;
     size_t n_buckets, max_groups;
-    size_t va, ci, to, perm, row_slot, starts, chunk_words, table, order, scan, flags, total;
+    size_t va, ci, to, perm, row_slot, starts, chunk_words, table, order, scan, flag, total;
 };
 static BinsLayout bins_layout(uint32_t n_slabs, int rows, int nnz)
 {
@@ -708,7 +738,7 @@ static BinsLayout bins_layout(uint32_t n_slabs, int rows, int nnz)
     L.table = o;        o += pad256(((size_t)L.n_chunks + 1) * sizeof(BinChunk));
     L.order = o;        o += pad256((size_t)L.n_chunks * bins_entry_stride(n_slabs) * 2);
     L.scan = o;         o += pad256(scan_scratch_words(L.n_buckets + 1) * 4 + 4);
-    L.flags = o;        o += 256;
+    L.flag = o;         o += 256;
     L.total = o;
     return L;
 }
@@ -721,13 +751,22 @@ size_t bins_workspace_bytes(uint32_t n_slabs, int nnz)
     return pad256((size_t)n * bins_stride(n_slabs) * 4) + carry_workspace_bytes(n);
 }
 
-const uint32_t *bins_flags(const void *plan_mem, int rows, int cols, int nnz)
+void launch_bins_judge(int rows, int cols, int nnz, const int *rp, const int *ci, void *plan_mem, bool always,
+                       FeatureRaw *mailbox_dev, uint64_t seq, hipStream_t st)
 {
-    return reinterpret_cast<const uint32_t *>(static_cast<const char *>(plan_mem) + bins_layout(bins_num_slabs(cols), rows, nnz).flags);
+    const BinsLayout L = bins_layout(bins_num_slabs(cols), rows, nnz);
+    char *base = static_cast<char *>(plan_mem);
+    uint32_t *starts = reinterpret_cast<uint32_t *>(base + L.starts), *votes = reinterpret_cast<uint32_t *>(base + L.order);
+    BinChunk *table = reinterpret_cast<BinChunk *>(base + L.table);
+    hipLaunchKernelGGL(bins_table_kernel, dim3(L.n_chunks / (kWG / kWave) + 1u), dim3(kWG), 0, st, rows, (uint32_t)nnz,
+                       L.n_chunks, rp, ci, table, starts + L.n_buckets, votes);
+    hipLaunchKernelGGL(bins_judge_kernel, dim3(1), dim3(kBinWG), 0, st, L.n_chunks, (uint32_t)nnz,
+                       static_cast<const BinChunk *>(table), static_cast<const uint32_t *>(votes), always ? 1 : 0,
+                       reinterpret_cast<uint32_t *>(base + L.flag), mailbox_dev, seq);
 }
 
-hipError_t launch_bins_prepare(int rows, int cols, int nnz, const int *rp, const int *ci, const float *va, void *plan_mem,
-                               bool always, hipStream_t st)
+void launch_bins_prepare(int rows, int cols, int nnz, const int *rp, const int *ci, const float *va, void *plan_mem,
+                         FeatureRaw *mailbox_dev, uint64_t seq, hipStream_t st)
 {
     const uint32_t S = bins_num_slabs(cols);
     const BinsLayout L = bins_layout(S, rows, nnz);
@@ -737,26 +776,21 @@ hipError_t launch_bins_prepare(int rows, int cols, int nnz, const int *rp, const
     BinChunk *table = reinterpret_cast<BinChunk *>(base + L.table);
     uint16_t *order = reinterpret_cast<uint16_t *>(base + L.order);
     uint16_t *perm = reinterpret_cast<uint16_t *>(base + L.perm);
-    uint32_t *flags = reinterpret_cast<uint32_t *>(base + L.flags);
-    const hipError_t e = hipMemsetAsync(flags, 0, kBinFlags * 4, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(bins_table_kernel, dim3(L.n_chunks / (kWG / kWave) + 1u), dim3(kWG), 0, st, rows, (uint32_t)nnz,
-                       L.n_chunks, rp, ci, table, starts + L.n_buckets, always ? 1 : 0, flags);
+    uint32_t *bad = reinterpret_cast<uint32_t *>(base + L.flag);
     const dim3 grid(tiles_per_xcd(L.n_chunks) * kXCD);
     const size_t sort_lds = (size_t)bins_entry_stride(S) * 2 + kBinMost / 64u * 12u + kBinMost / 32u * 4u +
                             (kBinWaves + kBinWG + (size_t)(2u + kBinWaves) * kParts * S) * 4 +
                             bins_entry_stride(S) / kBinGroup * 2u;
     hipLaunchKernelGGL(bins_sort_kernel, grid, dim3(kBinWG), sort_lds, st, rows, cols, S, L.n_chunks, rp, ci, table, starts,
-                       chunk_words, perm, order, reinterpret_cast<uint16_t *>(base + L.row_slot), flags);
+                       chunk_words, perm, order, reinterpret_cast<uint16_t *>(base + L.row_slot), bad);
     launch_scan_exclusive(starts, L.n_buckets + 1, reinterpret_cast<uint32_t *>(base + L.scan), st);
     const size_t fill_lds = (kBinMost + kBinWaves + 2u * (bins_entry_stride(S) / kBinGroup)) * 4;
     hipLaunchKernelGGL(bins_fill_kernel, grid, dim3(kBinWG), fill_lds, st, S, L.n_chunks, ci, va,
                        static_cast<const BinChunk *>(table), static_cast<const uint32_t *>(starts),
                        static_cast<const uint16_t *>(order),
-                       static_cast<const uint32_t *>(flags),
                        reinterpret_cast<float *>(base + L.va), reinterpret_cast<uint16_t *>(base + L.ci),
                        reinterpret_cast<uint32_t *>(base + L.to));
-    return hipGetLastError();
+    hipLaunchKernelGGL(bins_report_kernel, dim3(1), dim3(1), 0, st, static_cast<const uint32_t *>(bad), mailbox_dev, seq);
 }
 
 void launch_bins(const SpmvArgs &a, uint32_t n_slabs, bool cut_rows, const void *plan_mem, void *workspace, hipStream_t st)

@@ -167,3 +167,29 @@ def test_lines_shared_within_a_long_row(by_bins):
     if by_bins:
         x = G.dense_vector(A.cols, 5)
         assert_parity(product(plan, upload(A), x), *oracle_of(A, x), A.name)
+
+
+def test_more_preparations_at_once_than_mailboxes(bins):
+    """A preparation waits for the device twice, each time with one of 64 result mailboxes: 70 at once end."""
+    import threading
+
+    import torch
+    A = G.random_lengths(3_001, 600_011, 0, 30, 33)
+    announce(f"70 preparations at once {A.name}")
+    dA, x = upload(A), G.dense_vector(A.cols, 3)
+    mem = [S.alloc_workspace(S.slab_plan_bytes(A.rows, A.cols, A.nnz)) for _ in range(70)]
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    plans = [None] * len(mem)
+
+    def prepare(k):
+        plans[k] = S.seer_spmv_prepare(S.CSR_S, dA, plan_mem=mem[k], stream=streams[k % 4])
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=prepare, args=(k,)) for k in range(len(mem))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    y_ref, bound = oracle_of(A, x)
+    for plan in plans[::10]:
+        assert_parity(product(plan, dA, x), y_ref, bound, A.name)
+    assert all(int(p.c.split_rows) == int(plans[0].c.split_rows) for p in plans)
