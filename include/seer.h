@@ -348,7 +348,8 @@ size_t seer_slab_plan_bytes(int32_t rows, int32_t cols, int32_t nnz);
  * plan->n_blocks = S, plan->split_rows = K.
  * A matrix of 9 * 2^20 nonzeros or more and at most 2^23 columns whose columns are not local (256
  * consecutive entries, looked at in 64 places, mostly touch 128 lines of x or more, or 32 where they
- * descend at most four times) is kept in bins
+ * descend at most four times), and that has no long run of empty rows (some 15360 consecutive nonzeros
+ * with more rows among them than twice the mean and nnz / 160), is kept in bins
  * instead: w = 15, n_blocks = ceil(cols / 2^15), split_rows = -1 or -2; what plan_mem holds then is
  * the library's own affair, and a product takes 4.5 to 7 bytes of workspace per nonzero.
  * plan_mem must hold seer_slab_plan_bytes(rows, cols, nnz) (SEER_EWORKSPACE otherwise, with
@@ -440,8 +441,8 @@ int seer_csr_check(const seer_csr *A, int64_t *bad_row_ptr, int64_t *bad_col_idx
  *               column range and the workspace has room; default: from 2^28 nonzeros on with 64
  *               or more to a row on average and at most 2^22 rows.  The size functions of CSR,WO and
  *               seer_spmv_auto follow it; with less workspace (their sizes under 0) the stage is left out
- *   "slab_bins" CSR,S: 0: never in bins; 1: in bins whatever nnz is and however local the columns
- *               are; default: from 9 * 2^20 nonzeros on, columns not local (seer_spmv_prepare)
+ *   "slab_bins" CSR,S: 0: never in bins; 1: in bins whatever nnz is, however local the columns
+ *               are and whatever rows are empty; default: as said at seer_spmv_prepare
  *   "coo_runs"  COO,WM: 1 (default): a lane sums a run of eight consecutive triples,
  *               0: lane <-> triple in rounds of 64
  *   "poll"      0: seer_features, seer_csr_check and the preparation of CSR,S wait with

@@ -162,25 +162,33 @@ __global__ __launch_bounds__(kWG) void bins_table_kernel(
     }
 }
 
+// A chunk's rows are one workgroup's, empty ones among them, 0.43 ns each in a product and 0.6 to 1.2 in the
+// preparation: a long run of empty rows holds up everything (12 M nonzeros, 4 M columns, 15 M empty rows in one place: 6497 us a
+// product and 9600 to 18 100 of preparation, the other form 119 and 900).  most_rows is where that takes what
+// the form gains: with so many in one chunk the other form is taken.
+//
 // What was seen, into pinned host memory: whether the other form is to be taken (max_len) and whether some row is cut
 // (min_len).  The host waits for that before it enqueues the rest: a matrix that is not for this form then pays for these
 // two launches and the wait, 15 us at 10 M nonzeros and 24 at 200 M (57 and 83 with the rest enqueued, too, to return
 // at once, a prefix sum run for nothing and the flags copied to the host; where the form is taken 10 us less, as well).
 __global__ __launch_bounds__(kBinWG) void bins_judge_kernel(
-    uint32_t n_chunks, uint32_t nnz, const BinChunk *__restrict__ table, const uint32_t *__restrict__ votes, int always,
-    uint32_t *__restrict__ bad, FeatureRaw *__restrict__ mailbox, uint64_t seq)
+    uint32_t n_chunks, uint32_t nnz, const BinChunk *__restrict__ table, const uint32_t *__restrict__ votes, uint32_t most_rows,
+    int always, uint32_t *__restrict__ bad, FeatureRaw *__restrict__ mailbox, uint64_t seq)
 {
     const uint32_t tid = threadIdx.x;
-    bool cut = false;
-    for (uint32_t k = tid; k < n_chunks; k += kBinWG) cut |= table[k].cut != 0;
-    const bool any_cut = __syncthreads_or(cut ? 1 : 0) != 0;
+    bool cut = false, empty = false;
+    for (uint32_t k = tid; k < n_chunks; k += kBinWG) {
+        cut |= table[k].cut != 0;
+        empty |= table[k + 1u].first_row - table[k].first_row > most_rows;
+    }
+    const bool any_cut = __syncthreads_or(cut ? 1 : 0) != 0, any_empty = __syncthreads_or(empty ? 1 : 0) != 0;
     if (tid >= kBinLooks) return;
     static_assert(kBinLooks == kWave, "a vote per lane of one wave");
     const bool looked = tid < n_chunks && bins_looks(tid * bins_apart(n_chunks), n_chunks, nnz);
     const uint32_t looks = (uint32_t)__popcll(__ballot(looked)), local = (uint32_t)__popcll(__ballot(looked && votes[tid] != 0));
     if (tid != 0) return;
     *bad = 0;                                                   // (for the next kernels)
-    mailbox->max_len = 2u * local > looks && !always ? 1 : 0;
+    mailbox->max_len = (2u * local > looks || any_empty) && !always ? 1 : 0;
     mailbox->min_len = any_cut ? 1 : 0;
     __threadfence_system();
     *reinterpret_cast<volatile uint64_t *>(&mailbox->seq) = seq;
@@ -719,6 +727,12 @@ struct BinsLayout {
     size_t n_buckets, max_groups;
     size_t va, ci, to, perm, row_slot, starts, chunk_words, table, order, scan, flag, total;
 };
+// Twice the chunks' mean, and so many beyond that as a product gains in time by this form: runs of 128 Ki empty rows
+// among 12 M nonzeros 108 us, the other form 94 (without a run 54 and 93), 256 Ki among 40 M 246 and 279, 512 Ki 357
+// and 278, 256 Ki among 60 M 349 and 432, 512 Ki 500 and 433.  Where rows are many but spread evenly all chunks take as
+// long: 100 M rows, 12 M nonzeros, 128 K rows a chunk, 337 and 339.
+static uint32_t bins_most_rows(int rows, int nnz) { return 2u * ((uint32_t)rows / bins_num_chunks(nnz)) + (uint32_t)nnz / 160u; }
+
 static BinsLayout bins_layout(uint32_t n_slabs, int rows, int nnz)
 {
     BinsLayout L;
@@ -761,7 +775,8 @@ void launch_bins_judge(int rows, int cols, int nnz, const int *rp, const int *ci
     hipLaunchKernelGGL(bins_table_kernel, dim3(L.n_chunks / (kWG / kWave) + 1u), dim3(kWG), 0, st, rows, (uint32_t)nnz,
                        L.n_chunks, rp, ci, table, starts + L.n_buckets, votes);
     hipLaunchKernelGGL(bins_judge_kernel, dim3(1), dim3(kBinWG), 0, st, L.n_chunks, (uint32_t)nnz,
-                       static_cast<const BinChunk *>(table), static_cast<const uint32_t *>(votes), always ? 1 : 0,
+                       static_cast<const BinChunk *>(table), static_cast<const uint32_t *>(votes), bins_most_rows(rows, nnz),
+                       always ? 1 : 0,
                        reinterpret_cast<uint32_t *>(base + L.flag), mailbox_dev, seq);
 }
 

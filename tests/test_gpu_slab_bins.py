@@ -193,3 +193,19 @@ def test_more_preparations_at_once_than_mailboxes(bins):
     for plan in plans[::10]:
         assert_parity(product(plan, dA, x), y_ref, bound, A.name)
     assert all(int(p.c.split_rows) == int(plans[0].c.split_rows) for p in plans)
+
+
+@pytest.mark.parametrize("where", ["first", "middle", "last"])
+@pytest.mark.parametrize("run", [30_000, 400_000])
+def test_a_long_run_of_empty_rows_is_not_for_bins(where, run):
+    """One workgroup would have it to itself, in the preparation and in every product."""
+    n, at = 320_003, {"first": 0, "middle": 150_001, "last": 320_003}[where]
+    lens = np.full(n, 30)
+    lens[0] += 7
+    A = G.explicit_lengths(np.insert(lens, at, np.zeros(run, lens.dtype)).tolist(), 1_300_001, 91, f"{run}-empty-rows-{where}")
+    announce(f"CSR,S by rule {A.name} nnz={A.nnz}")
+    assert A.nnz >= 9 << 20
+    plan = S.seer_spmv_prepare(S.CSR_S, upload(A))
+    assert (int(plan.c.split_rows) < 0) == (run == 30_000)
+    x = G.dense_vector(A.cols, 5)
+    assert_parity(product(plan, upload(A), x), *oracle_of(A, x), A.name)
