@@ -295,7 +295,8 @@ typedef struct {
     int32_t ell_width;    /* SEER_ELL_TM: slots per row = the longest row; SEER_CSR_S: log2
                              of the columns per slab                                     */
     void *device;         /* DEVICE, inside plan_mem; NULL for kernels without a plan   */
-    size_t device_bytes;
+    size_t device_bytes;  /* bytes of plan_mem that the plan occupies, from `device` on: the
+                             rest of a larger plan_mem is the caller's again                */
 } seer_plan;
 
 /* Device bytes seer_spmv_prepare needs for `kernel_id` (0 for ids that need none, and for
@@ -330,9 +331,10 @@ size_t seer_slab_plan_bytes(int32_t rows, int32_t cols, int32_t nnz);
  * writes cols[j * R + i] / vals[j * R + i] = the j-th entry of row i in CSR order, or
  * -1 / 0 where the row is shorter, R = roundup(rows, 64), cols first, vals at half of
  * seer_ell_plan_bytes(rows, longest row).  If plan_mem has room for R / 64 * (longest row) more
- * words, padded to 256 bytes, and 256 bytes, and the arrays take 16 MB or more, the distance from row to column of every 64 rows and
- * slot is kept there, and where it is mostly one for the 64 rows (stencils, bands) a product hardly
- * reads the columns.  If plan_mem is too small the call returns
+ * words, padded to 256 bytes, and 256 bytes, and the arrays take 16 MB or more, the distance from
+ * row to column of every 64 rows and slot is written there, too.  Where it is mostly one for the
+ * 64 rows (stencils, bands) it is part of the plan (n_blocks 1, device_bytes with that room) and a
+ * product hardly reads the columns.  If plan_mem is too small the call returns
  * SEER_EWORKSPACE and stores the bytes needed in plan->device_bytes, the one output written
  * on an error (the rest of *plan stays as it was): seer_features_workspace_bytes(rows) while
  * plan_mem cannot even hold the reduction's workspace, the size of the ELL form after that,

@@ -490,7 +490,7 @@ class Plan:
         import torch
         rows_pad = -(-int(self.c.rows) // 64) * 64
         n = rows_pad * self.ell_width
-        half = int(self.c.device_bytes) // 2
+        half = ell_plan_bytes(int(self.c.rows), int(self.c.ell_width)) // 2
         cols = self.plan_mem[: n * 4].view(torch.int32).cpu().numpy().reshape(self.ell_width, rows_pad)
         vals = self.plan_mem[half: half + n * 4].view(torch.float32).cpu().numpy().reshape(self.ell_width, rows_pad)
         return cols, vals

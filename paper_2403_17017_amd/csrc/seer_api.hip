@@ -1259,6 +1259,7 @@ static int prepare_ell(const seer_csr *A, void *plan_mem, size_t plan_bytes, voi
     e = hipStreamSynchronize(st);
     if (e != hipSuccess) return hip_fail(e);
     plan->n_blocks = with_shift && ell_shift_pays(A->rows, (int)max_len, sampled) ? 1 : 0;
+    if (plan->n_blocks) plan->device_bytes = need + ell_shift_bytes(A->rows, (int)max_len);   // products read them
     plan->ell_width = (int32_t)max_len;
     plan->device = plan_mem;
     return SEER_OK;
@@ -1384,7 +1385,7 @@ int seer_spmv_prepared(const seer_plan *plan, const seer_csr *A, const float *x,
     if (plan->kernel_id == SEER_ELL_TM) {
         const bool with_shift = plan->n_blocks == 1;       // then the columns, half of the bytes, are hardly read
         SpmvArgs a{A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, x, y, use_remap(),
-                   use_nt_repeated((uint64_t)plan->device_bytes / (with_shift ? 2u : 1u) +
+                   use_nt_repeated((uint64_t)ell_plan_bytes(A->rows, plan->ell_width) / (with_shift ? 2u : 1u) +
                                    4ull * ((uint64_t)A->rows + (uint64_t)A->cols))};
         launch_ell(a, plan->ell_width, with_shift, plan->device, static_cast<hipStream_t>(stream));
         const hipError_t e = hipGetLastError();

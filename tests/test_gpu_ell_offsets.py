@@ -47,11 +47,16 @@ def test_same_bits_with_and_without(k):
     x = G.dense_vector(A.cols, 3)
     x[A.cols // 2] = np.inf                          # reaches exactly the rows that have the column
     xd = torch.from_numpy(x).cuda()
-    plan = S.seer_spmv_prepare(S.ELL_TM, dA)
+    need = S.ell_plan_bytes(A.rows, width)
+    arena = S.alloc_workspace(max(need, S.features_workspace_bytes(A.rows)) + need // 100 + (1 << 20))
+    plan = S.seer_spmv_prepare(S.ELL_TM, dA, plan_mem=arena)
+    used = int(plan.c.device_bytes)
+    assert used == need + (-(-A.rows // 64) * width * 4 + 255) // 256 * 256 + 256 if kept else used == need
+    arena[used:] = 0x5A                              # what lies behind the plan is the program's again
     exact = S.alloc_workspace(max(S.ell_plan_bytes(A.rows, width), S.features_workspace_bytes(A.rows)))
     # (the reduction's workspace may leave room behind a small matrix's arrays: cut it off)
     plain = S.seer_spmv_prepare(S.ELL_TM, dA, plan_mem=exact)
-    assert plan.n_blocks == int(kept) and plain.n_blocks == 0
+    assert plan.n_blocks == int(kept) and plain.n_blocks == 0 and int(plain.c.device_bytes) == need
     ys = []
     for p in (plan, plain):
         y = torch.full((A.rows,), float("nan"), dtype=torch.float32, device="cuda:0")
