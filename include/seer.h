@@ -316,7 +316,8 @@ size_t seer_ell_plan_bytes(int32_t rows, int32_t max_len);
  * The slab width: w = 19 (2 MiB of x); w = 20 if that gives at least four slabs and fewer
  * than three entries are to be expected per piece of a row (nnz / rows < 3 * ceil(cols / 2^19));
  * the "slab_shift" tuning knob overrides both.  The plan keeps its w in ell_width.  Where the
- * preparation may choose bins (see seer_spmv_prepare) the larger of both forms' sizes. */
+ * preparation may choose bins (see seer_spmv_prepare) the larger of both forms' sizes; with what
+ * this gives while "slab_bins" is 0 the preparation leaves bins out. */
 size_t seer_slab_plan_bytes(int32_t rows, int32_t cols, int32_t nnz);
 
 /* Runs the preprocessing of `kernel_id` for A on `stream` and fills *plan.  For
@@ -354,8 +355,8 @@ size_t seer_slab_plan_bytes(int32_t rows, int32_t cols, int32_t nnz);
  * with more rows among them than twice the mean and nnz / 160), is kept in bins
  * instead: w = 15, n_blocks = ceil(cols / 2^15), split_rows = -1 or -2; what plan_mem holds then is
  * the library's own affair, and a product takes 4.5 to 7 bytes of workspace per nonzero.
- * plan_mem must hold seer_slab_plan_bytes(rows, cols, nnz) (SEER_EWORKSPACE otherwise, with
- * the bytes needed in plan->device_bytes, as for SEER_ELL_TM).  SEER_EINVAL if the form does
+ * plan_mem must hold seer_slab_plan_bytes(rows, cols, nnz), or at least the arrays above
+ * (SEER_EWORKSPACE otherwise, with the size for both in plan->device_bytes, as for SEER_ELL_TM).  SEER_EINVAL if the form does
  * not apply: by size (seer_slab_plan_bytes gives 0), or because some row's columns do not
  * ascend -- a virtual row must be one contiguous piece of its row.
  * HOST-SYNCHRONOUS: returns after the pass has finished (it reads back whether any row

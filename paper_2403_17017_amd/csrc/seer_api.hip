@@ -1188,10 +1188,12 @@ static int prepare_slab(const seer_csr *A, void *plan_mem, size_t plan_bytes, vo
     const int shift = slab_shift(A->rows, A->cols, A->nnz);
     const uint32_t S = slab_count(A->rows, A->cols, shift);
     if (S == 0) return SEER_EINVAL;                        // one slab, or too many virtual rows
-    const size_t need = seer_slab_plan_bytes(A->rows, A->cols, A->nnz);
-    plan->device_bytes = need;
+    const size_t both = seer_slab_plan_bytes(A->rows, A->cols, A->nnz), need = slab_plan_bytes(A->rows, A->cols, A->nnz, shift);
+    plan->device_bytes = both;
     if (!plan_mem || !aligned16(plan_mem) || plan_bytes < need) return SEER_EWORKSPACE;
-    if (slab_bins(A->cols, A->nnz)) {
+    if (plan_bytes < both) {
+        plan->device_bytes = need;                         // no room for bins
+    } else if (slab_bins(A->cols, A->nnz)) {
         bool taken = false;
         const int rc = prepare_bins(A, plan_mem, stream, plan, &taken);
         if (rc != SEER_OK || taken) return rc;

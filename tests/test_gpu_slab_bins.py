@@ -209,3 +209,31 @@ def test_a_long_run_of_empty_rows_is_not_for_bins(where, run):
     assert (int(plan.c.split_rows) < 0) == (run == 30_000)
     x = G.dense_vector(A.cols, 5)
     assert_parity(product(plan, upload(A), x), *oracle_of(A, x), A.name)
+
+
+def test_memory_for_the_arrays_alone_is_enough():
+    """Where bins take more than the arrays (few rows, many columns) memory for the arrays still gives them; less is
+    refused; and what the library chooses is prepared rather than another schedule."""
+    import ctypes as C
+    A = G.explicit_lengths([2_001] * 5_003, 8_000_011, 61, "few-rows-many-columns")
+    announce(f"CSR,S with memory for the arrays alone {A.name} nnz={A.nnz}")
+    assert A.nnz >= 9 << 20
+    both = S.slab_plan_bytes(A.rows, A.cols, A.nnz)
+    S.set_tuning("slab_bins", 0)
+    arrays = S.slab_plan_bytes(A.rows, A.cols, A.nnz)
+    S.set_tuning("slab_bins", -1)
+    assert 0 < arrays < both
+    dA, x = upload(A), G.dense_vector(A.cols, 5)
+    y_ref, bound = oracle_of(A, x)
+    model = S.Model(S.Tree.constant(S.CSR_S), S.Tree.constant(S.CSR_S), S.Tree([-1], [0.0], [-1], [-1], [0], n_classes=2))
+    for size, in_bins in ((both, True), (both - 1, False), (arrays, False)):
+        mem = S.alloc_workspace(both)
+        mem[size:] = 0x5A
+        for plan in (S.seer_spmv_prepare(S.CSR_S, dA, plan_mem=mem[:size]), S.seer_spmv_plan(dA, model, 50, plan_mem=mem[:size])[0]):
+            assert plan.kernel_id == S.CSR_S and (int(plan.c.split_rows) < 0) == in_bins
+            assert int(plan.c.device_bytes) == (both if in_bins else arrays)
+            assert_parity(product(plan, dA, x), y_ref, bound, A.name)
+        assert bool((mem[size:] == 0x5A).all())
+    cs, c, mem = dA.c_struct(), S.binding.seer_plan(), S.alloc_workspace(arrays)
+    rc = S.lib().seer_spmv_prepare(S.CSR_S, C.byref(cs), mem.data_ptr(), arrays - 1, None, C.byref(c))
+    assert rc == -4 and c.device_bytes == both and c.kernel_id == 0
