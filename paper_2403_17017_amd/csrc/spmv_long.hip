@@ -64,9 +64,9 @@ __global__ __launch_bounds__(kWG) void long_list_kernel(
     // two looks at the rows found: how many of each class, then each into its class's place
     for (uint32_t look = 0; look < 2; ++look) {
         uint32_t at[kLongClasses] = {0, s_class[0], s_class[0] + s_class[1]};
-        __syncthreads();
         if (look == 1 && tid == 0)
             *reinterpret_cast<uint4 *>(counts + 4u * blockIdx.x) = make_uint4(s_class[0], s_class[1], s_class[2], first);
+        __syncthreads();                                        // (all lanes have read s_class)
         if (look == 1 && tid < kLongClasses) s_class[tid] = 0;
         __syncthreads();
         for (uint32_t i = tid; i < n; i += kWG) {
