@@ -194,7 +194,8 @@ constexpr int kAutoFusedGrid = 1024;        // the product's launch selects for 
 constexpr int kAutoFusedMaxRows = 0;        // ... and, whatever its grid, up to this many rows (off: measured slower; the first pass
                                             // of at most kAutoFusedParts workgroups is the slower way to read row_ptr)
 constexpr uint32_t kAutoFusedParts = 64;    // partials the first pass leaves for it (one per lane of the folding wave)
-constexpr uint32_t kAutoWmGrid = 4096;      // combined kernel: CSR,WM loops beyond max(this, the other schedules' grids)
+constexpr uint32_t kAutoWmGrid = 4096;      // combined kernel: CSR,WM loops beyond max(this, or kAutoFusedGrid if
+                                            // the selection may then run inside the launch; the other schedules' grids)
 struct AutoPolicy {                         // when the selection runs inside the product's launch
     int fused_rows, fused_grid, fused_max_rows;
     int select_wave;                        // 1: the selection launch is a single wave (0: a workgroup of 1024 lanes)

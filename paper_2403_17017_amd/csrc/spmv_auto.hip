@@ -410,10 +410,11 @@ size_t auto_workspace_bytes(int rows, int nnz)
 // The first pass ahead of a product that selects for itself: at most kAutoFusedParts
 // partials, sixteen rows (four 16-byte loads in flight) per lane and trip; workgroups of
 // 1024 lanes once 256-lane ones would need more than one trip.
+constexpr uint32_t kAutoFusedOneTrip = kAutoFusedParts * kFeatPartWG * 16u;
 static uint32_t launch_fused_partials(const SpmvArgs &a, FeatPartial *part, bool rp_vec, hipStream_t st)
 {
     const uint32_t rows = (uint32_t)a.rows;
-    if (rows <= kAutoFusedParts * kFeatPartWG * 16u) {
+    if (rows <= kAutoFusedOneTrip) {
         const uint32_t n = (rows + kFeatPartWG * 16u - 1u) / (kFeatPartWG * 16u);
         if (rp_vec) hipLaunchKernelGGL((features_partial_kernel<true, kFeatPartWG, 4>), dim3(n), dim3(kFeatPartWG), 0, st, a.rows, a.rp, part);
         else hipLaunchKernelGGL((features_partial_kernel<false, kFeatPartWG>), dim3(n), dim3(kFeatPartWG), 0, st, a.rows, a.rp, part);
@@ -441,12 +442,15 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
     const auto reachable = [&](int k) { return ((shape.reachable >> k) & 1u) != 0; };
 
     // One workgroup per tile of the reachable schedule with the most tiles -- except CSR,WM,
-    // whose tiles (64/G rows per wave) can be several times the others': beyond kAutoWmGrid
-    // workgroups its share is capped at the others' maximum and its workgroups loop, so a
+    // whose tiles (64/G rows per wave) can be several times the others': its share is capped at
+    // kAutoWmGrid workgroups, or the others' maximum if that is more, and they loop, so that a
     // grid that runs another schedule does not launch thousands of workgroups to no purpose.
-    // Where the others alone would let the selection run inside the product's launch, CSR,WM's
-    // tiles do not stand in its way (20 011 rows of 20, 1251 of them: 10.8 us a step with a selection launch, now
-    // 10.1; a band of 61, 7001 rows, where CSR,WM is chosen and loops: 9.8 and 8.5; 300 x 300 grid 9.0 and 8.7).
+    // Where the others alone would let the selection run inside the product's launch, CSR,WM's tiles do not
+    // stand in its way: the cap is that launch's limit then (20 011 rows of 20, 1251 of them: 10.8 us a step with
+    // a selection launch, now 10.1; a band of 61, 7001 rows, where CSR,WM is chosen and loops: 9.8 and 8.5; 300 x 300 grid 9.0
+    // and 8.7).  Only for as many rows as the first pass reads in one trip: a tree of CSR,BM and CSR,WM alone
+    // on 250 003 rows of 0 to 6 entries 10.2 and 9.8 us where CSR,BM is chosen, 9.8 and 9.9 where CSR,WM is, on 500 003
+    // rows 14.7 and 15.3, 14.6 and 16.8.
     uint32_t grid = 0, wm_grid = 0;
     for (int k = 0; k < SEER_NUM_DIRECT_KERNELS; ++k) {
         if (!reachable(k)) continue;
@@ -455,7 +459,8 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
         else grid = g > grid ? g : grid;
     }
     if (reachable(SEER_CSR_WM)) {
-        const uint32_t least = heap && !shape.ranges.count && grid <= (uint32_t)policy.fused_grid && !decided
+        const uint32_t least = heap && !shape.ranges.count && grid <= (uint32_t)policy.fused_grid && !decided &&
+                                       (uint32_t)a.rows <= kAutoFusedOneTrip
                                    ? (uint32_t)policy.fused_grid : kAutoWmGrid;
         const uint32_t cap = grid > least ? grid : least;
         const uint32_t g = wm_grid < cap ? wm_grid : cap;

@@ -405,3 +405,33 @@ def test_statistics_at_the_edges_of_the_reduction(rows):
         for k in ("max_len", "min_len", "empty_rows", "sum_sq_len"):
             assert int(getattr(f, k)) == int(want[k]), k
         assert f.vector().tobytes() == want["f"].tobytes()
+
+
+@pytest.mark.parametrize("rows,launches", [(200_003, 2), (262_144, 2), (262_145, 3), (500_003, 3)])
+def test_where_the_wavefront_schedule_lets_the_selection_into_the_product(rows, launches):
+    """CSR,BM or CSR,WM, selected on the device: a first pass and the product, up to as many rows as the first pass
+    reads in one trip; with a selection launch between them beyond, where CSR,WM would loop for too long."""
+    import ctypes
+
+    import torch
+    A = G.random_lengths(rows, rows, 0, 6, 61)
+    dA, x = upload(A), G.dense_vector(A.cols, 3)
+    xd, y = torch.from_numpy(x).cuda(), torch.empty(A.rows, device="cuda:0")
+    ws = S.alloc_workspace(S.spmv_auto_workspace_bytes(A.rows, A.nnz))
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+    y_ref, bound = oracle_of(A, x)
+    for kids in ((1, 2), (2, 1)):
+        tree = S.Tree([6, -1, -1], [50.0, 0, 0], [1, -1, -1], [2, -1, -1], [-1, *kids])
+        announce(f"launches of a step rows={rows} tree={kids}")
+        g = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(g):
+            S.seer_spmv_auto(dA, tree, xd, y, ws)
+        n = ctypes.c_size_t(0)
+        assert hip.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+        assert n.value == launches
+        g.instantiate()
+        for _ in range(2):
+            y.fill_(float("nan"))
+            g.replay()
+            torch.cuda.synchronize()
+            assert_parity(y.cpu().numpy(), y_ref, bound, f"tree {kids}")
