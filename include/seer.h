@@ -226,8 +226,10 @@ size_t seer_spmv_auto_workspace_bytes(int32_t rows, int32_t nnz);
  * the library itself holds in device memory, one copy per GPU, from the moment the library
  * is loaded on that GPU until the process ends.  The call allocates and frees nothing, on the
  * device or the host.
- *   - Limit: SEER_ELIMIT if seer_spmv_auto_workspace_bytes(rows, nnz) exceeds
- *     SEER_STATIC_SCRATCH_BYTES (about 4.6e8 rows + nonzeros); nothing is enqueued then.
+ *   - Limit: SEER_ELIMIT if seer_spmv_auto_workspace_bytes(rows, nnz), as it is while "long_rows"
+ *     is 0, exceeds SEER_STATIC_SCRATCH_BYTES (about 4.6e8 rows + nonzeros); nothing is enqueued then.
+ *     There is no room for the long rows of CSR,WO apart (see "long_rows"): where seer_spmv_auto
+ *     sums them so, the launches differ, and the order of those rows' sums.
  *   - The first call on a device looks the array's address up (hipGetSymbolAddress, with
  *     that device current); make that call before capturing a graph.
  *   - All calls on one GPU share the one array, and it keeps the last call's contents; the
@@ -349,12 +351,15 @@ size_t seer_slab_plan_bytes(int32_t rows, int32_t cols, int32_t nnz);
  * are pieces of row 0, then of row 1, ..., in slab order), rp_j (uint32 [rows + 1]: the pieces
  * before row i), then col_idx and values ([nnz + 1] each) in the order of the kept rows;
  * plan->n_blocks = S, plan->split_rows = K.
- * A matrix of 9 * 2^20 nonzeros or more and at most 2^23 columns whose columns are not local (256
+ * A matrix of 9 * 2^20 nonzeros or more and at most 2^23 columns, with at most 2^30 words of products
+ * (see below: 970 M nonzeros at 17 slabs, 660 M at 256), whose columns are not local (256
  * consecutive entries, looked at in 64 places, mostly touch 128 lines of x or more, or 32 where they
  * descend at most four times), and that has no long run of empty rows (some 15360 consecutive nonzeros
  * with more rows among them than twice the mean and nnz / 160), is kept in bins
- * instead: w = 15, n_blocks = ceil(cols / 2^15), split_rows = -1 or -2; what plan_mem holds then is
- * the library's own affair, and a product takes 4.5 to 7 bytes of workspace per nonzero.
+ * instead: w = 15, n_blocks = S = ceil(cols / 2^15), split_rows = -1 or -2; what plan_mem holds then is
+ * the library's own affair (the arrays above are to be had with "slab_bins" 0), and a product takes
+ * roundup(16384 + 33 * S, 16) words of workspace for every 15360 nonzeros, 4.4 bytes per nonzero at
+ * 17 slabs and 6.5 at 256, beside the carries.
  * plan_mem must hold seer_slab_plan_bytes(rows, cols, nnz), or at least the arrays above
  * (SEER_EWORKSPACE otherwise, with the size for both in plan->device_bytes, as for SEER_ELL_TM).  SEER_EINVAL if the form does
  * not apply: by size (seer_slab_plan_bytes gives 0), or because some row's columns do not
@@ -443,7 +448,9 @@ int seer_csr_check(const seer_csr *A, int64_t *bad_row_ptr, int64_t *bad_col_idx
  *               and more per 2^15 columns are summed apart, with x in LDS, where gathers go by
  *               column range and the workspace has room; default: from 2^28 nonzeros on with 64
  *               or more to a row on average and at most 2^22 rows.  The size functions of CSR,WO and
- *               seer_spmv_auto follow it; with less workspace (their sizes under 0) the stage is left out
+ *               seer_spmv_auto follow it, whatever the columns; with less workspace (their sizes under 0)
+ *               the stage is left out, as it is where gathers do not go by range, so that no more is
+ *               needed for matrices of at most 1 310 720 or more than 2^25 columns
  *   "slab_bins" CSR,S: 0: never in bins; 1: in bins whatever nnz is, however local the columns
  *               are and whatever rows are empty; default: as said at seer_spmv_prepare
  *   "coo_runs"  COO,WM: 1 (default): a lane sums a run of eight consecutive triples,

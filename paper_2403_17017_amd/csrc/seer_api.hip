@@ -185,9 +185,12 @@ uint32_t gather_ticks(const GatherRanges &g, int64_t nnz, double entries_per_wg)
 }
 
 // Whether CSR,WO sums its long rows apart, with slabs of x in LDS (where its gathers go by range and there is
-// scratch memory for it): from 2^28 nonzeros on, 64 or more to a row on average.  (Zipf rows, 2 M columns, without and
-// with: 471 M nonzeros 2385 and 1255 us, 171 M 928 and 593, 44 M 292 and 256.  A matrix without such rows pays
-// for four launches that find nothing, 12 to 15 us, which on smaller ones is more than the runs of one differ.)
+// scratch memory for it): from 2^28 nonzeros on, 64 or more to a row on average.  The line is not where the stage begins
+// to pay, which depends on row lengths that the host does not know, but where a matrix without such rows loses no more
+// than 1 % of a product by four launches that find nothing: random rows of 60 to 110, without and with, 255 M nonzeros
+// 1461 and 1475 us, 140 M 817 and 829, 70 M 427 and 438, 35 M 233 and 244.  With Zipf rows and 2 M columns the stage
+// gains far below it: 471 M nonzeros 2385 and 1255 us, 171 M 926 and 598, 44 M 288 and 255, 32 M 214 and 185; a
+// program that knows its rows sets the knob.
 // The "long_rows" knob: 0 never, 1 from 2^23 nonzeros on, whatever the mean.
 bool long_rows(int rows, int nnz)
 {
@@ -262,9 +265,11 @@ int slab_shift(int rows, int cols, int nnz)
 }
 
 // Whether CSR,S is prepared in bins (slabs of x in LDS) where its form applies and the columns are not
-// local: from 9.4 M nonzeros on.  Measured, products and preparation, the other form and this: 10 M nonzeros in
-// 4 MB of x 62 and 38 us, 200 and 135; 40 M in 8 MB 227 and 127, 590 and 396; Zipf rows, 62 M in 16 MB
-// 393 and 192, 972 and 626; 35 M in 28 MB 327 and 140.  (Below it, the arrays described in seer.h are what a program finds in plan_mem.)
+// local: from 9.4 M nonzeros on.  That is no crossover -- this form is the faster one at the line already -- but a
+// promise: below it, the arrays that seer.h describes are what a program finds in plan_mem.  Measured, products and
+// preparation, the other form and this: 10 M nonzeros in 4 MB of x 62 and 38 us, 200 and 135; 40 M in 8 MB 227 and 127,
+// 590 and 371; Zipf rows, 62 M in 16 MB 393 and 192, 972 and 580; 35 M in 28 MB 327 and 140; 12 M in 2.1 MB, the
+// least x that the form applies to, 75 and 44, 241 and 165.
 // The "slab_bins" knob: 0 never, 1 wherever the number of slabs allows it, also if columns are local; a slab
 // width set by "slab_shift" is the other form's.
 bool slab_bins(int cols, int nnz)

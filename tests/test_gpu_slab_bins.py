@@ -237,3 +237,18 @@ def test_memory_for_the_arrays_alone_is_enough():
     cs, c, mem = dA.c_struct(), S.binding.seer_plan(), S.alloc_workspace(arrays)
     rc = S.lib().seer_spmv_prepare(S.CSR_S, C.byref(cs), mem.data_ptr(), arrays - 1, None, C.byref(c))
     assert rc == -4 and c.device_bytes == both and c.kernel_id == 0
+
+
+@pytest.mark.parametrize("cols,in_bins", [(1 << 23, True), ((1 << 23) + 1, False)])
+def test_more_slabs_than_bins_hold(bins, cols, in_bins):
+    """256 slabs, and one more: size, preparation and product agree on the form."""
+    A = G.random_lengths(2_003, cols, 5, 60, 51)
+    announce(f"CSR,S of {cols} columns {A.name}")
+    dA, x = upload(A), G.dense_vector(A.cols, 5)
+    size = S.slab_plan_bytes(A.rows, A.cols, A.nnz)
+    plan = S.seer_spmv_prepare(S.CSR_S, dA)
+    assert (int(plan.c.split_rows) < 0) == in_bins and plan.n_blocks == (256 if in_bins else 9)
+    assert int(plan.c.device_bytes) == size
+    S.set_tuning("slab_bins", 0)
+    assert (S.slab_plan_bytes(A.rows, A.cols, A.nnz) == size) == (not in_bins)
+    assert_parity(product(plan, dA, x), *oracle_of(A, x), A.name)
