@@ -26,8 +26,8 @@
  *   - Every call returns SEER_OK (0) or a negative seer_status; on error no output
  *     is written.  Nothing throws or aborts.  Matrix contents (monotone row_ptr,
  *     column range) are NOT validated: they are the caller's contract.
- *   - The first seer_features or seer_csr_check call, or preparation of SEER_CSR_S, allocates 4096 bytes
- *     of pinned host memory per process (64 result mailboxes); no other state is kept, on the host
+ *   - The first seer_features or seer_csr_check call, or preparation of SEER_ELL_TM or SEER_CSR_S,
+ *     allocates 4096 bytes of pinned host memory per process (64 result mailboxes); no other state is kept, on the host
  *     or the device.
  *   - Calls that use the same workspace must not overlap in time.  Such calls of different threads
  *     run side by side, up to 64 of them; a further one waits until one of those has ended.

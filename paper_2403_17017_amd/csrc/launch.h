@@ -71,12 +71,11 @@ void launch_adaptive(const SpmvArgs &a, bool vec, const void *plan_mem, void *ca
 // ELL,TM: plan_mem holds the ELL columns, then the ELL values (ell_plan_bytes())
 uint32_t ell_rows_pad(int rows);
 size_t ell_plan_bytes(int rows, int width);
-// with_shift: behind the arrays lie ell_shift_bytes() more, the distances from row to column of every 64 rows;
-// ell_sampled(): kEllSampled words that the conversion leaves for ell_shift_pays()
-constexpr size_t kEllSampled = 64;
-bool ell_shift_pays(int rows, int width, const uint32_t *sampled);     // three quarters of the slots looked at have one distance
+// with_shift: behind the arrays lie ell_shift_bytes() more, the distances from row to column of every 64 rows, and a
+// sample, from which launch_ell_judge says whether products are to use them (the mailbox's max_len)
 size_t ell_shift_bytes(int rows, int width);
-uint32_t *ell_sampled(void *plan_mem, int rows, int width);
+struct FeatureRaw;
+void launch_ell_judge(int rows, int width, void *plan_mem, FeatureRaw *mailbox_dev, uint64_t seq, hipStream_t st);
 void launch_ell_convert(int rows, int width, const int *rp, const int *ci, const float *va, void *plan_mem,
                         bool with_shift, hipStream_t st);
 void launch_ell(const SpmvArgs &a, int width, bool with_shift, const void *plan_mem, hipStream_t st);
@@ -117,7 +116,6 @@ size_t bins_workspace_bytes(uint32_t n_slabs, int nnz);
 // In two steps, each of which leaves its answer in a mailbox.  The first: max_len 1: the other form is faster for the
 // matrix (not if `always`), min_len 1: some row is cut, so that products leave carries.  The second, only if the first
 // says 0: max_len 1: columns do not ascend in a row, or lie outside the matrix.
-struct FeatureRaw;
 void launch_bins_judge(int rows, int cols, int nnz, const int *rp, const int *ci, void *plan_mem, bool always,
                        FeatureRaw *mailbox_dev, uint64_t seq, hipStream_t st);
 void launch_bins_prepare(int rows, int cols, int nnz, const int *rp, const int *ci, const float *va, void *plan_mem,

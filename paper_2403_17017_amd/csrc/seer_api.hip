@@ -55,7 +55,7 @@ std::atomic<int> g_tune_coo_runs{-1};
 std::atomic<int> g_tune_slab_shift{-1};
 std::atomic<int> g_tune_gather_range{-1};
 
-// Where the waiting calls (seer_features, seer_csr_check, seer_spmv_prepare for CSR,S) get their results: kMailboxes slots of
+// Where the waiting calls (seer_features, seer_csr_check, seer_spmv_prepare for ELL,TM and CSR,S) get their results: kMailboxes slots of
 // pinned, mapped host memory, one per call under way, so that calls of different threads do not
 // wait for each other's streams.
 constexpr int kMailboxes = 64;
@@ -1254,19 +1254,30 @@ static int prepare_ell(const seer_csr *A, void *plan_mem, size_t plan_bytes, voi
     // With room behind the arrays the distances from row to column are kept, too, and used if three
     // quarters of those sampled are one for their 64 rows: the others cost a product a scalar load for
     // nothing before their columns are asked for.  Not for arrays below 16 MB: their products are a launch and
-    // a chain of loads whatever they read, and the sample's way to the host takes about 8 us.
+    // a chain of loads whatever they read.  (A product, without and with, the arrays in the caches and not: 17.4 MB 2.7 and
+    // 3.0 us, 11.1 and 8.7; 19.6 MB 2.85 and 3.3, 12.2 and 9.2; 22.4 MB 3.1 and 3.2, 13.2 and 9.4; 25.6 MB 4.2 and 3.7, 14.8
+    // and 11.8; 42 MB 8.7 and 5.3, 21.7 and 17.0: up to 22 MB the line is for those that come from memory.)  The sample comes by
+    // mailbox: the preparation of matrices that do not use it 57 -> 63 us and 71 -> 77, with a copy to the host 70 and 84.
     const bool with_shift = need >= 16u << 20 && plan_bytes - need >= ell_shift_bytes(A->rows, (int)max_len);
-    uint32_t sampled[kEllSampled] = {};
     launch_ell_convert(A->rows, (int)max_len, A->row_ptr, A->col_idx, A->values, plan_mem, with_shift, st);
+    Mailbox mail;
+    FeatureRaw judged = {};
+    if (with_shift) {
+        const int rc = mail.take();
+        if (rc != SEER_OK) return rc;
+        launch_ell_judge(A->rows, (int)max_len, plan_mem, mail.device(), mail.seq(), st);
+    }
     hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return hip_fail(e);
-    if (with_shift)
-        e = hipMemcpyAsync(sampled, ell_sampled(plan_mem, A->rows, (int)max_len), sizeof sampled, hipMemcpyDeviceToHost, st);
-    if (e != hipSuccess) return hip_fail(e);
-    e = hipStreamSynchronize(st);
-    if (e != hipSuccess) return hip_fail(e);
-    plan->n_blocks = with_shift && ell_shift_pays(A->rows, (int)max_len, sampled) ? 1 : 0;
-    if (plan->n_blocks) plan->device_bytes = need + ell_shift_bytes(A->rows, (int)max_len);   // products read them
+    if (with_shift) {
+        const int rc = mail.wait(st, &judged);                 // (it is there)
+        if (rc != SEER_OK) return rc;
+    }
+    if (judged.max_len != 0) {
+        plan->n_blocks = 1;
+        plan->device_bytes = need + ell_shift_bytes(A->rows, (int)max_len);     // products read them
+    }
     plan->ell_width = (int32_t)max_len;
     plan->device = plan_mem;
     return SEER_OK;

@@ -39,22 +39,32 @@ size_t ell_shift_bytes(int rows, int width)
 {
     return (((size_t)(ell_rows_pad(rows) / kEllRowMultiple) * (size_t)width * 4 + 255) & ~(size_t)255) + 256;
 }
-uint32_t *ell_sampled(void *plan_mem, int rows, int width)
+static uint32_t *ell_sampled(void *plan_mem, int rows, int width)
 {
-    static_assert(kEllSampled == kEllSamples && kEllSampled * 4 == 256, "the sample's place");
+    static_assert(kEllSamples * 4 == 256, "the sample's place");
     return reinterpret_cast<uint32_t *>(static_cast<char *>(plan_mem) + ell_plan_bytes(rows, width) +
-                                        ell_shift_bytes(rows, width) - kEllSampled * 4);
+                                        ell_shift_bytes(rows, width) - kEllSamples * 4);
 }
 
-bool ell_shift_pays(int rows, int width, const uint32_t *sampled)
+// Whether three quarters of the slots sampled have one distance, into pinned host memory (max_len).  One wave, a
+// sample per lane.
+__global__ __launch_bounds__(kWave) void ell_judge_kernel(
+    uint32_t rows_pad, uint32_t width, const uint32_t *__restrict__ sampled, FeatureRaw *__restrict__ mailbox, uint64_t seq)
 {
-    const uint32_t rows_pad = ell_rows_pad(rows), apart = ell_sample_stride(rows_pad);
-    uint64_t one = 0, all = 0;
-    for (uint32_t k = 0; k * apart < rows_pad / kEllRowMultiple; ++k) {
-        one += sampled[k];
-        all += (uint64_t)width;
-    }
-    return 4u * one >= 3u * all;
+    static_assert(kEllSamples == kWave, "a sample per lane");
+    const bool is = threadIdx.x * ell_sample_stride(rows_pad) < rows_pad / kEllRowMultiple;
+    const auto add = [](uint32_t a, uint32_t b) { return a + b; };   // (64 rows of `width` slots are fewer than 2^31)
+    const uint32_t one = wave_fold(is ? sampled[threadIdx.x] : 0u, add), all = wave_fold(is ? width : 0u, add);
+    if (threadIdx.x != 0) return;
+    mailbox->max_len = 4ull * one >= 3ull * all ? 1 : 0;
+    __threadfence_system();
+    *reinterpret_cast<volatile uint64_t *>(&mailbox->seq) = seq;
+}
+
+void launch_ell_judge(int rows, int width, void *plan_mem, FeatureRaw *mailbox_dev, uint64_t seq, hipStream_t st)
+{
+    hipLaunchKernelGGL(ell_judge_kernel, dim3(1), dim3(kWave), 0, st, ell_rows_pad(rows), (uint32_t)width,
+                       static_cast<const uint32_t *>(ell_sampled(plan_mem, rows, width)), mailbox_dev, seq);
 }
 
 static float *ell_values(void *plan_mem, int rows, int width)
