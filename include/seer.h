@@ -27,8 +27,8 @@
  *     is written.  Nothing throws or aborts.  Matrix contents (monotone row_ptr,
  *     column range) are NOT validated: they are the caller's contract.
  *   - The first seer_features or seer_csr_check call, or preparation of SEER_ELL_TM or SEER_CSR_S,
- *     allocates 4096 bytes of pinned host memory per process (64 result mailboxes); no other state is kept, on the host
- *     or the device.
+ *     allocates 4096 bytes of pinned host memory per process (64 result mailboxes); but for the
+ *     array of seer_spmv_auto_static no other state is kept, on the host or the device.
  *   - Calls that use the same workspace must not overlap in time.  Such calls of different threads
  *     run side by side, up to 64 of them; a further one waits until one of those has ended.
  */
