@@ -449,7 +449,7 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
     // stand in its way: the cap is that launch's limit then (20 011 rows of 20, 1251 of them: 10.8 us a step with
     // a selection launch, now 10.1; a band of 61, 7001 rows, where CSR,WM is chosen and loops: 9.8 and 8.5; 300 x 300 grid 9.0
     // and 8.7).  Only for as many rows as the first pass reads in one trip: a tree of CSR,BM and CSR,WM alone
-    // on 250 003 rows of 0 to 6 entries 10.2 and 9.8 us where CSR,BM is chosen, 9.8 and 9.9 where CSR,WM is, on 500 003
+    // on 250 003 rows of 0 to 6 entries 10.2 and 9.8 us where CSR,BM is chosen, 9.8 to 10.1 and 9.9 where CSR,WM is, on 500 003
     // rows 14.7 and 15.3, 14.6 and 16.8.
     uint32_t grid = 0, wm_grid = 0;
     for (int k = 0; k < SEER_NUM_DIRECT_KERNELS; ++k) {
