@@ -378,6 +378,9 @@ public:
     ~Mailbox()
     {
         if (slot_ < 0) return;
+        // A call that returns early, because some launch or runtime call failed, waits for what it enqueued: the
+        // kernels write into the slot, which may be another call's as soon as it is free.
+        if (pending_) (void)hipStreamSynchronize(stream_);
         {
             std::lock_guard<std::mutex> lock(g_mailbox_mutex);
             g_mailbox_free |= 1ull << slot_;
@@ -412,14 +415,20 @@ public:
         return SEER_OK;
     }
 
-    FeatureRaw *device() const { return dev_; }
+    // The slot's address for kernels about to be enqueued on st.
+    FeatureRaw *device(hipStream_t st)
+    {
+        stream_ = st;
+        pending_ = true;
+        return dev_;
+    }
     uint64_t seq() const { return seq_; }
 
     // Waits until the kernel that writes seq() into the slot has done so, and copies the slot out.
     // The kernel writes its result, then the sequence number, into pinned host memory.  Watching
     // that word is quicker than waiting for the stream; if it does not show up soon, wait for the
     // stream and look again.
-    int wait(hipStream_t st, FeatureRaw *raw) const
+    int wait(FeatureRaw *raw)
     {
         const volatile uint64_t *seq_word = &host_->seq;
         bool seen = false;
@@ -434,17 +443,20 @@ public:
             }
         }
         if (!seen) {
-            const hipError_t e = hipStreamSynchronize(st);
+            const hipError_t e = hipStreamSynchronize(stream_);
             if (e != hipSuccess) return hip_fail(e);
             if (*seq_word != seq_) return hip_fail(hipErrorUnknown);
         }
         std::atomic_thread_fence(std::memory_order_acquire);
         std::memcpy(raw, host_, sizeof *raw);
+        pending_ = false;
         return SEER_OK;
     }
 
 private:
     int slot_ = -1;
+    bool pending_ = false;
+    hipStream_t stream_ = nullptr;
     uint64_t seq_ = 0;
     FeatureRaw *host_ = nullptr, *dev_ = nullptr;
 };
@@ -725,11 +737,11 @@ int seer_features(const seer_csr *A, seer_features_t *out, void *workspace, size
         const int mrc = mail.take();
         if (mrc != SEER_OK) return mrc;
         hipStream_t st = static_cast<hipStream_t>(stream);
-        launch_features(A->rows, A->row_ptr, workspace, mail.device(), mail.seq(), st);
+        launch_features(A->rows, A->row_ptr, workspace, mail.device(st), mail.seq(), st);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e);
         FeatureRaw raw;
-        const int wrc = mail.wait(st, &raw);
+        const int wrc = mail.wait(&raw);
         if (wrc != SEER_OK) return wrc;
         o.nnz = (int64_t)raw.last - (int64_t)raw.first;
         o.max_len = raw.max_len;
@@ -1009,9 +1021,9 @@ static int csr_check_once(const seer_csr *A, bool count, void *workspace, hipStr
     Mailbox mail;
     const int rc = mail.take();
     if (rc != SEER_OK) return rc;
-    launch_csr_check(A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, workspace, count, mail.device(), mail.seq(), st);
+    launch_csr_check(A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, workspace, count, mail.device(st), mail.seq(), st);
     const hipError_t e = hipGetLastError();
-    return e == hipSuccess ? mail.wait(st, raw) : hip_fail(e);
+    return e == hipSuccess ? mail.wait(raw) : hip_fail(e);
 }
 
 int seer_csr_check(const seer_csr *A, int64_t *bad_row_ptr, int64_t *bad_col_idx, void *workspace,
@@ -1160,9 +1172,9 @@ static int prepare_bins(const seer_csr *A, void *plan_mem, void *stream, seer_pl
         int rc = mail.take();
         if (rc != SEER_OK) return rc;
         launch_bins_judge(A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, plan_mem, g_tune_slab_bins.load() > 0,
-                          mail.device(), mail.seq(), st);
+                          mail.device(st), mail.seq(), st);
         const hipError_t e = hipGetLastError();
-        rc = e == hipSuccess ? mail.wait(st, &judged) : hip_fail(e);
+        rc = e == hipSuccess ? mail.wait(&judged) : hip_fail(e);
         if (rc != SEER_OK) return rc;
     }
     *taken = judged.max_len == 0;
@@ -1171,10 +1183,10 @@ static int prepare_bins(const seer_csr *A, void *plan_mem, void *stream, seer_pl
         Mailbox mail;
         int rc = mail.take();
         if (rc != SEER_OK) return rc;
-        launch_bins_prepare(A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, plan_mem, mail.device(), mail.seq(), st);
+        launch_bins_prepare(A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, plan_mem, mail.device(st), mail.seq(), st);
         hipError_t e = hipGetLastError();
         if (e == hipSuccess) e = hipStreamSynchronize(st);      // (the plan may be used on another stream next)
-        rc = e == hipSuccess ? mail.wait(st, &made) : hip_fail(e);
+        rc = e == hipSuccess ? mail.wait(&made) : hip_fail(e);
         if (rc != SEER_OK) return rc;
     }
     if (made.max_len != 0) return SEER_EINVAL;
@@ -1265,13 +1277,13 @@ static int prepare_ell(const seer_csr *A, void *plan_mem, size_t plan_bytes, voi
     if (with_shift) {
         const int rc = mail.take();
         if (rc != SEER_OK) return rc;
-        launch_ell_judge(A->rows, (int)max_len, plan_mem, mail.device(), mail.seq(), st);
+        launch_ell_judge(A->rows, (int)max_len, plan_mem, mail.device(st), mail.seq(), st);
     }
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return hip_fail(e);
     if (with_shift) {
-        const int rc = mail.wait(st, &judged);                 // (it is there)
+        const int rc = mail.wait(&judged);                 // (it is there)
         if (rc != SEER_OK) return rc;
     }
     if (judged.max_len != 0) {

@@ -194,29 +194,35 @@ def test_calls_share_nothing_but_what_they_are_handed():
     assert results == {"bad": {want}, "good": {(0, 0)}}
 
 
-def test_a_call_that_returns_early_disturbs_no_other():
-    """An error that another library left in the thread is reported behind the launches, so such a call returns
-    while its kernels run: calls that follow it at once get their own counts."""
+@pytest.mark.parametrize("call", ["check", "features", "prepare CSR,S", "prepare ELL,TM"])
+def test_a_call_that_fails_leaves_no_kernel_behind(call):
+    """An error that another library left in the thread is reported behind the launches.  Such a call ends when its
+    kernels have: they write into a result mailbox that is another call's next."""
     import ctypes
 
     import torch
-    hip = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
-    nnz = 400_000_000
-    far = torch.full((nnz,), 9, dtype=torch.int32, device="cuda:0")             # every column outside
-    big = S.DeviceCSR(1, 9, torch.tensor([0, nnz], dtype=torch.int32, device="cuda:0"), far,
-                      far.view(torch.float32), nnz)
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+    A = G.random_lengths(300_007, 1_300_000, 20, 50, 77) if call != "prepare ELL,TM" else G.banded(699_968, 1, 5)
+    dA = S.DeviceCSR.from_host(A)
     good = S.DeviceCSR.from_host(G.random_lengths(2_003, 5_000, 0, 20, 7))
     busy, other = torch.cuda.Stream(), torch.cuda.Stream()
-    ws_big, ws = S.alloc_workspace(16), S.alloc_workspace(16)
-    assert tuple(S.seer_csr_check(big, ws_big, busy)) == (0, nnz)
+    ws = S.alloc_workspace(max(S.features_workspace_bytes(A.rows), 256))
+    mem = S.alloc_workspace(1 << 30) if call.startswith("prepare") else None
+    run = {"check": lambda: S.seer_csr_check(dA, ws, busy), "features": lambda: S.seer_features(dA, ws, busy),
+           "prepare CSR,S": lambda: S.seer_spmv_prepare(S.CSR_S, dA, plan_mem=mem, stream=busy),
+           "prepare ELL,TM": lambda: S.seer_spmv_prepare(S.ELL_TM, dA, plan_mem=mem, stream=busy)}[call]
+    run()
     assert tuple(S.seer_csr_check(good, ws, other)) == (0, 0)
     torch.cuda.synchronize()
-    announce("seer_csr_check that returns early")
-    assert ctypes.CDLL(hip).hipSetDevice(12345) != 0                            # refused; remembered by the runtime
+    announce(f"{call} with an error left in the thread")
+    with torch.cuda.stream(busy):
+        torch.cuda._sleep(20_000_000)                                          # 8 ms and more of the GPU's clock
+    assert hip.hipSetDevice(12345) != 0                                        # refused; remembered by the runtime
     with pytest.raises(S.SeerError) as ei:
-        S.seer_csr_check(big, ws_big, busy)
+        run()
     assert ei.value.status == -5
-    for _ in range(100):
+    assert busy.query(), "the call's kernels were still to run"
+    for _ in range(20):
         assert tuple(S.seer_csr_check(good, ws, other)) == (0, 0)
+    run()
     torch.cuda.synchronize()
-    assert tuple(S.seer_csr_check(big, ws_big, busy)) == (0, nnz)
