@@ -188,7 +188,9 @@ int seer_tree_reachable(const seer_tree *tree, const seer_features_t *known, uin
  * valid for every matrix and gives the same y up to fp32 summation order.
  * rows == 0: nothing is written.  Asynchronous on `stream`.
  * workspace: at least seer_spmv_workspace_bytes(kernel_id, rows, nnz) bytes (0 for
- * ids 0-2, then workspace may be NULL).
+ * ids 0-2, then workspace may be NULL).  Below 2^23 nonzeros and up to 2^25 rows the parts of rows that CSR,MP
+ * and CSR,WO cut between workgroups meet there, 64 bytes for each workgroup; with at least 8 bytes for each the call
+ * is accepted, too, and adds the parts up in a second launch, in another order.
  * SEER_CSR_A and SEER_COO_WM in this single call run their preprocessing pass first, every
  * time (what one product with them costs); seer_spmv_prepare / seer_spmv_prepared split the two.
  * SEER_ELL_TM and SEER_CSR_S have no one-call form (SEER_EKERNEL): whether they apply and
@@ -207,7 +209,8 @@ size_t seer_spmv_workspace_bytes(int kernel_id, int32_t rows, int32_t nnz);
  * the features seer_features would return (all three bit for bit).
  * Before anything is enqueued the host prunes the tree with what it knows from rows,
  * cols and nnz (seer_tree_reachable): the launches are sized for the schedules that stay
- * reachable, the carry fix-up of CSR,MP / CSR,WO is enqueued only if one of them does,
+ * reachable, the carry fix-up of CSR,MP / CSR,WO (see seer_spmv: where their cut rows do not
+ * meet in the workspace) is enqueued only if one of them does,
  * and if a single kernel is left the matrix is not looked at: that kernel is launched and
  * nothing is gathered (Sec. III-B: collection only where it is justified).
  * tree: HOST, at most 127 nodes, no cycles, every leaf a kernel id below

@@ -30,6 +30,14 @@ struct GatherRanges {
 struct LongSkip { uint16_t head, tail; };
 constexpr uint16_t kLongWhole = 0x8000u;
 
+// Where the parts of a row that a tile boundary cuts meet (meet_row): a slot of 64 bytes per boundary, slots null:
+// the parts go out as carries.  The marks are the process's own.
+struct Meet {
+    unsigned long long *slots = nullptr;
+    uint32_t mark = 0, proof = 0;
+};
+constexpr uint32_t kMeetWords = 8;
+
 struct SpmvArgs {
     int rows, cols, nnz;
     const int *rp, *ci;
@@ -39,6 +47,7 @@ struct SpmvArgs {
     int nt;     // 1: matrix streams are loaded with the non-temporal hint (keeps x in L2)
     GatherRanges ranges = GatherRanges{};   // count > 0 only where the 16-byte loads are used, too
     const LongSkip *skip = nullptr;         // CSR,WO with ranges only; null: no entry is left out
+    Meet meet = Meet{};                     // CSR,MP and CSR,WO: only where meet_applies()
 };
 
 bool tm_short_rows(int rows, int nnz);
@@ -57,6 +66,12 @@ void launch_mp(const SpmvArgs &a, int ipt, bool vec, void *workspace, hipStream_
 uint32_t wo_num_tiles(int rows, int nnz);
 void launch_wo(const SpmvArgs &a, bool vec, void *workspace, hipStream_t st);
 size_t carry_workspace_bytes(uint32_t n_tiles);
+// Cut rows meet inside the product (no carries, no fix-up launch) below 2^23 nonzeros and at up to 2^25 rows (so that the
+// slots fit seer_spmv_auto_static's array), if
+// the workspace has the room: by the sizes alone, so that every path to CSR,MP or CSR,WO adds a row up in the same order.
+// From 2^23 nonzeros on a product takes 35 us and more, of which the launch is 3.
+inline bool meet_applies(int rows, int nnz) { return nnz < (1 << 23) && rows <= (1 << 25); }
+inline size_t meet_workspace_bytes(uint32_t n_tiles) { return (size_t)n_tiles * kMeetWords * 8; }
 void launch_carry_fixup(int rows, uint32_t n_tiles, const int *carry_row, const float *carry_val, float *y,
                         hipStream_t st);
 
@@ -180,13 +195,15 @@ struct AutoShape {                          // launch shapes, all from rows and 
     int tm_remap;                           // CSR,TM's tile order: 1 XCD-contiguous, 0 round-robin
     GatherRanges ranges;                    // as in SpmvArgs; ticks: CSR,WO's
     const LongSkip *skip;                   // as in SpmvArgs
+    Meet meet;                              // as in SpmvArgs
     uint32_t bm_ticks, mp_ticks;
     int bm_ranged;                          // CSR,BM orders its gathers, too
     uint32_t reachable;                     // bit k: the tree can answer kernel k given rows, cols and nnz (never 0)
 };
 constexpr size_t kAutoSelOffset = 32768;    // after the 1024 feature partials of 32 bytes
 constexpr size_t kAutoCarryOffset = 32768 + 256;
-size_t auto_workspace_bytes(int rows, int nnz);
+size_t auto_workspace_bytes(int rows, int nnz);         // the least: with carries
+size_t auto_meet_workspace_bytes(int rows, int nnz);    // ... with room for cut rows to meet where they may
 constexpr int kAutoFusedRows = 8192;        // up to here every workgroup gathers and selects for itself, no first pass
 constexpr int kAutoFusedGrid = 1024;        // the product's launch selects for itself up to this many workgroups ...
 constexpr int kAutoFusedMaxRows = 0;        // ... and, whatever its grid, up to this many rows (off: measured slower; the first pass

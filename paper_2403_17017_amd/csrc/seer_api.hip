@@ -16,6 +16,8 @@
 #include <cstring>
 #include <mutex>
 
+#include <sys/random.h>
+
 using namespace seer;
 
 // Scratch of seer_spmv_auto_static, the entry point for callers that cannot allocate: feature
@@ -54,6 +56,22 @@ std::atomic<int> g_tune_poll{-1};
 std::atomic<int> g_tune_coo_runs{-1};
 std::atomic<int> g_tune_slab_shift{-1};
 std::atomic<int> g_tune_gather_range{-1};
+
+// The marks by which a product knows the sums in its slots (meet_next) from what a workspace held before: random, the process's own.
+Meet meet_at(void *slots, size_t bytes, int rows, int nnz, uint32_t n_tiles)
+{
+    if (!meet_applies(rows, nnz) || bytes < meet_workspace_bytes(n_tiles)) return Meet{};
+    static const uint64_t marks = [] {
+        uint64_t m = 0;
+        if (getrandom(&m, sizeof m, GRND_NONBLOCK) != (ssize_t)sizeof m)
+            m = ((uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() ^ (uint64_t)reinterpret_cast<uintptr_t>(&g_scratch_mutex)) *
+                0x9E3779B97F4A7C15ull;
+        return m;
+    }();
+    const uint32_t mark = (uint32_t)(marks >> 32) | 1u;          // (a slot at rest is zero)
+    const uint32_t proof = (uint32_t)marks == mark ? mark ^ 2u : (uint32_t)marks;
+    return Meet{static_cast<unsigned long long *>(slots), mark, proof};
+}
 
 // Where the waiting calls (seer_features, seer_csr_check, seer_spmv_prepare for ELL,TM and CSR,S) get their results: kMailboxes slots of
 // pinned, mapped host memory, one per call under way, so that calls of different threads do not
@@ -677,14 +695,19 @@ size_t seer_features_workspace_bytes(int32_t rows) { return rows < 0 ? 0 : featu
 size_t seer_spmv_workspace_bytes(int kernel_id, int32_t rows, int32_t nnz)
 {
     if (rows <= 0 || nnz < 0) return 0;
-    if (kernel_id == SEER_CSR_WO) return carry_workspace_bytes(wo_num_tiles(rows, nnz)) + (long_rows(rows, nnz) ? long_workspace_most(rows, nnz) : 0);
+    if (kernel_id == SEER_CSR_WO) {
+        const uint32_t n = wo_num_tiles(rows, nnz);
+        if (meet_applies(rows, nnz)) return std::max(carry_workspace_bytes(n), meet_workspace_bytes(n));
+        return carry_workspace_bytes(n) + (long_rows(rows, nnz) ? long_workspace_most(rows, nnz) : 0);
+    }
     if (kernel_id == SEER_CSR_A)   // the carries, then the plan that the call builds for itself
         return carry_workspace_bytes(adaptive_num_tiles(rows, nnz)) + adaptive_plan_bytes(rows, nnz);
     if (kernel_id == SEER_COO_WM)
         return carry_workspace_bytes(coo_num_intervals(rows, nnz)) + coo_plan_bytes(rows, nnz);
     if (kernel_id != SEER_CSR_MP) return 0;
     // the small tile gives the larger count; cover either choice
-    return mp_workspace_bytes(rows, nnz, kMpIptSmall);
+    const size_t carries = mp_workspace_bytes(rows, nnz, kMpIptSmall);
+    return meet_applies(rows, nnz) ? std::max(carries, meet_workspace_bytes(mp_num_tiles(rows, nnz, kMpIptSmall))) : carries;
 }
 
 int seer_derive_features(seer_features_t *io)
@@ -794,7 +817,7 @@ int seer_tree_reachable(const seer_tree *tree, const seer_features_t *known, uin
 size_t seer_spmv_auto_workspace_bytes(int32_t rows, int32_t nnz)
 {
     if (rows < 0 || nnz < 0) return 0;
-    return auto_workspace_bytes(rows, nnz) + (long_rows(rows, nnz) ? long_workspace_most(rows, nnz) : 0);
+    return auto_meet_workspace_bytes(rows, nnz) + (long_rows(rows, nnz) ? long_workspace_most(rows, nnz) : 0);
 }
 
 // Everything seer_spmv_auto checks before it needs scratch memory.  SEER_OK with *enqueue
@@ -846,11 +869,13 @@ static int auto_enqueue(const seer_csr *A, const seer_tree *tree, const float *x
     if (sh.ranges.count && long_rows(A->rows, A->nnz) && workspace_bytes >= before_long &&
         workspace_bytes - before_long >= long_workspace_bytes(A->rows, A->cols, A->nnz))
         long_ws = static_cast<char *>(workspace) + before_long;
+    sh.meet = meet_at(static_cast<char *>(workspace) + kAutoCarryOffset, workspace_bytes - kAutoCarryOffset, A->rows, A->nnz,
+                      std::max(sh.tiles[SEER_CSR_MP], sh.tiles[SEER_CSR_WO]));
     sh.ranges.ticks = gather_ticks(sh.ranges, A->nnz, wo_entries(A->nnz));
     sh.bm_ticks = gather_ticks(sh.ranges, A->nnz, bm_entries(A->rows, A->nnz, sh.bm_rows));
     sh.mp_ticks = gather_ticks(sh.ranges, A->nnz, mp_entries(A->rows, A->nnz, sh.mp_ipt));
     // What the host knows without looking at the matrix prunes the tree: the grid is sized
-    // for the schedules that stay reachable, the carry fix-up is enqueued only if merge path
+    // for the schedules that stay reachable, a carry fix-up is enqueued only if merge path
     // or the nonzero split is among them, and if a single kernel is left nothing is gathered.
     seer_features_t kf;
     (void)seer_known_features(A->rows, A->cols, A->nnz, &kf);
@@ -1128,6 +1153,7 @@ static int spmv_dispatch(int kernel_id, const seer_csr *A, const float *x, float
             if (workspace_bytes - before >= long_workspace_bytes(A->rows, A->cols, A->nnz))
                 a.skip = launch_long(a, nullptr, static_cast<char *>(workspace) + before, st);
         }
+        a.meet = meet_at(workspace, workspace_bytes, A->rows, A->nnz, wo_num_tiles(A->rows, A->nnz));
         launch_wo(a, vec, workspace, st);
         break;
     default: {
@@ -1135,6 +1161,7 @@ static int spmv_dispatch(int kernel_id, const seer_csr *A, const float *x, float
         if (!workspace || !aligned16(workspace) || workspace_bytes < mp_workspace_bytes(A->rows, A->nnz, ipt))
             return SEER_EWORKSPACE;
         a.ranges.ticks = gather_ticks(a.ranges, A->nnz, mp_entries(A->rows, A->nnz, ipt));
+        a.meet = meet_at(workspace, workspace_bytes, A->rows, A->nnz, mp_num_tiles(A->rows, A->nnz, ipt));
         launch_mp(a, ipt, vec, workspace, st);
         break;
     }

@@ -9,9 +9,9 @@
 //      preprocessing; every workgroup reads the chosen id and runs that schedule's
 //      body (the grid is sized for the reachable schedule that needs the most workgroups,
 //      the rest exit);
-//   3. spmv_auto_fixup_kernel: the carry fix-up of merge path and of the nonzero
-//      split; exits at once unless one of them was chosen, and is not enqueued at all if
-//      the host can tell from rows, cols and nnz that the tree cannot answer either.
+//   3. from 2^23 nonzeros on (below, cut rows meet inside the product: Meet) spmv_auto_fixup_kernel: the carry
+//      fix-up of merge path and of the nonzero split; exits at once unless one of them was chosen, and is not enqueued
+//      at all if the host can tell from rows, cols and nnz that the tree cannot answer either.
 // When the product's grid is small, steps 1 and 2 share a launch (or, for a small
 // matrix, are one launch): see spmv_auto_fused_kernel.  When the known features leave the
 // tree a single answer, step 1 is dropped: see spmv_auto_decided_kernel.
@@ -310,11 +310,12 @@ __device__ __forceinline__ void auto_dispatch(
         else
             wo_body<kWoChunk, VEC, true, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile,
                                                  reinterpret_cast<float *>(smem),
-                                                 reinterpret_cast<uint32_t *>(smem) + bm_lds_words<kWoChunk>(), shape.ranges);
+                                                 reinterpret_cast<uint32_t *>(smem) + bm_lds_words<kWoChunk>(), shape.ranges, nullptr,
+                                                 shape.meet);
     } else {
         GatherRanges g = shape.ranges;
         g.ticks = shape.mp_ticks;
-        mp_body<IPT, VEC, true, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile, smem, g);
+        mp_body<IPT, VEC, true, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile, smem, g, shape.meet);
     }
 }
 
@@ -407,6 +408,15 @@ size_t auto_workspace_bytes(int rows, int nnz)
     return kAutoCarryOffset + (mp > wo ? mp : wo);
 }
 
+size_t auto_meet_workspace_bytes(int rows, int nnz)
+{
+    const size_t least = auto_workspace_bytes(rows, nnz);
+    if (!meet_applies(rows, nnz)) return least;
+    const uint32_t mp = mp_num_tiles(rows, nnz, kMpIptSmall), wo = wo_num_tiles(rows, nnz);
+    const size_t meet = kAutoCarryOffset + meet_workspace_bytes(mp > wo ? mp : wo);
+    return meet > least ? meet : least;
+}
+
 // The first pass ahead of a product that selects for itself: at most kAutoFusedParts
 // partials, sixteen rows (four 16-byte loads in flight) per lane and trip; workgroups of
 // 1024 lanes once 256-lane ones would need more than one trip.
@@ -466,9 +476,9 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
         const uint32_t g = wm_grid < cap ? wm_grid : cap;
         grid = g > grid ? g : grid;
     }
-    // The fix-up launch finds nothing to do unless merge path or the nonzero split ran: it
-    // is only enqueued if the tree can get to one of them from what the host knows.
-    const bool carries = reachable(SEER_CSR_MP) || reachable(SEER_CSR_WO);
+    // The fix-up launch is only enqueued where cut rows do not meet inside the product.  It finds nothing to do unless merge path
+    // or the nonzero split ran: it is left out, too, if the tree cannot get to one of them from what the host knows.
+    const bool carries = !shape.meet.slots && (reachable(SEER_CSR_MP) || reachable(SEER_CSR_WO));
 
     if (decided) {
         if (long_workspace && decided->kernel_id == SEER_CSR_WO) shape.skip = launch_long(a, nullptr, long_workspace, st);

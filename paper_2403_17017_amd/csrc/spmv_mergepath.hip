@@ -8,12 +8,13 @@ template <int IPT, bool VEC, bool NT, bool RANGED = false>
 __global__ __launch_bounds__(kWG) void spmv_mp_kernel(
     int rows, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
-    int *__restrict__ carry_row, float *__restrict__ carry_val, uint32_t n_tiles, int remap, const GatherRanges g)
+    int *__restrict__ carry_row, float *__restrict__ carry_val, uint32_t n_tiles, int remap, const GatherRanges g,
+    const Meet meet)
 {
     __shared__ int smem[mp_lds_words<IPT>()];
     const uint32_t tile = tile_of_block(blockIdx.x, n_tiles, remap);
     if (tile >= n_tiles) return;
-    mp_body<IPT, VEC, NT, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile, smem, g);
+    mp_body<IPT, VEC, NT, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile, smem, g, meet);
 }
 
 __global__ __launch_bounds__(kWG) void spmv_mp_fixup_kernel(
@@ -53,7 +54,7 @@ static void launch_mp_ipt(const SpmvArgs &a, bool vec, void *workspace, hipStrea
     const dim3 grid(a.remap ? tiles_per_xcd(n_tiles) * kXCD : n_tiles);
 #define SEER_MP_LAUNCH(...)                                                                             \
     hipLaunchKernelGGL((spmv_mp_kernel<IPT, __VA_ARGS__>), grid, dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, a.va, \
-                       a.x, a.y, carry_row, carry_val, n_tiles, a.remap, a.ranges)
+                       a.x, a.y, carry_row, carry_val, n_tiles, a.remap, a.ranges, a.meet)
     if (a.ranges.count) {
         if (a.nt) SEER_MP_LAUNCH(true, true, true); else SEER_MP_LAUNCH(true, false, true);
     } else if (vec) {
@@ -62,7 +63,7 @@ static void launch_mp_ipt(const SpmvArgs &a, bool vec, void *workspace, hipStrea
         if (a.nt) SEER_MP_LAUNCH(false, true); else SEER_MP_LAUNCH(false, false);
     }
 #undef SEER_MP_LAUNCH
-    launch_carry_fixup(a.rows, n_tiles, carry_row, carry_val, a.y, st);
+    if (!a.meet.slots) launch_carry_fixup(a.rows, n_tiles, carry_row, carry_val, a.y, st);
 }
 
 void launch_mp(const SpmvArgs &a, int ipt, bool vec, void *workspace, hipStream_t st)

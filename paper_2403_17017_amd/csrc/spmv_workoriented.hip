@@ -1,6 +1,6 @@
 // Stand-alone kernel and launcher of CSR,WO (work oriented, equal shares of nonzeros);
-// the device code and the description of the split are in spmv_bodies.hiph.  The carries
-// of rows cut by a chunk boundary are added to y by the same fix-up kernel as CSR,MP's.
+// the device code and the description of the split are in spmv_bodies.hiph.  The parts of rows cut by a
+// chunk boundary meet inside the product, or go out as carries for the same fix-up kernel as CSR,MP's.
 #include "spmv_bodies.hiph"
 
 namespace seer {
@@ -10,13 +10,13 @@ __global__ __launch_bounds__(kWG) void spmv_wo_kernel(
     int rows, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
     int *__restrict__ carry_row, float *__restrict__ carry_val, uint32_t n_tiles, int remap, const GatherRanges g,
-    const LongSkip *__restrict__ skip)
+    const LongSkip *__restrict__ skip, const Meet meet)
 {
     __shared__ __attribute__((aligned(16))) float s_prod[bm_lds_words<CH>()];
     __shared__ uint32_t s_bounds[2];
     const uint32_t tile = tile_of_block(blockIdx.x, n_tiles, remap);
     if (tile >= n_tiles) return;
-    wo_body<CH, VEC, NT, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile, s_prod, s_bounds, g, skip);
+    wo_body<CH, VEC, NT, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile, s_prod, s_bounds, g, skip, meet);
 }
 
 uint32_t wo_num_tiles(int rows, int nnz)
@@ -44,7 +44,7 @@ void launch_wo(const SpmvArgs &a, bool vec, void *workspace, hipStream_t st)
     const dim3 grid(a.remap ? tiles_per_xcd(n_tiles) * kXCD : n_tiles);
 #define SEER_WO_LAUNCH(C, ...)                                                                                 \
     hipLaunchKernelGGL((spmv_wo_kernel<C, __VA_ARGS__>), grid, dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, a.va, \
-                       a.x, a.y, carry_row, carry_val, n_tiles, a.remap, a.ranges, a.skip)
+                       a.x, a.y, carry_row, carry_val, n_tiles, a.remap, a.ranges, a.skip, a.meet)
 #define SEER_WO_PICK(C)                                                                     \
     if (a.ranges.count) {                                                                   \
         if (a.nt) SEER_WO_LAUNCH(C, true, true, true); else SEER_WO_LAUNCH(C, true, false, true); \
@@ -56,7 +56,7 @@ void launch_wo(const SpmvArgs &a, bool vec, void *workspace, hipStream_t st)
     if (wo_chunk_of(a.nnz) == kWoChunkLarge) { SEER_WO_PICK(kWoChunkLarge) } else { SEER_WO_PICK(kWoChunk) }
 #undef SEER_WO_PICK
 #undef SEER_WO_LAUNCH
-    launch_carry_fixup(a.rows, n_tiles, carry_row, carry_val, a.y, st);
+    if (!a.meet.slots) launch_carry_fixup(a.rows, n_tiles, carry_row, carry_val, a.y, st);
 }
 
 } // namespace seer
