@@ -29,6 +29,14 @@ struct GatherRanges {
 // (kLongWhole: all of them, and the row goes on) and the last `tail`.
 struct LongSkip { uint16_t head, tail; };
 constexpr uint16_t kLongWhole = 0x8000u;
+// What CSR,WO is told of them: a word per chunk (null: no entry is left out), and, if there are such rows, the chunks that
+// have something left and the ticks of the gather ranges, whose turn lasts as long as that needs.
+struct LongNumbers { uint32_t n[3], all, ticks, active; };     // rows of each class, all of them; as above; how many chunks
+struct LongStage {
+    const LongSkip *skip = nullptr;
+    const LongNumbers *numbers = nullptr;
+    const uint32_t *active = nullptr;
+};
 
 // Where the parts of a row that a tile boundary cuts meet (meet_row): a slot of 64 bytes per boundary, slots null:
 // the parts go out as carries.  The marks are the process's own.
@@ -46,7 +54,7 @@ struct SpmvArgs {
     int remap;  // 1: tiles laid out contiguously per XCD
     int nt;     // 1: matrix streams are loaded with the non-temporal hint (keeps x in L2)
     GatherRanges ranges = GatherRanges{};   // count > 0 only where the 16-byte loads are used, too
-    const LongSkip *skip = nullptr;         // CSR,WO with ranges only; null: no entry is left out
+    LongStage longs = LongStage{};          // CSR,WO with ranges only
     Meet meet = Meet{};                     // CSR,MP and CSR,WO: only where meet_applies()
 };
 
@@ -181,11 +189,12 @@ struct AutoSel {                            // what the selection leaves in the 
     float f[SEER_NUM_FEATURES];
 };
 // The long rows of CSR,WO with slabs of x in LDS.  sel: null, or the selection (nothing is done unless it says
-// CSR,WO).  Returns the words for the chunks of CSR,WO (of kWoChunkLarge entries), which lie in the workspace.
+// CSR,WO).  What CSR,WO (chunks of kWoChunkLarge entries) is told lies in the workspace; chunks that have nothing left get the
+// carry of a chunk that cuts no row (carry_row).
 bool long_rows_fit(int rows);                           // rows the stage can list
 size_t long_workspace_bytes(int rows, int cols, int nnz);
 size_t long_workspace_most(int rows, int nnz);          // for any number of columns
-const LongSkip *launch_long(const SpmvArgs &a, const AutoSel *sel, void *workspace, hipStream_t st);
+LongStage launch_long(const SpmvArgs &a, const AutoSel *sel, int *carry_row, void *workspace, hipStream_t st);
 
 struct AutoShape {                          // launch shapes, all from rows and nnz alone
     uint32_t tiles[SEER_NUM_DIRECT_KERNELS];
@@ -194,7 +203,7 @@ struct AutoShape {                          // launch shapes, all from rows and 
     int tm_pair;                            // ... and takes two rows per lane (tiles of 512 rows)
     int tm_remap;                           // CSR,TM's tile order: 1 XCD-contiguous, 0 round-robin
     GatherRanges ranges;                    // as in SpmvArgs; ticks: CSR,WO's
-    const LongSkip *skip;                   // as in SpmvArgs
+    LongStage longs;                        // as in SpmvArgs
     Meet meet;                              // as in SpmvArgs
     uint32_t bm_ticks, mp_ticks;
     int bm_ranged;                          // CSR,BM orders its gathers, too

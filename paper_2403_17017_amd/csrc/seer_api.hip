@@ -863,7 +863,7 @@ static int auto_enqueue(const seer_csr *A, const seer_tree *tree, const float *x
     sh.tiles[SEER_CSR_MP] = mp_num_tiles(A->rows, A->nnz, sh.mp_ipt);
     sh.tiles[SEER_CSR_WO] = wo_num_tiles(A->rows, A->nnz);
     SpmvArgs a{A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, x, y, use_remap(), 1};
-    sh.skip = nullptr;
+    sh.longs = LongStage{};
     void *long_ws = nullptr;            // behind the rest, where there is room
     const size_t before_long = auto_workspace_bytes(A->rows, A->nnz);
     if (sh.ranges.count && long_rows(A->rows, A->nnz) && workspace_bytes >= before_long &&
@@ -872,6 +872,7 @@ static int auto_enqueue(const seer_csr *A, const seer_tree *tree, const float *x
     sh.meet = meet_at(static_cast<char *>(workspace) + kAutoCarryOffset, workspace_bytes - kAutoCarryOffset, A->rows, A->nnz,
                       std::max(sh.tiles[SEER_CSR_MP], sh.tiles[SEER_CSR_WO]));
     sh.ranges.ticks = gather_ticks(sh.ranges, A->nnz, wo_entries(A->nnz));
+    a.ranges = sh.ranges;
     sh.bm_ticks = gather_ticks(sh.ranges, A->nnz, bm_entries(A->rows, A->nnz, sh.bm_rows));
     sh.mp_ticks = gather_ticks(sh.ranges, A->nnz, mp_entries(A->rows, A->nnz, sh.mp_ipt));
     // What the host knows without looking at the matrix prunes the tree: the grid is sized
@@ -1151,7 +1152,7 @@ static int spmv_dispatch(int kernel_id, const seer_csr *A, const float *x, float
         if (a.ranges.count && long_rows(A->rows, A->nnz)) {
             const size_t before = carry_workspace_bytes(wo_num_tiles(A->rows, A->nnz));      // (a multiple of 512)
             if (workspace_bytes - before >= long_workspace_bytes(A->rows, A->cols, A->nnz))
-                a.skip = launch_long(a, nullptr, static_cast<char *>(workspace) + before, st);
+                a.longs = launch_long(a, nullptr, static_cast<int *>(workspace), static_cast<char *>(workspace) + before, st);
         }
         a.meet = meet_at(workspace, workspace_bytes, A->rows, A->nnz, wo_num_tiles(A->rows, A->nnz));
         launch_wo(a, vec, workspace, st);

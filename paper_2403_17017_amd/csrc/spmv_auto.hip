@@ -277,6 +277,14 @@ __device__ __forceinline__ void auto_dispatch(
         }
         return;
     }
+    if constexpr (RANGED) {
+        if (k == SEER_CSR_WO && shape.longs.skip) {      // (from 2^23 nonzeros on: the larger chunks)
+            static_assert(bm_lds_words<kWoChunkLarge>() + 2 <= kAutoLds, "LDS overlay too small");
+            wo_long_body<VEC, true>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, n_tiles, remap, reinterpret_cast<float *>(smem),
+                                    reinterpret_cast<uint32_t *>(smem) + bm_lds_words<kWoChunkLarge>(), shape.ranges, shape.longs);
+            return;
+        }
+    }
     const uint32_t tile = tile_of_block(blockIdx.x, n_tiles, k == SEER_CSR_TM ? (remap && shape.tm_remap) : remap);
     if (tile >= n_tiles) return;
     if (k == SEER_CSR_TM) {
@@ -306,12 +314,11 @@ __device__ __forceinline__ void auto_dispatch(
             wo_body<kWoChunkLarge, VEC, true, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile,
                                                       reinterpret_cast<float *>(smem),
                                                       reinterpret_cast<uint32_t *>(smem) + bm_lds_words<kWoChunkLarge>(),
-                                                      shape.ranges, shape.skip);
+                                                      shape.ranges);
         else
             wo_body<kWoChunk, VEC, true, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile,
                                                  reinterpret_cast<float *>(smem),
-                                                 reinterpret_cast<uint32_t *>(smem) + bm_lds_words<kWoChunk>(), shape.ranges, nullptr,
-                                                 shape.meet);
+                                                 reinterpret_cast<uint32_t *>(smem) + bm_lds_words<kWoChunk>(), shape.ranges, shape.meet);
     } else {
         GatherRanges g = shape.ranges;
         g.ticks = shape.mp_ticks;
@@ -481,7 +488,7 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
     const bool carries = !shape.meet.slots && (reachable(SEER_CSR_MP) || reachable(SEER_CSR_WO));
 
     if (decided) {
-        if (long_workspace && decided->kernel_id == SEER_CSR_WO) shape.skip = launch_long(a, nullptr, long_workspace, st);
+        if (long_workspace && decided->kernel_id == SEER_CSR_WO) shape.longs = launch_long(a, nullptr, carry_row, long_workspace, st);
 #define SEER_DECIDED_LAUNCH(...)                                                                           \
     hipLaunchKernelGGL((spmv_auto_decided_kernel<__VA_ARGS__>), dim3(grid), dim3(kWG), 0, st, a.rows, a.nnz, a.rp, \
                        a.ci, a.va, a.x, a.y, carry_row, carry_val, sel, *decided, shape, a.remap)
@@ -547,7 +554,7 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
 #undef SEER_WAVE_LAUNCH
 #undef SEER_SELECT_LAUNCH
 
-    if (long_workspace && reachable(SEER_CSR_WO)) shape.skip = launch_long(a, sel, long_workspace, st);
+    if (long_workspace && reachable(SEER_CSR_WO)) shape.longs = launch_long(a, sel, carry_row, long_workspace, st);
 #define SEER_AUTO_LAUNCH(...)                                                                              \
     hipLaunchKernelGGL((spmv_auto_kernel<__VA_ARGS__>), dim3(grid), dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, \
                        a.va, a.x, a.y, carry_row, carry_val, sel, shape, a.remap)

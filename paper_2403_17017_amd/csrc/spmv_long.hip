@@ -13,9 +13,11 @@
 // The cuts are right for any order of columns: a cut is a place in the row, cuts never descend
 // (each is raised to the ones before it), and an entry whose column lies outside the slab of its piece
 // is gathered from x.
-// 471 M nonzeros, Zipf s = 1.6: list 10 us, cuts 79, products 664 (five sixths of the nonzeros, read at 4.8 TB/s),
-// sums 7, CSR,WO over the rest 480; all of them by CSR,WO 2370.  Tried: rows from 16 entries per slab on, the same
-// with twice the scratch memory; a wave per piece from 128 entries on, 1289 in all against 1255.
+// 472 M nonzeros, Zipf s = 1.6: list 14 us, cuts 80, products 674 (nine tenths of the nonzeros, read at 5.0 TB/s),
+// sums 7, CSR,WO over the rest 415; all of them by CSR,WO 2370.  Tried: rows from 16 entries per slab on, the same
+// with twice the scratch memory; a wave per piece from 128 entries on, 1289 in all against 1255 at the time.
+// CSR,WO over the rest took 513 while every chunk had a workgroup, to find nothing in four of five, and its gather
+// ranges lasted as long as full chunks need.
 #include "spmv_bodies.hiph"
 
 namespace seer {
@@ -24,6 +26,7 @@ constexpr uint32_t kLongShift = 15;
 constexpr uint32_t kLongCols = 1u << kLongShift;    // columns per slab: 128 KB of LDS
 constexpr uint32_t kLongWG = 1024;
 constexpr uint32_t kLongGrid = 256;                 // workgroups of long_multiply_kernel: one per CU
+constexpr uint32_t kLongCutGrid = 512;              // ... of long_cut_kernel: two per CU
 constexpr uint32_t kLongRows = 4096;                // rows per workgroup of long_list_kernel
 // Rows by the length of their pieces: 8 lanes, 16 lanes and a wave take a piece of class 0 (32 entries on
 // average and more), 1 (64) and 2 (256).
@@ -39,99 +42,122 @@ static uint32_t long_slabs(int cols) { return ((uint32_t)cols + kLongCols - 1u) 
 // counted by atomics (a list per class filled that way took 13 us and a launch to clear its counters, 2 M rows; this 9).
 __host__ __device__ inline uint32_t long_part(uint32_t nnz_before, uint32_t least, uint32_t part) { return nnz_before / least + part; }
 
+struct LongPart { uint32_t n[kLongClasses], first, entries, whole, pad[2]; };   // rows of each class, where they lie in the list;
+                                                                                // their entries and the chunks that hold nothing else
+static_assert(sizeof(LongPart) == 32, "two 16-byte loads");
+
 __global__ __launch_bounds__(kWG) void long_list_kernel(
     int rows, uint32_t cols, uint32_t n_slabs, const int *__restrict__ rp, const int *__restrict__ ci,
-    uint32_t *__restrict__ counts /* [parts][4]: rows of each class, where the part begins */, LongRow *__restrict__ list,
-    uint32_t *__restrict__ skip_words, uint32_t n_skip, const AutoSel *__restrict__ sel)
+    LongPart *__restrict__ parts, LongRow *__restrict__ list, LongNumbers *__restrict__ numbers, uint32_t *__restrict__ skip_words,
+    uint32_t n_skip, const AutoSel *__restrict__ sel)
 {
-    __shared__ uint32_t s_row[kLongRows], s_n, s_class[kLongClasses];
+    // a row found: its place in the part, later its class and its number in that class, too
+    constexpr uint32_t kClassAt = 12, kNumberAt = 14;
+    static_assert(kLongRows == 1u << kClassAt && kLongClasses < 4u, "12 + 2 + 13 bits");
+    __shared__ uint32_t s_row[kLongRows], s_n, s_class[kLongClasses], s_entries, s_whole;
     if (sel && sel->kernel_id != SEER_CSR_WO) return;
     const uint32_t r0 = blockIdx.x * kLongRows, tid = threadIdx.x, r1 = min(r0 + kLongRows, (uint32_t)rows);
-    if (tid == 0) s_n = 0;
+    if (tid == 0) s_n = s_entries = s_whole = 0;
+    if (blockIdx.x == 0 && tid == 0) numbers->active = 0;       // (long_multiply_kernel counts them)
     if (tid < kLongClasses) s_class[tid] = 0;
     for (uint32_t i = blockIdx.x * kWG + tid; i < n_skip; i += gridDim.x * kWG) skip_words[i] = 0;
     __syncthreads();
     const uint32_t least = long_class_piece(0) * n_slabs;
 #pragma unroll 8
     for (uint32_t i = 0; i < kLongRows / kWG; ++i) {
-        const uint32_t r = r0 + i * kWG + tid, rc = min(r, r1 - 1u);
+        const uint32_t at = i * kWG + tid, rc = min(r0 + at, r1 - 1u);
         const uint32_t a = (uint32_t)rp[rc], e = (uint32_t)rp[rc + 1u];
-        if (r < r1 && e - a >= least && a / kWoChunkLarge != (e - 1u) / kWoChunkLarge) s_row[atomicAdd(&s_n, 1u)] = r;
+        if (r0 + at < r1 && e - a >= least && a / kWoChunkLarge != (e - 1u) / kWoChunkLarge) s_row[atomicAdd(&s_n, 1u)] = at;
     }
     __syncthreads();
     const uint32_t n = s_n;
-    const uint32_t first = long_part(r0 < r1 ? (uint32_t)rp[r0] : 0u, least, blockIdx.x);
-    // two looks at the rows found: how many of each class, then each into its class's place
-    for (uint32_t look = 0; look < 2; ++look) {
-        uint32_t at[kLongClasses] = {0, s_class[0], s_class[0] + s_class[1]};
-        if (look == 1 && tid == 0)
-            *reinterpret_cast<uint4 *>(counts + 4u * blockIdx.x) = make_uint4(s_class[0], s_class[1], s_class[2], first);
-        __syncthreads();                                        // (all lanes have read s_class)
-        if (look == 1 && tid < kLongClasses) s_class[tid] = 0;
-        __syncthreads();
-        for (uint32_t i = tid; i < n; i += kWG) {
-            const uint32_t row = s_row[i], a = (uint32_t)rp[row], e = (uint32_t)rp[row + 1], len = e - a;
-            bool spread = true;
+    for (uint32_t i = tid; i < n; i += kWG) {
+        const uint32_t at = s_row[i], a = (uint32_t)rp[r0 + at], e = (uint32_t)rp[r0 + at + 1u], len = e - a;
+        bool spread = true;
 #pragma unroll
-            for (uint32_t q = 1; q < 4; ++q) {
-                const int64_t want = (int64_t)(cols / 4u) * q, got = ci[a + (uint32_t)((uint64_t)len * q / 4u)];
-                spread = spread && (got > want ? got - want : want - got) <= (int64_t)(cols / 16u);
-            }
-            if (!spread) continue;
-            const uint32_t k = len >= long_class_piece(2) * n_slabs ? 2u : len >= long_class_piece(1) * n_slabs ? 1u : 0u;
-            const uint32_t j = atomicAdd(&s_class[k], 1u);
-            if (look == 1) list[first + at[k] + j] = LongRow{row, a, e, 0u};
+        for (uint32_t q = 1; q < 4; ++q) {
+            const int64_t want = (int64_t)(cols / 4u) * q, got = ci[a + (uint32_t)((uint64_t)len * q / 4u)];
+            spread = spread && (got > want ? got - want : want - got) <= (int64_t)(cols / 16u);
         }
-        __syncthreads();
+        uint32_t k = kLongClasses, j = 0;
+        if (spread) {
+            k = len >= long_class_piece(2) * n_slabs ? 2u : len >= long_class_piece(1) * n_slabs ? 1u : 0u;
+            j = atomicAdd(&s_class[k], 1u);
+            atomicAdd(&s_entries, len);
+            atomicAdd(&s_whole, (e - 1u) / kWoChunkLarge - a / kWoChunkLarge - 1u);
+        }
+        s_row[i] = at | k << kClassAt | j << kNumberAt;
+    }
+    __syncthreads();
+    const uint32_t first = long_part(r0 < r1 ? (uint32_t)rp[r0] : 0u, least, blockIdx.x);
+    if (tid == 0) parts[blockIdx.x] = LongPart{{s_class[0], s_class[1], s_class[2]}, first, s_entries, s_whole, {0, 0}};
+    for (uint32_t i = tid; i < n; i += kWG) {
+        const uint32_t w = s_row[i], k = w >> kClassAt & 3u, row = r0 + (w & (kLongRows - 1u));
+        if (k == kLongClasses) continue;
+        const uint32_t before = (k > 0u ? s_class[0] : 0u) + (k > 1u ? s_class[1] : 0u);
+        list[first + before + (w >> kNumberAt)] = LongRow{row, (uint32_t)rp[row], (uint32_t)rp[row + 1u], 0u};
     }
 }
 
 // ---- 2: the cuts.  The parts of the list, class by class, make one order of all long rows: number j of the
 // first part's class 0 row, then the next part's ..., then class 1, class 2.  Every workgroup finds
-// the parts' first numbers for itself (s_from).  Returns N, the number of long rows.  kWG lanes; parts > 0.
+// the parts' first numbers for itself (s_from).  Returns N, the number of long rows, and their entries and whole
+// chunks.  kLongWG lanes; parts > 0.
+constexpr uint32_t kLongWaves = kLongWG / kWave, kLongSums = (kLongClasses + 2u) * kLongWaves;
 constexpr uint32_t kLongParts = 1024;                // of the list, at most: 4 M rows (long_rows_fit)
 __device__ __forceinline__ uint32_t long_numbers(
-    uint32_t parts, const uint32_t *__restrict__ counts, uint32_t *s_from /* LDS [kLongClasses * parts + 1] */,
-    uint32_t *s_w /* LDS [kWG / kWave] */, uint32_t *s_n /* LDS [kLongClasses]: rows of each class */)
+    uint32_t parts, const LongPart *__restrict__ of, uint32_t *s_from /* LDS [kLongClasses * parts + 1] */,
+    uint32_t *s_w /* LDS [kLongSums] */, uint32_t *s_n /* LDS [kLongClasses]: rows of each class */,
+    uint32_t &entries, uint32_t &whole)
 {
-    constexpr uint32_t E = kLongParts / kWG;
+    constexpr uint32_t E = kLongParts / kLongWG;
     const uint32_t tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-    uint4 c[E];                                                  // of consecutive parts, all fetched at once
+    LongPart c[E];                                               // of consecutive parts, all fetched at once
 #pragma unroll
     for (uint32_t i = 0; i < E; ++i) {
-        const uint32_t p = min(tid * E + i, parts - 1u);
-        c[i] = *reinterpret_cast<const uint4 *>(counts + 4u * p);
-        if (tid * E + i >= parts) c[i] = make_uint4(0, 0, 0, 0);
+        c[i] = of[min(tid * E + i, parts - 1u)];
+        if (tid * E + i >= parts) c[i] = LongPart{};
     }
-    uint32_t run = 0;
+    constexpr uint32_t K = kLongClasses + 2u;                    // (the last two: sums only)
+    uint32_t v[K][E], incl[K], sum[K];
 #pragma unroll
-    for (uint32_t k = 0; k < kLongClasses; ++k) {
-        uint32_t v[E], sum = 0;
+    for (uint32_t k = 0; k < K; ++k) {
+        sum[k] = 0;
 #pragma unroll
         for (uint32_t i = 0; i < E; ++i) {
-            v[i] = sum;
-            sum += k == 0 ? c[i].x : k == 1 ? c[i].y : c[i].z;
+            v[k][i] = sum[k];
+            sum[k] += k < kLongClasses ? c[i].n[k] : k == kLongClasses ? c[i].entries : c[i].whole;
         }
-        uint32_t incl = sum;
+        incl[k] = sum[k];
 #pragma unroll
         for (int off = 1; off < kWave; off <<= 1) {
-            const uint32_t up = (uint32_t)__shfl_up((int)incl, off);
-            if ((int)lane >= off) incl += up;
+            const uint32_t up = (uint32_t)__shfl_up((int)incl[k], off);
+            if ((int)lane >= off) incl[k] += up;
         }
-        if (lane == kWave - 1) s_w[wave] = incl;
-        __syncthreads();
-        uint32_t before = run + incl - sum, all = 0;
+        if (lane == kWave - 1) s_w[k * kLongWaves + wave] = incl[k];
+    }
+    __syncthreads();
+    uint32_t run = 0;
 #pragma unroll
-        for (uint32_t w = 0; w < kWG / kWave; ++w) {
-            before += w < wave ? s_w[w] : 0u;
-            all += s_w[w];
+    for (uint32_t k = 0; k < K; ++k) {
+        uint32_t before = run + incl[k] - sum[k], all = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < kLongWaves; ++w) {
+            const uint32_t of_wave = s_w[k * kLongWaves + w];
+            before += w < wave ? of_wave : 0u;
+            all += of_wave;
         }
+        if (k < kLongClasses) {
 #pragma unroll
-        for (uint32_t i = 0; i < E; ++i)
-            if (tid * E + i < parts) s_from[k * parts + tid * E + i] = before + v[i];
-        if (tid == 0) s_n[k] = all;
-        run += all;
-        __syncthreads();
+            for (uint32_t i = 0; i < E; ++i)
+                if (tid * E + i < parts) s_from[k * parts + tid * E + i] = before + v[k][i];
+            if (tid == 0) s_n[k] = all;
+            run += all;
+        } else if (k == kLongClasses) {
+            entries = all;
+        } else {
+            whole = all;
+        }
     }
     if (tid == 0) s_from[kLongClasses * parts] = run;
     __syncthreads();
@@ -142,26 +168,33 @@ __device__ __forceinline__ uint32_t long_numbers(
 // column would be if the row's columns were spread evenly, comes nearer twice by the distance of the column
 // found, then widens in steps that double; every one ends at the row's ends at the latest.  The words per
 // chunk are set here, too, and the rows listed by number for the last pass.
-__global__ __launch_bounds__(kWG) void long_cut_kernel(
-    uint32_t cols, uint32_t n_slabs, uint32_t parts, const int *__restrict__ ci, const uint32_t *__restrict__ counts,
-    const LongRow *__restrict__ list, uint32_t *__restrict__ numbers /* [4]: rows of each class, all */,
-    uint32_t *__restrict__ rows_by_number, uint32_t *__restrict__ cut, LongSkip *__restrict__ skip, const AutoSel *__restrict__ sel)
+__global__ __launch_bounds__(kLongWG) void long_cut_kernel(
+    uint32_t cols, uint32_t nnz, uint32_t n_slabs, uint32_t parts, const int *__restrict__ ci, const LongPart *__restrict__ of,
+    const LongRow *__restrict__ list, LongNumbers *__restrict__ numbers, uint32_t ticks, uint32_t *__restrict__ rows_by_number,
+    uint32_t *__restrict__ cut, LongSkip *__restrict__ skip, const AutoSel *__restrict__ sel)
 {
-    __shared__ uint32_t s_from[kLongClasses * kLongParts + 1], s_w[kWG / kWave], s_n[kLongClasses];
+    __shared__ uint32_t s_from[kLongClasses * kLongParts + 1], s_w[kLongSums], s_n[kLongClasses];
     if (sel && sel->kernel_id != SEER_CSR_WO) return;
-    const uint32_t N = long_numbers(parts, counts, s_from, s_w, s_n);
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-        *reinterpret_cast<uint4 *>(numbers) = make_uint4(s_n[0], s_n[1], s_n[2], N);
-    const uint32_t lane = threadIdx.x % kWave, waves = gridDim.x * (kWG / kWave);
-    for (uint32_t j = blockIdx.x * (kWG / kWave) + threadIdx.x / kWave; j < N; j += waves) {
+    uint32_t entries = 0, whole = 0;
+    const uint32_t N = long_numbers(parts, of, s_from, s_w, s_n, entries, whole);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        for (uint32_t k = 0; k < kLongClasses; ++k) numbers->n[k] = s_n[k];
+        numbers->all = N;
+        // A turn over the ranges has to last as long as the gathers under way take, and the chunks of CSR,WO that have something
+        // left are no longer full (Zipf, s = 1.6: 24 000 of 119 000, of 4096 entries 2000).
+        const uint32_t chunks = (nnz + kWoChunkLarge - 1u) / kWoChunkLarge, left = max(chunks - min(whole, chunks), 1u);
+        numbers->ticks = max((uint32_t)((uint64_t)ticks * (nnz - entries) / ((uint64_t)left * kWoChunkLarge)), 1u);
+    }
+    const uint32_t lane = threadIdx.x % kWave, waves = gridDim.x * kLongWaves;
+    for (uint32_t j = blockIdx.x + threadIdx.x / kWave * gridDim.x; j < N; j += waves) {      // (few rows: on all CUs)
         uint32_t lo_f = 0, hi_f = kLongClasses * parts;         // the last part whose first number is at most j
         while (lo_f + 1u < hi_f) {
             const uint32_t mid = (lo_f + hi_f) / 2u;
             if (s_from[mid] <= j) lo_f = mid; else hi_f = mid;
         }
         const uint32_t k = lo_f / parts, part = lo_f - k * parts;
-        const uint4 c4 = *reinterpret_cast<const uint4 *>(counts + 4u * part);
-        const LongRow r = list[c4.w + (k > 0u ? c4.x : 0u) + (k > 1u ? c4.y : 0u) + (j - s_from[lo_f])];
+        const LongPart c = of[part];
+        const LongRow r = list[c.first + (k > 0u ? c.n[0] : 0u) + (k > 1u ? c.n[1] : 0u) + (j - s_from[lo_f])];
         const uint32_t len = r.end - r.start;
         if (lane == 0) rows_by_number[j] = r.row;
         {
@@ -288,15 +321,42 @@ __device__ __forceinline__ void long_pieces(
 }
 
 __global__ __launch_bounds__(kLongWG) void long_multiply_kernel(
-    uint32_t cols, uint32_t nnz, uint32_t n_slabs, uint32_t Q, const int *__restrict__ ci, const float *__restrict__ va,
-    const float *__restrict__ x, const uint32_t *__restrict__ numbers, const uint32_t *__restrict__ cut,
-    float *__restrict__ part, const AutoSel *__restrict__ sel)
+    int rows, uint32_t cols, uint32_t nnz, uint32_t n_slabs, uint32_t Q, const int *__restrict__ ci, const float *__restrict__ va,
+    const float *__restrict__ x, LongNumbers *__restrict__ numbers, const uint32_t *__restrict__ cut,
+    float *__restrict__ part, const LongSkip *__restrict__ skip, uint32_t chunks, uint32_t *__restrict__ active,
+    int *__restrict__ carry_row, const AutoSel *__restrict__ sel)
 {
     __shared__ __attribute__((aligned(16))) float s_x[kLongCols];
     if (sel && sel->kernel_id != SEER_CSR_WO) return;
-    const uint4 n = *reinterpret_cast<const uint4 *>(numbers);
-    const uint32_t N = n.w, tid = threadIdx.x;
+    const uint32_t n[kLongClasses] = {numbers->n[0], numbers->n[1], numbers->n[2]}, N = numbers->all, tid = threadIdx.x;
     if (N == 0) return;
+    // The chunks that have something left are listed, workgroup after workgroup as they come (which workgroup of CSR,WO takes
+    // a chunk does not show in y); one addition each to the common count, for these are served one after the other.
+    uint32_t *s_w = reinterpret_cast<uint32_t *>(s_x);
+    for (uint32_t c0 = blockIdx.x * kLongWG; c0 < chunks; c0 += gridDim.x * kLongWG) {
+        const uint32_t c = c0 + tid, lane = tid % kWave;
+        const bool in = c < chunks, whole = in && (skip[in ? c : 0u].head & kLongWhole) != 0;
+        const uint64_t left = __ballot(in && !whole);
+        if (lane == 0) s_w[tid / kWave] = (uint32_t)__popcll(left);
+        __syncthreads();
+        if (tid < kWave) {
+            const uint32_t mine = lane < kLongWaves ? s_w[lane] : 0u;
+            uint32_t incl = mine;
+#pragma unroll
+            for (int off = 1; off < kWave; off <<= 1) {
+                const uint32_t up = (uint32_t)__shfl_up((int)incl, off);
+                if ((int)lane >= off) incl += up;
+            }
+            uint32_t base = 0;
+            if (lane == kWave - 1) base = atomicAdd(&numbers->active, incl);
+            base = (uint32_t)__builtin_amdgcn_readlane((int)base, kWave - 1);
+            if (lane < kLongWaves) s_w[lane] = base + incl - mine;
+        }
+        __syncthreads();
+        if (whole) carry_row[c] = rows;
+        else if (in) active[s_w[tid / kWave] + (uint32_t)__popcll(left & ((1ull << lane) - 1ull))] = c;
+        __syncthreads();
+    }
     for (uint32_t task = tile_of_block(blockIdx.x, gridDim.x, 1); task < n_slabs * Q; task += gridDim.x) {
         const uint32_t s = task / Q, q = task - s * Q;
         const uint32_t c0 = s << kLongShift, nc = min(cols - c0, kLongCols);
@@ -320,19 +380,19 @@ __global__ __launch_bounds__(kLongWG) void long_multiply_kernel(
                 *reinterpret_cast<v4f *>(s_x + 4u * (m * kLongWG + tid)) = t[m];
         }
         __syncthreads();
-        long_pieces<64>(n.x + n.y, n.z, q, Q, N, s, c0, nc, nnz, ci, va, x, s_x, cut, part);
-        long_pieces<16>(n.x, n.y, q, Q, N, s, c0, nc, nnz, ci, va, x, s_x, cut, part);
-        long_pieces<8>(0u, n.x, q, Q, N, s, c0, nc, nnz, ci, va, x, s_x, cut, part);
+        long_pieces<64>(n[0] + n[1], n[2], q, Q, N, s, c0, nc, nnz, ci, va, x, s_x, cut, part);
+        long_pieces<16>(n[0], n[1], q, Q, N, s, c0, nc, nnz, ci, va, x, s_x, cut, part);
+        long_pieces<8>(0u, n[0], q, Q, N, s, c0, nc, nnz, ci, va, x, s_x, cut, part);
     }
 }
 
 // ---- 4: each long row's pieces, added up in slab order by eight sums.
 __global__ __launch_bounds__(kWG) void long_total_kernel(
-    uint32_t n_slabs, const uint32_t *__restrict__ numbers, const uint32_t *__restrict__ rows_by_number,
+    uint32_t n_slabs, const LongNumbers *__restrict__ numbers, const uint32_t *__restrict__ rows_by_number,
     const float *__restrict__ part, float *__restrict__ y, const AutoSel *__restrict__ sel)
 {
     if (sel && sel->kernel_id != SEER_CSR_WO) return;
-    const uint32_t N = numbers[3];
+    const uint32_t N = numbers->all;
     for (uint32_t j = blockIdx.x * kWG + threadIdx.x; j < N; j += gridDim.x * kWG) {
         float t[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         uint32_t s = 0;
@@ -348,7 +408,7 @@ __global__ __launch_bounds__(kWG) void long_total_kernel(
 // ------------------------------------------------------------------ host side
 static size_t pad256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-struct LongLayout { size_t numbers, counts, skip, list, rows, cut, part, total; uint32_t parts, skip_words; };
+struct LongLayout { size_t numbers, counts, skip, active, list, rows, cut, part, total; uint32_t parts, skip_words; };
 static LongLayout long_layout(int rows, uint32_t nnz, uint32_t n_slabs)
 {
     LongLayout L;
@@ -358,8 +418,9 @@ static LongLayout long_layout(int rows, uint32_t nnz, uint32_t n_slabs)
     L.parts = ((uint32_t)rows + kLongRows - 1) / kLongRows;
     L.skip_words = (uint32_t)(tiles * sizeof(LongSkip) / 4);
     L.numbers = o;   o += 256;
-    L.counts = o;    o += pad256((size_t)L.parts * 16);
+    L.counts = o;    o += pad256((size_t)L.parts * sizeof(LongPart));
     L.skip = o;      o += pad256((size_t)L.skip_words * 4);
+    L.active = o;    o += pad256(tiles * 4);
     L.list = o;      o += pad256((most + L.parts) * sizeof(LongRow));
     L.rows = o;      o += pad256(most * 4 + 4);
     L.cut = o;       o += pad256(((size_t)n_slabs + 1) * most * 4 + 4);
@@ -375,23 +436,25 @@ size_t long_workspace_bytes(int rows, int cols, int nnz) { return long_layout(ro
 size_t long_workspace_most(int rows, int nnz)
 {
     const size_t n = (size_t)nnz, parts = ((size_t)rows + kLongRows - 1) / kLongRows;
-    return 24 * (n / 64) + 8 * (n / 32) + (n / kWoChunkLarge + 1) * sizeof(LongSkip) + 32 * parts + 4096;
+    return 24 * (n / 64) + 8 * (n / 32) + (n / kWoChunkLarge + 1) * (sizeof(LongSkip) + 4) + 48 * parts + 4096;
 }
 
-const LongSkip *launch_long(const SpmvArgs &a, const AutoSel *sel, void *workspace, hipStream_t st)
+LongStage launch_long(const SpmvArgs &a, const AutoSel *sel, int *carry_row, void *workspace, hipStream_t st)
 {
     const uint32_t S = long_slabs(a.cols), nnz = (uint32_t)a.nnz;
     const LongLayout L = long_layout(a.rows, nnz, S);
     char *base = static_cast<char *>(workspace);
-    uint32_t *numbers = reinterpret_cast<uint32_t *>(base + L.numbers), *counts = reinterpret_cast<uint32_t *>(base + L.counts);
+    LongNumbers *numbers = reinterpret_cast<LongNumbers *>(base + L.numbers);
+    LongPart *of = reinterpret_cast<LongPart *>(base + L.counts);
     LongSkip *skip = reinterpret_cast<LongSkip *>(base + L.skip);
+    uint32_t *active = reinterpret_cast<uint32_t *>(base + L.active);
     LongRow *list = reinterpret_cast<LongRow *>(base + L.list);
     uint32_t *rows = reinterpret_cast<uint32_t *>(base + L.rows), *cut = reinterpret_cast<uint32_t *>(base + L.cut);
     float *part = reinterpret_cast<float *>(base + L.part);
-    hipLaunchKernelGGL(long_list_kernel, dim3(L.parts), dim3(kWG), 0, st, a.rows, (uint32_t)a.cols, S, a.rp, a.ci, counts, list,
-                       reinterpret_cast<uint32_t *>(skip), L.skip_words, sel);
-    hipLaunchKernelGGL(long_cut_kernel, dim3(2048), dim3(kWG), 0, st, (uint32_t)a.cols, S, L.parts, a.ci,
-                       static_cast<const uint32_t *>(counts), static_cast<const LongRow *>(list), numbers, rows, cut, skip, sel);
+    hipLaunchKernelGGL(long_list_kernel, dim3(L.parts), dim3(kWG), 0, st, a.rows, (uint32_t)a.cols, S, a.rp, a.ci, of, list,
+                       numbers, reinterpret_cast<uint32_t *>(skip), L.skip_words, sel);
+    hipLaunchKernelGGL(long_cut_kernel, dim3(kLongCutGrid), dim3(kLongWG), 0, st, (uint32_t)a.cols, nnz, S, L.parts, a.ci,
+                       static_cast<const LongPart *>(of), static_cast<const LongRow *>(list), numbers, a.ranges.ticks, rows, cut, skip, sel);
     // tasks per slab: so many that the tasks fill whole rounds of the grid best
     uint32_t Q = 1;
     double best = 0.0;
@@ -400,11 +463,12 @@ const LongSkip *launch_long(const SpmvArgs &a, const AutoSel *sel, void *workspa
         const double filled = (double)tasks / ((double)rounds * kLongGrid);
         if (rounds <= 4 && filled > best + 0.01) { best = filled; Q = q; }
     }
-    hipLaunchKernelGGL(long_multiply_kernel, dim3(kLongGrid), dim3(kLongWG), 0, st, (uint32_t)a.cols, nnz, S, Q, a.ci, a.va,
-                       a.x, static_cast<const uint32_t *>(numbers), static_cast<const uint32_t *>(cut), part, sel);
-    hipLaunchKernelGGL(long_total_kernel, dim3(256), dim3(kWG), 0, st, S, static_cast<const uint32_t *>(numbers),
+    hipLaunchKernelGGL(long_multiply_kernel, dim3(kLongGrid), dim3(kLongWG), 0, st, a.rows, (uint32_t)a.cols, nnz, S, Q, a.ci, a.va,
+                       a.x, numbers, static_cast<const uint32_t *>(cut), part, static_cast<const LongSkip *>(skip), L.skip_words, active,
+                       carry_row, sel);
+    hipLaunchKernelGGL(long_total_kernel, dim3(256), dim3(kWG), 0, st, S, static_cast<const LongNumbers *>(numbers),
                        static_cast<const uint32_t *>(rows), static_cast<const float *>(part), a.y, sel);
-    return skip;
+    return LongStage{skip, numbers, active};
 }
 
 } // namespace seer

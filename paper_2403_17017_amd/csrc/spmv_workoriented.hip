@@ -10,13 +10,26 @@ __global__ __launch_bounds__(kWG) void spmv_wo_kernel(
     int rows, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
     int *__restrict__ carry_row, float *__restrict__ carry_val, uint32_t n_tiles, int remap, const GatherRanges g,
-    const LongSkip *__restrict__ skip, const Meet meet)
+    const Meet meet)
 {
     __shared__ __attribute__((aligned(16))) float s_prod[bm_lds_words<CH>()];
     __shared__ uint32_t s_bounds[2];
     const uint32_t tile = tile_of_block(blockIdx.x, n_tiles, remap);
     if (tile >= n_tiles) return;
-    wo_body<CH, VEC, NT, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile, s_prod, s_bounds, g, skip, meet);
+    wo_body<CH, VEC, NT, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile, s_prod, s_bounds, g, meet);
+}
+
+// ... without the entries of long rows (spmv_long.hip)
+template <bool NT>
+__global__ __launch_bounds__(kWG, 8) void spmv_wo_long_kernel(
+    int rows, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
+    const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
+    int *__restrict__ carry_row, float *__restrict__ carry_val, uint32_t n_tiles, int remap, const GatherRanges g,
+    const LongStage longs)
+{
+    __shared__ __attribute__((aligned(16))) float s_prod[bm_lds_words<kWoChunkLarge>()];
+    __shared__ uint32_t s_bounds[2];
+    wo_long_body<true, NT>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, n_tiles, remap, s_prod, s_bounds, g, longs);
 }
 
 uint32_t wo_num_tiles(int rows, int nnz)
@@ -42,9 +55,18 @@ void launch_wo(const SpmvArgs &a, bool vec, void *workspace, hipStream_t st)
     int *carry_row = static_cast<int *>(workspace);
     float *carry_val = reinterpret_cast<float *>(static_cast<char *>(workspace) + one);
     const dim3 grid(a.remap ? tiles_per_xcd(n_tiles) * kXCD : n_tiles);
+    if (a.longs.skip) {
+        const dim3 some(grid.x < kWoLongGrid ? grid.x : kWoLongGrid);
+        if (a.nt) hipLaunchKernelGGL(spmv_wo_long_kernel<true>, some, dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, a.va, a.x, a.y,
+                                     carry_row, carry_val, n_tiles, a.remap, a.ranges, a.longs);
+        else hipLaunchKernelGGL(spmv_wo_long_kernel<false>, some, dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, a.va, a.x, a.y,
+                                carry_row, carry_val, n_tiles, a.remap, a.ranges, a.longs);
+        launch_carry_fixup(a.rows, n_tiles, carry_row, carry_val, a.y, st);
+        return;
+    }
 #define SEER_WO_LAUNCH(C, ...)                                                                                 \
     hipLaunchKernelGGL((spmv_wo_kernel<C, __VA_ARGS__>), grid, dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, a.va, \
-                       a.x, a.y, carry_row, carry_val, n_tiles, a.remap, a.ranges, a.skip, a.meet)
+                       a.x, a.y, carry_row, carry_val, n_tiles, a.remap, a.ranges, a.meet)
 #define SEER_WO_PICK(C)                                                                     \
     if (a.ranges.count) {                                                                   \
         if (a.nt) SEER_WO_LAUNCH(C, true, true, true); else SEER_WO_LAUNCH(C, true, false, true); \
