@@ -206,7 +206,9 @@ size_t seer_spmv_workspace_bytes(int kernel_id, int32_t rows, int32_t nnz);
  * graph.  This is the runtime flow of Sec. III-B with the cost of feature
  * collection (Sec. III-C) cut down to the reduction kernel itself.
  * y is the same as seer_spmv would give with the id seer_select would return for
- * the features seer_features would return (all three bit for bit).
+ * the features seer_features would return (all three bit for bit; but from 2^25 nonzeros on, where
+ * CSR,WO is chosen and this call sums its long rows apart (see "long_rows"), rows of more than
+ * 1300 entries may be added up in another order).
  * Before anything is enqueued the host prunes the tree with what it knows from rows,
  * cols and nnz (seer_tree_reachable): the launches are sized for the schedules that stay
  * reachable, the carry fix-up of CSR,MP / CSR,WO (see seer_spmv: where their cut rows do not
@@ -450,7 +452,9 @@ int seer_csr_check(const seer_csr *A, int64_t *bad_row_ptr, int64_t *bad_col_idx
  *   "long_rows" CSR,WO: 1: from 2^23 nonzeros on and whatever the mean, 0: never: rows of 32 entries
  *               and more per 2^15 columns are summed apart, with x in LDS, where gathers go by
  *               column range and the workspace has room; default: from 2^28 nonzeros on with 64
- *               or more to a row on average and at most 2^22 rows.  The size functions of CSR,WO and
+ *               or more to a row on average and at most 2^22 rows, and in seer_spmv_auto, where it
+ *               gathers the features, from 2^25 nonzeros on at as many rows, if such rows hold 2^23
+ *               entries or more together.  The size functions of CSR,WO and
  *               seer_spmv_auto follow it, whatever the columns; with less workspace (their sizes under 0)
  *               the stage is left out, as it is where gathers do not go by range, so that no more is
  *               needed for matrices of at most 1 310 720 or more than 2^25 columns

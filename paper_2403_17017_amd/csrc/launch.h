@@ -29,13 +29,16 @@ struct GatherRanges {
 // (kLongWhole: all of them, and the row goes on) and the last `tail`.
 struct LongSkip { uint16_t head, tail; };
 constexpr uint16_t kLongWhole = 0x8000u;
-// What CSR,WO is told of them: a word per chunk (null: no entry is left out), and, if there are such rows, the chunks that
-// have something left and the ticks of the gather ranges, whose turn lasts as long as that needs.
+// What CSR,WO is told of them: a word per chunk (null: no entry is left out), and, if there are such rows, the ticks of the
+// gather ranges, whose turn lasts as long as what is left needs, and the chunks that have something left.
 struct LongNumbers { uint32_t n[3], all, ticks, active; };     // rows of each class, all of them; as above; how many chunks
 struct LongStage {
     const LongSkip *skip = nullptr;
-    const LongNumbers *numbers = nullptr;
+    LongNumbers *numbers = nullptr;
     const uint32_t *active = nullptr;
+    const uint32_t *rows = nullptr;          // the long rows by number, and their pieces' sums
+    const float *part = nullptr;
+    uint32_t slabs = 0;
 };
 
 // Where the parts of a row that a tile boundary cuts meet (meet_row): a slot of 64 bytes per boundary, slots null:
@@ -183,18 +186,29 @@ bool flatten_tree(const seer_tree *tree, AutoHeap *heap);   // false: deeper tha
 
 struct AutoSel {                            // what the selection leaves in the workspace
     int32_t kernel_id, valid;               // valid: 1 gathered on the device; 2 decided on the host, no statistics
+    int32_t no_longs, pad;                  // 1: no long rows of CSR,WO go apart (0: their numbers say which)
     int64_t rows, cols, nnz;
     int32_t max_len, min_len;
     uint64_t sum_sq, empty;
     float f[SEER_NUM_FEATURES];
 };
-// The long rows of CSR,WO with slabs of x in LDS.  sel: null, or the selection (nothing is done unless it says
-// CSR,WO).  What CSR,WO (chunks of kWoChunkLarge entries) is told lies in the workspace; chunks that have nothing left get the
-// carry of a chunk that cuts no row (carry_row).
+// The long rows of CSR,WO with slabs of x in LDS.  select.sel: null: CSR,WO it is; else the selection.  select.heap: null: it
+// has been made (nothing is done unless it says CSR,WO); else it is made here: the first pass leaves the feature partials in
+// select.part, too, and the next launch the selection (select.all: however few entries long rows have).  What CSR,WO (chunks of
+// kWoChunkLarge entries) is told lies in the workspace, which begins with the slots where its cut rows meet: beside long rows it
+// leaves no carries, and it writes the long rows' y.
+struct FeatPartial;
+struct LongSelect {
+    const AutoHeap *heap = nullptr;
+    FeatPartial *part = nullptr;
+    AutoSel *sel = nullptr;
+    uint32_t reachable = 0;
+    bool all = false;
+};
 bool long_rows_fit(int rows);                           // rows the stage can list
 size_t long_workspace_bytes(int rows, int cols, int nnz);
 size_t long_workspace_most(int rows, int nnz);          // for any number of columns
-LongStage launch_long(const SpmvArgs &a, const AutoSel *sel, int *carry_row, void *workspace, hipStream_t st);
+LongStage launch_long(const SpmvArgs &a, const LongSelect &select, void *workspace, hipStream_t st);
 
 struct AutoShape {                          // launch shapes, all from rows and nnz alone
     uint32_t tiles[SEER_NUM_DIRECT_KERNELS];
@@ -204,7 +218,7 @@ struct AutoShape {                          // launch shapes, all from rows and 
     int tm_remap;                           // CSR,TM's tile order: 1 XCD-contiguous, 0 round-robin
     GatherRanges ranges;                    // as in SpmvArgs; ticks: CSR,WO's
     LongStage longs;                        // as in SpmvArgs
-    Meet meet;                              // as in SpmvArgs
+    Meet meet, long_meet;                   // as in SpmvArgs; for CSR,WO beside long rows
     uint32_t bm_ticks, mp_ticks;
     int bm_ranged;                          // CSR,BM orders its gathers, too
     uint32_t reachable;                     // bit k: the tree can answer kernel k given rows, cols and nnz (never 0)
@@ -213,6 +227,7 @@ constexpr size_t kAutoSelOffset = 32768;    // after the 1024 feature partials o
 constexpr size_t kAutoCarryOffset = 32768 + 256;
 size_t auto_workspace_bytes(int rows, int nnz);         // the least: with carries
 size_t auto_meet_workspace_bytes(int rows, int nnz);    // ... with room for cut rows to meet where they may
+size_t auto_slots_bytes(int rows, int nnz);             // slots for the cut rows of CSR,MP or CSR,WO
 constexpr int kAutoFusedRows = 8192;        // up to here every workgroup gathers and selects for itself, no first pass
 constexpr int kAutoFusedGrid = 1024;        // the product's launch selects for itself up to this many workgroups ...
 constexpr int kAutoFusedMaxRows = 0;        // ... and, whatever its grid, up to this many rows (off: measured slower; the first pass
@@ -224,6 +239,7 @@ struct AutoPolicy {                         // when the selection runs inside th
     int fused_rows, fused_grid, fused_max_rows;
     int select_wave;                        // 1: the selection launch is a single wave (0: a workgroup of 1024 lanes)
     uint32_t part_rows;                     // rows per workgroup of the first pass (0: the default)
+    int long_all;                           // 1: long rows go apart however few entries they have
 };
 // heap: the flattened tree, or null if it is too deep (then the node array is walked).
 // decided: null, or the record of a choice the host could make alone (shape.reachable has

@@ -58,9 +58,8 @@ std::atomic<int> g_tune_slab_shift{-1};
 std::atomic<int> g_tune_gather_range{-1};
 
 // The marks by which a product knows the sums in its slots (meet_next) from what a workspace held before: random, the process's own.
-Meet meet_at(void *slots, size_t bytes, int rows, int nnz, uint32_t n_tiles)
+Meet meet_in(void *slots)
 {
-    if (!meet_applies(rows, nnz) || bytes < meet_workspace_bytes(n_tiles)) return Meet{};
     static const uint64_t marks = [] {
         uint64_t m = 0;
         if (getrandom(&m, sizeof m, GRND_NONBLOCK) != (ssize_t)sizeof m)
@@ -71,6 +70,10 @@ Meet meet_at(void *slots, size_t bytes, int rows, int nnz, uint32_t n_tiles)
     const uint32_t mark = (uint32_t)(marks >> 32) | 1u;          // (a slot at rest is zero)
     const uint32_t proof = (uint32_t)marks == mark ? mark ^ 2u : (uint32_t)marks;
     return Meet{static_cast<unsigned long long *>(slots), mark, proof};
+}
+Meet meet_at(void *slots, size_t bytes, int rows, int nnz, uint32_t n_tiles)
+{
+    return meet_applies(rows, nnz) && bytes >= meet_workspace_bytes(n_tiles) ? meet_in(slots) : Meet{};
 }
 
 // Where the waiting calls (seer_features, seer_csr_check, seer_spmv_prepare for ELL,TM and CSR,S) get their results: kMailboxes slots of
@@ -209,7 +212,17 @@ uint32_t gather_ticks(const GatherRanges &g, int64_t nnz, double entries_per_wg)
 // 1461 and 1475 us, 140 M 817 and 829, 70 M 427 and 438, 35 M 233 and 244.  With Zipf rows and 2 M columns the stage
 // gains far below it: 471 M nonzeros 2385 and 1255 us, 171 M 926 and 598, 44 M 288 and 255, 32 M 214 and 185; a
 // program that knows its rows sets the knob.
+// That is for a matrix that is not looked at.  Where features are gathered (auto_long_rows) the first pass sees the long
+// rows, and a matrix without pays for one launch and a longer selection, 2 to 4 us: from 2^25 nonzeros on.  Steps, us
+// without and with: Zipf rows, 47 M nonzeros in 2 M columns 317 and 247, 53 M in 3 M 441 and 270; without long
+// rows, 40 M random 286.5 and 288.5, 48 M 363 and 366.5, a band of 21 77 and 80.5, a 7-point grid of 200^3 106.5 both.
+// Below, Zipf rows (33 M, s = 2.0) 299 and 273, 18 M random 133 and 137, a band of 11 (19 M) 40.5 and 44.
 // The "long_rows" knob: 0 never, 1 from 2^23 nonzeros on, whatever the mean.
+bool auto_long_rows(int rows, int nnz)
+{
+    const int t = g_tune_long_rows.load();
+    return t != 0 && long_rows_fit(rows) && nnz >= (t == 1 ? 1 << 23 : 1 << 25);
+}
 bool long_rows(int rows, int nnz)
 {
     const int t = g_tune_long_rows.load();
@@ -817,7 +830,8 @@ int seer_tree_reachable(const seer_tree *tree, const seer_features_t *known, uin
 size_t seer_spmv_auto_workspace_bytes(int32_t rows, int32_t nnz)
 {
     if (rows < 0 || nnz < 0) return 0;
-    return auto_meet_workspace_bytes(rows, nnz) + (long_rows(rows, nnz) ? long_workspace_most(rows, nnz) : 0);
+    if (!auto_long_rows(rows, nnz)) return auto_meet_workspace_bytes(rows, nnz);
+    return auto_workspace_bytes(rows, nnz) + long_workspace_most(rows, nnz);
 }
 
 // Everything seer_spmv_auto checks before it needs scratch memory.  SEER_OK with *enqueue
@@ -864,11 +878,6 @@ static int auto_enqueue(const seer_csr *A, const seer_tree *tree, const float *x
     sh.tiles[SEER_CSR_WO] = wo_num_tiles(A->rows, A->nnz);
     SpmvArgs a{A->rows, A->cols, A->nnz, A->row_ptr, A->col_idx, A->values, x, y, use_remap(), 1};
     sh.longs = LongStage{};
-    void *long_ws = nullptr;            // behind the rest, where there is room
-    const size_t before_long = auto_workspace_bytes(A->rows, A->nnz);
-    if (sh.ranges.count && long_rows(A->rows, A->nnz) && workspace_bytes >= before_long &&
-        workspace_bytes - before_long >= long_workspace_bytes(A->rows, A->cols, A->nnz))
-        long_ws = static_cast<char *>(workspace) + before_long;
     sh.meet = meet_at(static_cast<char *>(workspace) + kAutoCarryOffset, workspace_bytes - kAutoCarryOffset, A->rows, A->nnz,
                       std::max(sh.tiles[SEER_CSR_MP], sh.tiles[SEER_CSR_WO]));
     sh.ranges.ticks = gather_ticks(sh.ranges, A->nnz, wo_entries(A->nnz));
@@ -892,12 +901,19 @@ static int auto_enqueue(const seer_csr *A, const seer_tree *tree, const float *x
         record.empty = ~0ull;
         for (int i = 0; i < SEER_NUM_FEATURES; ++i) record.f[i] = kf.f[i];
     }
+    AutoHeap heap;
+    const bool flat = flatten_tree(tree, &heap);
+    void *long_ws = nullptr;            // behind the rest, where there is room
+    const size_t before_long = auto_workspace_bytes(A->rows, A->nnz);
+    if (sh.ranges.count && (decided ? long_rows(A->rows, A->nnz) : auto_long_rows(A->rows, A->nnz))) {
+        const bool wo = ((sh.reachable >> SEER_CSR_WO) & 1u) != 0;
+        if (wo && workspace_bytes >= before_long && workspace_bytes - before_long >= long_workspace_bytes(A->rows, A->cols, A->nnz))
+            sh.long_meet = meet_in(long_ws = static_cast<char *>(workspace) + before_long);
+    }
     const int fg = g_tune_fused_grid.load(), fm = g_tune_fused_max_rows.load();
     const int pr = g_tune_part_rows.load();
     const AutoPolicy policy{auto_fused_rows(), fg < 0 ? kAutoFusedGrid : fg, fm < 0 ? kAutoFusedMaxRows : fm,
-                            g_tune_select_wave.load() != 0, pr >= 256 ? (uint32_t)pr : 0u};
-    AutoHeap heap;
-    const bool flat = flatten_tree(tree, &heap);
+                            g_tune_select_wave.load() != 0, pr >= 256 ? (uint32_t)pr : 0u, g_tune_long_rows.load() == 1};
     AutoTree dt;                        // three kilobytes that only a tree too deep for the heap needs
     if (!flat) {
         std::memset(&dt, 0, sizeof dt);
@@ -1151,10 +1167,13 @@ static int spmv_dispatch(int kernel_id, const seer_csr *A, const float *x, float
         a.ranges.ticks = gather_ticks(a.ranges, A->nnz, wo_entries(A->nnz));
         if (a.ranges.count && long_rows(A->rows, A->nnz)) {
             const size_t before = carry_workspace_bytes(wo_num_tiles(A->rows, A->nnz));      // (a multiple of 512)
-            if (workspace_bytes - before >= long_workspace_bytes(A->rows, A->cols, A->nnz))
-                a.longs = launch_long(a, nullptr, static_cast<int *>(workspace), static_cast<char *>(workspace) + before, st);
+            if (workspace_bytes - before >= long_workspace_bytes(A->rows, A->cols, A->nnz)) {
+                void *long_ws = static_cast<char *>(workspace) + before;
+                a.longs = launch_long(a, LongSelect{}, long_ws, st);
+                a.meet = meet_in(long_ws);
+            }
         }
-        a.meet = meet_at(workspace, workspace_bytes, A->rows, A->nnz, wo_num_tiles(A->rows, A->nnz));
+        if (!a.longs.skip) a.meet = meet_at(workspace, workspace_bytes, A->rows, A->nnz, wo_num_tiles(A->rows, A->nnz));
         launch_wo(a, vec, workspace, st);
         break;
     default: {

@@ -25,175 +25,10 @@
 // division, one rounding to fp32), so both give the same bits.
 #include "../../include/seer.h"
 #include "features_bodies.hiph"
+#include "select_bodies.hiph"
 #include "spmv_bodies.hiph"
 
 namespace seer {
-
-// Correctly rounded (nearest-even) conversion of a 128-bit unsigned integer: keep
-// the top 64 bits, fold everything below into the lowest kept bit (sticky), convert
-// (64 -> 53 bits rounds once, and the sticky bit makes that the rounding of the
-// full number), scale back exactly.
-__device__ __forceinline__ double u128_to_double(unsigned __int128 n)
-{
-    const uint64_t hi = (uint64_t)(n >> 64);
-    if (hi == 0) return (double)(uint64_t)n;
-    const int s = 64 - __clzll((long long)hi);            // 1..64
-    uint64_t top = (uint64_t)(n >> s);
-    const unsigned __int128 below = n - ((unsigned __int128)top << s);
-    top |= (uint64_t)(below != 0);
-    return ldexp((double)top, s);
-}
-
-__device__ __forceinline__ void derive_features_device(
-    int64_t rows, int64_t cols, int64_t nnz, int64_t max_len, int64_t min_len, int64_t empty,
-    uint64_t sum_sq, float *f)
-{
-    for (int i = 0; i < SEER_NUM_FEATURES; ++i) f[i] = 0.0f;
-    f[SEER_F_COLS] = (float)(double)cols;
-    f[SEER_F_ITERATIONS] = 1.0f;   // this path is the single product
-    if (rows <= 0) return;
-    const double R = (double)rows;
-    const double mean = (double)nnz / R;
-    const unsigned __int128 num = (unsigned __int128)(uint64_t)rows * (unsigned __int128)sum_sq -
-                                  (unsigned __int128)(uint64_t)nnz * (unsigned __int128)(uint64_t)nnz;
-    const double var = u128_to_double(num) / (double)((uint64_t)rows * (uint64_t)rows);
-    f[SEER_F_ROWS] = (float)R;
-    f[SEER_F_NNZ] = (float)(double)nnz;
-    f[SEER_F_MEAN_LEN] = (float)mean;
-    f[SEER_F_MAX_LEN] = (float)(double)max_len;
-    f[SEER_F_MIN_LEN] = (float)(double)min_len;
-    f[SEER_F_VAR_LEN] = (float)var;
-    f[SEER_F_EMPTY_FRAC] = (float)((double)empty / R);
-    if (cols > 0) {
-        const double C = (double)cols;
-        f[SEER_F_MEAN_DENSITY] = (float)(mean / C);
-        f[SEER_F_MAX_DENSITY] = (float)((double)max_len / C);
-        f[SEER_F_MIN_DENSITY] = (float)((double)min_len / C);
-        f[SEER_F_VAR_DENSITY] = (float)(var / (C * C));
-    }
-}
-
-// One lane's work once it holds the matrix's statistics: derive the
-// feature vector (into LDS, so that the tree can index it without forcing it into
-// private scratch memory), walk the tree where it lies in the kernel arguments, and, if
-// `sel` is given, leave the record that seer_spmv_auto_result reads.  Returns the kernel
-// id.  (Sharing the derivation between the waves and staging the tree in LDS first was
-// measured: it is slower by more than a microsecond, the bulk read of the 3 KB argument
-// block costs more than the few nodes a walk touches.)
-__device__ __forceinline__ int select_on_device(
-    int rows, int cols, const int *__restrict__ rp, const FeatTotals &t, float *s_f, const AutoTree &tree,
-    uint32_t reachable, AutoSel *__restrict__ sel)
-{
-    const int64_t nnz = (int64_t)rp[rows] - (int64_t)rp[0];
-    derive_features_device(rows, cols, nnz, t.mx, t.mn, (int64_t)t.em, t.sq, s_f);
-    int n = 0, k = SEER_CSR_MP;            // a malformed tree cannot get here (host checks); MP is the safe answer
-    for (int steps = 0; steps <= tree.n_nodes; ++steps) {
-        const int feature = tree.nodes[n].feature;
-        if (feature < 0) { k = tree.nodes[n].klass; break; }
-        n = ((double)s_f[feature] <= tree.nodes[n].threshold) ? tree.nodes[n].left : tree.nodes[n].right;
-    }
-    k = (k >= 0 && k < SEER_NUM_DIRECT_KERNELS) ? k : SEER_CSR_MP;
-    if (!((reachable >> k) & 1u)) k = __ffs((int)reachable) - 1;   // (see select_in_wave)
-    if (sel) {
-        sel->kernel_id = k;
-        sel->valid = 1;
-        sel->rows = rows; sel->cols = cols; sel->nnz = nnz;
-        sel->max_len = t.mx; sel->min_len = t.mn;
-        sel->sum_sq = t.sq; sel->empty = t.em;
-#pragma unroll
-        for (int i = 0; i < SEER_NUM_FEATURES; ++i) sel->f[i] = s_f[i];
-    }
-    return k;
-}
-
-// ---- selection from the flattened tree (depth <= 6), by the first wave of a workgroup.
-// Walking the node array costs one dependent load from the kernel-argument memory per
-// level (measured: 2.3 us of a 26 us step for a depth-6 tree).  Here every lane fetches one
-// slot when the kernel starts, long before the statistics are ready; afterwards all
-// comparisons are evaluated at once and the leaf is found with two ballots.
-struct HeapRegs {
-    int feature;
-    double threshold;
-    int klass_inner, klass_leaf;   // of slot lane, and of slot 63 + lane
-};
-
-__device__ __forceinline__ HeapRegs heap_load(const AutoHeap &h)
-{
-    const int l = threadIdx.x % kWave;
-    return HeapRegs{h.feature[l], h.threshold[l], (int)h.klass[l], (int)h.klass[kHeapInternal + l]};
-}
-
-// Entry `l` of the feature vector (l < SEER_NUM_FEATURES; other lanes get 1).  The same
-// operations as derive_features_device, arranged so that every lane of a wave runs the same
-// instructions on its own operands: f[l] = fl32((a / b) / c) with b, c = 1 where the entry
-// has fewer divisions (x / 1 is exact), so the thirteen entries cost two fp64 divisions
-// instead of seven one after the other.  rows > 0.
-__device__ __forceinline__ float derive_feature_lane(int rows, int cols, int64_t nnz, const FeatTotals &t, int l)
-{
-    const double R = (double)(int64_t)rows, C = (double)(int64_t)cols, N = (double)nnz;
-    const unsigned __int128 num = (unsigned __int128)(uint64_t)rows * (unsigned __int128)t.sq -
-                                  (unsigned __int128)(uint64_t)nnz * (unsigned __int128)(uint64_t)nnz;
-    const double VN = u128_to_double(num), RR = (double)((uint64_t)rows * (uint64_t)rows);
-    const double MX = (double)(int64_t)t.mx, MN = (double)(int64_t)t.mn, E = (double)(int64_t)t.em;
-    const bool density = l >= SEER_F_MEAN_DENSITY && l <= SEER_F_VAR_DENSITY;
-    double a = 1.0, b = 1.0, c = 1.0;           // SEER_F_ITERATIONS: 1 on this path
-    if (l == SEER_F_ROWS) a = R;
-    if (l == SEER_F_COLS) a = C;
-    if (l == SEER_F_NNZ || l == SEER_F_MEAN_LEN || l == SEER_F_MEAN_DENSITY) a = N;
-    if (l == SEER_F_MAX_LEN || l == SEER_F_MAX_DENSITY) a = MX;
-    if (l == SEER_F_MIN_LEN || l == SEER_F_MIN_DENSITY) a = MN;
-    if (l == SEER_F_VAR_LEN || l == SEER_F_VAR_DENSITY) a = VN;
-    if (l == SEER_F_EMPTY_FRAC) a = E;
-    if (l == SEER_F_MEAN_LEN || l == SEER_F_EMPTY_FRAC || l == SEER_F_MEAN_DENSITY) b = R;
-    if (l == SEER_F_VAR_LEN || l == SEER_F_VAR_DENSITY) b = RR;
-    if (density) c = l == SEER_F_VAR_DENSITY ? C * C : C;
-    if (density && cols <= 0) { a = 0.0; b = 1.0; c = 1.0; }   // no columns: densities are 0
-    return (float)((a / b) / c);
-}
-
-// All 64 lanes of one wave, each holding its slot of the flattened tree in `r` and, for
-// lane < SEER_NUM_FEATURES, its entry of the feature vector in `f`.
-__device__ __forceinline__ int heap_walk_lanes(const HeapRegs &r, float f)
-{
-    const bool leaf = r.feature < 0;
-    const float fv = __shfl(f, leaf ? 0 : r.feature);
-    const bool right = !leaf && !((double)fv <= r.threshold);
-    const uint64_t leaf_mask = __ballot(leaf), right_mask = __ballot(right);
-    int i = 0;
-#pragma unroll
-    for (int d = 0; d < 6; ++d) {
-        if ((leaf_mask >> i) & 1) break;              // i <= 62 here
-        i = 2 * i + 1 + (int)((right_mask >> i) & 1);
-    }
-    const int k = i < kHeapInternal ? __shfl(r.klass_inner, i) : __shfl(r.klass_leaf, i - kHeapInternal);
-    return (k >= 0 && k < SEER_NUM_DIRECT_KERNELS) ? k : SEER_CSR_MP;
-}
-
-// One wave: from the matrix's statistics to the kernel id (the same in every lane), and, if
-// `sel` is given, the record seer_spmv_auto_result reads.  `reachable` has a bit per kernel
-// id the host found reachable from rows, cols and nnz alone and sized the grid for; the
-// device arrives at one of them unless nnz is not what row_ptr says, and then takes the
-// lowest of them rather than a schedule the grid cannot hold.
-__device__ __forceinline__ int select_in_wave(
-    int rows, int cols, int64_t nnz, const FeatTotals &t, const HeapRegs &hr, uint32_t reachable,
-    AutoSel *__restrict__ sel)
-{
-    const int l = threadIdx.x % kWave;
-    const float f = derive_feature_lane(rows, cols, nnz, t, l);
-    int k = heap_walk_lanes(hr, f);
-    if (!((reachable >> k) & 1u)) k = __ffs((int)reachable) - 1;
-    if (sel) {
-        if (l < SEER_NUM_FEATURES) sel->f[l] = f;
-        if (l == 0) {
-            sel->kernel_id = k;
-            sel->valid = 1;
-            sel->rows = rows; sel->cols = cols; sel->nnz = nnz;
-            sel->max_len = t.mx; sel->min_len = t.mn;
-            sel->sum_sq = t.sq; sel->empty = t.em;
-        }
-    }
-    return k;
-}
 
 // Finishing launch of the selection after a first pass: ONE wave folds the partials, derives
 // the features, walks the tree and leaves the record -- no LDS, no barrier (as a workgroup of
@@ -254,7 +89,8 @@ template <int IPT, bool VEC, bool RANGED = false>
 __device__ __forceinline__ void auto_dispatch(
     int k, int rows, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
-    int *__restrict__ carry_row, float *__restrict__ carry_val, const AutoShape &shape, int remap, int *smem)
+    int *__restrict__ carry_row, float *__restrict__ carry_val, const AutoShape &shape, int remap, int *smem,
+    bool no_longs = false /* as in AutoSel */)
 {
     static_assert(mp_lds_words<IPT>() <= kAutoLds, "LDS overlay too small");
     const uint32_t n_tiles = shape.tiles[k];
@@ -278,10 +114,10 @@ __device__ __forceinline__ void auto_dispatch(
         return;
     }
     if constexpr (RANGED) {
-        if (k == SEER_CSR_WO && shape.longs.skip) {      // (from 2^23 nonzeros on: the larger chunks)
+        if (k == SEER_CSR_WO && shape.longs.skip && !no_longs) {      // (from 2^23 nonzeros on: the larger chunks)
             static_assert(bm_lds_words<kWoChunkLarge>() + 2 <= kAutoLds, "LDS overlay too small");
-            wo_long_body<VEC, true>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, n_tiles, remap, reinterpret_cast<float *>(smem),
-                                    reinterpret_cast<uint32_t *>(smem) + bm_lds_words<kWoChunkLarge>(), shape.ranges, shape.longs);
+            wo_long_body<VEC, true>(rows, nnz, rp, ci, va, x, y, n_tiles, remap, reinterpret_cast<float *>(smem),
+                                    reinterpret_cast<uint32_t *>(smem) + bm_lds_words<kWoChunkLarge>(), shape.ranges, shape.longs, shape.long_meet);
             return;
         }
     }
@@ -334,7 +170,8 @@ __global__ __launch_bounds__(kWG, RANGED ? 8 : 1) void spmv_auto_kernel(
     const AutoShape shape, int remap)
 {
     __shared__ __attribute__((aligned(16))) int smem[kAutoLds];
-    auto_dispatch<IPT, VEC, RANGED>(sel->kernel_id, rows, nnz, rp, ci, va, x, y, carry_row, carry_val, shape, remap, smem);
+    const int k = sel->kernel_id, no_longs = sel->no_longs;              // (one load)
+    auto_dispatch<IPT, VEC, RANGED>(k, rows, nnz, rp, ci, va, x, y, carry_row, carry_val, shape, remap, smem, no_longs != 0);
 }
 
 // The product when the host could decide alone: every leaf the tree can reach from rows,
@@ -401,11 +238,11 @@ __global__ __launch_bounds__(kWG) void spmv_auto_fused_kernel(
 
 __global__ __launch_bounds__(kWG) void spmv_auto_fixup_kernel(
     int rows, uint32_t n_mp, uint32_t n_wo, const int *__restrict__ carry_row,
-    const float *__restrict__ carry_val, float *__restrict__ y, const AutoSel *__restrict__ sel)
+    const float *__restrict__ carry_val, float *__restrict__ y, const AutoSel *__restrict__ sel, bool longs)
 {
-    const int k = sel->kernel_id;
-    if (k != SEER_CSR_MP && k != SEER_CSR_WO) return;
-    mp_fixup_body(rows, k == SEER_CSR_MP ? n_mp : n_wo, carry_row, carry_val, y);
+    const int k = sel->kernel_id, no_longs = sel->no_longs;
+    if (k != SEER_CSR_MP && (k != SEER_CSR_WO || (longs && no_longs == 0))) return;      // (beside long rows, cut rows meet)
+    mp_fixup_body(rows, k == SEER_CSR_MP ? n_mp : n_wo, carry_row, carry_val, y, blockIdx.x * kWG + threadIdx.x);
 }
 
 size_t auto_workspace_bytes(int rows, int nnz)
@@ -415,13 +252,16 @@ size_t auto_workspace_bytes(int rows, int nnz)
     return kAutoCarryOffset + (mp > wo ? mp : wo);
 }
 
+size_t auto_slots_bytes(int rows, int nnz)
+{
+    const uint32_t mp = mp_num_tiles(rows, nnz, kMpIptSmall), wo = wo_num_tiles(rows, nnz);
+    return meet_workspace_bytes(mp > wo ? mp : wo);
+}
+
 size_t auto_meet_workspace_bytes(int rows, int nnz)
 {
-    const size_t least = auto_workspace_bytes(rows, nnz);
-    if (!meet_applies(rows, nnz)) return least;
-    const uint32_t mp = mp_num_tiles(rows, nnz, kMpIptSmall), wo = wo_num_tiles(rows, nnz);
-    const size_t meet = kAutoCarryOffset + meet_workspace_bytes(mp > wo ? mp : wo);
-    return meet > least ? meet : least;
+    const size_t least = auto_workspace_bytes(rows, nnz), meet = kAutoCarryOffset + auto_slots_bytes(rows, nnz);
+    return meet_applies(rows, nnz) && meet > least ? meet : least;
 }
 
 // The first pass ahead of a product that selects for itself: at most kAutoFusedParts
@@ -488,7 +328,8 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
     const bool carries = !shape.meet.slots && (reachable(SEER_CSR_MP) || reachable(SEER_CSR_WO));
 
     if (decided) {
-        if (long_workspace && decided->kernel_id == SEER_CSR_WO) shape.longs = launch_long(a, nullptr, carry_row, long_workspace, st);
+        if (long_workspace && decided->kernel_id == SEER_CSR_WO)
+            shape.longs = launch_long(a, LongSelect{}, long_workspace, st);
 #define SEER_DECIDED_LAUNCH(...)                                                                           \
     hipLaunchKernelGGL((spmv_auto_decided_kernel<__VA_ARGS__>), dim3(grid), dim3(kWG), 0, st, a.rows, a.nnz, a.rp, \
                        a.ci, a.va, a.x, a.y, carry_row, carry_val, sel, *decided, shape, a.remap)
@@ -501,7 +342,7 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
             if (vec) SEER_DECIDED_LAUNCH(kMpIptLarge, true); else SEER_DECIDED_LAUNCH(kMpIptLarge, false);
         }
 #undef SEER_DECIDED_LAUNCH
-        if (carries)
+        if (carries && !shape.longs.skip)
             launch_carry_fixup(a.rows, decided->kernel_id == SEER_CSR_MP ? n_mp : n_wo, carry_row, carry_val, a.y, st);
         return;
     }
@@ -527,12 +368,16 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
 #undef SEER_FUSED_LAUNCH_BY
         if (carries)
             hipLaunchKernelGGL(spmv_auto_fixup_kernel, dim3((n_carry + kWG - 1) / kWG), dim3(kWG), 0, st, a.rows, n_mp,
-                               n_wo, carry_row, carry_val, a.y, sel);
+                               n_wo, carry_row, carry_val, a.y, sel, false);
         return;
     }
 
+    // Where CSR,WO may have long rows to leave out, the first pass lists them, too, and the launch that cuts them selects: a matrix
+    // without such rows has one launch more than without the stage.
+    const bool longs = long_workspace && reachable(SEER_CSR_WO), long_select = longs && heap && policy.select_wave;
+    if (long_select) shape.longs = launch_long(a, LongSelect{heap, part, sel, shape.reachable, policy.long_all != 0}, long_workspace, st);
     const uint32_t n_part = features_num_parts(a.rows, policy.part_rows);
-    if (n_part) launch_feature_partials(a.rows, a.rp, part, n_part, rp_vec, st);
+    if (n_part && !long_select) launch_feature_partials(a.rows, a.rp, part, n_part, rp_vec, st);
     const bool one_wave = heap && n_part && policy.select_wave;
 #define SEER_WAVE_LAUNCH(U)                                                                                 \
     hipLaunchKernelGGL(features_select_wave_kernel<U>, dim3(1), dim3(kWave), 0, st, a.rows, a.cols, a.rp, part, n_part, sel, \
@@ -544,7 +389,8 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
     else                                                                                                    \
         hipLaunchKernelGGL(features_select_kernel<V>, dim3(1), dim3(kFeatWG), 0, st, a.rows, a.cols, a.rp, part, n_part, \
                            sel, tree, shape.reachable)
-    if (one_wave) {
+    if (long_select) {
+    } else if (one_wave) {
         if (fold_eight(n_part)) SEER_WAVE_LAUNCH(8); else SEER_WAVE_LAUNCH(4);
     } else if (rp_vec) {
         SEER_SELECT_LAUNCH(true);
@@ -554,7 +400,7 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
 #undef SEER_WAVE_LAUNCH
 #undef SEER_SELECT_LAUNCH
 
-    if (long_workspace && reachable(SEER_CSR_WO)) shape.longs = launch_long(a, sel, carry_row, long_workspace, st);
+    if (longs && !long_select) shape.longs = launch_long(a, LongSelect{nullptr, nullptr, sel, 0, true}, long_workspace, st);
 #define SEER_AUTO_LAUNCH(...)                                                                              \
     hipLaunchKernelGGL((spmv_auto_kernel<__VA_ARGS__>), dim3(grid), dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, \
                        a.va, a.x, a.y, carry_row, carry_val, sel, shape, a.remap)
@@ -569,7 +415,7 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
 #undef SEER_AUTO_LAUNCH
     if (carries)
         hipLaunchKernelGGL(spmv_auto_fixup_kernel, dim3((n_carry + kWG - 1) / kWG), dim3(kWG), 0, st, a.rows, n_mp,
-                           n_wo, carry_row, carry_val, a.y, sel);
+                           n_wo, carry_row, carry_val, a.y, sel, longs);
 }
 
 } // namespace seer

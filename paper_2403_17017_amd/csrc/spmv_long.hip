@@ -13,11 +13,13 @@
 // The cuts are right for any order of columns: a cut is a place in the row, cuts never descend
 // (each is raised to the ones before it), and an entry whose column lies outside the slab of its piece
 // is gathered from x.
-// 472 M nonzeros, Zipf s = 1.6: list 14 us, cuts 80, products 674 (nine tenths of the nonzeros, read at 5.0 TB/s),
-// sums 7, CSR,WO over the rest 415; all of them by CSR,WO 2370.  Tried: rows from 16 entries per slab on, the same
+// 472 M nonzeros, Zipf s = 1.6: list 10 us, cuts 80, products 680 (nine tenths of the nonzeros, read at 5.0 TB/s),
+// CSR,WO over the rest and the sums 415; all of them by CSR,WO 2370.  Tried: rows from 16 entries per slab on, the same
 // with twice the scratch memory; a wave per piece from 128 entries on, 1289 in all against 1255 at the time.
 // CSR,WO over the rest took 513 while every chunk had a workgroup, to find nothing in four of five, and its gather
 // ranges lasted as long as full chunks need.
+#include "features_bodies.hiph"
+#include "select_bodies.hiph"
 #include "spmv_bodies.hiph"
 
 namespace seer {
@@ -27,6 +29,7 @@ constexpr uint32_t kLongCols = 1u << kLongShift;    // columns per slab: 128 KB 
 constexpr uint32_t kLongWG = 1024;
 constexpr uint32_t kLongGrid = 256;                 // workgroups of long_multiply_kernel: one per CU
 constexpr uint32_t kLongCutGrid = 512;              // ... of long_cut_kernel: two per CU
+constexpr uint32_t kLongListWG = 512;
 constexpr uint32_t kLongRows = 4096;                // rows per workgroup of long_list_kernel
 // Rows by the length of their pieces: 8 lanes, 16 lanes and a wave take a piece of class 0 (32 entries on
 // average and more), 1 (64) and 2 (256).
@@ -46,10 +49,12 @@ struct LongPart { uint32_t n[kLongClasses], first, entries, whole, pad[2]; };   
                                                                                 // their entries and the chunks that hold nothing else
 static_assert(sizeof(LongPart) == 32, "two 16-byte loads");
 
-__global__ __launch_bounds__(kWG) void long_list_kernel(
+// FEATURES: the pass over the offsets leaves the feature partials (features_partial_kernel), too.  VEC: row_ptr lies on 16 bytes.
+template <bool FEATURES, bool VEC>
+__global__ __launch_bounds__(kLongListWG) void long_list_kernel(
     int rows, uint32_t cols, uint32_t n_slabs, const int *__restrict__ rp, const int *__restrict__ ci,
     LongPart *__restrict__ parts, LongRow *__restrict__ list, LongNumbers *__restrict__ numbers, uint32_t *__restrict__ skip_words,
-    uint32_t n_skip, const AutoSel *__restrict__ sel)
+    uint32_t n_skip, FeatPartial *__restrict__ features, const AutoSel *__restrict__ sel)
 {
     // a row found: its place in the part, later its class and its number in that class, too
     constexpr uint32_t kClassAt = 12, kNumberAt = 14;
@@ -58,20 +63,51 @@ __global__ __launch_bounds__(kWG) void long_list_kernel(
     if (sel && sel->kernel_id != SEER_CSR_WO) return;
     const uint32_t r0 = blockIdx.x * kLongRows, tid = threadIdx.x, r1 = min(r0 + kLongRows, (uint32_t)rows);
     if (tid == 0) s_n = s_entries = s_whole = 0;
-    if (blockIdx.x == 0 && tid == 0) numbers->active = 0;       // (long_multiply_kernel counts them)
+    if (blockIdx.x == 0 && tid == 0) *numbers = LongNumbers{};
     if (tid < kLongClasses) s_class[tid] = 0;
-    for (uint32_t i = blockIdx.x * kWG + tid; i < n_skip; i += gridDim.x * kWG) skip_words[i] = 0;
+    for (uint32_t i = blockIdx.x * kLongListWG + tid; i < n_skip; i += gridDim.x * kLongListWG) skip_words[i] = 0;
     __syncthreads();
     const uint32_t least = long_class_piece(0) * n_slabs;
-#pragma unroll 8
-    for (uint32_t i = 0; i < kLongRows / kWG; ++i) {
-        const uint32_t at = i * kWG + tid, rc = min(r0 + at, r1 - 1u);
-        const uint32_t a = (uint32_t)rp[rc], e = (uint32_t)rp[rc + 1u];
-        if (r0 + at < r1 && e - a >= least && a / kWoChunkLarge != (e - 1u) / kWoChunkLarge) s_row[atomicAdd(&s_n, 1u)] = at;
+    int32_t mx = INT32_MIN, mn = INT32_MAX;
+    uint64_t sq = 0;
+    uint32_t em = 0;
+    const auto take = [&](uint32_t at, uint32_t a, uint32_t e) {
+        if constexpr (FEATURES) take_row((int32_t)(e - a), mx, mn, sq, em);
+        if (e - a >= least && a / kWoChunkLarge != (e - 1u) / kWoChunkLarge) s_row[atomicAdd(&s_n, 1u)] = at;
+    };
+    if constexpr (VEC) {                                        // four rows per load, and the next one's offset
+        constexpr uint32_t U = kLongRows / 4u / kLongListWG;
+        v4i v[U];
+        int next[U];
+#pragma unroll
+        for (uint32_t j = 0; j < U; ++j) {
+            const uint32_t r = min(r0 + 4u * (j * kLongListWG + tid), (uint32_t)rows & ~3u);
+            const bool in = r + 4u <= r1;
+            v[j] = in ? *reinterpret_cast<const v4i *>(rp + r) : v4i{0, 0, 0, 0};
+            next[j] = in ? rp[r + 4u] : 0;
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < U; ++j) {
+            const uint32_t at = 4u * (j * kLongListWG + tid);
+            if (r0 + at + 4u > r1) continue;
+            take(at, (uint32_t)v[j].x, (uint32_t)v[j].y);
+            take(at + 1u, (uint32_t)v[j].y, (uint32_t)v[j].z);
+            take(at + 2u, (uint32_t)v[j].z, (uint32_t)v[j].w);
+            take(at + 3u, (uint32_t)v[j].w, (uint32_t)next[j]);
+        }
+        const uint32_t at = ((r1 - r0) & ~3u) + tid;            // the last three rows of the matrix
+        if (r0 + at < r1) take(at, (uint32_t)rp[r0 + at], (uint32_t)rp[r0 + at + 1u]);
+    } else {
+        for (uint32_t at = tid; r0 + at < r1; at += kLongListWG) take(at, (uint32_t)rp[r0 + at], (uint32_t)rp[r0 + at + 1u]);
+    }
+    FeatTotals t{};
+    if constexpr (FEATURES) {
+        __shared__ FeatLds s_feat;
+        t = features_block_fold<kLongListWG>(mx, mn, sq, em, &s_feat);
     }
     __syncthreads();
     const uint32_t n = s_n;
-    for (uint32_t i = tid; i < n; i += kWG) {
+    for (uint32_t i = tid; i < n; i += kLongListWG) {
         const uint32_t at = s_row[i], a = (uint32_t)rp[r0 + at], e = (uint32_t)rp[r0 + at + 1u], len = e - a;
         bool spread = true;
 #pragma unroll
@@ -90,8 +126,9 @@ __global__ __launch_bounds__(kWG) void long_list_kernel(
     }
     __syncthreads();
     const uint32_t first = long_part(r0 < r1 ? (uint32_t)rp[r0] : 0u, least, blockIdx.x);
+    if (FEATURES && tid == 0) features[blockIdx.x] = FeatPartial{t.mx, t.mn, t.sq, t.em, s_entries};
     if (tid == 0) parts[blockIdx.x] = LongPart{{s_class[0], s_class[1], s_class[2]}, first, s_entries, s_whole, {0, 0}};
-    for (uint32_t i = tid; i < n; i += kWG) {
+    for (uint32_t i = tid; i < n; i += kLongListWG) {
         const uint32_t w = s_row[i], k = w >> kClassAt & 3u, row = r0 + (w & (kLongRows - 1u));
         if (k == kLongClasses) continue;
         const uint32_t before = (k > 0u ? s_class[0] : 0u) + (k > 1u ? s_class[1] : 0u);
@@ -168,13 +205,44 @@ __device__ __forceinline__ uint32_t long_numbers(
 // column would be if the row's columns were spread evenly, comes nearer twice by the distance of the column
 // found, then widens in steps that double; every one ends at the row's ends at the latest.  The words per
 // chunk are set here, too, and the rows listed by number for the last pass.
+// SELECT: the selection is made here (every workgroup for itself if there are long rows, the first one leaves the
+// record), from one partial per part; and long rows of fewer than kLongLeast entries together stay where they are: cutting
+// them and a launch for their pieces take some 25 us, a gather saved 4.5 ps (4 M rows, Zipf s = 2.0, 12 M such entries:
+// 300 and 280 us a step; s = 2.3, 0.6 M: 140 and 179).
+constexpr uint32_t kLongLeast = 1u << 23;
+struct LongFeatures { int rows; const int *rp; const FeatPartial *part; uint32_t reachable, least /* entries of long rows for them to go apart */; };
+
+template <bool SELECT>
 __global__ __launch_bounds__(kLongWG) void long_cut_kernel(
     uint32_t cols, uint32_t nnz, uint32_t n_slabs, uint32_t parts, const int *__restrict__ ci, const LongPart *__restrict__ of,
     const LongRow *__restrict__ list, LongNumbers *__restrict__ numbers, uint32_t ticks, uint32_t *__restrict__ rows_by_number,
-    uint32_t *__restrict__ cut, LongSkip *__restrict__ skip, const AutoSel *__restrict__ sel)
+    uint32_t *__restrict__ cut, LongSkip *__restrict__ skip, AutoSel *__restrict__ sel, const LongFeatures f, const AutoHeap heap)
 {
     __shared__ uint32_t s_from[kLongClasses * kLongParts + 1], s_w[kLongSums], s_n[kLongClasses];
-    if (sel && sel->kernel_id != SEER_CSR_WO) return;
+    if (!SELECT && sel && sel->kernel_id != SEER_CSR_WO) return;
+    if constexpr (SELECT) {
+        // The first wave selects; of too few long rows the first workgroup says that there are none, the others have nothing to do.
+        if (threadIdx.x < kWave) {
+            const HeapRegs hr = heap_load(heap);
+            const int64_t nnz_dev = (int64_t)f.rp[f.rows] - (int64_t)f.rp[0];
+            uint32_t in_all = 0;
+            const FeatTotals t = fold_partials_wave<8, true>(f.part, parts, &in_all);
+            const bool few = in_all < f.least;
+            bool go = !few;
+            if (!few || blockIdx.x == 0)
+                go = select_in_wave(f.rows, (int)cols, nnz_dev, t, hr, f.reachable, blockIdx.x == 0 ? sel : nullptr) == SEER_CSR_WO && !few;
+            if (threadIdx.x == 0) {
+                s_w[0] = go;
+                if (blockIdx.x == 0 && !go) {
+                    numbers->all = 0;
+                    sel->no_longs = 1;
+                }
+            }
+        }
+        __syncthreads();
+        if (s_w[0] == 0) return;
+        __syncthreads();
+    }
     uint32_t entries = 0, whole = 0;
     const uint32_t N = long_numbers(parts, of, s_from, s_w, s_n, entries, whole);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -321,10 +389,10 @@ __device__ __forceinline__ void long_pieces(
 }
 
 __global__ __launch_bounds__(kLongWG) void long_multiply_kernel(
-    int rows, uint32_t cols, uint32_t nnz, uint32_t n_slabs, uint32_t Q, const int *__restrict__ ci, const float *__restrict__ va,
+    uint32_t cols, uint32_t nnz, uint32_t n_slabs, uint32_t Q, const int *__restrict__ ci, const float *__restrict__ va,
     const float *__restrict__ x, LongNumbers *__restrict__ numbers, const uint32_t *__restrict__ cut,
     float *__restrict__ part, const LongSkip *__restrict__ skip, uint32_t chunks, uint32_t *__restrict__ active,
-    int *__restrict__ carry_row, const AutoSel *__restrict__ sel)
+    const AutoSel *__restrict__ sel)
 {
     __shared__ __attribute__((aligned(16))) float s_x[kLongCols];
     if (sel && sel->kernel_id != SEER_CSR_WO) return;
@@ -335,8 +403,8 @@ __global__ __launch_bounds__(kLongWG) void long_multiply_kernel(
     uint32_t *s_w = reinterpret_cast<uint32_t *>(s_x);
     for (uint32_t c0 = blockIdx.x * kLongWG; c0 < chunks; c0 += gridDim.x * kLongWG) {
         const uint32_t c = c0 + tid, lane = tid % kWave;
-        const bool in = c < chunks, whole = in && (skip[in ? c : 0u].head & kLongWhole) != 0;
-        const uint64_t left = __ballot(in && !whole);
+        const bool in = c < chunks && (skip[c].head & kLongWhole) == 0;
+        const uint64_t left = __ballot(in);
         if (lane == 0) s_w[tid / kWave] = (uint32_t)__popcll(left);
         __syncthreads();
         if (tid < kWave) {
@@ -353,8 +421,7 @@ __global__ __launch_bounds__(kLongWG) void long_multiply_kernel(
             if (lane < kLongWaves) s_w[lane] = base + incl - mine;
         }
         __syncthreads();
-        if (whole) carry_row[c] = rows;
-        else if (in) active[s_w[tid / kWave] + (uint32_t)__popcll(left & ((1ull << lane) - 1ull))] = c;
+        if (in) active[s_w[tid / kWave] + (uint32_t)__popcll(left & ((1ull << lane) - 1ull))] = c;
         __syncthreads();
     }
     for (uint32_t task = tile_of_block(blockIdx.x, gridDim.x, 1); task < n_slabs * Q; task += gridDim.x) {
@@ -386,29 +453,10 @@ __global__ __launch_bounds__(kLongWG) void long_multiply_kernel(
     }
 }
 
-// ---- 4: each long row's pieces, added up in slab order by eight sums.
-__global__ __launch_bounds__(kWG) void long_total_kernel(
-    uint32_t n_slabs, const LongNumbers *__restrict__ numbers, const uint32_t *__restrict__ rows_by_number,
-    const float *__restrict__ part, float *__restrict__ y, const AutoSel *__restrict__ sel)
-{
-    if (sel && sel->kernel_id != SEER_CSR_WO) return;
-    const uint32_t N = numbers->all;
-    for (uint32_t j = blockIdx.x * kWG + threadIdx.x; j < N; j += gridDim.x * kWG) {
-        float t[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        uint32_t s = 0;
-        for (; s + 8u <= n_slabs; s += 8u) {
-#pragma unroll
-            for (uint32_t w = 0; w < 8; ++w) t[w] += part[(size_t)(s + w) * N + j];
-        }
-        for (; s < n_slabs; ++s) t[0] += part[(size_t)s * N + j];
-        y[rows_by_number[j]] = ((t[0] + t[4]) + (t[2] + t[6])) + ((t[1] + t[5]) + (t[3] + t[7]));
-    }
-}
-
 // ------------------------------------------------------------------ host side
 static size_t pad256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-struct LongLayout { size_t numbers, counts, skip, active, list, rows, cut, part, total; uint32_t parts, skip_words; };
+struct LongLayout { size_t slots, numbers, counts, skip, active, list, rows, cut, part, total; uint32_t parts, skip_words; };
 static LongLayout long_layout(int rows, uint32_t nnz, uint32_t n_slabs)
 {
     LongLayout L;
@@ -417,6 +465,7 @@ static LongLayout long_layout(int rows, uint32_t nnz, uint32_t n_slabs)
     size_t o = 0;
     L.parts = ((uint32_t)rows + kLongRows - 1) / kLongRows;
     L.skip_words = (uint32_t)(tiles * sizeof(LongSkip) / 4);
+    L.slots = o;     o += pad256(auto_slots_bytes(rows, (int)nnz));      // (first: the callers know them there)
     L.numbers = o;   o += 256;
     L.counts = o;    o += pad256((size_t)L.parts * sizeof(LongPart));
     L.skip = o;      o += pad256((size_t)L.skip_words * 4);
@@ -436,10 +485,10 @@ size_t long_workspace_bytes(int rows, int cols, int nnz) { return long_layout(ro
 size_t long_workspace_most(int rows, int nnz)
 {
     const size_t n = (size_t)nnz, parts = ((size_t)rows + kLongRows - 1) / kLongRows;
-    return 24 * (n / 64) + 8 * (n / 32) + (n / kWoChunkLarge + 1) * (sizeof(LongSkip) + 4) + 48 * parts + 4096;
+    return auto_slots_bytes(rows, nnz) + 24 * (n / 64) + 8 * (n / 32) + (n / kWoChunkLarge + 1) * (sizeof(LongSkip) + 4) + 48 * parts + 8192;
 }
 
-LongStage launch_long(const SpmvArgs &a, const AutoSel *sel, int *carry_row, void *workspace, hipStream_t st)
+LongStage launch_long(const SpmvArgs &a, const LongSelect &select, void *workspace, hipStream_t st)
 {
     const uint32_t S = long_slabs(a.cols), nnz = (uint32_t)a.nnz;
     const LongLayout L = long_layout(a.rows, nnz, S);
@@ -451,10 +500,21 @@ LongStage launch_long(const SpmvArgs &a, const AutoSel *sel, int *carry_row, voi
     LongRow *list = reinterpret_cast<LongRow *>(base + L.list);
     uint32_t *rows = reinterpret_cast<uint32_t *>(base + L.rows), *cut = reinterpret_cast<uint32_t *>(base + L.cut);
     float *part = reinterpret_cast<float *>(base + L.part);
-    hipLaunchKernelGGL(long_list_kernel, dim3(L.parts), dim3(kWG), 0, st, a.rows, (uint32_t)a.cols, S, a.rp, a.ci, of, list,
-                       numbers, reinterpret_cast<uint32_t *>(skip), L.skip_words, sel);
-    hipLaunchKernelGGL(long_cut_kernel, dim3(kLongCutGrid), dim3(kLongWG), 0, st, (uint32_t)a.cols, nnz, S, L.parts, a.ci,
-                       static_cast<const LongPart *>(of), static_cast<const LongRow *>(list), numbers, a.ranges.ticks, rows, cut, skip, sel);
+    const bool vec = (reinterpret_cast<uintptr_t>(a.rp) & 15u) == 0;
+    const AutoSel *made = select.heap ? nullptr : select.sel;    // (for the first two launches)
+#define SEER_LIST_LAUNCH(F, V)                                                                                       \
+    hipLaunchKernelGGL((long_list_kernel<F, V>), dim3(L.parts), dim3(kLongListWG), 0, st, a.rows, (uint32_t)a.cols, S, a.rp, a.ci, of, list, \
+                       numbers, reinterpret_cast<uint32_t *>(skip), L.skip_words, select.part, made)
+    if (select.heap) { if (vec) SEER_LIST_LAUNCH(true, true); else SEER_LIST_LAUNCH(true, false); }
+    else             { if (vec) SEER_LIST_LAUNCH(false, true); else SEER_LIST_LAUNCH(false, false); }
+#undef SEER_LIST_LAUNCH
+    const LongFeatures f{a.rows, a.rp, select.part, select.reachable, select.all ? 1u : kLongLeast};
+#define SEER_CUT_LAUNCH(S_, H)                                                                                       \
+    hipLaunchKernelGGL(long_cut_kernel<S_>, dim3(kLongCutGrid), dim3(kLongWG), 0, st, (uint32_t)a.cols, nnz, S, L.parts, a.ci, \
+                       static_cast<const LongPart *>(of), static_cast<const LongRow *>(list), numbers, a.ranges.ticks, rows, cut, skip, \
+                       select.sel, f, H)
+    if (select.heap) SEER_CUT_LAUNCH(true, *select.heap); else SEER_CUT_LAUNCH(false, AutoHeap{});
+#undef SEER_CUT_LAUNCH
     // tasks per slab: so many that the tasks fill whole rounds of the grid best
     uint32_t Q = 1;
     double best = 0.0;
@@ -463,12 +523,10 @@ LongStage launch_long(const SpmvArgs &a, const AutoSel *sel, int *carry_row, voi
         const double filled = (double)tasks / ((double)rounds * kLongGrid);
         if (rounds <= 4 && filled > best + 0.01) { best = filled; Q = q; }
     }
-    hipLaunchKernelGGL(long_multiply_kernel, dim3(kLongGrid), dim3(kLongWG), 0, st, a.rows, (uint32_t)a.cols, nnz, S, Q, a.ci, a.va,
+    hipLaunchKernelGGL(long_multiply_kernel, dim3(kLongGrid), dim3(kLongWG), 0, st, (uint32_t)a.cols, nnz, S, Q, a.ci, a.va,
                        a.x, numbers, static_cast<const uint32_t *>(cut), part, static_cast<const LongSkip *>(skip), L.skip_words, active,
-                       carry_row, sel);
-    hipLaunchKernelGGL(long_total_kernel, dim3(256), dim3(kWG), 0, st, S, static_cast<const LongNumbers *>(numbers),
-                       static_cast<const uint32_t *>(rows), static_cast<const float *>(part), a.y, sel);
-    return LongStage{skip, numbers, active};
+                       made);
+    return LongStage{skip, numbers, active, rows, part, S};
 }
 
 } // namespace seer

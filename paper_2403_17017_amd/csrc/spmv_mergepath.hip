@@ -21,7 +21,7 @@ __global__ __launch_bounds__(kWG) void spmv_mp_fixup_kernel(
     int rows, uint32_t n_tiles, const int *__restrict__ carry_row,
     const float *__restrict__ carry_val, float *__restrict__ y)
 {
-    mp_fixup_body(rows, n_tiles, carry_row, carry_val, y);
+    mp_fixup_body(rows, n_tiles, carry_row, carry_val, y, blockIdx.x * kWG + threadIdx.x);
 }
 
 uint32_t mp_num_tiles(int rows, int nnz, int ipt)

@@ -24,12 +24,11 @@ template <bool NT>
 __global__ __launch_bounds__(kWG, 8) void spmv_wo_long_kernel(
     int rows, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
-    int *__restrict__ carry_row, float *__restrict__ carry_val, uint32_t n_tiles, int remap, const GatherRanges g,
-    const LongStage longs)
+    uint32_t n_tiles, int remap, const GatherRanges g, const LongStage longs, const Meet meet)
 {
     __shared__ __attribute__((aligned(16))) float s_prod[bm_lds_words<kWoChunkLarge>()];
     __shared__ uint32_t s_bounds[2];
-    wo_long_body<true, NT>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, n_tiles, remap, s_prod, s_bounds, g, longs);
+    wo_long_body<true, NT>(rows, nnz, rp, ci, va, x, y, n_tiles, remap, s_prod, s_bounds, g, longs, meet);
 }
 
 uint32_t wo_num_tiles(int rows, int nnz)
@@ -58,10 +57,9 @@ void launch_wo(const SpmvArgs &a, bool vec, void *workspace, hipStream_t st)
     if (a.longs.skip) {
         const dim3 some(grid.x < kWoLongGrid ? grid.x : kWoLongGrid);
         if (a.nt) hipLaunchKernelGGL(spmv_wo_long_kernel<true>, some, dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, a.va, a.x, a.y,
-                                     carry_row, carry_val, n_tiles, a.remap, a.ranges, a.longs);
+                                     n_tiles, a.remap, a.ranges, a.longs, a.meet);
         else hipLaunchKernelGGL(spmv_wo_long_kernel<false>, some, dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, a.va, a.x, a.y,
-                                carry_row, carry_val, n_tiles, a.remap, a.ranges, a.longs);
-        launch_carry_fixup(a.rows, n_tiles, carry_row, carry_val, a.y, st);
+                                n_tiles, a.remap, a.ranges, a.longs, a.meet);
         return;
     }
 #define SEER_WO_LAUNCH(C, ...)                                                                                 \
