@@ -217,11 +217,11 @@ struct AutoShape {                          // launch shapes, all from rows and 
     int tm_pair;                            // ... and takes two rows per lane (tiles of 512 rows)
     int tm_remap;                           // CSR,TM's tile order: 1 XCD-contiguous, 0 round-robin
     GatherRanges ranges;                    // as in SpmvArgs; ticks: CSR,WO's
-    LongStage longs;                        // as in SpmvArgs
-    Meet meet, long_meet;                   // as in SpmvArgs; for CSR,WO beside long rows
     uint32_t bm_ticks, mp_ticks;
     int bm_ranged;                          // CSR,BM orders its gathers, too
     uint32_t reachable;                     // bit k: the tree can answer kernel k given rows, cols and nnz (never 0)
+    LongStage longs;                        // as in SpmvArgs
+    Meet meet, long_meet;                   // as in SpmvArgs; for CSR,WO beside long rows
 };
 constexpr size_t kAutoSelOffset = 32768;    // after the 1024 feature partials of 32 bytes
 constexpr size_t kAutoCarryOffset = 32768 + 256;

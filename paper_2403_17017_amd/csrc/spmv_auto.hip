@@ -162,12 +162,16 @@ __device__ __forceinline__ void auto_dispatch(
     }
 }
 
+// Eight waves per SIMD take at most 80 scalar registers each (800 in all, in sixteens, sixteen of every wave's the trap handler's):
+// with 85 a grid of 1024^2 under CSR,WM took 23.7 us a step instead of 19.2, under CSR,TM 15.6 instead of 15.2.
+#define SEER_EIGHT_WAVES __attribute__((amdgpu_num_sgpr(80)))
+
 template <int IPT, bool VEC, bool RANGED = false>
-__global__ __launch_bounds__(kWG, RANGED ? 8 : 1) void spmv_auto_kernel(
+__global__ SEER_EIGHT_WAVES __launch_bounds__(kWG, RANGED ? 8 : 1) void spmv_auto_kernel(
     int rows, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
     int *__restrict__ carry_row, float *__restrict__ carry_val, const AutoSel *__restrict__ sel,
-    const AutoShape shape, int remap)
+    int remap, const AutoShape shape)
 {
     __shared__ __attribute__((aligned(16))) int smem[kAutoLds];
     const int k = sel->kernel_id, no_longs = sel->no_longs;              // (one load)
@@ -178,11 +182,11 @@ __global__ __launch_bounds__(kWG, RANGED ? 8 : 1) void spmv_auto_kernel(
 // cols and nnz names the same kernel, so nothing is gathered.  Workgroup 0 leaves the record
 // (valid = 2: no statistics, known features only).
 template <int IPT, bool VEC, bool RANGED = false>
-__global__ __launch_bounds__(kWG, RANGED ? 8 : 1) void spmv_auto_decided_kernel(
+__global__ SEER_EIGHT_WAVES __launch_bounds__(kWG, RANGED ? 8 : 1) void spmv_auto_decided_kernel(
     int rows, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
     int *__restrict__ carry_row, float *__restrict__ carry_val, AutoSel *__restrict__ sel,
-    const AutoSel record, const AutoShape shape, int remap)
+    const AutoSel record, int remap, const AutoShape shape)
 {
     __shared__ __attribute__((aligned(16))) int smem[kAutoLds];
     if (blockIdx.x == 0 && threadIdx.x == 0) *sel = record;
@@ -205,11 +209,11 @@ __global__ __launch_bounds__(kWG, RANGED ? 8 : 1) void spmv_auto_decided_kernel(
 // to 4096 rows, and half of the code of eight, which every workgroup runs through for the first time:
 // 4096 rows of 16 5.87 -> 5.53 us a step, 1003 rows of 100 6.15 -> 5.80; more rows would take a second trip (5000 14.2 -> 14.6).
 template <int IPT, bool VEC, bool RPVEC, uint32_t RPU>
-__global__ __launch_bounds__(kWG) void spmv_auto_fused_kernel(
+__global__ SEER_EIGHT_WAVES __launch_bounds__(kWG) void spmv_auto_fused_kernel(
     int rows, int cols, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
     int *__restrict__ carry_row, float *__restrict__ carry_val, const FeatPartial *__restrict__ part,
-    uint32_t n_part, AutoSel *__restrict__ sel, const AutoHeap heap, const AutoShape shape, int remap)
+    uint32_t n_part, AutoSel *__restrict__ sel, const AutoHeap heap, int remap, const AutoShape shape)
 {
     __shared__ __attribute__((aligned(16))) int smem[kAutoLds];
     __shared__ FeatLds s;
@@ -332,7 +336,7 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
             shape.longs = launch_long(a, LongSelect{}, long_workspace, st);
 #define SEER_DECIDED_LAUNCH(...)                                                                           \
     hipLaunchKernelGGL((spmv_auto_decided_kernel<__VA_ARGS__>), dim3(grid), dim3(kWG), 0, st, a.rows, a.nnz, a.rp, \
-                       a.ci, a.va, a.x, a.y, carry_row, carry_val, sel, *decided, shape, a.remap)
+                       a.ci, a.va, a.x, a.y, carry_row, carry_val, sel, *decided, a.remap, shape)
         if (shape.ranges.count) {
             if (shape.mp_ipt == kMpIptSmall) SEER_DECIDED_LAUNCH(kMpIptSmall, true, true);
             else SEER_DECIDED_LAUNCH(kMpIptLarge, true, true);
@@ -354,7 +358,7 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
 #define SEER_FUSED_LAUNCH(I, V, R) SEER_FUSED_LAUNCH_BY(I, V, R, 8)
 #define SEER_FUSED_LAUNCH_BY(I, V, R, U)                                                                    \
     hipLaunchKernelGGL((spmv_auto_fused_kernel<I, V, R, U>), dim3(grid), dim3(kWG), 0, st, a.rows, a.cols, a.nnz, \
-                       a.rp, a.ci, a.va, a.x, a.y, carry_row, carry_val, part, n_part, sel, *heap, shape, a.remap)
+                       a.rp, a.ci, a.va, a.x, a.y, carry_row, carry_val, part, n_part, sel, *heap, a.remap, shape)
         if (shape.mp_ipt == kMpIptSmall && vec && rp_vec && a.rows <= (int)(kWG * 16u)) {
             SEER_FUSED_LAUNCH_BY(kMpIptSmall, true, true, 4);
         } else if (shape.mp_ipt == kMpIptSmall) {
@@ -403,7 +407,7 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
     if (longs && !long_select) shape.longs = launch_long(a, LongSelect{nullptr, nullptr, sel, 0, true}, long_workspace, st);
 #define SEER_AUTO_LAUNCH(...)                                                                              \
     hipLaunchKernelGGL((spmv_auto_kernel<__VA_ARGS__>), dim3(grid), dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, \
-                       a.va, a.x, a.y, carry_row, carry_val, sel, shape, a.remap)
+                       a.va, a.x, a.y, carry_row, carry_val, sel, a.remap, shape)
     if (shape.ranges.count) {
         if (shape.mp_ipt == kMpIptSmall) SEER_AUTO_LAUNCH(kMpIptSmall, true, true);
         else SEER_AUTO_LAUNCH(kMpIptLarge, true, true);
