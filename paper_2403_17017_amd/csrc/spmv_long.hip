@@ -13,7 +13,7 @@
 // The cuts are right for any order of columns: a cut is a place in the row, cuts never descend
 // (each is raised to the ones before it), and an entry whose column lies outside the slab of its piece
 // is gathered from x.
-// 472 M nonzeros, Zipf s = 1.6: list 10 us, cuts 80, products 680 (nine tenths of the nonzeros, read at 5.0 TB/s),
+// 472 M nonzeros, Zipf s = 1.6: list 10 us, cuts 80, products 598 (nine tenths of the nonzeros, read at 5.7 TB/s),
 // CSR,WO over the rest and the sums 415; all of them by CSR,WO 2370.  Tried: rows from 16 entries per slab on, the same
 // with twice the scratch memory; a wave per piece from 128 entries on, 1289 in all against 1255 at the time.
 // CSR,WO over the rest took 513 while every chunk had a workgroup, to find nothing in four of five, and its gather
@@ -334,17 +334,24 @@ template <uint32_t G>
 __device__ __forceinline__ void long_pieces(
     uint32_t j0, uint32_t n, uint32_t q, uint32_t Q, uint32_t N, uint32_t s, uint32_t c0, uint32_t nc, uint32_t nnz,
     const int *__restrict__ ci, const float *__restrict__ va, const float *__restrict__ x, const float *__restrict__ s_x,
-    const uint32_t *__restrict__ cut, float *__restrict__ part)
+    const uint32_t *__restrict__ cut, float *__restrict__ part, uint32_t *s_next /* LDS; G = 64 */)
 {
     constexpr uint32_t U = 2, kGroups = kLongWG / G;
     const uint32_t lg = threadIdx.x % G, group = threadIdx.x / G;
     const uint32_t *lo = cut + (size_t)s * N + j0, *hi = lo + N;
     const uint32_t stride = Q * kGroups;
-    uint32_t i = q + Q * group;
+    // Pieces for a whole wave differ the most in length, 256 to 3300 entries: a wave takes the next one when it is through with
+    // the last.  With every sixteenth piece for each wave: 472 M nonzeros 680 us instead of 598, 53 M 106 and 96, 46 M 66 and 61.
+    const auto grab = [&] {
+        uint32_t g = 0;
+        if (threadIdx.x % kWave == 0) g = atomicAdd(s_next, 1u);
+        return q + Q * (uint32_t)__builtin_amdgcn_readfirstlane((int)g);
+    };
+    uint32_t i = G == kWave ? grab() : q + Q * group;
     uint32_t a = i < n ? lo[i] : 0u, e = i < n ? hi[i] : 0u;
     // whole waves go on together (the sum below is over lanes): until no group of the wave has a piece
     while (__ballot(i < n)) {
-        const uint32_t next = i + stride;
+        const uint32_t next = G == kWave ? grab() : i + stride;
         const uint32_t na = next < n ? lo[next] : 0u, ne = next < n ? hi[next] : 0u;
         float t[4] = {0.f, 0.f, 0.f, 0.f};
         for (uint32_t k0 = a + 4u * lg; k0 < e; k0 += 4u * G * U) {
@@ -395,6 +402,7 @@ __global__ __launch_bounds__(kLongWG) void long_multiply_kernel(
     const AutoSel *__restrict__ sel)
 {
     __shared__ __attribute__((aligned(16))) float s_x[kLongCols];
+    __shared__ uint32_t s_next;
     if (sel && sel->kernel_id != SEER_CSR_WO) return;
     const uint32_t n[kLongClasses] = {numbers->n[0], numbers->n[1], numbers->n[2]}, N = numbers->all, tid = threadIdx.x;
     if (N == 0) return;
@@ -428,6 +436,7 @@ __global__ __launch_bounds__(kLongWG) void long_multiply_kernel(
         const uint32_t s = task / Q, q = task - s * Q;
         const uint32_t c0 = s << kLongShift, nc = min(cols - c0, kLongCols);
         __syncthreads();                                        // the slab before has been used
+        if (tid == 0) s_next = 0;
         {
             v4f t[kLongCols / 4u / kLongWG];
 #pragma unroll
@@ -447,9 +456,9 @@ __global__ __launch_bounds__(kLongWG) void long_multiply_kernel(
                 *reinterpret_cast<v4f *>(s_x + 4u * (m * kLongWG + tid)) = t[m];
         }
         __syncthreads();
-        long_pieces<64>(n[0] + n[1], n[2], q, Q, N, s, c0, nc, nnz, ci, va, x, s_x, cut, part);
-        long_pieces<16>(n[0], n[1], q, Q, N, s, c0, nc, nnz, ci, va, x, s_x, cut, part);
-        long_pieces<8>(0u, n[0], q, Q, N, s, c0, nc, nnz, ci, va, x, s_x, cut, part);
+        long_pieces<64>(n[0] + n[1], n[2], q, Q, N, s, c0, nc, nnz, ci, va, x, s_x, cut, part, &s_next);
+        long_pieces<16>(n[0], n[1], q, Q, N, s, c0, nc, nnz, ci, va, x, s_x, cut, part, &s_next);
+        long_pieces<8>(0u, n[0], q, Q, N, s, c0, nc, nnz, ci, va, x, s_x, cut, part, &s_next);
     }
 }
 
