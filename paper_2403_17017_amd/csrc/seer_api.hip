@@ -213,9 +213,9 @@ uint32_t gather_ticks(const GatherRanges &g, int64_t nnz, double entries_per_wg)
 // gains far below it: 471 M nonzeros 2385 and 1255 us, 171 M 926 and 598, 44 M 288 and 255, 32 M 214 and 185; a
 // program that knows its rows sets the knob.
 // That is for a matrix that is not looked at.  Where features are gathered (auto_long_rows) the first pass sees the long
-// rows, and a matrix without pays for one launch and a longer selection, 2 to 4 us: from 2^25 nonzeros on.  Steps, us
-// without and with: Zipf rows, 47 M nonzeros in 2 M columns 317 and 247, 53 M in 3 M 441 and 270; without long
-// rows, 40 M random 286.5 and 288.5, 48 M 363 and 366.5, a band of 21 77 and 80.5, a 7-point grid of 200^3 106.5 both.
+// rows, and a matrix without pays for one launch and a longer selection, 2 to 6 us: from 2^25 nonzeros on.  Steps, us
+// without and with: Zipf rows, 47 M nonzeros in 2 M columns 310 and 244, 53 M in 3 M 441 and 270; without long
+// rows, 40 M random 286.5 and 289, 48 M 360 and 367, a band of 21 (40 M) 75 and 80.5, a 7-point grid of 200^3 106.5 both.
 // Below, Zipf rows (33 M, s = 2.0) 299 and 273, 18 M random 133 and 137, a band of 11 (19 M) 40.5 and 44.
 // The "long_rows" knob: 0 never, 1 from 2^23 nonzeros on, whatever the mean.
 bool auto_long_rows(int rows, int nnz)

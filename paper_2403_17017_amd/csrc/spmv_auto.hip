@@ -85,7 +85,10 @@ static_assert(bm_lds_words<kWoChunk>() + 2 <= kAutoLds, "CSR,WO's products and i
 
 // This workgroup's share of schedule k (the same k in every workgroup of the grid).
 // RANGED: with gathers ordered by column range (shape.ranges), as the stand-alone kernels.
-template <int IPT, bool VEC, bool RANGED = false>
+// LONGS: long rows of CSR,WO may go apart (shape.longs; from 2^23 nonzeros on, where cut rows don't meet); an instance
+// of its own, because what that form needs of the arguments leaves too few scalar registers for the others (67 were kept
+// in vector lanes, 14 without; a band of 21, 29 M nonzeros, 60.0 and 58.7 us a step).
+template <int IPT, bool VEC, bool RANGED = false, bool LONGS = false>
 __device__ __forceinline__ void auto_dispatch(
     int k, int rows, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
@@ -113,8 +116,9 @@ __device__ __forceinline__ void auto_dispatch(
         }
         return;
     }
-    if constexpr (RANGED) {
-        if (k == SEER_CSR_WO && shape.longs.skip && !no_longs) {      // (from 2^23 nonzeros on: the larger chunks)
+    static_assert(RANGED || !LONGS, "long rows go apart where gathers go by range");
+    if constexpr (LONGS) {
+        if (k == SEER_CSR_WO && !no_longs) {      // (from 2^23 nonzeros on: the larger chunks)
             static_assert(bm_lds_words<kWoChunkLarge>() + 2 <= kAutoLds, "LDS overlay too small");
             wo_long_body<VEC, true>(rows, nnz, rp, ci, va, x, y, n_tiles, remap, reinterpret_cast<float *>(smem),
                                     reinterpret_cast<uint32_t *>(smem) + bm_lds_words<kWoChunkLarge>(), shape.ranges, shape.longs, shape.long_meet);
@@ -158,7 +162,7 @@ __device__ __forceinline__ void auto_dispatch(
     } else {
         GatherRanges g = shape.ranges;
         g.ticks = shape.mp_ticks;
-        mp_body<IPT, VEC, true, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile, smem, g, shape.meet);
+        mp_body<IPT, VEC, true, RANGED>(rows, nnz, rp, ci, va, x, y, carry_row, carry_val, tile, smem, g, LONGS ? Meet{} : shape.meet);
     }
 }
 
@@ -166,7 +170,7 @@ __device__ __forceinline__ void auto_dispatch(
 // with 85 a grid of 1024^2 under CSR,WM took 23.7 us a step instead of 19.2, under CSR,TM 15.6 instead of 15.2.
 #define SEER_EIGHT_WAVES __attribute__((amdgpu_num_sgpr(80)))
 
-template <int IPT, bool VEC, bool RANGED = false>
+template <int IPT, bool VEC, bool RANGED = false, bool LONGS = false>
 __global__ SEER_EIGHT_WAVES __launch_bounds__(kWG, RANGED ? 8 : 1) void spmv_auto_kernel(
     int rows, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
@@ -175,13 +179,13 @@ __global__ SEER_EIGHT_WAVES __launch_bounds__(kWG, RANGED ? 8 : 1) void spmv_aut
 {
     __shared__ __attribute__((aligned(16))) int smem[kAutoLds];
     const int k = sel->kernel_id, no_longs = sel->no_longs;              // (one load)
-    auto_dispatch<IPT, VEC, RANGED>(k, rows, nnz, rp, ci, va, x, y, carry_row, carry_val, shape, remap, smem, no_longs != 0);
+    auto_dispatch<IPT, VEC, RANGED, LONGS>(k, rows, nnz, rp, ci, va, x, y, carry_row, carry_val, shape, remap, smem, no_longs != 0);
 }
 
 // The product when the host could decide alone: every leaf the tree can reach from rows,
 // cols and nnz names the same kernel, so nothing is gathered.  Workgroup 0 leaves the record
 // (valid = 2: no statistics, known features only).
-template <int IPT, bool VEC, bool RANGED = false>
+template <int IPT, bool VEC, bool RANGED = false, bool LONGS = false>
 __global__ SEER_EIGHT_WAVES __launch_bounds__(kWG, RANGED ? 8 : 1) void spmv_auto_decided_kernel(
     int rows, int nnz, const int *__restrict__ rp, const int *__restrict__ ci,
     const float *__restrict__ va, const float *__restrict__ x, float *__restrict__ y,
@@ -190,7 +194,7 @@ __global__ SEER_EIGHT_WAVES __launch_bounds__(kWG, RANGED ? 8 : 1) void spmv_aut
 {
     __shared__ __attribute__((aligned(16))) int smem[kAutoLds];
     if (blockIdx.x == 0 && threadIdx.x == 0) *sel = record;
-    auto_dispatch<IPT, VEC, RANGED>(record.kernel_id, rows, nnz, rp, ci, va, x, y, carry_row, carry_val, shape, remap, smem);
+    auto_dispatch<IPT, VEC, RANGED, LONGS>(record.kernel_id, rows, nnz, rp, ci, va, x, y, carry_row, carry_val, shape, remap, smem);
 }
 
 // Selection inside the product's launch.  The first wave of every workgroup finishes the
@@ -337,7 +341,10 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
 #define SEER_DECIDED_LAUNCH(...)                                                                           \
     hipLaunchKernelGGL((spmv_auto_decided_kernel<__VA_ARGS__>), dim3(grid), dim3(kWG), 0, st, a.rows, a.nnz, a.rp, \
                        a.ci, a.va, a.x, a.y, carry_row, carry_val, sel, *decided, a.remap, shape)
-        if (shape.ranges.count) {
+        if (shape.longs.skip) {
+            if (shape.mp_ipt == kMpIptSmall) SEER_DECIDED_LAUNCH(kMpIptSmall, true, true, true);
+            else SEER_DECIDED_LAUNCH(kMpIptLarge, true, true, true);
+        } else if (shape.ranges.count) {
             if (shape.mp_ipt == kMpIptSmall) SEER_DECIDED_LAUNCH(kMpIptSmall, true, true);
             else SEER_DECIDED_LAUNCH(kMpIptLarge, true, true);
         } else if (shape.mp_ipt == kMpIptSmall) {
@@ -408,7 +415,10 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
 #define SEER_AUTO_LAUNCH(...)                                                                              \
     hipLaunchKernelGGL((spmv_auto_kernel<__VA_ARGS__>), dim3(grid), dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, \
                        a.va, a.x, a.y, carry_row, carry_val, sel, a.remap, shape)
-    if (shape.ranges.count) {
+    if (shape.longs.skip) {
+        if (shape.mp_ipt == kMpIptSmall) SEER_AUTO_LAUNCH(kMpIptSmall, true, true, true);
+        else SEER_AUTO_LAUNCH(kMpIptLarge, true, true, true);
+    } else if (shape.ranges.count) {
         if (shape.mp_ipt == kMpIptSmall) SEER_AUTO_LAUNCH(kMpIptSmall, true, true);
         else SEER_AUTO_LAUNCH(kMpIptLarge, true, true);
     } else if (shape.mp_ipt == kMpIptSmall) {
