@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/seer.h"
+#include "meet.hiph"
 
 namespace seer {
 
@@ -40,14 +41,6 @@ struct LongStage {
     const float *part = nullptr;
     uint32_t slabs = 0;
 };
-
-// Where the parts of a row that a tile boundary cuts meet (meet_row): a slot of 64 bytes per boundary, slots null:
-// the parts go out as carries.  The marks are the process's own.
-struct Meet {
-    unsigned long long *slots = nullptr;
-    uint32_t mark = 0, proof = 0;
-};
-constexpr uint32_t kMeetWords = 8;
 
 struct SpmvArgs {
     int rows, cols, nnz;
