@@ -27,10 +27,15 @@
  *     is written.  Nothing throws or aborts.  Matrix contents (monotone row_ptr,
  *     column range) are NOT validated: they are the caller's contract.
  *   - The first seer_features or seer_csr_check call, or preparation of SEER_ELL_TM or SEER_CSR_S,
- *     allocates 4096 bytes of pinned host memory per process (64 result mailboxes); but for the
- *     array of seer_spmv_auto_static no other state is kept, on the host or the device.
- *   - Calls that use the same workspace must not overlap in time.  Such calls of different threads
- *     run side by side, up to 64 of them; a further one waits until one of those has ended.
+ *     allocates 4096 bytes of pinned host memory per process (64 result mailboxes).  Such calls of different
+ *     threads run side by side, up to 64 of them; a further one waits until one of those has ended.
+ *     A random number and a count of calls, by which products tell their own sums in a workspace from
+ *     what it held before, are the process's, too; but for these and the array of
+ *     seer_spmv_auto_static no state is kept, on the host or the device.
+ *   - Calls that use the same workspace must not overlap in time.  If they do, their results are
+ *     undefined; later calls on it are right again.  Replays of a captured product count as the one call
+ *     that was captured: one that has overlapped another call is to be captured again, or the same product run once
+ *     on that workspace by a call of its own, before it is replayed again.
  */
 #ifndef SEER_H
 #define SEER_H
@@ -237,10 +242,12 @@ size_t seer_spmv_auto_workspace_bytes(int32_t rows, int32_t nnz);
  *     sums them so, the launches differ, and the order of those rows' sums.
  *   - The first call on a device looks the array's address up (hipGetSymbolAddress, with
  *     that device current); make that call before capturing a graph.
- *   - All calls on one GPU share the one array, and it keeps the last call's contents; the
- *     kernels overwrite every word they later read, so nothing needs clearing.  Two calls
+ *   - All calls on one GPU share the one array, and it keeps the last call's contents; what an
+ *     earlier call left there is no later call's, so nothing needs clearing.  Two calls
  *     on the same GPU must not overlap in time: on different streams without an ordering
- *     between them they race on the array and both results are undefined.
+ *     between them they race on the array and both results are undefined, those of later calls are not.
+ *     A captured product that has overlapped another call is to be captured again, or the same product
+ *     run once by a call of its own: its replays count as one call (see above).
  *   - There is no way to ask what was selected (seer_spmv_auto_result takes a workspace). */
 #define SEER_STATIC_SCRATCH_BYTES (2u << 20)
 int seer_spmv_auto_static(const seer_csr *A, const seer_tree *tree, const float *x, float *y,

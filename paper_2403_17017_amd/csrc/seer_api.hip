@@ -57,19 +57,19 @@ std::atomic<int> g_tune_coo_runs{-1};
 std::atomic<int> g_tune_slab_shift{-1};
 std::atomic<int> g_tune_gather_range{-1};
 
-// The marks by which a product knows the sums in its slots (meet_next) from what a workspace held before: random, the process's own.
+// The marks by which a product knows the sums in its slots (meet_next) from what a workspace held before: random, and the
+// call's own.
 Meet meet_in(void *slots)
 {
-    static const uint64_t marks = [] {
+    static std::atomic<uint64_t> calls{0};
+    static const uint64_t random = [] {
         uint64_t m = 0;
         if (getrandom(&m, sizeof m, GRND_NONBLOCK) != (ssize_t)sizeof m)
             m = ((uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() ^ (uint64_t)reinterpret_cast<uintptr_t>(&g_scratch_mutex)) *
                 0x9E3779B97F4A7C15ull;
         return m;
     }();
-    const uint32_t mark = (uint32_t)(marks >> 32) | 1u;          // (a slot at rest is zero)
-    const uint32_t proof = (uint32_t)marks == mark ? mark ^ 2u : (uint32_t)marks;
-    return Meet{static_cast<unsigned long long *>(slots), mark, proof};
+    return meet_of_call(slots, random, calls.fetch_add(1, std::memory_order_relaxed));
 }
 Meet meet_at(void *slots, size_t bytes, int rows, int nnz, uint32_t n_tiles)
 {

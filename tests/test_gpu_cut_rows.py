@@ -111,3 +111,28 @@ def test_cut_rows_same_bits_on_every_run(kid):
     for y in runs:
         S.seer_spmv(kid, A, x, y, workspace=ws)
     assert torch.equal(runs, runs[:1].expand_as(runs))
+
+
+@pytest.mark.parametrize("kid", [S.CSR_WO, S.CSR_MP])
+@pytest.mark.parametrize("call", ["direct", "auto"])
+def test_marks_are_the_calls_own(kid, call):
+    """What one call leaves in the slots is never taken for another call's: the second words show its proof."""
+    import torch
+    A, rp, ci, va = matrix(lengths()["one row"], 5)
+    x = torch.ones(COLS, device="cuda:0")
+    y = torch.empty(A.rows, device="cuda:0")
+    ws = torch.zeros(1 << 20, dtype=torch.uint8, device="cuda:0")
+    announce(f"marks of each call, kernel {kid}, {call}")
+    slots = 0 if call == "direct" else 33024                 # (behind the partials and the record)
+    seen = set()
+    for k in range(4):
+        if call == "auto":
+            S.seer_spmv_auto(A, S.Tree.constant(kid), x, y, ws)
+        else:
+            S.seer_spmv(kid, A, x, y, workspace=ws)
+        words = ws[slots:slots + 64 * 16].cpu().numpy().view(np.uint64).reshape(16, 8)
+        assert not words[:, 0].any()                         # at rest
+        proofs = set((words[:, 1] >> np.uint64(32)).tolist())
+        assert len(proofs) == 1 and not proofs & seen, (k, proofs, seen)
+        seen |= proofs
+        assert np.array_equal(y.cpu().numpy(), product(rp, ci, va, np.ones(COLS, dtype=np.float32)))

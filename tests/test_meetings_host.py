@@ -145,6 +145,35 @@ int main(int, char **argv)
                 })) ++bad;
             if (!run(slots, [&](int n) { return (int)(rng() % n); })) ++bad;       // and the next product
         }
+    } else if (!std::strcmp(what, "left over")) {
+        // sums of an earlier call in any slots, as two calls at a time leave them, then calls in order
+        for (int k = 0; k < 4000; ++k) {
+            ts = rng() % 20; te = ts + 1 + rng() % 6;
+            std::vector<Word> slots = at_rest;
+            const uint64_t random = (uint64_t)rng() << 32 | rng();
+            const uint64_t call = k % 5 == 0 ? (0ull - random) / 3 : rng();
+            const Meet old = seer::meet_of_call(slots.data(), random, call);
+            for (size_t b = 0; b < slots.size() / 8; ++b)
+                if (rng() % 2) {
+                    const uint32_t bits = __builtin_bit_cast(uint32_t, 1e6f + (float)(rng() % 1000));
+                    slots[8 * b] = word(old.mark, bits);
+                    slots[8 * b + 1] = word(old.proof, bits);
+                }
+            for (uint64_t later = 1; later < 4; ++later) {
+                meet = seer::meet_of_call(slots.data(), random, call + later);
+                if (!run(slots, [&](int n) { return (int)(rng() % n); })) ++bad;
+            }
+            meet = old;                                  // a replay of the earlier call after them
+            if (!run(slots, [&](int n) { return (int)(rng() % n); })) ++bad;
+        }
+    } else if (!std::strcmp(what, "marks")) {
+        for (int k = 0; k < 200000; ++k) {
+            const uint64_t random = (uint64_t)rng() << 32 | rng(), call = rng(), apart = 1 + rng() % 100000;
+            const Meet a = seer::meet_of_call(nullptr, random, call), b = seer::meet_of_call(nullptr, random, call + apart);
+            if ((a.mark == b.mark && a.proof == b.proof) || a.mark == 0 || b.mark == 0) ++bad;
+        }
+    } else {
+        return 2;
     }
     return bad != 0;
 }
@@ -160,7 +189,7 @@ def driver(tmp_path_factory):
     return str(d / "driver")
 
 
-@pytest.mark.parametrize("what", ["orders", "many", "anything"])
+@pytest.mark.parametrize("what", ["orders", "many", "anything", "left over", "marks"])
 def test_cut_rows_meet_in_any_order(driver, what):
     out = subprocess.run([driver, what], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0, out.stdout[-2000:]
