@@ -130,3 +130,16 @@ def test_deep_trees_misaligned_offsets_and_little_memory(matrix):
     plain = torch.empty_like(y)
     S.seer_spmv(S.CSR_WO, A, x, plain)
     assert torch.equal(auto(A, tree(S.CSR_WO), x, small, S.CSR_WO), plain)
+
+
+def test_short_rows_have_the_bits_of_the_direct_product(matrix):
+    """Rows too short to go apart are added up as without the stage, also in a chunk that a long row shares."""
+    import torch
+    name, A, x, _, _ = matrix
+    announce(f"rows beside long rows {name}")
+    ws = S.alloc_workspace(S.spmv_auto_workspace_bytes(A.rows, A.nnz))
+    y = auto(A, tree(S.CSR_WO), x, ws, S.CSR_WO)
+    plain = torch.empty_like(y)
+    S.seer_spmv(S.CSR_WO, A, x, plain)
+    short = A.row_ptr[1:] - A.row_ptr[:-1] < LEAST
+    assert int((y != plain)[short].sum()) == 0
