@@ -187,7 +187,8 @@ struct AutoSel {                            // what the selection leaves in the 
 };
 // The long rows of CSR,WO with slabs of x in LDS.  select.sel: null: CSR,WO it is; else the selection.  select.heap: null: it
 // has been made (nothing is done unless it says CSR,WO); else it is made here: the first pass leaves the feature partials in
-// select.part, too, and the next launch the selection (select.all: however few entries long rows have).  What CSR,WO (chunks of
+// select.part, too, and the next launch the selection.  Where there is a selection, long rows of few entries together stay
+// (select.all: however few they have, they go).  What CSR,WO (chunks of
 // kWoChunkLarge entries) is told lies in the workspace, which begins with the slots where its cut rows meet: beside long rows it
 // leaves no carries, and it writes the long rows' y.
 struct FeatPartial;

@@ -411,7 +411,7 @@ void launch_auto(const SpmvArgs &a, const AutoTree &tree, const AutoHeap *heap, 
 #undef SEER_WAVE_LAUNCH
 #undef SEER_SELECT_LAUNCH
 
-    if (longs && !long_select) shape.longs = launch_long(a, LongSelect{nullptr, nullptr, sel, 0, true}, long_workspace, st);
+    if (longs && !long_select) shape.longs = launch_long(a, LongSelect{nullptr, nullptr, sel, 0, policy.long_all != 0}, long_workspace, st);
 #define SEER_AUTO_LAUNCH(...)                                                                              \
     hipLaunchKernelGGL((spmv_auto_kernel<__VA_ARGS__>), dim3(grid), dim3(kWG), 0, st, a.rows, a.nnz, a.rp, a.ci, \
                        a.va, a.x, a.y, carry_row, carry_val, sel, a.remap, shape)

@@ -206,8 +206,8 @@ __device__ __forceinline__ uint32_t long_numbers(
 // found, then widens in steps that double; every one ends at the row's ends at the latest.  The words per
 // chunk are set here, too, and the rows listed by number for the last pass.
 // SELECT: the selection is made here (every workgroup for itself if there are long rows, the first one leaves the
-// record), from one partial per part; and long rows of fewer than kLongLeast entries together stay where they are: cutting
-// them and a launch for their pieces take some 25 us, a gather saved 4.5 ps (4 M rows, Zipf s = 2.0, 12 M such entries:
+// record), from one partial per part.  Where the device selects, here or before, long rows of fewer than kLongLeast entries
+// together stay where they are: cutting them and a launch for their pieces take some 25 us, a gather saved 4.5 ps (4 M rows, Zipf s = 2.0, 12 M such entries:
 // 300 and 280 us a step; s = 2.3, 0.6 M: 140 and 179).
 constexpr uint32_t kLongLeast = 1u << 23;
 struct LongFeatures { int rows; const int *rp; const FeatPartial *part; uint32_t reachable, least /* entries of long rows for them to go apart */; };
@@ -245,6 +245,10 @@ __global__ __launch_bounds__(kLongWG) void long_cut_kernel(
     }
     uint32_t entries = 0, whole = 0;
     const uint32_t N = long_numbers(parts, of, s_from, s_w, s_n, entries, whole);
+    if (!SELECT && sel && entries < f.least) {                   // (their number is zero since the launch before)
+        if (blockIdx.x == 0 && threadIdx.x == 0) sel->no_longs = 1;
+        return;
+    }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         for (uint32_t k = 0; k < kLongClasses; ++k) numbers->n[k] = s_n[k];
         numbers->all = N;

@@ -143,3 +143,20 @@ def test_short_rows_have_the_bits_of_the_direct_product(matrix):
     S.seer_spmv(S.CSR_WO, A, x, plain)
     short = A.row_ptr[1:] - A.row_ptr[:-1] < LEAST
     assert int((y != plain)[short].sum()) == 0
+
+
+@pytest.mark.parametrize("walk", ["deep", "workgroup"])
+def test_few_long_rows_stay_whoever_selects(matrix, walk):
+    """A tree that the nodes are walked for, or a selection by a workgroup: the same rows go apart as where one wave selects."""
+    import torch
+    name, A, x, _, _ = matrix
+    announce(f"gathered long rows {name}, selection {walk}")
+    ws = S.alloc_workspace(S.spmv_auto_workspace_bytes(A.rows, A.nnz))
+    y = auto(A, tree(S.CSR_WO), x, ws, S.CSR_WO)
+    t = deep_tree(S.CSR_WO) if walk == "deep" else tree(S.CSR_WO)
+    S.set_tuning("auto_select_wave", 0 if walk == "workgroup" else -1)
+    try:
+        z = auto(A, t, x, ws, S.CSR_WO)
+    finally:
+        S.set_tuning("auto_select_wave", -1)
+    assert torch.equal(z, y)
