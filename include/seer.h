@@ -224,7 +224,9 @@ size_t seer_spmv_workspace_bytes(int kernel_id, int32_t rows, int32_t nnz);
  * SEER_NUM_DIRECT_KERNELS (SEER_ETREE otherwise; validated before anything is
  * enqueued).  f[SEER_F_ITERATIONS] is 1 on this path.
  * workspace: DEVICE, 16-byte aligned, >= seer_spmv_auto_workspace_bytes(rows, nnz);
- * it must stay untouched until the work has run. */
+ * it must stay untouched until the work has run.  A smaller one is accepted, too, down to what the
+ * selection and the carries take (33 024 bytes and 8 for each workgroup of CSR,MP or CSR,WO, whichever has more): cut rows do
+ * not meet there then, as in seer_spmv with its smaller workspace, nor are long rows of CSR,WO summed apart. */
 int seer_spmv_auto(const seer_csr *A, const seer_tree *tree, const float *x, float *y,
                    void *workspace, size_t workspace_bytes, void *stream);
 size_t seer_spmv_auto_workspace_bytes(int32_t rows, int32_t nnz);

@@ -72,7 +72,8 @@ void launch_wo(const SpmvArgs &a, bool vec, void *workspace, hipStream_t st);
 size_t carry_workspace_bytes(uint32_t n_tiles);
 // Cut rows meet inside the product (no carries, no fix-up launch) below 2^23 nonzeros and at up to 2^25 rows (so that the
 // slots fit seer_spmv_auto_static's array), if
-// the workspace has the room: by the sizes alone, so that every path to CSR,MP or CSR,WO adds a row up in the same order.
+// the workspace has the room: with workspaces of the sizes that the size functions give, every path to CSR,MP or CSR,WO adds a row
+// up in the same order; with less, but room for carries, each goes on as before there were meetings, in the order of the fix-up.
 // From 2^23 nonzeros on a product takes 35 us and more, of which the launch is 3.
 inline bool meet_applies(int rows, int nnz) { return nnz < (1 << 23) && rows <= (1 << 25); }
 inline size_t meet_workspace_bytes(uint32_t n_tiles) { return (size_t)n_tiles * kMeetWords * 8; }

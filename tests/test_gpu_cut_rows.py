@@ -136,3 +136,29 @@ def test_marks_are_the_calls_own(kid, call):
         assert len(proofs) == 1 and not proofs & seen, (k, proofs, seen)
         seen |= proofs
         assert np.array_equal(y.cpu().numpy(), product(rp, ci, va, np.ones(COLS, dtype=np.float32)))
+
+
+@pytest.mark.parametrize("kid", [S.CSR_WO, S.CSR_MP])
+def test_less_workspace_gives_the_bits_of_the_direct_product_with_less(kid):
+    """Both calls take a workspace with room for carries alone, and add cut rows up in the same order then."""
+    import torch
+    A, *_ = matrix(lengths()["rows over several tiles"], 6)
+    A.values.copy_(torch.rand(A.nnz, device="cuda:0"))
+    x = torch.rand(COLS, device="cuda:0")
+    announce(f"cut rows, little workspace, kernel {kid}")
+
+    def run(auto, ws):
+        y = torch.full((A.rows,), float("nan"), device="cuda:0")
+        if auto:
+            S.seer_spmv_auto(A, S.Tree.constant(kid), x, y, ws)
+        else:
+            S.seer_spmv(kid, A, x, y, workspace=ws)
+        return y
+
+    carries = carries_bytes(max(-(-A.nnz // CHUNK), -(-(A.rows + A.nnz) // MP_TILE)))
+    few, much = (torch.zeros(n, dtype=torch.uint8, device="cuda:0") for n in (33024 + carries, 4 << 20))
+    assert few.numel() < S.spmv_auto_workspace_bytes(A.rows, A.nnz)
+    assert torch.equal(run(True, few), run(False, few[:carries]))
+    assert torch.equal(run(True, much), run(False, much))
+    with pytest.raises(S.SeerError):
+        run(True, few[:-256])
