@@ -463,8 +463,8 @@ int seer_csr_check(const seer_csr *A, int64_t *bad_row_ptr, int64_t *bad_col_idx
  *               column range and the workspace has room; default: from 2^28 nonzeros on with 64
  *               or more to a row on average and at most 2^22 rows, and in seer_spmv_auto, where it
  *               gathers the features, from 2^25 nonzeros on at as many rows, if such rows hold 2^23
- *               entries or more together.  The size functions of CSR,WO and
- *               seer_spmv_auto follow it, whatever the columns; with less workspace (their sizes under 0)
+ *               entries or more together (a matrix without them pays for one launch there, 2 to 4
+ *               us).  The size functions of CSR,WO and seer_spmv_auto follow it, whatever the columns; with less workspace (their sizes under 0)
  *               the stage is left out, as it is where gathers do not go by range, so that no more is
  *               needed for matrices of at most 1 310 720 or more than 2^25 columns
  *   "slab_bins" CSR,S: 0: never in bins; 1: in bins whatever nnz is, however local the columns

@@ -74,7 +74,10 @@ size_t carry_workspace_bytes(uint32_t n_tiles);
 // slots fit seer_spmv_auto_static's array), if
 // the workspace has the room: with workspaces of the sizes that the size functions give, every path to CSR,MP or CSR,WO adds a row
 // up in the same order; with less, but room for carries, each goes on as before there were meetings, in the order of the fix-up.
-// From 2^23 nonzeros on a product takes 35 us and more, of which the launch is 3.
+// From 2^23 nonzeros on, the wait for an exchange at the end of every workgroup, over several generations of them, is more than
+// the launch where columns are near each other.  Products and steps at those sizes, us with the launch and with meetings: a band of 61 (61 M
+// nonzeros), CSR,WO 94 and 102, CSR,MP 127 and 136; a band of 21 (40 M) 80 and 83; rows of 10 000 (30 M) 151 and 158.5; 8 M short
+// rows (23 M) 146.2 and 147.4; scattered columns, 10 M 67.5 and 66.8, 20 M 145.0 and 144.5, Zipf rows (32 M) 219.2 and 217.4.
 inline bool meet_applies(int rows, int nnz) { return nnz < (1 << 23) && rows <= (1 << 25); }
 inline size_t meet_workspace_bytes(uint32_t n_tiles) { return (size_t)n_tiles * kMeetWords * 8; }
 void launch_carry_fixup(int rows, uint32_t n_tiles, const int *carry_row, const float *carry_val, float *y,

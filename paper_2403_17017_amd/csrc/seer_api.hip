@@ -213,10 +213,13 @@ uint32_t gather_ticks(const GatherRanges &g, int64_t nnz, double entries_per_wg)
 // gains far below it: 471 M nonzeros 2385 and 1255 us, 171 M 926 and 598, 44 M 288 and 255, 32 M 214 and 185; a
 // program that knows its rows sets the knob.
 // That is for a matrix that is not looked at.  Where features are gathered (auto_long_rows) the first pass sees the long
-// rows, and a matrix without pays for one launch and a longer selection, 2 to 6 us: from 2^25 nonzeros on.  Steps, us
-// without and with: Zipf rows, 47 M nonzeros in 2 M columns 310 and 244, 53 M in 3 M 441 and 270; without long
-// rows, 40 M random 286.5 and 289, 48 M 360 and 367, a band of 21 (40 M) 75 and 80.5, a 7-point grid of 200^3 106.5 both.
-// Below, Zipf rows (33 M, s = 2.0) 299 and 273, 18 M random 133 and 137, a band of 11 (19 M) 40.5 and 44.
+// rows, and a matrix without them pays for one launch, 2 to 4 us whatever its size (an empty kernel in the place of
+// the one that multiplies long rows costs the same).  The line, 2^25 nonzeros, is where that is at most 6 % of the fastest product there is
+// of the size, a band, and 1 % where columns are scattered, against 16 to 40 % on the rows it is for.  Steps, us without and
+// with: a band of 21, 34 M nonzeros 67 and 71, 40 M 73.4 and 77.2, 67 M 122 and 126; Poisson rows, 34 M 308 and 312, 48 M 360.5 and 364.7;
+// random rows, 40 M 286 and 288; a 7-point grid of 200^3 106.5 both; Zipf rows, 35 M in 2 M columns (s = 1.7) 238 and 166, 38 M (s = 1.9) 288 and
+// 243, 46 M in 4 M columns 485 and 327, 47 M in 2 M 316 and 243, 53 M in 3 M 433 and 262.  At 2^24 both would be 9 %: Zipf rows
+// (33 M, s = 2.0) 299 and 273, a band of 11 (19 M) 40.5 and 44, 18 M random 133 and 137.  A program that knows its rows to be short sets the knob.
 // The "long_rows" knob: 0 never, 1 from 2^23 nonzeros on, whatever the mean.
 bool auto_long_rows(int rows, int nnz)
 {

@@ -18,9 +18,11 @@
 //     places kept by the preparation) and sums the rows from there, as CSR,WO does.
 //
 // 16 bytes are moved per single entry (6 read + 4 written, 6 read), 7 to 9 where rows have runs,
-// beside rows and padding, and that bounds both kernels: 40 M nonzeros, 2 M columns, rows of 20: 427 MB in
+// beside rows and padding, and that bounds both kernels where rows are even: 40 M nonzeros, 2 M columns, rows of 20: 427 MB in
 // 84 us (5.1 TB/s, a third of it written) and 258 MB in 43 us (6.0 TB/s); the form with slabs in L2 takes
-// 210 + 5 + 13 us, bound by its gathers.  Zipf rows (s = 1.9), 62 M nonzeros, 4 M columns: 129 + 58 + 5 us
+// 210 + 5 + 13 us, bound by its gathers.  Where they are not, the row sums are bound by the longest row of a wave: of a chunk of
+// several hundred rows a lane adds up one of up to 128 products by itself, longer ones go to the whole wave one after
+// the other (Zipf rows, s = 1.85, 47 M nonzeros: 110 MB in 39 us, 2.8 TB/s; the products 405 MB in 87, 4.6 TB/s).  Zipf rows (s = 1.9), 62 M nonzeros, 4 M columns: 129 + 58 + 5 us
 // and 372 + 6 + 18.  Preparation, kernels alone, 40 M: 170 (sort) + 162 (fill) + 20 us, against about 480.
 // Tried: without the sums of fours and sixteens, Zipf 133 + 109 us; the parts of all buckets of a slab
 // one after the other, so that a bucket's p is written at three times, 134 instead of 129; streaming stores
